@@ -1,17 +1,23 @@
 // After the eviction path: one decoding step on the compacted cache (paper Sec. 1 / Sec. 4.6: decoding runs on
 // the retained tokens only). Every query head attends to the b_h packed rows of its KV head.
 //
-// Pure streaming: each K and V row is read once, so the bound is HBM. A workgroup takes one chunk of kChunk
-// consecutive rows of one KV head (rows of a head are contiguous in the packed cache) and all G query heads of
-// its group:
+// Pure streaming: each K and V row is read once, so the bound is HBM. A workgroup takes one chunk of consecutive
+// rows of one KV head (rows of a head are contiguous in the packed cache) and all G query heads of its group:
 //   1. logits  Q (G x d, padded to 8 or 16 rows, stationary) times the chunk's K rows on the matrix cores
-//              (16 keys per MFMA group, 16-byte loads straight from HBM into the B operand), into LDS;
-//   2. softmax statistics of the chunk per query head (one wave per query head), weights back into LDS;
+//              (16 keys per MFMA group, 16-byte loads straight from HBM into the B operand), into LDS; each wave
+//              keeps the maxima of the logits that it writes;
+//   2. weights exp2(logit - chunk maximum), a thread on four query heads of a row, and their sums;
 //   3. weights times V on the vector ALUs: a thread owns 8 channels of every (256 / (d/8))-th row, so a wave's
 //      load covers whole consecutive rows; fp32 accumulators, reduced over the threads of a channel at the end.
+// What a workgroup costs is latency: the first V rows are requested before K, K loads of 128 rows are all in flight
+// before the first MFMA (left alone the compiler keeps three), two barriers separate the phases.
 // Chunks of a head are combined by a second small kernel (max / sum rescaling in base 2). No atomics.
-// Budgets differ from head to head, so a first tiny kernel numbers the chunks of all heads consecutively; the
-// grid then holds (almost) no empty workgroups, whatever the spread of the budgets.
+//
+// Budgets differ from head to head and are known on the device only. Chunk c of head g has slot
+//     floor(cu_b[g] / R) + g + c        (R rows per chunk)
+// and a workgroup finds its head by a binary search for its slot: the slots of a head start one past the last that
+// the head before can use (ceil(n / R) <= floor((b + n) / R) - floor(b / R) + 1), so they never meet, and at most one
+// slot per head stays empty. No table of chunks has to be written first.
 #include "common.h"
 
 namespace audiokv {
@@ -23,104 +29,114 @@ typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kThreads = 256;
-// rows per workgroup: as many as the weights' LDS buffer allows (8 or 16 padded query heads per KV head)
-__host__ __device__ constexpr int chunk_rows(int GP) { return GP <= 8 ? 1024 : 512; }
+// Rows per workgroup at most: what the weights' LDS buffer (4 bytes per row and padded query head, 32 KiB) holds, four
+// workgroups per CU. At least one trip of phase 1 (128 rows).
+__host__ __device__ constexpr int max_chunk_rows(int GP) { return GP <= 8 ? 1024 : 512; }
+constexpr int kMinChunkRows = 128;
 
 __device__ __forceinline__ float bf16_lo(unsigned int w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf16_hi(unsigned int w) { return __uint_as_float(w & 0xffff0000u); }
 
-// workspace: per (head, chunk): G * D accumulators, then G * 2 statistics (max in base-2 units, sum)
-__host__ __device__ inline size_t part_stride(int G, int D) { return (size_t)G * (D + 2); }
-
-// rows of head g that are used: its budget, cut so that nothing past total_rows is ever read
-__device__ __forceinline__ int head_rows(const int32_t* __restrict__ cu_b, int g, long long total_rows) {
-    const long long b0 = cu_b[g], b1 = cu_b[g + 1];
-    const long long hi = b1 < total_rows ? b1 : total_rows;
-    return hi > b0 ? (int)(hi - b0) : 0;
+// start of head g's rows, cut so that nothing past total_rows is ever read
+__device__ __forceinline__ int head_start(const int32_t* __restrict__ cu_b, int g, int total_rows) {
+    return min(cu_b[g], total_rows);
+}
+__device__ __forceinline__ int first_slot(const int32_t* __restrict__ cu_b, int g, int total_rows, int log_r) {
+    return (head_start(cu_b, g, total_rows) >> log_r) + g;
 }
 
-// first[g] = number of chunks of the heads before g (exclusive scan of ceil(rows / kChunk)); first[n_heads] = total
-// table[c] = (head, first cache row, number of rows) of chunk c, so that a workgroup finds its work with one load
-__global__ __launch_bounds__(1024) void decode_chunks_kernel(const int32_t* __restrict__ cu_b, int n_heads,
-                                                             long long total_rows, int kChunk,
-                                                             int32_t* __restrict__ first,
-                                                             int4* __restrict__ table, int table_len)
-{
-    __shared__ int sc[1024];
-    __shared__ int carry;
-    const int tid = threadIdx.x;
-    if (tid == 0) carry = 0;
-    __syncthreads();
-    for (int base = 0; base < n_heads; base += 1024) {
-        const int g = base + tid;
-        const int mine = g < n_heads ? (head_rows(cu_b, g, total_rows) + kChunk - 1) / kChunk : 0;
-        sc[tid] = mine;
-        __syncthreads();
-        for (int off = 1; off < 1024; off <<= 1) {
-            const int add = tid >= off ? sc[tid - off] : 0;
-            __syncthreads();
-            sc[tid] += add;
-            __syncthreads();
-        }
-        if (g < n_heads) {
-            const int f = carry + sc[tid] - mine;
-            first[g] = f;
-            const int rows = head_rows(cu_b, g, total_rows), b0 = cu_b[g];
-            for (int c = 0; c < mine && f + c < table_len; ++c)
-                table[f + c] = make_int4(g, b0 + c * kChunk, min(kChunk, rows - c * kChunk), c);
-        }
-        __syncthreads();
-        if (tid == 1023) carry += sc[1023];
-        __syncthreads();
-    }
-    if (tid == 0) first[n_heads] = carry;
+// a, b <- sums over lanes 32 apart of a (lower half of the wave) and of b (upper half), in a. (asm: see score_impl.h
+// on v_permlane32_swap; the wait states cover the vector writes that produce the operands)
+__device__ __forceinline__ float fold32(float a, float b) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("s_nop 1\n\tv_permlane32_swap_b32 %0, %1" : "+v"(a), "+v"(b));
+#endif
+    return a + b;
+}
+// the same over lanes 16 apart: even rows of 16 lanes get the sum of a, odd rows that of b
+__device__ __forceinline__ float fold16(float a, float b) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("s_nop 1\n\tv_permlane16_swap_b32 %0, %1" : "+v"(a), "+v"(b));
+#endif
+    return a + b;
 }
 
 template <int D, int GP>
-__global__ __launch_bounds__(kThreads) void decode_partial_kernel(
+__global__ __launch_bounds__(kThreads)
+__attribute__((amdgpu_waves_per_eu(GP > 8 ? 2 : D == 256 ? 3 : 4, GP > 8 ? 2 : D == 256 ? 3 : 4)))   // no spills
+void decode_partial_kernel(
     Geom g, const __bf16* __restrict__ q, const __bf16* __restrict__ kc, const __bf16* __restrict__ vc,
-    const int32_t* __restrict__ first, const int4* __restrict__ table, int n_heads, float* __restrict__ part)
+    const int32_t* __restrict__ cu_b, int n_heads, int total_rows, int log_r,
+    float* __restrict__ part,            // [slot][G][D] accumulators
+    float* __restrict__ stats)           // [slot][G][2] = (max in base-2 units, sum)
 {
     constexpr int VPR = D / 8;                 // 16-byte pieces (lanes) per row
     constexpr int KQ = kThreads / VPR;         // rows in flight per pass of phase 3
     constexpr int KK = D / 32;                 // MFMA k-steps
-    constexpr int kChunk = chunk_rows(GP);
-    __shared__ __attribute__((aligned(16))) float lg[kChunk * GP];      // logits, then weights: [row][query head]
-    __shared__ float st_m[GP], st_l[GP];
-    __shared__ __attribute__((aligned(16))) float red[GP * D];          // accumulators summed over the waves, in wave order
+    constexpr int UN = D == 64 ? 4 : 8;        // V rows in flight per thread
+    constexpr int TRIP = 128;                  // rows of one trip of phase 1; phases 2 and 3 go in whole trips, too
+    static_assert(TRIP % (KQ * UN) == 0 && kMinChunkRows % TRIP == 0, "a chunk is whole trips of every phase");
+    // logits, then weights: [row][query head]; at the end the four waves' accumulators: [wave][query head][channel]
+    extern __shared__ __attribute__((aligned(16))) float lg[];
+    __shared__ float st_m[4][GP], st_l[4][GP];
 
+    // The last head whose first slot is not past this one. Every round probes 64 heads at equal distances, one per
+    // lane: one load latency for up to 64 heads, two up to 4096 (a binary search pays one per doubling).
     const int cid = blockIdx.x;
-    if (cid >= first[n_heads]) return;         // uniform: the grid is sized from an upper bound
-    const int4 job = table[cid];
-    const int head = job.x, rows = job.z;
+    int head = 0;
+    for (int span = n_heads; span > 1;) {
+        const int step = (span + 63) >> 6;
+        const int probe = head + (int)(threadIdx.x & 63) * step;
+        const bool at_or_before = probe < head + span && first_slot(cu_b, min(probe, n_heads - 1), total_rows, log_r) <= cid;
+        const int n = __builtin_popcountll(__builtin_amdgcn_ballot_w64(at_or_before));   // a prefix of the lanes
+        const int skip = n > 0 ? (n - 1) * step : 0;
+        head += skip;
+        span = min(step, span - skip);
+    }
+    head = __builtin_amdgcn_readfirstlane(head);
+    const int chunk = cid - first_slot(cu_b, head, total_rows, log_r);
+    const int64_t row_b = head_start(cu_b, head, total_rows) + ((int64_t)chunk << log_r);
+    const int rows = (int)min((int64_t)1 << log_r, head_start(cu_b, head + 1, total_rows) - row_b);
+    if (chunk < 0 || rows <= 0) return;        // uniform: the slot that this head leaves empty
     const int item = head / g.H_kv, h = head - item * g.H_kv;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int G = g.G;
-    const __bf16* krow0 = kc + (size_t)job.y * D;
-    const __bf16* vrow0 = vc + (size_t)job.y * D;
+    const __bf16* krow0 = kc + (size_t)row_b * D;
+    const __bf16* vrow0 = vc + (size_t)row_b * D;
+    const int trips = (rows + TRIP - 1) / TRIP;
+
+    // the first V rows of phase 3 (all of a 128-row chunk at d <= 128) are requested first: one latency for K and V
+    const int c8 = tid % VPR, kq = tid / VPR;
+    u32x4 vv[UN];
+    auto load_v = [&](int r0) {
+#pragma unroll
+        for (int u = 0; u < UN; ++u) {
+            const int rc = min(r0 + kq + u * KQ, rows - 1);      // rows past the end carry weight 0
+            vv[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(vrow0 + (size_t)rc * D) + c8);
+        }
+    };
+    load_v(0);
 
     // ---- phase 1: logits in base-2 units ----
     {
         const int qr = lane & 15, kgrp = lane >> 4;             // A operand: query row qr, channels 8*kgrp + 32*kk
         bf16x8 qa[KK];
+        const __bf16* qsrc = q + ((size_t)item * g.H_q + (size_t)h * G + min(qr, G - 1)) * D + kgrp * 8;
 #pragma unroll
-        for (int kk = 0; kk < KK; ++kk) {
-            bf16x8 z = {0, 0, 0, 0, 0, 0, 0, 0};
-            if (qr < G)
-                z = *reinterpret_cast<const bf16x8*>(q + ((size_t)item * g.H_q + (size_t)h * G + qr) * D + kgrp * 8 + kk * 32);
-            qa[kk] = z;
-        }
-        const int groups = (rows + 15) >> 4;                    // 16 keys per MFMA group
-        for (int gi = wave; gi < groups; gi += 8) {             // two groups per trip: loads of both in flight
-            const int gj = gi + 4;
-            const int ka = min(gi * 16 + qr, rows - 1);         // B operand: key = lane & 15 (clamped, masked below)
-            const int kb = min(gj * 16 + qr, rows - 1);
+        for (int kk = 0; kk < KK; ++kk) qa[kk] = *reinterpret_cast<const bf16x8*>(qsrc + kk * 32);   // rows >= G: unused copies
+        f32x4 top = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+        for (int t = 0; t < trips; ++t) {
+            // B operand: key = lane & 15 of two groups of 16 keys (rows past the end are clamped, masked below)
+            const int keya = t * TRIP + wave * 16 + qr, keyb = keya + TRIP / 2;
+            const __bf16* pa = krow0 + (size_t)min(keya, rows - 1) * D + kgrp * 8;
+            const __bf16* pb = krow0 + (size_t)min(keyb, rows - 1) * D + kgrp * 8;
             bf16x8 fa[KK], fb[KK];
 #pragma unroll
             for (int kk = 0; kk < KK; ++kk) {
-                fa[kk] = *reinterpret_cast<const bf16x8*>(krow0 + (size_t)ka * D + kgrp * 8 + kk * 32);
-                fb[kk] = *reinterpret_cast<const bf16x8*>(krow0 + (size_t)kb * D + kgrp * 8 + kk * 32);
+                fa[kk] = *reinterpret_cast<const bf16x8*>(pa + kk * 32);
+                fb[kk] = *reinterpret_cast<const bf16x8*>(pb + kk * 32);
             }
+            __builtin_amdgcn_sched_barrier(0);                  // all loads of the trip before its first MFMA
             f32x4 ca = {0.f, 0.f, 0.f, 0.f}, cb = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int kk = 0; kk < KK; ++kk) {
@@ -128,76 +144,64 @@ __global__ __launch_bounds__(kThreads) void decode_partial_kernel(
                 cb = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qa[kk], fb[kk], cb, 0, 0, 0);
             }
             // result: lane holds key (lane & 15), query rows 4 * (lane >> 4) + i
-            if (kgrp * 4 < GP) {
-                const int keya = gi * 16 + qr, keyb = gj * 16 + qr;
-                f32x4 oa, ob;
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    oa[i] = keya < rows ? ca[i] * g.c_log2 : -INFINITY;
-                    ob[i] = keyb < rows ? cb[i] * g.c_log2 : -INFINITY;
-                }
-                *reinterpret_cast<f32x4*>(&lg[keya * GP + kgrp * 4]) = oa;
-                if (gj < groups) *reinterpret_cast<f32x4*>(&lg[keyb * GP + kgrp * 4]) = ob;
+            for (int i = 0; i < 4; ++i) {
+                ca[i] = keya < rows ? ca[i] * g.c_log2 : -INFINITY;
+                cb[i] = keyb < rows ? cb[i] * g.c_log2 : -INFINITY;
+                top[i] = fmaxf(top[i], fmaxf(ca[i], cb[i]));
+            }
+            if (kgrp * 4 < GP) {
+                *reinterpret_cast<f32x4*>(&lg[keya * GP + kgrp * 4]) = ca;
+                *reinterpret_cast<f32x4*>(&lg[keyb * GP + kgrp * 4]) = cb;
             }
         }
-    }
-    // the first V rows of phase 3 are requested now: their latency passes under the softmax statistics
-    const int c8 = tid % VPR, kq = tid / VPR;
-    constexpr int UN = 8;                                       // rows in flight per thread
-    u32x4 vv[UN];
 #pragma unroll
-    for (int u = 0; u < UN; ++u) {
-        const int rc = min(kq + u * KQ, rows - 1);
-        vv[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(vrow0 + (size_t)rc * D) + c8);
+        for (int o = 8; o > 0; o >>= 1)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) top[i] = fmaxf(top[i], __shfl_xor(top[i], o, 64));
+        if (qr == 0 && kgrp * 4 < GP)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) st_m[wave][kgrp * 4 + i] = top[i];
     }
     __syncthreads();
 
-    // ---- phase 2: per query head, max and sum over the chunk; logits become weights ----
-    const int rows16 = ((rows + 15) >> 4) << 4;                 // rows that phase 1 wrote (the tail holds -inf)
-    for (int qh = wave; qh < GP; qh += 4) {
-        if (qh < G) {
-            float m = -INFINITY;
-            for (int r = lane; r < rows16; r += 64) m = fmaxf(m, lg[r * GP + qh]);
+    // ---- phase 2: logits become weights; sums over the chunk ----
+    {
+        constexpr int QPR = GP / 4;                             // threads per row
+        const int qd = tid % QPR, r0 = tid / QPR;
+        f32x4 m, l = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
-            float l = 0.f;
-            for (int r = lane; r < rows16; r += 64) {
-                const float p = __builtin_amdgcn_exp2f(lg[r * GP + qh] - m);
-                lg[r * GP + qh] = p;
-                l += p;
-            }
+        for (int i = 0; i < 4; ++i)
+            m[i] = fmaxf(fmaxf(st_m[0][qd * 4 + i], st_m[1][qd * 4 + i]), fmaxf(st_m[2][qd * 4 + i], st_m[3][qd * 4 + i]));
+        for (int r = r0; r < trips * TRIP; r += kThreads / QPR) {
+            f32x4 p = *reinterpret_cast<const f32x4*>(&lg[r * GP + qd * 4]);
 #pragma unroll
-            for (int o = 32; o > 0; o >>= 1) l += __shfl_xor(l, o, 64);
-            if (lane == 0) { st_m[qh] = m; st_l[qh] = l; }
-        } else {
-            for (int r = lane; r < rows16; r += 64) lg[r * GP + qh] = 0.f;
+            for (int i = 0; i < 4; ++i) p[i] = __builtin_amdgcn_exp2f(p[i] - m[i]);
+            l += p;
+            *reinterpret_cast<f32x4*>(&lg[r * GP + qd * 4]) = p;
         }
+#pragma unroll
+        for (int o = 32; o >= QPR; o >>= 1)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) l[i] += __shfl_xor(l[i], o, 64);
+        if (lane < QPR)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) st_l[wave][lane * 4 + i] = l[i];
     }
     __syncthreads();
 
     // ---- phase 3: weights times V ----
-    float acc[GP][8];
+    float acc[GP * 8];                                          // [query head][channel c8 * 8 + i]
 #pragma unroll
-    for (int qh = 0; qh < GP; ++qh)
-#pragma unroll
-        for (int i = 0; i < 8; ++i) acc[qh][i] = 0.f;
-    for (int r = kq; r < rows16; r += KQ * UN) {
-        int rr[UN];
+    for (int e = 0; e < GP * 8; ++e) acc[e] = 0.f;
+    for (int r = 0; r < trips * TRIP; r += KQ * UN) {
+        if (r) load_v(r);                                       // (the first batch is already on its way)
 #pragma unroll
         for (int u = 0; u < UN; ++u) {
-            rr[u] = r + u * KQ;
-            if (r != kq) {                                      // (the first batch is already on its way)
-                const int rc = min(rr[u], rows - 1);            // clamped rows carry weight 0 (or are skipped below)
-                vv[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(vrow0 + (size_t)rc * D) + c8);
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < UN; ++u) {
-            if (rr[u] >= rows16) continue;                      // past the rows that hold weights
             float p[GP];
 #pragma unroll
             for (int q4 = 0; q4 < GP / 4; ++q4) {
-                const f32x4 t = *reinterpret_cast<const f32x4*>(&lg[rr[u] * GP + q4 * 4]);
+                const f32x4 t = *reinterpret_cast<const f32x4*>(&lg[(r + kq + u * KQ) * GP + q4 * 4]);
                 p[q4 * 4 + 0] = t[0]; p[q4 * 4 + 1] = t[1]; p[q4 * 4 + 2] = t[2]; p[q4 * 4 + 3] = t[3];
             }
             float v[8];
@@ -206,89 +210,105 @@ __global__ __launch_bounds__(kThreads) void decode_partial_kernel(
 #pragma unroll
             for (int qh = 0; qh < GP; ++qh)
 #pragma unroll
-                for (int i = 0; i < 8; ++i) acc[qh][i] = fmaf(p[qh], v[i], acc[qh][i]);
+                for (int i = 0; i < 8; ++i) acc[qh * 8 + i] = fmaf(p[qh], v[i], acc[qh * 8 + i]);
         }
     }
-    // threads of one wave that share c8 (fixed order: xor tree), then the four waves through LDS, in wave order
+    // Threads of one wave that share c8, halving the values with the lanes: after a fold over lanes 32 apart the upper
+    // half of the wave holds the upper half of the query heads, after one over lanes 16 apart odd rows of 16 lanes
+    // the upper half of those.
+    constexpr int N32 = GP * 4, N16 = VPR <= 16 ? N32 / 2 : N32;
 #pragma unroll
-    for (int o = VPR; o < 64; o <<= 1)
+    for (int e = 0; e < N32; ++e) acc[e] = fold32(acc[e], acc[e + N32]);
+    int qh0 = (lane >> 5) * (GP / 2);
+    if constexpr (VPR <= 16) {
 #pragma unroll
-        for (int qh = 0; qh < GP; ++qh)
-#pragma unroll
-            for (int i = 0; i < 8; ++i) acc[qh][i] += __shfl_xor(acc[qh][i], o, 64);
-    for (int w = 0; w < 4; ++w) {
-        if (wave == w && lane < VPR) {
-#pragma unroll
-            for (int qh = 0; qh < GP; ++qh)
-#pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    float* slot = &red[qh * D + c8 * 8 + i];
-                    *slot = w == 0 ? acc[qh][i] : *slot + acc[qh][i];
-                }
-        }
-        __syncthreads();
+        for (int e = 0; e < N16; ++e) acc[e] = fold16(acc[e], acc[e + N16]);
+        qh0 += ((lane >> 4) & 1) * (GP / 4);
     }
-    float* out = part + (size_t)cid * part_stride(G, D);
-    for (int e = tid; e < G * D; e += kThreads) out[e] = red[e];
+    if constexpr (VPR == 8) {
+#pragma unroll
+        for (int e = 0; e < N16; ++e) acc[e] += __shfl_xor(acc[e], 8, 64);
+    }
+    __syncthreads();                                            // every wave is done with the weights
+#pragma unroll
+    for (int e = 0; e < N16; e += 4)
+        *reinterpret_cast<f32x4*>(&lg[(wave * GP + qh0 + e / 8) * D + c8 * 8 + e % 8]) =
+            f32x4{acc[e], acc[e + 1], acc[e + 2], acc[e + 3]};
+    __syncthreads();
+    float* out = part + (size_t)cid * G * D;
+    for (int e = tid; e < G * D; e += kThreads)
+        out[e] = ((lg[e] + lg[GP * D + e]) + lg[2 * GP * D + e]) + lg[3 * GP * D + e];
     if (tid < G) {
-        out[(size_t)G * D + 2 * tid] = st_m[tid];
-        out[(size_t)G * D + 2 * tid + 1] = st_l[tid];
+        stats[((size_t)cid * G + tid) * 2] = fmaxf(fmaxf(st_m[0][tid], st_m[1][tid]), fmaxf(st_m[2][tid], st_m[3][tid]));
+        stats[((size_t)cid * G + tid) * 2 + 1] = ((st_l[0][tid] + st_l[1][tid]) + st_l[2][tid]) + st_l[3][tid];
     }
 }
 
-// one workgroup per (KV head, query head of its group): combine the chunks
-__global__ __launch_bounds__(256) void decode_merge_kernel(
-    Geom g, const int32_t* __restrict__ first, int grid_chunks, const float* __restrict__ part, float* __restrict__ out)
+// One workgroup per (KV head, query head of its group): combine the chunks. A chain of loads from end to end, so as
+// many as possible are in flight: the statistics one chunk per thread, then the accumulators with a thread on four
+// channels of every (256 / (D/4))-th chunk. Every sum has a fixed order.
+constexpr int kMergeThreads = 256;
+constexpr int kMergeLds = 2048;           // chunks whose weights fit the LDS array (more: recomputed where used)
+
+__global__ __launch_bounds__(kMergeThreads) void decode_merge_kernel(
+    Geom g, const int32_t* __restrict__ cu_b, int total_rows, int log_r, const float* __restrict__ part,
+    const float* __restrict__ stats, float* __restrict__ out)
 {
     const int head = blockIdx.x / g.G, qh = blockIdx.x - head * g.G;
     const int item = head / g.H_kv, h = head - item * g.H_kv;
-    const int c0 = min(first[head], grid_chunks), c1 = min(first[head + 1], grid_chunks);
-    const size_t stride = part_stride(g.G, g.D);
-    const float* st0 = part + (size_t)g.G * g.D + 2 * qh;       // statistics of chunk c at st0 + c * stride
-    const int nc = c1 - c0;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int b0 = head_start(cu_b, head, total_rows), n = head_start(cu_b, head + 1, total_rows) - b0;
+    const int c0 = (b0 >> log_r) + head, nc = n > 0 ? (n + (1 << log_r) - 1) >> log_r : 0;
     float* o = out + ((size_t)item * g.H_q + (size_t)h * g.G + qh) * g.D;
-    constexpr int kFast = 256;                                  // chunks whose statistics fit the LDS arrays
-    __shared__ float wgt[kFast], sm[kFast], sl[kFast];
-    if (nc <= kFast) {
-        // chunk weights 2^(m_c - M) / sum: all statistics are fetched at once (one chunk per thread), not in a chain
-        if ((int)threadIdx.x < nc) {
-            sm[threadIdx.x] = st0[(c0 + threadIdx.x) * stride];
-            sl[threadIdx.x] = st0[(c0 + threadIdx.x) * stride + 1];
-        }
-        __syncthreads();
-        float M = -INFINITY;
-        for (int c = 0; c < nc; ++c) M = fmaxf(M, sm[c]);
-        float den = 0.f;
-        for (int c = 0; c < nc; ++c) den += sl[c] * __builtin_amdgcn_exp2f(sm[c] - M);
-        if ((int)threadIdx.x < nc) wgt[threadIdx.x] = __builtin_amdgcn_exp2f(sm[threadIdx.x] - M) / den;
-        __syncthreads();
-        for (int ch = threadIdx.x; ch < g.D; ch += blockDim.x) {
-            const float* col = part + (size_t)c0 * stride + (size_t)qh * g.D + ch;
-            float num = 0.f;
-            int c = 0;
-            for (; c + 4 <= nc; c += 4) {                       // four loads in flight; the order of the adds is fixed
-                const float a0 = col[(size_t)c * stride], a1 = col[(size_t)(c + 1) * stride];
-                const float a2 = col[(size_t)(c + 2) * stride], a3 = col[(size_t)(c + 3) * stride];
-                num += a0 * wgt[c];
-                num += a1 * wgt[c + 1];
-                num += a2 * wgt[c + 2];
-                num += a3 * wgt[c + 3];
-            }
-            for (; c < nc; ++c) num += col[(size_t)c * stride] * wgt[c];
-            o[ch] = nc > 0 ? num : 0.f;
-        }
-        return;
+    __shared__ float wgt[kMergeLds];
+    __shared__ float wave_m[kMergeThreads / 64], wave_l[kMergeThreads / 64];
+    __shared__ __attribute__((aligned(16))) f32x4 red[kMergeThreads];
+
+    const float2* st = reinterpret_cast<const float2*>(stats) + (size_t)c0 * g.G + qh;     // chunk c at st[c * G]
+    float m = -INFINITY, l = 0.f;
+    for (int c = tid; c < nc; c += kMergeThreads) {
+        const float2 s = st[(size_t)c * g.G];
+        if (c < kMergeLds) wgt[c] = s.x;
+        const float m2 = fmaxf(m, s.x);                          // a chunk holds at least one row: s.x is finite
+        l = l * __builtin_amdgcn_exp2f(m - m2) + s.y * __builtin_amdgcn_exp2f(s.x - m2);
+        m = m2;
     }
-    // a head with more than 256 chunks (beyond a quarter of a million rows): the same sums straight from memory
-    float M = -INFINITY;
-    for (int c = c0; c < c1; ++c) M = fmaxf(M, st0[c * stride]);
+    float M = m;
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) M = fmaxf(M, __shfl_xor(M, off, 64));
+    if (lane == 0) wave_m[wave] = M;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < kMergeThreads / 64; ++w) M = fmaxf(M, wave_m[w]);
+    l = m == -INFINITY ? 0.f : l * __builtin_amdgcn_exp2f(m - M);
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) l += __shfl_xor(l, off, 64);
+    if (lane == 0) wave_l[wave] = l;
+    for (int c = tid; c < min(nc, kMergeLds); c += kMergeThreads) wgt[c] = __builtin_amdgcn_exp2f(wgt[c] - M);
+    __syncthreads();
     float den = 0.f;
-    for (int c = c0; c < c1; ++c) den += st0[c * stride + 1] * __builtin_amdgcn_exp2f(st0[c * stride] - M);
-    for (int ch = threadIdx.x; ch < g.D; ch += blockDim.x) {
-        float num = 0.f;
-        for (int c = c0; c < c1; ++c)
-            num += part[c * stride + (size_t)qh * g.D + ch] * (__builtin_amdgcn_exp2f(st0[c * stride] - M) / den);
-        o[ch] = num;
+#pragma unroll
+    for (int w = 0; w < kMergeThreads / 64; ++w) den += wave_l[w];
+
+    const int quads = g.D >> 2, groups = kMergeThreads / quads;  // D = 64, 128, 256: 16, 8, 4 chunks at a time
+    const int ch4 = tid % quads, grp = tid / quads;
+    const f32x4* col = reinterpret_cast<const f32x4*>(part + ((size_t)c0 * g.G + qh) * g.D) + ch4;
+    const size_t stride = (size_t)g.G * quads;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+    for (int c = grp; c < nc; c += groups) {
+        const float w = c < kMergeLds ? wgt[c] : __builtin_amdgcn_exp2f(st[(size_t)c * g.G].x - M);
+        acc += col[(size_t)c * stride] * w;
+    }
+    red[tid] = acc;
+    __syncthreads();
+    if (grp == 0) {
+        f32x4 num = acc;
+        for (int k = 1; k < groups; ++k) num += red[k * quads + ch4];
+        const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+        num = nc > 0 ? num / den : zero;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) o[ch4 * 4 + i] = num[i];     // `out` need not be aligned beyond its floats
     }
 }
 
@@ -296,35 +316,45 @@ __global__ __launch_bounds__(256) void decode_merge_kernel(
 
 bool decode_supported(int G) { return G >= 1 && G <= 16; }
 
-// upper bound on the number of chunks: every head wastes less than one
-static size_t chunk_bound(const Geom& g, long long total_rows) {
-    return (size_t)(total_rows / chunk_rows(g.G)) + (size_t)g.n_items * g.H_kv;
+// Rows per chunk (a power of two): the largest that still gives every CU four workgroups (what its registers hold at
+// d <= 128), within what the kernel can hold. Both kernels of a call, d = 128, fixed 1024-row chunks -> this rule:
+// 3.3 k rows 36 -> 14 us, 105 k rows 42 -> 20, 367 k rows 59 -> 43 (4.4 TB/s), 1.47 M rows 157 -> 142 (5.3 TB/s);
+// with one workgroup per CU instead of four 367 k rows take 47 us and 734 k rows 86 instead of 78.
+constexpr int kChunksPerCu = 4;
+static int log_chunk_rows(const Geom& g, long long total_rows) {
+    int lg = 7;                                                   // kMinChunkRows
+    static_assert((1 << 7) == kMinChunkRows, "log2 of the smallest chunk");
+    while ((2 << lg) <= max_chunk_rows(g.G) && (total_rows >> (lg + 1)) >= 256 * kChunksPerCu) ++lg;
+    return lg;
 }
-static size_t first_bytes(const Geom& g) { return (((size_t)g.n_items * g.H_kv + 1) * sizeof(int32_t) + 255) & ~(size_t)255; }
-static size_t table_bytes(size_t bound) { return (bound * sizeof(int4) + 255) & ~(size_t)255; }
+// slots of chunks: every head leaves at most one empty
+static size_t slot_bound(const Geom& g, long long total_rows) {
+    return (size_t)(total_rows >> log_chunk_rows(g, total_rows)) + (size_t)g.n_items * g.H_kv;
+}
+static size_t stats_bytes(const Geom& g, size_t bound) { return (bound * g.G * 2 * sizeof(float) + 255) & ~(size_t)255; }
 
 size_t decode_workspace_bytes(const Geom& g, long long total_rows) {
-    const size_t bound = chunk_bound(g, total_rows);
-    return first_bytes(g) + table_bytes(bound) + bound * part_stride(g.G, g.D) * sizeof(float);
+    const size_t bound = slot_bound(g, total_rows);
+    return stats_bytes(g, bound) + bound * g.G * g.D * sizeof(float);
 }
 
 hipError_t launch_decode(const Geom& g, const void* q, const void* k_cache, const void* v_cache,
                          const int32_t* cu_budgets, long long total_rows, float* out, void* workspace, hipStream_t s)
 {
     const int n_heads = g.n_items * g.H_kv;
-    const size_t bound = chunk_bound(g, total_rows);
+    const size_t bound = slot_bound(g, total_rows);
     if (total_rows < 0 || bound > (size_t)INT32_MAX || !decode_supported(g.G)) return hipErrorInvalidValue;
-    int32_t* first = static_cast<int32_t*>(workspace);
-    int4* table = reinterpret_cast<int4*>(static_cast<char*>(workspace) + first_bytes(g));
-    float* part = reinterpret_cast<float*>(static_cast<char*>(workspace) + first_bytes(g) + table_bytes(bound));
-    hipLaunchKernelGGL(decode_chunks_kernel, dim3(1), dim3(1024), 0, s, cu_budgets, n_heads, total_rows,
-                       chunk_rows(g.G), first, table, (int)bound);
+    const int log_r = log_chunk_rows(g, total_rows);
+    float* stats = static_cast<float*>(workspace);
+    float* part = reinterpret_cast<float*>(static_cast<char*>(workspace) + stats_bytes(g, bound));
     const dim3 grid((unsigned)bound);
-#define AUDIOKV_LAUNCH_DECODE(DD, GG)                                                                           \
-    hipLaunchKernelGGL((decode_partial_kernel<DD, GG>), grid, dim3(kThreads), 0, s, g, (const __bf16*)q,       \
-                       (const __bf16*)k_cache, (const __bf16*)v_cache, (const int32_t*)first,                  \
-                       (const int4*)table, n_heads, part)
     const bool wide = g.G > 8;
+    const unsigned gp = wide ? 16 : 8;
+    const unsigned lds = (unsigned)sizeof(float) * gp * (4u * g.D > (1u << log_r) ? 4u * g.D : (1u << log_r));
+#define AUDIOKV_LAUNCH_DECODE(DD, GG)                                                                           \
+    hipLaunchKernelGGL((decode_partial_kernel<DD, GG>), grid, dim3(kThreads), lds, s, g, (const __bf16*)q,     \
+                       (const __bf16*)k_cache, (const __bf16*)v_cache, cu_budgets, n_heads, (int)total_rows,   \
+                       log_r, part, stats)
     switch (g.D) {
         case 64:  if (wide) AUDIOKV_LAUNCH_DECODE(64, 16);  else AUDIOKV_LAUNCH_DECODE(64, 8);  break;
         case 128: if (wide) AUDIOKV_LAUNCH_DECODE(128, 16); else AUDIOKV_LAUNCH_DECODE(128, 8); break;
@@ -334,8 +364,8 @@ hipError_t launch_decode(const Geom& g, const void* q, const void* k_cache, cons
 #undef AUDIOKV_LAUNCH_DECODE
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(decode_merge_kernel, dim3((unsigned)(n_heads * g.G)), dim3(256), 0, s, g,
-                       (const int32_t*)first, (int)bound, (const float*)part, out);
+    hipLaunchKernelGGL(decode_merge_kernel, dim3((unsigned)(n_heads * g.G)), dim3(kMergeThreads), 0, s, g, cu_budgets,
+                       (int)total_rows, log_r, (const float*)part, (const float*)stats, out);
     return hipGetLastError();
 }
 

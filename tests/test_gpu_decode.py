@@ -121,3 +121,33 @@ def test_decode_consumes_the_output_of_evict(A):
         ref = O.decode_attend(bf16_bits_to_f64(qn_bits[i]), kr, vr)
         assert rel_err(out[i], ref) <= SCORE_RTOL
         assert np.abs(out[i] - ref).max() <= 1e-4 * np.abs(ref).max()
+
+
+@pytest.mark.parametrize("H_q,H_kv,d,n_items,budgets", [
+    (4, 2, 64, 35, lambda g: (2, 1, 127, 128, 129, 300)[g % 6]),       # more than 64 heads: two rounds of the head search
+    (14, 2, 128, 2, lambda g: (128, 256, 128, 257)[g]),                # chunk starts that fall on multiples of the chunk
+    (10, 1, 256, 3, lambda g: (1, 513, 127)[g]),
+    (8, 1, 128, 1, lambda g: 128 * 2048 - 1),                          # the longest call of 128-row chunks, 2048 for one head
+    (8, 1, 128, 1, lambda g: 128 * 2048),                              # the shortest of 256-row chunks
+    (3, 1, 256, 2, lambda g: (1024 * 512 - 5, 5)[g]),                  # the same edge one chunk size up, ending in a short head
+])
+def test_decode_chunk_edges(A, H_q, H_kv, d, n_items, budgets):
+    run_case(A, np.random.default_rng(n_items * d), H_q, H_kv, d, [budgets(g) for g in range(n_items * H_kv)], n_items,
+             k_scale=0.5)
+
+
+def test_decode_more_chunks_than_weights_fit_on_chip(A):
+    # 16-wide group padding: chunks of at most 512 rows, 2051 of them in one head
+    run_case(A, np.random.default_rng(9), 9, 1, 64, [2050 * 512 + 9], 1, k_scale=0.5)
+
+
+def test_decode_empty_heads_between_full_ones(A):
+    # zero queries: every head's output is the mean of its own rows, zeros for the heads that kept none
+    n, d, pool = 130, 64, (0, 0, 128, 1, 0, 129, 256)
+    budgets = np.array([pool[g % 7] for g in range(n)])
+    cu = np.concatenate([[0], np.cumsum(budgets)]).astype(np.int32)
+    v = torch.arange(int(cu[-1]), dtype=torch.float32).remainder(251).repeat_interleave(d).to(torch.bfloat16).cuda()
+    q = torch.zeros(n * d, dtype=torch.bfloat16, device="cuda")
+    out = A.decode_attend(A.Params(1, 1, d, 1), q, v, v, torch.from_numpy(cu).cuda(), n, int(cu[-1])).cpu().numpy()
+    want = [(np.arange(cu[g], cu[g + 1]) % 251).mean() if budgets[g] else 0.0 for g in range(n)]
+    np.testing.assert_allclose(out[:, 0], np.repeat(np.array(want)[:, None], d, 1), rtol=2e-6)     # fp32 sums of <= 256 terms
