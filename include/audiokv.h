@@ -252,14 +252,14 @@ int32_t audiokv_compact(const audiokv_params* params,
  * [n_items * n_kv_heads], one per KV head. Intermediate scores live in the
  * workspace. Outputs as in the per-stage calls; the result equals the five
  * calls composed. The budget allocation does not depend on the scores, nor do
- * the tables that smoothing needs for lengths that are not powers of two: for
- * pools of 32 heads or more, or when such tables are needed, they are forked
- * onto a helper stream owned by the library (created on first use, default
- * priority) and joined back into `stream` with events after the scoring
- * (smaller pools are allocated on `stream` itself, in the launch that merges
- * the softmax statistics between the two scoring sweeps); everything is
- * ordered after prior work on
- * `stream` and before later work on it. Calls on different streams may be in
+ * the filters that smoothing needs for lengths that are not powers of two: for
+ * pools of 32 heads or more, or when such filters take several launches (a
+ * length shared by more than eight heads, an energy-adaptive cutoff), they are
+ * forked onto a helper stream owned by the library (created on first use,
+ * default priority) and joined back into `stream` with events after the scoring
+ * (otherwise they stay on `stream`, in the launch that merges the softmax
+ * statistics between the two scoring sweeps); everything is ordered after prior
+ * work on `stream` and before later work on it. Calls on different streams may be in
  * flight together (separate workspaces and outputs), also from several host
  * threads: the helper stream and its two events are shared, so the part of a
  * call between the fork and the join holds a lock. */

@@ -9,8 +9,10 @@
 // The merge of the score sweeps' per-range row statistics lives here too: it is
 // as small as the allocation, neither depends on the other, and inside one
 // call on one stream a launch costs more than either's work, so the
-// allocation can ride along in extra workgroups of the merge launch.
+// allocation can ride along in extra workgroups of the merge launch, and so can
+// the taps of the smoothing's filter.
 #include "common.h"
+#include "conv_filter.h"
 
 #pragma clang fp contract(off)
 
@@ -268,9 +270,11 @@ __device__ __forceinline__ void merge_row(const float* __restrict__ stats, int n
     cst[(size_t)head * rows_pad + r] = out;
 }
 
-// Workgroups [0, alloc_blocks) allocate one pool each (alloc_blocks = 0: none), the others merge kThreads rows each.
+// Workgroups [0, alloc_blocks) allocate one pool each (alloc_blocks = 0: none), the next tap_blocks evaluate kThreads
+// filter taps each, the others merge kThreads rows each.
 __global__ __launch_bounds__(kThreads) void merge_allocate_kernel(
     const float* __restrict__ stats, int nsplit, int rows_pad, int R, float* __restrict__ cst, int alloc_blocks,
+    int tap_blocks, ConvFilterJob taps,
     const float* __restrict__ weights, int n_segments, int n, int weight_group, int window,
     const int32_t* __restrict__ cu_seq, double ratio, double beta,
     int32_t* __restrict__ budgets, int32_t* __restrict__ cu_budgets)
@@ -280,7 +284,11 @@ __global__ __launch_bounds__(kThreads) void merge_allocate_kernel(
         allocate_pool(smem_raw, blockIdx.x, weights, n_segments, n, weight_group, window, cu_seq, ratio, beta, budgets, cu_budgets);
         return;
     }
-    const int mb = blockIdx.x - alloc_blocks;
+    if ((int)blockIdx.x < alloc_blocks + tap_blocks) {
+        conv_filter_block(taps, blockIdx.x - alloc_blocks);
+        return;
+    }
+    const int mb = blockIdx.x - alloc_blocks - tap_blocks;
     const int blocks_per_head = (rows_pad + kThreads - 1) / kThreads;
     const int head = mb / blocks_per_head;
     merge_row(stats, nsplit, rows_pad, R, head, (mb - head * blocks_per_head) * kThreads + threadIdx.x, cst);
@@ -293,8 +301,9 @@ size_t alloc_smem_bytes(int n) {
 }  // namespace
 
 hipError_t launch_score_merge(const Geom& g, const float* stats, int nsplit, int rows_pad, float* cst,
-                              const AllocateJob* job, hipStream_t s)
+                              const AllocateJob* job, const ConvFilterJob* taps, hipStream_t s)
 {
+    static_assert(kConvFilterThreads == kThreads, "the taps share the launch's workgroup size");
     const int n_heads = g.n_items * g.H_kv;
     const unsigned merge_blocks = (unsigned)(n_heads * ((rows_pad + kThreads - 1) / kThreads));
     size_t smem = 0;
@@ -306,8 +315,9 @@ hipError_t launch_score_merge(const Geom& g, const float* stats, int nsplit, int
         if (smem > 64 * 1024) return hipErrorInvalidValue;
         alloc_blocks = j.n_segments;
     }
-    hipLaunchKernelGGL(merge_allocate_kernel, dim3(merge_blocks + (unsigned)alloc_blocks), dim3(kThreads), smem, s, stats,
-                       nsplit, rows_pad, g.G * g.W, cst, alloc_blocks, j.weights, j.n_segments, j.heads_per_segment,
+    const int tap_blocks = taps && taps->h ? taps->blocks_per_item * taps->n_items : 0;
+    hipLaunchKernelGGL(merge_allocate_kernel, dim3(merge_blocks + (unsigned)(alloc_blocks + tap_blocks)), dim3(kThreads), smem, s,
+                       stats, nsplit, rows_pad, g.G * g.W, cst, alloc_blocks, tap_blocks, taps ? *taps : ConvFilterJob{}, j.weights, j.n_segments, j.heads_per_segment,
                        j.weight_group, g.W, j.cu_seqlens, j.ratio, j.floor_frac, j.budgets, j.cu_budgets);
     return hipGetLastError();
 }

@@ -7,6 +7,7 @@
 #include <mutex>
 
 #include "common.h"
+#include "conv_filter.h"
 
 using namespace audiokv;
 
@@ -484,22 +485,23 @@ int32_t evict_entry(const audiokv_params* params, const void* q_win, const void*
     // in_line: everything on the caller's stream, no library-owned stream or event is touched (or created)
     const bool prof = !in_line && g_prof.enabled && g_prof.created;
     // Work that does not depend on the scores goes to the helper stream, beside the score sweeps: the allocation, and
-    // for lengths that are not powers of two the chirp tables and filter spectra of the smoothing (35 us of small
-    // kernels). A small pool alone is allocated faster than a fork and a join are issued (55 us of host time): then
-    // everything stays in line.
-    const bool chirp = alpha != 0.0 && smooth_workspace_required(seqlens_host, n_items, params->n_kv_heads) > 0;
-    const bool side = !in_line && !prof && (hps >= 32 || chirp);
-    const bool side_filters = side && chirp;
+    // what smoothing prepares for its lengths if that takes more than one small launch. A small pool alone is allocated
+    // faster than a fork and a join are issued (55 us of host time): then everything stays in line.
+    const SmoothFilters filters = alpha != 0.0 ? smooth_filters(g, cu_seqlens_dev, seqlens_host, n_items, cutoff_frac, ws + w.fft_off)
+                                               : SmoothFilters{};
+    const bool side = !in_line && !prof && (hps >= 32 || filters.long_work);
+    const bool side_filters = side && (filters.long_work || filters.taps.h);
     std::unique_lock<std::mutex> helper_lock(g_helper.mu, std::defer_lock);
     if (side) helper_lock.lock();
 #define AUDIOKV_MARK(i) do { if (prof) AUDIOKV_HIP(hipEventRecord(g_prof.ev[i], s), "hipEventRecord"); } while (0)
     AUDIOKV_MARK(0);
-    // In line and without stage timing, the allocation rides along with the launch that merges the row statistics
-    // between the two sweeps (one launch less on the critical path of a call); with the caller's log-sum-exp there
-    // is no such launch.
+    // In line and without stage timing, the allocation and the taps of the smoothing's filter ride along with the launch
+    // that merges the row statistics between the two sweeps (one launch less each on the critical path of a call); with
+    // the caller's log-sum-exp there is no such launch.
     const AllocateJob alloc_job{weights_dev, n_seg, hps, 1, cu_seqlens_dev, ratio, (double)params->floor_frac,
                                 budgets_dev, cu_budgets_dev};
     const bool ride = !side && !prof && !lse_dev;
+    const bool ride_taps = ride && filters.taps.h;
     if (!side && !ride) {
         // (stage timing wants one kernel per interval: then, too, the allocation stays in line)
         AUDIOKV_HIP(launch_allocate(g, weights_dev, n_seg, hps, 1, cu_seqlens_dev, ratio, (double)params->floor_frac,
@@ -510,18 +512,17 @@ int32_t evict_entry(const audiokv_params* params, const void* q_win, const void*
         AUDIOKV_HIP(hipStreamWaitEvent(g_helper.stream, g_helper.fork, 0), "hipStreamWaitEvent");
         AUDIOKV_HIP(launch_allocate(g, weights_dev, n_seg, hps, 1, cu_seqlens_dev, ratio, (double)params->floor_frac,
                                     budgets_dev, cu_budgets_dev, g_helper.stream), "allocate kernel");
-        // the chirp tables and filter spectra of lengths that are not powers of two depend on the lengths and the
-        // cutoff only: half a dozen small kernels that also fit under the score sweeps
         if (side_filters)
             AUDIOKV_HIP(launch_smooth_filters(g, cu_seqlens_dev, seqlens_host, n_items, cutoff_frac, ws + w.fft_off,
-                                              g_helper.stream), "chirp-z filter kernels");
+                                              g_helper.stream), "smoothing filter kernels");
         AUDIOKV_HIP(hipEventRecord(g_helper.join, g_helper.stream), "hipEventRecord");
     }
     AUDIOKV_MARK(1);
     AUDIOKV_HIP(launch_score(g, q_win, k, cu_seqlens_dev, seqlens_host, stats, raw, s,
                              prof ? g_prof.ev[AUDIOKV_PROFILE_STAGES + 1] : nullptr, lse_dev,
                              w.raw2 ? reinterpret_cast<float*>(ws + w.raw2_off) : nullptr,
-                             (size_t)b.total_tokens * params->n_kv_heads, ride ? &alloc_job : nullptr), "score kernels");
+                             (size_t)b.total_tokens * params->n_kv_heads, ride ? &alloc_job : nullptr,
+                             ride_taps ? &filters.taps : nullptr), "score kernels");
     AUDIOKV_MARK(2);
     if (side) {
         // budgets (needed by select) and filters (needed by smooth) are ready; by now the helper's work is long done
@@ -529,7 +530,7 @@ int32_t evict_entry(const audiokv_params* params, const void* q_win, const void*
         helper_lock.unlock();
     }
     AUDIOKV_HIP(launch_smooth(g, raw, params->pool_kernel != 1, cu_seqlens_dev, seqlens_host, n_items, cutoff_frac,
-                              alpha, smoothed, ws + w.fft_off, w.total - w.fft_off, nullptr, false, s, side_filters),
+                              alpha, smoothed, ws + w.fft_off, w.total - w.fft_off, nullptr, false, s, side_filters || ride_taps),
                 "smooth kernel");
     AUDIOKV_MARK(3);
     AUDIOKV_HIP(launch_select(g, smoothed, budgets_dev, cu_budgets_dev, cu_seqlens_dev, b.max_L, indices_dev, s),

@@ -50,11 +50,13 @@ struct AllocateJob {
     const float* weights; int n_segments, heads_per_segment, weight_group; const int32_t* cu_seqlens;
     double ratio, floor_frac; int32_t* budgets; int32_t* cu_budgets;
 };
+struct ConvFilterJob;      // taps of the smoothing's filter (conv_filter.h)
 // Merge of the per-range row statistics of sweep 1 (stats: [head][nsplit][rows_pad][2]) into one constant per row
-// (cst: [head][rows_pad], max + log2(sum); +inf for rows >= R). With `job`, the same launch also runs the budget
-// allocation in extra workgroups: neither depends on the other, and each launch costs more than either's work.
+// (cst: [head][rows_pad], max + log2(sum); +inf for rows >= R). With `job` and `taps`, the same launch also runs the
+// budget allocation and evaluates the smoothing's filter in extra workgroups: none depends on another, and each launch
+// costs more than any one's work.
 hipError_t launch_score_merge(const Geom& g, const float* stats, int nsplit, int rows_pad, float* cst,
-                              const AllocateJob* job, hipStream_t s);
+                              const AllocateJob* job, const ConvFilterJob* taps, hipStream_t s);
 
 // Number of key-range splits per head used by the score kernels; a pure
 // function of the batch so that the workspace query and the launch agree.
@@ -64,12 +66,13 @@ int score_padded_rows(int rows, int D);
 
 // between_sweeps: optional event recorded on `s` after the first sweep (timing aid), or nullptr.
 // lse: optional fp32 [items][H_q][W] natural-log softmax denominators of the window rows; given, sweep 1 is skipped.
-// ride_along: optional allocation to run in the launch that merges the row statistics (ignored with lse: the caller
-// must check score_merge_runs(lse) and launch the allocation itself when there is no merge).
+// ride_along, ride_taps: optional allocation and filter taps to run in the launch that merges the row statistics
+// (ignored with lse, where there is no such launch: the caller launches them itself).
 hipError_t launch_score(const Geom& g, const void* q_win, const void* k, const int32_t* cu_seqlens,
                         const int32_t* seqlens_host, float* stats_ws, float* raw_out, hipStream_t s,
                         hipEvent_t between_sweeps = nullptr, const float* lse = nullptr,
-                        float* raw_second = nullptr, size_t raw_elems = 0, const AllocateJob* ride_along = nullptr);
+                        float* raw_second = nullptr, size_t raw_elems = 0, const AllocateJob* ride_along = nullptr,
+                        const ConvFilterJob* ride_taps = nullptr);
 // More than 448 window rows (d <= 128): sweep 2 runs as two launches and needs a second buffer of the size of the
 // scores (raw_second, raw_elems floats).
 bool score_needs_second_raw(int rows, int D);
@@ -93,8 +96,13 @@ hipError_t launch_smooth(const Geom& g, const float* in, bool pool_on_load, cons
                          const int32_t* seqlens_host, int n_items, double cutoff_frac, double alpha,
                          float* out, void* workspace, size_t workspace_bytes, int32_t* kstar_out, bool cutoffs_only,
                          hipStream_t s, bool filters_ready = false);
-// Lengths that are not powers of two convolve with filters that depend on the lengths and the cutoff only:
-// launch_smooth_filters prepares them in the workspace (launch_smooth does it itself unless told they are ready).
+// What lengths that are not powers of two need that depends on the lengths and the cutoff only: launch_smooth_filters
+// prepares it in the workspace (launch_smooth does it itself unless told that it is ready). smooth_filters says how much
+// that is: several launches (long_work, worth a stream of its own), or the taps alone, which can ride along elsewhere,
+// or nothing.
+struct SmoothFilters;
+SmoothFilters smooth_filters(const Geom& g, const int32_t* cu_seqlens, const int32_t* seqlens_host, int n_items,
+                             double cutoff_frac, void* workspace);
 hipError_t launch_smooth_filters(const Geom& g, const int32_t* cu_seqlens, const int32_t* seqlens_host, int n_items,
                                  double cutoff_frac, void* workspace, hipStream_t s);
 

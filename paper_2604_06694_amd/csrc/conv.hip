@@ -1,0 +1,574 @@
+// Spectral Score Smoothing with a fixed cutoff as a convolution (paper Sec. 3.3, Eqs. 17-20), for lengths that are
+// not powers of two.
+//
+// With the mask known in advance, RFFT -> mask -> IRFFT of a sequence of L samples is a circular convolution of length
+// L with the mask's taps h (conv_filter.h). The L samples meet taps h[-(L-1)] .. h[L-1], so the circular convolution
+// is a window of a linear one with 2L - 1 taps, and that fits a negacyclic convolution of length 2N, N = the power of
+// two >= L (products that wrap around fall outside the window, whatever their sign). A real negacyclic convolution of
+// length 2N costs one complex transform of N points each way and no untangling of real spectra:
+//     z[n] = (x[n] + i x[n+N]) w^n,  w = exp(i pi / 2N):   polynomials mod X^N - i, of which mod X^N + i is the mirror.
+// The samples have x[n+N] = 0, and only the real parts of the first L results are wanted:
+//     out[n] = Re( w^-n IFFT_N( FFT_N(s w^n) . FFT_N(g w^n) ) ),   g[n] = h[n] - i h[N-n]
+// (a chirp-z transform needs two such convolutions of at least L + K points for K kept bins).
+//
+// A head runs on R workgroups, one per residue of the bins mod R. Workgroup r forms its own C = N / R point input from
+// all R C samples, which costs two multiply-adds per sample because the twist and the R-point butterfly merge into
+// R constants, transforms it in LDS, multiplies by the filter's bins and transforms back; conv_join_kernel combines
+// the R results. Calls whose lengths are shared by few heads transform the filter inside the same workgroups instead
+// of in a launch of its own.
+//
+// What bounds all of this is latency: the chain of LDS exchanges of a transform (a thread keeps eight points, three
+// radix-2 stages per exchange) and, for a launch whose every wave runs through the code once, fetching the
+// instructions. So there is one copy of everything that repeats: one forward transform for filter and samples, rolled
+// loops over a head's blocks and over the twiddle table, loads without branches. (Unrolled, with a sincospi per twiddle,
+// the kernel had 63 KB of code and took 36 us per launch at any chunk size.)
+// Pool + smooth of one layer of four heads inside evict, chirp-z path before -> this: L = 13577 41 us in six launches beside
+// 50 us of filter preparation on another stream -> 19 us in two (chunks 14, join 5) and nothing beside; a smooth call on 24
+// sequences of two heads, 1500 to 30000 samples, 147 -> 41 us (taps 8, chunks 31, join 4); one layer of 30011 alone 78 -> 22,
+// 28 layers 144 -> 68. Error against 64 bits 5.2e-7 -> 1.5e-7 (2-norm, relative).
+#include <atomic>
+
+#include "smooth_common.h"
+#include "conv_filter.h"
+#include "conv.h"
+
+// Every fused multiply-add is written out: the kernels below exist in several instantiations (pooling on load or not, a
+// filter formed here or there) that have to agree to the last bit, and what the compiler contracts is up to each.
+#pragma clang fp contract(off)
+
+namespace audiokv {
+namespace {
+
+__device__ __forceinline__ cf mul(cf a, cf b) {
+    return {fmaf(a.re, b.re, -(a.im * b.im)), fmaf(a.re, b.im, a.im * b.re)};
+}
+__device__ __forceinline__ float mix(float s0, float smoothed, float alpha) { return fmaf(alpha, smoothed, (1.f - alpha) * s0); }
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));    // any head start: heads are L floats apart
+
+// exp(i pi x), |x| <= 2^16: x - k/2 is exact, and on [-1/4, 1/4] the Taylor series of cos and sin (remainders below
+// 3e-9 and 3e-10)
+__device__ __forceinline__ cf cis_pi(float x) {
+    const float k = rintf(2.f * x), r = fmaf(-0.5f, k, x), s = r * r;
+    const int q = (int)k;
+    constexpr float P2 = 9.86960440108935862f, P1 = 3.14159265358979324f;         // pi^2, pi
+    const float u = s * P2;
+    const float c = fmaf(u, fmaf(u, fmaf(u, fmaf(u, 1.f / 40320.f, -1.f / 720.f), 1.f / 24.f), -0.5f), 1.f);
+    const float v = P1 * r * fmaf(u, fmaf(u, fmaf(u, fmaf(u, 1.f / 362880.f, -1.f / 5040.f), 1.f / 120.f), -1.f / 6.f), 1.f);
+    const float a = q & 1 ? v : c, b = q & 1 ? c : v;                               // quarter turns: swap, then signs
+    return {(q + 1) & 2 ? -a : a, q & 2 ? -b : b};
+}
+
+// 4- and 8-point DFTs in registers, natural order in and out; S = -1 forwards (exp(-2 pi i / n)), +1 backwards
+template <int S>
+__device__ __forceinline__ cf mul_i(cf a) { return S < 0 ? cf{a.im, -a.re} : cf{-a.im, a.re}; }     // times S * i
+template <int S>
+__device__ __forceinline__ void dft4(cf& a, cf& b, cf& c, cf& d) {
+    const cf s0 = cadd(a, c), s1 = csub(a, c), s2 = cadd(b, d), s3 = mul_i<S>(csub(b, d));
+    a = cadd(s0, s2); b = cadd(s1, s3); c = csub(s0, s2); d = csub(s1, s3);
+}
+template <int S>
+__device__ __forceinline__ void dft8(cf (&v)[8]) {
+    constexpr float H = 0.70710678118654752f;
+    cf e0 = cadd(v[0], v[4]), e1 = cadd(v[1], v[5]), e2 = cadd(v[2], v[6]), e3 = cadd(v[3], v[7]);
+    cf o0 = csub(v[0], v[4]), o1 = csub(v[1], v[5]), o2 = csub(v[2], v[6]), o3 = csub(v[3], v[7]);
+    o1 = S < 0 ? cf{H * (o1.re + o1.im), H * (o1.im - o1.re)} : cf{H * (o1.re - o1.im), H * (o1.im + o1.re)};
+    o2 = mul_i<S>(o2);
+    o3 = S < 0 ? cf{H * (o3.im - o3.re), -H * (o3.re + o3.im)} : cf{-H * (o3.re + o3.im), H * (o3.re - o3.im)};
+    dft4<S>(e0, e1, e2, e3);
+    dft4<S>(o0, o1, o2, o3);
+    v[0] = e0; v[2] = e1; v[4] = e2; v[6] = e3;
+    v[1] = o0; v[3] = o1; v[5] = o2; v[7] = o3;
+}
+
+// In-place transforms of C = 2^LOGC points by C / 8 threads. Forwards the passes take the index bits from the top,
+// three at a time, and leave every group's outputs where its inputs were, so the bins end in a digit-reversed order
+// that nobody has to know: the filter's bins are in the same order, and backwards the passes mirror it.
+//   first layout: thread t holds points t + (C/8) q;  last layout: thread t holds slots 8 t + e  (e, q = 0..7)
+template <int LOGC>
+struct Fft {
+    static constexpr int C = 1 << LOGC, THREADS = C / 8;
+    static constexpr int P8 = LOGC / 3;                       // radix-8 passes
+    static constexpr int REM = LOGC - 3 * P8;                 // bits left for a pass of radix 2 or 4 on the last layout
+    static constexpr int TW = REM ? P8 : P8 - 1;              // passes with twiddles
+    struct Twiddles { cf w1[TW], w2[TW], w4[TW]; };           // root_{8m}^(j0 {1, 2, 4}) of this thread, per pass
+    static constexpr int low_bit(int p) { return LOGC - 3 * (p + 1); }
+
+    __device__ __forceinline__ static int base(int p, int t) {
+        const int sb = low_bit(p);
+        return ((t >> sb) << (sb + 3)) | (t & ((1 << sb) - 1));
+    }
+    // roots of unity exp(-2 pi i e / C), e < C/2, four per thread
+    __device__ __forceinline__ static void fill_table(cf* table, int t) {
+#pragma unroll 1
+        for (int e = t; e < C / 2; e += THREADS) table[e] = cis_pi(-(float)e / (float)(C / 2));
+    }
+    __device__ __forceinline__ static void init(Twiddles& tw, const cf* table, int t) {
+#pragma unroll
+        for (int p = 0; p < TW; ++p) {
+            const int e = (t & ((1 << low_bit(p)) - 1)) << (3 * p);      // j0 / 8m in units of 1 / C; 4 e < C / 2
+            tw.w1[p] = table[e]; tw.w2[p] = table[2 * e]; tw.w4[p] = table[4 * e];
+        }
+    }
+    template <bool CONJ>
+    __device__ __forceinline__ static void twist(cf (&v)[8], const Twiddles& tw, int p) {
+        const cf w1 = CONJ ? cconj(tw.w1[p]) : tw.w1[p], w2 = CONJ ? cconj(tw.w2[p]) : tw.w2[p];
+        const cf w4 = CONJ ? cconj(tw.w4[p]) : tw.w4[p], w3 = mul(w1, w2);
+        v[1] = mul(v[1], w1); v[2] = mul(v[2], w2); v[3] = mul(v[3], w3); v[4] = mul(v[4], w4);
+        v[5] = mul(v[5], mul(w1, w4)); v[6] = mul(v[6], mul(w2, w4)); v[7] = mul(v[7], mul(w3, w4));
+    }
+    template <int S>
+    __device__ __forceinline__ static void small_dfts(cf (&v)[8]) {
+        if constexpr (REM == 1) {
+#pragma unroll
+            for (int e = 0; e < 8; e += 2) { const cf a = v[e], b = v[e + 1]; v[e] = cadd(a, b); v[e + 1] = csub(a, b); }
+        } else if constexpr (REM == 2) {
+            dft4<S>(v[0], v[1], v[2], v[3]);
+            dft4<S>(v[4], v[5], v[6], v[7]);
+        }
+    }
+    __device__ __forceinline__ static void put(cf* z, const cf (&v)[8], int b, int sb) {
+#pragma unroll
+        for (int q = 0; q < 8; ++q) z[pad(b + (q << sb))] = v[q];
+    }
+    __device__ __forceinline__ static void get(const cf* z, cf (&v)[8], int b, int sb) {
+#pragma unroll
+        for (int q = 0; q < 8; ++q) v[q] = z[pad(b + (q << sb))];
+    }
+    // first layout in, last layout out; every thread's own first-layout slots are free
+    __device__ __forceinline__ static void forward(cf (&v)[8], cf* z, const Twiddles& tw, int t) {
+#pragma unroll
+        for (int p = 0; p < P8; ++p) {
+            const int sb = low_bit(p), b = base(p, t);
+            if (p) get(z, v, b, sb);
+            dft8<-1>(v);
+            if (p < TW) twist<false>(v, tw, p);
+            if (p + 1 < P8 || REM) { put(z, v, b, sb); __syncthreads(); }
+        }
+        if (REM) { get(z, v, 8 * t, 0); small_dfts<-1>(v); }
+    }
+    // last layout in, first layout out, unnormalised
+    __device__ __forceinline__ static void backward(cf (&v)[8], cf* z, const Twiddles& tw, int t) {
+        if (REM) { small_dfts<1>(v); put(z, v, 8 * t, 0); __syncthreads(); }
+#pragma unroll
+        for (int p = P8 - 1; p >= 0; --p) {
+            const int sb = low_bit(p), b = base(p, t);
+            if (p + 1 < P8 || REM) get(z, v, b, sb);
+            if (p < TW) twist<true>(v, tw, p);
+            dft8<1>(v);
+            if (p) { put(z, v, b, sb); __syncthreads(); }
+        }
+    }
+};
+
+// Pooled values around samples 4 .. 11 of a window of 16. Same taps, order of additions and reciprocal as pooled_at
+// (which is what makes the fused path equal the staged one): POOL = 7, the usual size, spelled out; POOL = 9 for any
+// size up to 9, where the taps outside the kernel are replaced by the padding's neutral value.
+template <int POOL>
+__device__ __forceinline__ void pooled_window(const float (&w)[16], int kernel, int mode, float (&o)[8]) {
+    const int half = POOL == 7 ? 3 : kernel >> 1;
+    if (mode == AUDIOKV_POOL_AVG) {
+        const float inv = POOL == 7 ? 1.0f / 7.0f : 1.0f / (float)kernel;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            float a = 0.f;
+#pragma unroll
+            for (int u = -(POOL / 2); u <= POOL / 2; ++u) a += POOL == 7 || (u < 0 ? -u : u) <= half ? w[4 + e + u] : 0.f;
+            o[e] = a * inv;
+        }
+    } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            float a = -INFINITY;
+#pragma unroll
+            for (int u = -(POOL / 2); u <= POOL / 2; ++u)
+                a = fmaxf(a, POOL == 7 || (u < 0 ? -u : u) <= half ? w[4 + e + u] : -INFINITY);
+            o[e] = a;
+        }
+    }
+}
+// N consecutive floats from `at` (any alignment)
+template <int N>
+__device__ __forceinline__ void window_load(const float* __restrict__ at, float (&w)[N]) {
+#pragma unroll
+    for (int u = 0; u < N / 4; ++u) {
+        const f32x4 a = *reinterpret_cast<const f32x4u*>(at + 4 * u);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) w[4 * u + e] = a[e];
+    }
+}
+
+struct ConvHead { int L, log_n, R, owner; size_t off; };
+
+__device__ __forceinline__ bool conv_head(const Geom& g, const ConvFilterJob& job, int head, int log_c, ConvHead& w) {
+    const int item = head / g.H_kv, h = head - item * g.H_kv;
+    const int tok0 = job.cu_seqlens[item];
+    w.L = job.cu_seqlens[item + 1] - tok0;
+    if (!conv_item(job, w.L)) return false;
+    w.log_n = conv_log_points(w.L, log_c);
+    w.R = 1 << (w.log_n - log_c);
+    w.owner = conv_owner(job.cu_seqlens, item, w.L);
+    w.off = (size_t)tok0 * g.H_kv + (size_t)h * w.L;
+    return true;
+}
+
+// What both transforms of a workgroup start from: points n = 8 t + e + C k of all R blocks k, weighted by the constants
+// c[k], summed over k. U blocks' loads are in flight together, none behind a branch: what lies outside the sequence
+// is read and masked where the memory around it is known to be there, and clamped where it is not.
+
+// sum_k s[8 t + e + C k] c[k], zero from L on. POOL != 0: samples pooled; they lie inside a workspace that extends at
+// least 16 floats to either side of every head.
+template <int U, int POOL>
+__device__ __forceinline__ void gather_samples(const float* __restrict__ src, const ConvHead& w, int C, int kernel, int mode,
+                                               const cf* __restrict__ c, int t, cf (&acc)[8]) {
+    constexpr int LEN = POOL ? 16 : 8, AT = POOL ? 4 : 0;
+    const float fill = POOL && mode == AUDIOKV_POOL_MAX ? -INFINITY : 0.f;
+#pragma unroll 1
+    for (int k0 = 0; k0 < w.R; k0 += U) {
+        float x[U][LEN];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int n0 = (k0 + u) * C + 8 * t;
+            // (blocks past the end: from L on. Unpooled, the last block that holds samples: moved to end at L - 1, undone below)
+            if (POOL || w.L >= 8) {                          // (uniform)
+                window_load(src + (POOL ? min(n0, w.L) - AT : min(n0, w.L - 8)), x[u]);
+            } else {
+#pragma unroll
+                for (int j = 0; j < LEN; ++j) x[u][j] = src[min(j, w.L - 1)];
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int n0 = (k0 + u) * C + 8 * t;
+            float o[8];
+            if constexpr (POOL != 0) {
+                // the first and the last window of a head reach beyond it
+                if (n0 < AT || n0 + LEN - AT > w.L) {
+#pragma unroll
+                    for (int j = 0; j < LEN; ++j) x[u][j] = n0 - AT + j >= 0 && n0 - AT + j < w.L ? x[u][j] : fill;
+                }
+                pooled_window<POOL>(x[u], kernel, mode, o);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) o[e] = n0 + e < w.L ? o[e] : 0.f;
+            } else {
+                const int moved = n0 - max(min(n0, w.L - 8), 0);         // 0 except from the last block on
+#pragma unroll
+                for (int e = 0; e < 8; ++e) o[e] = n0 + e < w.L || moved > 0 ? x[u][e] : 0.f;
+                if (moved > 0) {
+#pragma unroll
+                    for (int s = 4; s > 0; s >>= 1)
+                        if (moved & s) {
+#pragma unroll
+                            for (int e = 0; e < 8; ++e) o[e] = e + s < 8 ? o[e + s < 8 ? e + s : 0] : 0.f;
+                        }
+                    if (moved >= 8) {
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) o[e] = 0.f;
+                    }
+                }
+            }
+            const cf ck = c[(k0 + u) & 15];                  // (blocks past R hold no samples: their constant is unused)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) { acc[e].re = fmaf(o[e], ck.re, acc[e].re); acc[e].im = fmaf(o[e], ck.im, acc[e].im); }
+        }
+    }
+}
+
+// sum_k (h[n] - i h[N - n]) c[k], n = 8 t + e + C k; taps from L on are zero, and so is h[N] for n = 0 (a negacyclic
+// sequence has no element N). Memory past the taps is there for 8 floats.
+template <int U>
+__device__ __forceinline__ void gather_taps(const float* __restrict__ h, const ConvHead& w, int C, const cf* __restrict__ c,
+                                            int t, cf (&acc)[8]) {
+    const int N = 1 << w.log_n;
+#pragma unroll 1
+    for (int k0 = 0; k0 < w.R; k0 += U) {
+        float a[U][8], b[U][8];                              // b holds h[low .. low + 7], low = N - n0 - 7, read forwards
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int n0 = (k0 + u) * C + 8 * t;
+            window_load(h + min(n0, w.L), a[u]);
+            window_load(h + min(max(N - n0 - 7, 0), w.L), b[u]);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int n0 = (k0 + u) * C + 8 * t, low = N - n0 - 7;       // low >= 1, or <= -7 past the last block
+            const cf ck = c[(k0 + u) & 15];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {                    // (a - i b) c
+                const float p = n0 + e < w.L ? a[u][e] : 0.f;
+                const float q = low > 0 && low + 7 - e < w.L ? b[u][7 - e] : 0.f;
+                acc[e].re = fmaf(p, ck.re, fmaf(q, ck.im, acc[e].re));
+                acc[e].im = fmaf(p, ck.im, fmaf(-q, ck.re, acc[e].im));
+            }
+        }
+    }
+}
+
+// LDS of a workgroup: the padded points, the roots of unity, and the constants of residue r:
+//   c[k] = exp(i pi k (1 - 4 r) / 2R), k < R;  step[e] = exp(i pi e (1 - 4 r) / 2N) and
+//   back[q] = exp(i pi q (4 r - 1) / 16 R), e, q < 8: factors of the twists of points 8 t + e and t + (C/8) q
+template <int LOGC>
+struct ConvLds {
+    cf z[padded_len((size_t)1 << LOGC)];
+    cf table[1 << (LOGC - 1)];
+    cf c[16], step[8], back[8];
+};
+template <int LOGC>
+__device__ __forceinline__ void fill_constants(ConvLds<LOGC>& m, const ConvHead& w, int r, int t) {
+    Fft<LOGC>::fill_table(m.table, t);
+    if (t < 32) {
+        const float a = (float)(1 - 4 * r);
+        const float x = t < 16 ? (float)(t & (w.R - 1)) * a / (float)(2 * w.R)
+                      : t < 24 ? (float)(t - 16) * a / (float)(2 << w.log_n) : -(float)(t - 24) * a / (float)(16 * w.R);
+        const cf v = cis_pi(x);
+        if (t < 16) m.c[t] = v;
+        else if (t < 24) m.step[t - 16] = v;
+        else m.back[t - 24] = v;
+    }
+    __syncthreads();
+}
+// acc, points 8 t + e, twisted and transformed: the bins of residue r in the last layout
+template <int LOGC>
+__device__ __forceinline__ void to_bins(ConvLds<LOGC>& m, const typename Fft<LOGC>::Twiddles& tw, cf tw0, int t, const cf (&acc)[8],
+                                        cf (&v)[8]) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = mul(acc[e], mul(tw0, m.step[e]));
+    Fft<LOGC>::put(m.z, v, 8 * t, 0);
+    __syncthreads();
+    Fft<LOGC>::get(m.z, v, t, LOGC - 3);
+    Fft<LOGC>::forward(v, m.z, tw, t);
+}
+
+// the filter's bins of every distinct length, for calls in which many heads share them
+template <int LOGC>
+__global__ __launch_bounds__(Fft<LOGC>::THREADS) void conv_spectrum_kernel(Geom g, ConvFilterJob job, cf* __restrict__ spec,
+                                                                           size_t spec_stride)
+{
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    ConvLds<LOGC>& m = *reinterpret_cast<ConvLds<LOGC>*>(smem);
+    ConvHead w;
+    const int item = blockIdx.y, r = blockIdx.x, t = threadIdx.x;
+    if (!conv_head(g, job, item * g.H_kv, LOGC, w) || w.owner != item || r >= w.R) return;
+    fill_constants<LOGC>(m, w, r, t);
+    typename Fft<LOGC>::Twiddles tw;
+    Fft<LOGC>::init(tw, m.table, t);
+    cf acc[8], v[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) acc[e] = {0.f, 0.f};
+    gather_taps<4>(job.h + item * job.item_stride, w, 1 << LOGC, m.c, t, acc);
+    to_bins<LOGC>(m, tw, cis_pi((float)(8 * t) * (float)(1 - 4 * r) / (float)(2 << w.log_n)), t, acc, v);
+    cf* out = spec + (size_t)item * spec_stride + ((size_t)r << LOGC) + 8 * t;
+#pragma unroll
+    for (int e = 0; e < 8; e += 2)
+        *reinterpret_cast<f32x4*>(out + e) = f32x4{v[e].re, v[e].im, v[e + 1].re, v[e + 1].im};
+}
+
+template <int LOGC, int POOL>
+__global__ __launch_bounds__(Fft<LOGC>::THREADS) void conv_chunk_kernel(
+    Geom g, const float* __restrict__ in, ConvFilterJob job, const cf* __restrict__ spec, size_t spec_stride,
+    cf* __restrict__ part, size_t part_stride, float alpha, float* __restrict__ out)
+{
+    constexpr int C = 1 << LOGC, T = Fft<LOGC>::THREADS;
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    ConvLds<LOGC>& m = *reinterpret_cast<ConvLds<LOGC>*>(smem);
+    constexpr int U = LOGC == 13 ? 2 : 4;                        // (1024 threads: 128 registers)
+    ConvHead w;
+    const int head = blockIdx.y, r = blockIdx.x, t = threadIdx.x;
+    if (!conv_head(g, job, head, LOGC, w) || r >= w.R) return;
+    fill_constants<LOGC>(m, w, r, t);
+    typename Fft<LOGC>::Twiddles tw;
+    Fft<LOGC>::init(tw, m.table, t);
+    const float a = (float)(1 - 4 * r);
+    const cf tw0 = cis_pi((float)(8 * t) * a / (float)(2 << w.log_n));
+    const float* src = in + w.off;
+
+    cf f[8], v[8];
+    if (spec) {
+        const cf* b = spec + (size_t)w.owner * spec_stride + ((size_t)r << LOGC) + 8 * t;
+#pragma unroll
+        for (int e = 0; e < 8; e += 2) {
+            const f32x4 p = *reinterpret_cast<const f32x4*>(b + e);
+            v[e] = {p[0], p[1]}; v[e + 1] = {p[2], p[3]};
+        }
+    }
+#pragma unroll 1
+    for (int pass = spec ? 1 : 0; pass < 2; ++pass) {
+        cf acc[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) { f[e] = v[e]; acc[e] = {0.f, 0.f}; }
+        if (pass == 0) gather_taps<U>(job.h + w.owner * job.item_stride, w, C, m.c, t, acc);
+        else gather_samples<U, POOL>(src, w, C, g.pool_kernel, g.pool_mode, m.c, t, acc);
+        to_bins<LOGC>(m, tw, tw0, t, acc, v);
+    }
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = mul(v[e], f[e]);
+    Fft<LOGC>::backward(v, m.z, tw, t);
+
+    // twisted back: point n = t + T q of residue r by exp(i pi n (4 r - 1) / 2N); 1/N completes the inverse transform
+    const float inv_n = 1.0f / (float)(1 << w.log_n);
+    cf back0 = cis_pi(-(float)t * a / (float)(2 << w.log_n));
+    back0 = {back0.re * inv_n, back0.im * inv_n};
+    cf* dst = part + (size_t)head * part_stride + (size_t)r * C;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+        const cf u = mul(v[q], mul(back0, m.back[q]));
+        const int n = t + T * q;
+        if (w.R > 1) dst[n] = u;
+        else if (n < w.L) {                                      // a head of one workgroup is done
+            float st = u.re;
+            if (alpha != 1.f) {
+                const float s0 = POOL ? pooled_at(src, w.L, n, g.pool_kernel, g.pool_mode) : src[n];
+                st = mix(s0, st, alpha);
+            }
+            out[w.off + n] = st;
+        }
+    }
+}
+
+// out[n + C t] = Re sum_r part_r[n] exp(i pi (4 r - 1) t / 2R), t = 0..R-1: an R-point inverse DFT and a rotation
+template <int R>
+__device__ __forceinline__ void join(const cf* __restrict__ p, int C, int n, float* o) {
+    cf v[16];
+#pragma unroll
+    for (int r = 0; r < R; ++r) v[r] = p[(size_t)r * C + n];
+    if constexpr (R == 2) { const cf a = v[0]; v[0] = cadd(a, v[1]); v[1] = csub(a, v[1]); }
+    else if constexpr (R == 4) dft4<1>(v[0], v[1], v[2], v[3]);
+    else if constexpr (R == 8) dft8<1>(reinterpret_cast<cf(&)[8]>(v));
+    else {
+        // sixteen points as two of eight: even and odd residues
+        cf e[8], d[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) { e[k] = v[2 * k]; d[k] = v[2 * k + 1]; }
+        dft8<1>(e);
+        dft8<1>(d);
+        constexpr float C1 = 0.92387953251128674f, S1 = 0.38268343236508977f, H = 0.70710678118654752f;
+        constexpr cf root[8] = {{1.f, 0.f}, {C1, S1}, {H, H}, {S1, C1}, {0.f, 1.f}, {-S1, C1}, {-H, H}, {-C1, S1}};
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            const cf x = mul(d[k], root[k]);
+            v[k] = cadd(e[k], x);
+            v[k + 8] = csub(e[k], x);
+        }
+    }
+    // exp(-i pi t / 2R)
+    constexpr cf unit[16] = {{1.f, 0.f}, {0.99518472667219689f, 0.098017140329560602f}, {0.98078528040323045f, 0.19509032201612827f},
+                             {0.95694033573220887f, 0.29028467725446237f}, {0.92387953251128676f, 0.38268343236508977f},
+                             {0.88192126434835503f, 0.47139673682599764f}, {0.83146961230254524f, 0.55557023301960222f},
+                             {0.77301045336273696f, 0.63439328416364549f}, {0.70710678118654752f, 0.70710678118654752f},
+                             {0.63439328416364549f, 0.77301045336273696f}, {0.55557023301960222f, 0.83146961230254524f},
+                             {0.47139673682599764f, 0.88192126434835503f}, {0.38268343236508977f, 0.92387953251128676f},
+                             {0.29028467725446237f, 0.95694033573220887f}, {0.19509032201612827f, 0.98078528040323045f},
+                             {0.098017140329560602f, 0.99518472667219689f}};      // cos, sin of pi t / 32
+#pragma unroll
+    for (int t = 0; t < R; ++t) {
+        const cf c = unit[t * (16 / R)];
+        o[t] = fmaf(v[t].re, c.re, v[t].im * c.im);
+    }
+}
+
+constexpr int kJoinThreads = 64;
+
+__global__ __launch_bounds__(kJoinThreads) void conv_join_kernel(
+    Geom g, const float* __restrict__ in, int pool_on_load, ConvFilterJob job, int log_c, const cf* __restrict__ part,
+    size_t part_stride, float alpha, float* __restrict__ out)
+{
+    ConvHead w;
+    const int head = blockIdx.y, C = 1 << log_c;
+    if (!conv_head(g, job, head, log_c, w) || w.R == 1) return;
+    const int n = blockIdx.x * kJoinThreads + threadIdx.x;               // grid.x * kJoinThreads = C
+    const cf* p = part + (size_t)head * part_stride;
+    const float* src = in + w.off;
+    float* dst = out + w.off;
+    float o[16];
+    switch (w.R) {
+        case 2:  join<2>(p, C, n, o); break;
+        case 4:  join<4>(p, C, n, o); break;
+        case 8:  join<8>(p, C, n, o); break;
+        default: join<16>(p, C, n, o); break;
+    }
+#pragma unroll
+    for (int t = 0; t < 16; ++t) {
+        const int j = n + t * C;
+        if (t < w.R && j < w.L) {
+            float st = o[t];
+            if (alpha != 1.f) {
+                const float s0 = pool_on_load ? pooled_at(src, w.L, j, g.pool_kernel, g.pool_mode) : src[j];
+                st = mix(s0, st, alpha);
+            }
+            dst[j] = st;
+        }
+    }
+}
+
+__global__ __launch_bounds__(kConvFilterThreads) void conv_filter_kernel(ConvFilterJob job) { conv_filter_block(job, blockIdx.x); }
+
+template <int LOGC, int POOL>
+hipError_t launch_chunks(const Geom& g, const ConvCall& c, const float* in, float alpha, float* out, hipStream_t s) {
+    const int lds = (int)sizeof(ConvLds<LOGC>);
+    if (lds > 48 * 1024) {
+        static std::atomic<bool> attr_set{false};
+        if (!attr_set) {
+            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(conv_chunk_kernel<LOGC, POOL>),
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+            if (e != hipSuccess) return e;
+            attr_set = true;
+        }
+    }
+    hipLaunchKernelGGL((conv_chunk_kernel<LOGC, POOL>), dim3((unsigned)c.max_r, (unsigned)(g.n_items * g.H_kv)),
+                       dim3(Fft<LOGC>::THREADS), lds, s, g, in, c.job, (const cf*)c.spec, c.points, (cf*)c.part, c.points, alpha, out);
+    return hipGetLastError();
+}
+template <int LOGC>
+hipError_t launch_chunks(const Geom& g, const ConvCall& c, const float* in, bool pool_on_load, float alpha, float* out, hipStream_t s) {
+    if (!pool_on_load) return launch_chunks<LOGC, 0>(g, c, in, alpha, out, s);
+    if (g.pool_kernel == 7) return launch_chunks<LOGC, 7>(g, c, in, alpha, out, s);
+    return launch_chunks<LOGC, 9>(g, c, in, alpha, out, s);
+}
+template <int LOGC>
+hipError_t launch_spectra(const Geom& g, const ConvCall& c, hipStream_t s) {
+    const int lds = (int)sizeof(ConvLds<LOGC>);
+    if (lds > 48 * 1024) {
+        static std::atomic<bool> attr_set{false};
+        if (!attr_set) {
+            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(conv_spectrum_kernel<LOGC>),
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+            if (e != hipSuccess) return e;
+            attr_set = true;
+        }
+    }
+    hipLaunchKernelGGL((conv_spectrum_kernel<LOGC>), dim3((unsigned)c.max_r, (unsigned)g.n_items), dim3(Fft<LOGC>::THREADS), lds, s,
+                       g, c.job, (cf*)c.spec, c.points);
+    return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_conv_filter(const Geom& g, const ConvCall& c, hipStream_t s) {
+    hipLaunchKernelGGL(conv_filter_kernel, dim3((unsigned)(c.job.blocks_per_item * c.job.n_items)), dim3(kConvFilterThreads),
+                       0, s, c.job);
+    if (!c.spec) return hipGetLastError();
+    switch (c.log_c) {
+        case 10: return launch_spectra<10>(g, c, s);
+        case 11: return launch_spectra<11>(g, c, s);
+        case 12: return launch_spectra<12>(g, c, s);
+        default: return launch_spectra<13>(g, c, s);
+    }
+}
+
+hipError_t launch_conv(const Geom& g, const ConvCall& c, const float* in, bool pool_on_load, float alpha, float* out, hipStream_t s) {
+    if (pool_on_load && g.pool_kernel > kConvMaxPool) return hipErrorInvalidValue;      // (pooled beforehand)
+    hipError_t e;
+    switch (c.log_c) {
+        case 10: e = launch_chunks<10>(g, c, in, pool_on_load, alpha, out, s); break;
+        case 11: e = launch_chunks<11>(g, c, in, pool_on_load, alpha, out, s); break;
+        case 12: e = launch_chunks<12>(g, c, in, pool_on_load, alpha, out, s); break;
+        default: e = launch_chunks<13>(g, c, in, pool_on_load, alpha, out, s); break;
+    }
+    if (e != hipSuccess || c.max_r == 1) return e;
+    hipLaunchKernelGGL(conv_join_kernel, dim3((1u << c.log_c) / kJoinThreads, (unsigned)(g.n_items * g.H_kv)), dim3(kJoinThreads),
+                       0, s, g, in, pool_on_load ? 1 : 0, c.job, c.log_c, (const cf*)c.part, c.points, alpha, out);
+    return hipGetLastError();
+}
+
+}  // namespace audiokv

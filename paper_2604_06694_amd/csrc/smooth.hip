@@ -13,16 +13,16 @@
 // that depends on the position inside the 16-point group is a constant 16th
 // root of unity.
 //
-// Any other length (the transform length must be exactly L: zero-padding would be a different circular
-// filter) goes through Bluestein's chirp-z identity: a length-L DFT is a convolution with a chirp, done with
-// power-of-two FFTs in a per-head global-memory workspace. Only the K = k* + T + 1 lowest bins are ever needed
-// (everything above is masked), so the convolutions have L + K - 1 significant points and the transform size is
-// M >= L + K - 1 rather than 2L - 1: half the size for most lengths at the usual cutoffs. Stages whose span
-// exceeds the LDS (M > 16384) run on global memory, the rest on 16384-point chunks inside LDS.
+// With a fixed cutoff any other length is convolved with the mask's taps (conv.hip). What is left for lengths that are not powers of two is the energy-adaptive cutoff, which needs the whole
+// spectrum before there is a mask: Bluestein's chirp-z identity (the transform length must be exactly L: zero-padding
+// would be a different circular filter), a convolution with a chirp done with power-of-two FFTs in a per-head
+// global-memory workspace, M >= L + L/2 points. Stages whose span exceeds the LDS (M > 16384) run on global memory,
+// the rest on 16384-point chunks inside LDS.
 #include <atomic>
 #include <type_traits>
 #include <algorithm>
-#include "common.h"
+#include "smooth_common.h"
+#include "conv.h"
 
 namespace audiokv {
 
@@ -30,79 +30,16 @@ namespace {
 
 // ----------------------------- pooling --------------------------------------
 
-// Pooled value at position j of one head's sequence x[0..L) (global or LDS).
-__device__ __forceinline__ float pooled_at(const float* x, int L, int j, int kernel, int mode) {
-    const int half = kernel >> 1;
-    if (mode == AUDIOKV_POOL_AVG) {
-        float acc = 0.f;
-        for (int t = -half; t <= half; ++t) {
-            const int p = j + t;
-            acc += (p >= 0 && p < L) ? x[p] : 0.f;       // zero padding
-        }
-        return acc * (1.0f / (float)kernel);              // divisor is always the kernel size (one rounded reciprocal)
-    }
-    float acc = -INFINITY;
-    for (int t = -half; t <= half; ++t) {
-        const int p = j + t;
-        if (p >= 0 && p < L) acc = fmaxf(acc, x[p]);
-    }
-    return acc;
-}
-
-// Pooled values at positions j0 and j0 + 1 of a sequence held in LDS, kernel size K known at compile time. Same
-// taps, padding, order of operations and reciprocal as pooled_at, so both give the same bits.
-template <int K>
-__device__ __forceinline__ void pooled_pair_lds(const float* x, int L, int j0, int mode, float& o0, float& o1) {
-    const float fill = mode == AUDIOKV_POOL_AVG ? 0.f : -INFINITY;
-    float w[K + 1];
-    if (j0 - K / 2 >= 0 && j0 + 1 + K / 2 < L) {     // every tap inside the sequence: all but the edge threads
-#pragma unroll
-        for (int u = 0; u <= K; ++u) w[u] = x[j0 - K / 2 + u];
-    } else {
-#pragma unroll
-        for (int u = 0; u <= K; ++u) {
-            const int p = j0 - K / 2 + u;
-            const float v = x[min(max(p, 0), L - 1)];
-            w[u] = (p >= 0 && p < L) ? v : fill;
-        }
-    }
-    if (mode == AUDIOKV_POOL_AVG) {
-        float a0 = 0.f, a1 = 0.f;
-#pragma unroll
-        for (int u = 0; u < K; ++u) { a0 += w[u]; a1 += w[u + 1]; }
-        o0 = a0 * (1.0f / (float)K);
-        o1 = a1 * (1.0f / (float)K);
-    } else {
-        float a0 = -INFINITY, a1 = -INFINITY;
-#pragma unroll
-        for (int u = 0; u < K; ++u) { a0 = fmaxf(a0, w[u]); a1 = fmaxf(a1, w[u + 1]); }
-        o0 = a0;
-        o1 = a1;
-    }
-}
-
-// Pooled values at positions j0 and j0 + 1 of x[0..L) (global memory or LDS): the common kernel sizes take all their
-// taps at once (independent loads), any other size goes tap by tap. Same bits either way.
-__device__ __forceinline__ void pooled_pair(const float* x, int L, int j0, int kernel, int mode, float& o0, float& o1) {
-    switch (kernel) {
-        case 3:  pooled_pair_lds<3>(x, L, j0, mode, o0, o1); break;
-        case 5:  pooled_pair_lds<5>(x, L, j0, mode, o0, o1); break;
-        case 7:  pooled_pair_lds<7>(x, L, j0, mode, o0, o1); break;
-        case 9:  pooled_pair_lds<9>(x, L, j0, mode, o0, o1); break;
-        default:
-            o0 = pooled_at(x, L, j0, kernel, mode);
-            o1 = pooled_at(x, L, j0 + 1, kernel, mode);
-    }
-}
-
 __global__ __launch_bounds__(256) void pool_kernel(Geom g, const float* __restrict__ raw,
                                                    const int32_t* __restrict__ cu_seq,
-                                                   float* __restrict__ pooled)
+                                                   float* __restrict__ pooled,
+                                                   ConvFilterJob only)     // if only.h: the heads of that job
 {
     const int head = blockIdx.y;
     const int item = head / g.H_kv, h = head - item * g.H_kv;
     const int tok0 = cu_seq[item];
     const int L = cu_seq[item + 1] - tok0;
+    if (only.h && !conv_item(only, L)) return;
     const size_t off = (size_t)tok0 * g.H_kv + (size_t)h * L;
     for (int j = blockIdx.x * blockDim.x + threadIdx.x; j < L; j += gridDim.x * blockDim.x)
         pooled[off + j] = pooled_at(raw + off, L, j, g.pool_kernel, g.pool_mode);
@@ -111,26 +48,13 @@ __global__ __launch_bounds__(256) void pool_kernel(Geom g, const float* __restri
 // ------------------------ LDS-resident real FFT ------------------------------
 
 constexpr int kFftThreads = 1024;
-constexpr int kMaxPow2L = 32768;          // 128 KiB of fp32 in LDS
 constexpr int kTwLo = 128;
 
-__host__ __device__ inline bool pow2_length(int L) { return L >= 4 && L <= kMaxPow2L && (L & (L - 1)) == 0; }
-
-struct cf { float re, im; };
-__device__ __forceinline__ cf cmul(cf a, cf b) { return {a.re * b.re - a.im * b.im, a.re * b.im + a.im * b.re}; }
-__device__ __forceinline__ cf cadd(cf a, cf b) { return {a.re + b.re, a.im + b.im}; }
-__device__ __forceinline__ cf csub(cf a, cf b) { return {a.re - b.re, a.im - b.im}; }
-__device__ __forceinline__ cf cconj(cf a) { return {a.re, -a.im}; }
 
 // exp(-2*pi*i*e/L) for 0 <= e <= L/2
 __device__ __forceinline__ cf twiddle(const cf* lo, const cf* hi, int e) {
     return cmul(hi[e >> 7], lo[e & (kTwLo - 1)]);
 }
-
-// LDS slot of complex element i. One spare slot per 16 elements: a thread's 16-point group at stride 1 or 4 would
-// otherwise sit in a single bank.
-__device__ __forceinline__ int pad(int i) { return i + (i >> 4); }
-__host__ __device__ constexpr size_t padded_len(size_t n) { return n + (n >> 4) + 1; }
 
 // w * exp(-2*pi*i*k/16) for k = 0..7; k is a compile-time constant once the callers' loops are unrolled
 __device__ __forceinline__ cf mul_root16(cf w, int k) {
@@ -241,16 +165,6 @@ __device__ __forceinline__ float mask_weight(int k, int kstar, int T) {
     return 0.5f * (1.f + cospif((float)(k - kstar) / (float)(T + 1)));
 }
 
-// Masks for which the filter needs no transform at all, and for which a transform would only add rounding noise to
-// what is exactly a plateau or exactly the input (the selection that follows breaks ties by index, so the noise
-// would decide instead): 2 = every bin is kept with weight 1 (Eq. 19 returns s itself), 1 = only the DC bin
-// survives (Eq. 19 returns the mean of s at every position), 0 = anything else.
-__host__ __device__ inline int degenerate_mask(int L, int kstar, int T) {
-    if (kstar >= (L >> 1)) return 2;
-    if (kstar + T == 0) return 1;
-    return 0;
-}
-
 // The result for a degenerate mask, by all kFftThreads threads of the workgroup; `part` holds kFftThreads doubles.
 // The mean is one value (float64 sum in a fixed order, rounded once), written to every position. In place is fine:
 // all reads of the mean case come before a barrier, and the copy case reads position n only to write position n.
@@ -348,7 +262,7 @@ __global__ __launch_bounds__(kFftThreads) void smooth_pow2_kernel(
             dst[j] = pool_on_load ? pooled_at(src, L, j, g.pool_kernel, g.pool_mode) : src[j];
         return;
     }
-    if (!pow2_length(L)) return;                      // the chirp-z kernel owns this head
+    if (!pow2_length(L)) return;                      // other kernels own this head
     if (skip_dec && dec_owns(g, L, cutoff_frac)) return;   // spread over several workgroups by the dec_* kernels
     const int T = g.taper_bins;
     if (g.cutoff_mode == AUDIOKV_CUTOFF_FRACTION && cutoffs_only) {
@@ -699,7 +613,7 @@ __global__ __launch_bounds__(kDecThreads) void dec_inverse_kernel(
 // ------------------------ arbitrary length: Bluestein over global memory -----------------------
 
 constexpr int kChunkLog = 14;                     // 16384 complex = 128 KiB: the part of an FFT that fits in LDS
-constexpr int kWideMinLog = 12;                   // transforms of 4096 points and more are spread over four workgroups,
+constexpr int kWideMinLog = 12;                   // filters of 4096 points and more are prepared by four workgroups,
 constexpr int kWideMaxLog = 18;                   // in chunks of at most 16384 points: four up to 65536, then 8 or 16
 constexpr int kMaxBluesteinLog = 18;              // M <= 262144: any L <= 131072 at any cutoff
 __host__ __device__ inline bool wide_size(int logM) { return logM >= kWideMinLog && logM <= kWideMaxLog; }
@@ -952,7 +866,7 @@ __global__ __launch_bounds__(kFftThreads) void bluestein_prepare_kernel(const in
 __global__ __launch_bounds__(kFftThreads) void smooth_bluestein_kernel(
     Geom g, const float* __restrict__ in, int pool_on_load, const int32_t* __restrict__ cu_seq,
     double cutoff_frac, float alpha, float* __restrict__ out, BluesteinWs ws,
-    int32_t* __restrict__ kstar_out, int cutoffs_only, int skip_wide)
+    int32_t* __restrict__ kstar_out, int cutoffs_only, ConvFilterJob conv)
 {
     extern __shared__ float smem[];
     const int head = blockIdx.x;
@@ -965,9 +879,7 @@ __global__ __launch_bounds__(kFftThreads) void smooth_bluestein_kernel(
     // the transform size would have been)
     const int fixed_kind = g.cutoff_mode == AUDIOKV_CUTOFF_FRACTION
                                ? degenerate_mask(L, (int)floor(cutoff_frac * (double)(L >> 1)), T) : 0;
-    // all but the small transforms are spread over several workgroups by the kernels below
-    if (skip_wide && fixed_kind == 0 &&
-        wide_size(bluestein_log(L, wanted_bins(L, cutoff_frac, g.cutoff_mode, g.taper_bins)))) return;
+    if (conv.h && conv_item(conv, L)) return;         // smoothed by the convolution path
     const size_t off = (size_t)tok0 * g.H_kv + (size_t)h * L;
     const float* src = in + off;
     float* dst = out + off;
@@ -1060,14 +972,10 @@ __global__ __launch_bounds__(kFftThreads) void smooth_bluestein_kernel(
     }
 }
 
-// ---- transforms of 4096 points and more, spread over several workgroups (fixed-fraction cutoff) -------------------
-// The same convolutions as above, cut at the points where every element of the array has to be complete:
-//   wide_first   chirped input formed on the fly, forward top stage(s)            (one thread per butterfly)
-//   wide_chunk   per chunk of M / 4 points: forward LDS stages, x filter, inverse LDS stages
-//   wide_middle  inverse top stage(s) -> bins; mask; input of the inverse transform; forward top stage(s)
-//   wide_chunk   again, with the second filter
-//   wide_last    inverse top stage(s) -> samples; residual mix; store
-// Few heads (one layer of a prefill) then use 8-64 workgroups per head instead of one.
+// ---- the filters of transforms of 4096 points and more, prepared by several workgroups --------------------------
+// One workgroup per head runs the energy-adaptive transforms themselves, but their filters depend on the length only
+// and are cut where every element of the array has to be complete: chirp table; wrapped filter + forward top
+// stage(s), one thread per butterfly; chunk-local stages in LDS; second filter by the frequency-negating gather.
 
 constexpr int kWideThreads = 256;
 
@@ -1082,8 +990,6 @@ __device__ __forceinline__ bool wide_head(const Geom& g, const int32_t* __restri
     const int tok0 = cu_seq[item];
     w.L = cu_seq[item + 1] - tok0;
     if (pow2_length(w.L)) return false;
-    // (the multi-workgroup sequence runs with a fixed cutoff only) masks that need no transform: single-workgroup kernel
-    if (degenerate_mask(w.L, (int)floor(cutoff_frac * (double)(w.L >> 1)), g.taper_bins) != 0) return false;
     w.K = wanted_bins(w.L, cutoff_frac, g.cutoff_mode, g.taper_bins);
     w.logM = bluestein_log(w.L, w.K);
     if (!wide_size(w.logM)) return false;              // small or very large: the single-workgroup kernel owns it
@@ -1165,8 +1071,6 @@ __device__ __forceinline__ void top_butterfly(cf* v, int i, int M, int extra, bo
     v[0] = a0; v[1] = a1; v[2] = a2; v[3] = a3;
 }
 
-// preparation of the filters of a wide transform, spread the same way: chirp table; wrapped filter + forward top
-// stage(s); chunk-local stages (wide_chunk_kernel, which_filter = -1); second filter by the frequency-negating gather.
 // Grids run over the first head of every item; only items that own their length work.
 __device__ __forceinline__ bool wide_owner(const Geom& g, const int32_t* __restrict__ cu_seq, int item, double cutoff_frac,
                                            WideHead& w) {
@@ -1228,45 +1132,13 @@ __global__ __launch_bounds__(kWideThreads) void wide_prep_second_kernel(Geom g, 
     }
 }
 
-template <int MAXR>
-__global__ __launch_bounds__(kWideThreads) void wide_first_kernel(
-    Geom g, const float* __restrict__ in, int pool_on_load, const int32_t* __restrict__ cu_seq, double cutoff_frac,
-    BluesteinWs ws)
-{
-    WideHead w;
-    const int head = blockIdx.y;
-    if (!wide_head(g, cu_seq, head, cutoff_frac, w)) return;
-    if (w.R > MAXR) return;                             // (the launcher picks the instantiation that holds every head)
-    const int i = blockIdx.x * kWideThreads + threadIdx.x;
-    if (i >= w.q) return;
-    const float* src = in + w.off;
-    const cf* ch = ws.chirp_of(w.owner);
-    cf* A = ws.a_of(head);
-    cf v[MAXR];
-#pragma unroll
-    for (int r = 0; r < MAXR; ++r) {          // (guards, not breaks: the loop must unroll for v to stay in registers)
-        const int n = i + r * w.q;
-        cf a = {0.f, 0.f};
-        if (r < w.R && n < w.L) {
-            const cf c = ch[n];
-            const float sv = pool_on_load ? pooled_at(src, w.L, n, g.pool_kernel, g.pool_mode) : src[n];
-            a = {sv * c.re, sv * c.im};
-        }
-        v[r] = a;
-    }
-    top_butterfly<MAXR>(v, i, w.M, w.extra, false);
-#pragma unroll
-    for (int r = 0; r < MAXR; ++r)
-        if (r < w.R) A[i + r * w.q] = v[r];
-}
-
-__global__ __launch_bounds__(kFftThreads) void wide_chunk_kernel(
-    Geom g, const int32_t* __restrict__ cu_seq, double cutoff_frac, BluesteinWs ws, int which_filter)
+__global__ __launch_bounds__(kFftThreads) void wide_prep_chunk_kernel(
+    Geom g, const int32_t* __restrict__ cu_seq, double cutoff_frac, BluesteinWs ws)
 {
     extern __shared__ float smem[];
     WideHead w;
-    const int head = blockIdx.y;
-    if (!wide_head(g, cu_seq, head, cutoff_frac, w)) return;
+    const int item = blockIdx.y;
+    if (!wide_owner(g, cu_seq, item, cutoff_frac, w)) return;
     const int chunk = blockIdx.x;
     if (chunk >= w.R) return;
     const int logC = w.logM - w.extra;
@@ -1275,105 +1147,10 @@ __global__ __launch_bounds__(kFftThreads) void wide_chunk_kernel(
     cf* lo = z + padded_len(C);
     cf* hi = lo + kTwLo;
     fill_tables(lo, hi, (w.M >> 8) + 1, w.M);
-    if (which_filter < 0) {
-        // preparation: chunk-local forward stages of the first filter itself (one head per item does it)
-        const int item = head / g.H_kv;
-        if (head != item * g.H_kv || w.owner != item) return;
-        cf* b = ws.bhat_of(item, 0) + (size_t)chunk * C;
-        chunk_load(z, b, C);
-        fft_lds(z, logC, w.logM - 1, false, lo, hi);
-        chunk_store(b, z, C);
-        return;
-    }
-    cf* x = ws.a_of(head) + (size_t)chunk * C;
-    const cf* bhat = ws.bhat_of(w.owner, which_filter) + (size_t)chunk * C;
-    chunk_load(z, x, C);                                // ends with a barrier: the tables are complete too
+    cf* b = ws.bhat_of(item, 0) + (size_t)chunk * C;
+    chunk_load(z, b, C);                                // ends with a barrier: the tables are complete too
     fft_lds(z, logC, w.logM - 1, false, lo, hi);
-    for (int i = 2 * threadIdx.x; i < C; i += 2 * kFftThreads) {
-        cf b0, b1;
-        ld2(bhat, i, b0, b1);
-        z[pad(i)] = cmul(z[pad(i)], b0);
-        z[pad(i + 1)] = cmul(z[pad(i + 1)], b1);
-    }
-    __syncthreads();
-    fft_lds(z, logC, w.logM - 1, true, lo, hi);
-    chunk_store(x, z, C);
-}
-
-template <int MAXR>
-__global__ __launch_bounds__(kWideThreads) void wide_middle_kernel(
-    Geom g, const int32_t* __restrict__ cu_seq, double cutoff_frac, BluesteinWs ws, int32_t* __restrict__ kstar_out)
-{
-    WideHead w;
-    const int head = blockIdx.y;
-    if (!wide_head(g, cu_seq, head, cutoff_frac, w)) return;
-    if (w.R > MAXR) return;                             // (the launcher picks the instantiation that holds every head)
-    const int i = blockIdx.x * kWideThreads + threadIdx.x;
-    const int kstar = (int)floor(cutoff_frac * (double)(w.L >> 1));
-    if (kstar_out && i == 0) kstar_out[head] = kstar;
-    if (i >= w.q) return;
-    const cf* ch = ws.chirp_of(w.owner);
-    cf* A = ws.a_of(head);
-    const float inv_m = 1.0f / (float)w.M;
-    const int T = g.taper_bins;
-    cf v[MAXR];
-#pragma unroll
-    for (int r = 0; r < MAXR; ++r) v[r] = r < w.R ? A[i + r * w.q] : cf{0.f, 0.f};
-    top_butterfly<MAXR>(v, i, w.M, w.extra, true);            // v[r] is now the convolution at position k = i + r*q
-#pragma unroll
-    for (int r = 0; r < MAXR; ++r) {
-        const int k = i + r * w.q;
-        cf o = {0.f, 0.f};
-        if (r < w.R && k < w.K) {
-            const float wgt = mask_weight(k, kstar, T) * ((k == 0 || 2 * k == w.L) ? 1.f : 2.f);
-            if (wgt > 0.f) {
-                const cf c = ch[k];
-                cf F = cmul(c, v[r]);
-                F = {F.re * inv_m * wgt, F.im * inv_m * wgt};
-                o = cmul(cconj(F), c);
-            }
-        }
-        v[r] = o;
-    }
-    top_butterfly<MAXR>(v, i, w.M, w.extra, false);
-#pragma unroll
-    for (int r = 0; r < MAXR; ++r)
-        if (r < w.R) A[i + r * w.q] = v[r];
-}
-
-template <int MAXR>
-__global__ __launch_bounds__(kWideThreads) void wide_last_kernel(
-    Geom g, const float* __restrict__ in, int pool_on_load, const int32_t* __restrict__ cu_seq, double cutoff_frac,
-    float alpha, float* __restrict__ out, BluesteinWs ws)
-{
-    WideHead w;
-    const int head = blockIdx.y;
-    if (!wide_head(g, cu_seq, head, cutoff_frac, w)) return;
-    if (w.R > MAXR) return;                             // (the launcher picks the instantiation that holds every head)
-    const int i = blockIdx.x * kWideThreads + threadIdx.x;
-    if (i >= w.q) return;
-    const float* src = in + w.off;
-    float* dst = out + w.off;
-    const cf* ch = ws.chirp_of(w.owner);
-    const cf* A = ws.a_of(head);
-    const float scale = 1.0f / (float)w.M / (float)w.L;
-    cf v[MAXR];
-#pragma unroll
-    for (int r = 0; r < MAXR; ++r) v[r] = r < w.R ? A[i + r * w.q] : cf{0.f, 0.f};
-    top_butterfly<MAXR>(v, i, w.M, w.extra, true);
-#pragma unroll
-    for (int r = 0; r < MAXR; ++r) {
-        const int n = i + r * w.q;
-        if (r < w.R && n < w.L) {
-            const cf y = cmul(ch[n], v[r]);
-            const float st = y.re * scale;
-            if (alpha == 1.f) dst[n] = st;
-            else {
-                const float s0 = pool_on_load ? pooled_at(src, w.L, n, g.pool_kernel, g.pool_mode) : src[n];
-                dst[n] = (1.f - alpha) * s0 + alpha * st;
-            }
-        }
-    }
+    chunk_store(b, z, C);
 }
 
 }  // namespace
@@ -1383,15 +1160,17 @@ hipError_t launch_pool(const Geom& g, const float* raw, const int32_t* cu_seqlen
 {
     const int n_heads = g.n_items * g.H_kv;
     const int bx = max(1, min(64, (max_L + 255) / 256));
-    hipLaunchKernelGGL(pool_kernel, dim3(bx, n_heads), dim3(256), 0, s, g, raw, cu_seqlens, pooled);
+    hipLaunchKernelGGL(pool_kernel, dim3(bx, n_heads), dim3(256), 0, s, g, raw, cu_seqlens, pooled,
+                       ConvFilterJob{});
     return hipGetLastError();
 }
 
 bool smooth_supported(int L) { return pow2_length(L) || (L >= 1 && L <= 131072 && bluestein_log_max(L) <= kMaxBluesteinLog); }
 
 namespace {
-// scratch of the chirp-z transforms (lengths that are not powers of two), sized for the largest transform any cutoff
-// can ask for (all bins wanted): per head the working array (M), per item the two filter spectra and the chirp table
+// scratch for lengths that are not powers of two, sized for the chirp-z transforms of an energy-adaptive cutoff (all
+// bins wanted): per head the working array (M), per item the two filter spectra and the chirp table. The convolution
+// path of a fixed cutoff fits in the same space.
 size_t bluestein_bytes(const int32_t* seqlens_host, int n_items, int H_kv) {
     int max_log = 0;
     for (int i = 0; i < n_items; ++i)
@@ -1414,7 +1193,7 @@ size_t dec_bytes(const int32_t* seqlens_host, int n_items, int H_kv) {
 }
 }  // namespace
 
-// The two regions follow each other in the workspace (chirp-z first). Only the first is indispensable: without room
+// The two regions follow each other in the workspace (other lengths first). Only the first is indispensable: without room
 // for the second, power-of-two heads simply stay on one workgroup each.
 size_t smooth_workspace_bytes(const int32_t* seqlens_host, int n_items, int H_kv) {
     return bluestein_bytes(seqlens_host, n_items, H_kv) + dec_bytes(seqlens_host, n_items, H_kv);
@@ -1424,18 +1203,66 @@ size_t smooth_workspace_required(const int32_t* seqlens_host, int n_items, int H
 }
 
 namespace {
-struct SmoothPlan { int max_pow2 = 0, max_log = 0; bool any_wide = false; };
+struct SmoothPlan {
+    int max_pow2 = 0, max_log = 0;        // longest power of two, log2 of the largest chirp-z transform
+    bool any_wide = false;
+    bool one_wg_other = false;            // lengths that are not powers of two and run in one workgroup per head
+    ConvCall conv;                        // the convolution path's share of them
+};
 
-SmoothPlan plan_smooth(const Geom& g, const int32_t* seqlens_host, int n_items, double cutoff_frac) {
+// Chunks of a convolution: 4096 points or the whole transform if that is shorter (one chunk, no launch to join
+// results). One layer of 4 heads, all launches of a smooth call, chunks of 1024 / 2048 / 4096 / 8192 points: L = 4001 19.5 /
+// 18.9 / 16.6 / 16.5 us, 13577 23.5 / 20.7 / 19.9 / 32.4, 30011 24.5 / 24.6 / 22.5 / 34.8; 28 layers: 45.8 / 41.4 / 36.9 /
+// 56.5 at 13577. Every chunk gathers from the whole head, so shorter ones repeat more of that, and 8192 points take
+// 1024 threads with too few registers each: only for transforms of 131072 points, which would be 32 chunks.
+int conv_chunk_log(int max_len) {
+    const int log_n = conv_log_points(max_len, kConvMinLogC);
+    return max(min(log_n, 12), log_n - kConvMaxLogR);
+}
+
+SmoothPlan plan_smooth(const Geom& g, const int32_t* cu_seqlens, const int32_t* seqlens_host, int n_items, double cutoff_frac,
+                       void* workspace) {
     SmoothPlan p;
+    const int n_heads = n_items * g.H_kv;
+    const bool fixed = g.cutoff_mode == AUDIOKV_CUTOFF_FRACTION;
+    int longest = 0;                      // of the convolution path's heads
     for (int i = 0; i < n_items; ++i) {
-        if (pow2_length(seqlens_host[i])) p.max_pow2 = max(p.max_pow2, seqlens_host[i]);
-        else {
-            const int lg = bluestein_log(seqlens_host[i], wanted_bins(seqlens_host[i], cutoff_frac, g.cutoff_mode, g.taper_bins));
-            p.max_log = max(p.max_log, lg);
-            p.any_wide = p.any_wide || wide_size(lg);
-        }
+        const int L = seqlens_host[i];
+        if (pow2_length(L)) { p.max_pow2 = max(p.max_pow2, L); continue; }
+        const int lg = bluestein_log(L, wanted_bins(L, cutoff_frac, g.cutoff_mode, g.taper_bins));
+        p.max_log = max(p.max_log, lg);
+        p.any_wide = p.any_wide || wide_size(lg);
+        if (fixed && degenerate_mask(L, (int)floor(cutoff_frac * (double)(L >> 1)), g.taper_bins) == 0) longest = max(longest, L);
+        else p.one_wg_other = true;
     }
+    if (!longest || !workspace) return p;
+    ConvCall& c = p.conv;
+    c.any = true;
+    c.log_c = conv_chunk_log(longest);
+    const int log_n = conv_log_points(longest, c.log_c);
+    c.max_r = 1 << (log_n - c.log_c);
+    c.points = (size_t)1 << log_n;
+    // per head the chunks' results, per item the filter's bins, per item the taps: M points each at most
+    const size_t M = bluestein_bytes(seqlens_host, n_items, g.H_kv) / (((size_t)n_heads + 3 * (size_t)n_items) * sizeof(cf));
+    c.part = workspace;
+    c.job.h = reinterpret_cast<float*>(static_cast<cf*>(workspace) + ((size_t)n_heads + n_items) * M);
+    c.job.item_stride = (int64_t)M;
+    c.job.cu_seqlens = cu_seqlens;
+    c.job.n_items = n_items;
+    c.job.cutoff_frac = cutoff_frac;
+    c.job.taper_bins = g.taper_bins;
+    c.job.blocks_per_item = (longest + kConvFilterThreads - 1) / kConvFilterThreads;
+    // Lengths shared by more than eight heads: their filter is transformed once, by a launch of its own, instead of by
+    // every workgroup for itself (a third transform beside the two that it runs anyway).
+    bool equal = true;
+    for (int i = 1; i < n_items && equal; ++i) equal = seqlens_host[i] == seqlens_host[0];
+    long long distinct = equal ? 1 : 0;
+    for (int i = 0; i < n_items && !equal; ++i) {
+        bool seen = false;                              // (long mixed lists: taken as all different)
+        for (int k = 0; k < i && !seen && n_items <= 64; ++k) seen = seqlens_host[k] == seqlens_host[i];
+        distinct += !seen;
+    }
+    if (n_heads > 8 * distinct && c.points <= M) c.spec = static_cast<cf*>(workspace) + (size_t)n_heads * M;
     return p;
 }
 
@@ -1451,7 +1278,7 @@ hipError_t smooth_kernel_attributes() {
         e = hipFuncSetAttribute(reinterpret_cast<const void*>(bluestein_prepare_kernel),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     if (e == hipSuccess)
-        e = hipFuncSetAttribute(reinterpret_cast<const void*>(wide_chunk_kernel),
+        e = hipFuncSetAttribute(reinterpret_cast<const void*>(wide_prep_chunk_kernel),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     if (e == hipSuccess) attr_set = true;
     return e;
@@ -1462,35 +1289,53 @@ size_t bluestein_smem(const Geom& g, size_t M) {
     const size_t C = M < ((size_t)1 << kChunkLog) ? M : ((size_t)1 << kChunkLog);
     return std::max((padded_len(C) + kTwLo + (M >> 8) + 1) * sizeof(cf) + extra, (size_t)kFftThreads * sizeof(double));
 }
-}  // namespace
 
-hipError_t launch_smooth_filters(const Geom& g, const int32_t* cu_seqlens, const int32_t* seqlens_host, int n_items,
-                                 double cutoff_frac, void* workspace, hipStream_t s)
+hipError_t launch_filters(const Geom& g, const SmoothPlan& pl, const int32_t* cu_seqlens, int n_items, double cutoff_frac,
+                          void* workspace, hipStream_t s)
 {
-    const SmoothPlan pl = plan_smooth(g, seqlens_host, n_items, cutoff_frac);
-    if (pl.max_log == 0) return hipSuccess;
+    hipError_t e = hipSuccess;
+    if (pl.conv.any) e = launch_conv_filter(g, pl.conv, s);
+    if (e != hipSuccess || pl.max_log == 0 || g.cutoff_mode == AUDIOKV_CUTOFF_FRACTION) return e;
     if (!workspace) return hipErrorInvalidValue;
-    hipError_t e = smooth_kernel_attributes();
+    e = smooth_kernel_attributes();
     if (e != hipSuccess) return e;
     const size_t M = (size_t)1 << pl.max_log;
     const BluesteinWs bw{static_cast<cf*>(workspace), M, g.n_items * g.H_kv};
     const bool wide = pl.any_wide;
-    hipLaunchKernelGGL(bluestein_prepare_kernel, dim3(g.n_items), dim3(kFftThreads), bluestein_smem(g, M), s, cu_seqlens,
+    hipLaunchKernelGGL(bluestein_prepare_kernel, dim3(n_items), dim3(kFftThreads), bluestein_smem(g, M), s, cu_seqlens,
                        bw, cutoff_frac, g.cutoff_mode, g.taper_bins, wide ? 1 : 0);
     if (wide) {
         const int extra_stages = pl.max_log - kChunkLog > 2 ? pl.max_log - kChunkLog : 2;    // of the largest transform
         const unsigned q = (unsigned)(M >> extra_stages);
-        const dim3 ew((q + kWideThreads - 1) / kWideThreads, (unsigned)g.n_items);
+        const dim3 ew((q + kWideThreads - 1) / kWideThreads, (unsigned)n_items);
         hipLaunchKernelGGL(wide_prep_chirp_kernel, ew, dim3(kWideThreads), 0, s, g, cu_seqlens, cutoff_frac, bw);
         if (extra_stages <= 2)
             hipLaunchKernelGGL(wide_prep_first_kernel<4>, ew, dim3(kWideThreads), 0, s, g, cu_seqlens, cutoff_frac, bw);
         else
             hipLaunchKernelGGL(wide_prep_first_kernel<kWideMaxR>, ew, dim3(kWideThreads), 0, s, g, cu_seqlens, cutoff_frac, bw);
-        hipLaunchKernelGGL(wide_chunk_kernel, dim3((unsigned)1 << extra_stages, (unsigned)(g.n_items * g.H_kv)),
-                           dim3(kFftThreads), bluestein_smem(g, M), s, g, cu_seqlens, cutoff_frac, bw, -1);
+        hipLaunchKernelGGL(wide_prep_chunk_kernel, dim3((unsigned)1 << extra_stages, (unsigned)n_items), dim3(kFftThreads),
+                           bluestein_smem(g, M), s, g, cu_seqlens, cutoff_frac, bw);
         hipLaunchKernelGGL(wide_prep_second_kernel, ew, dim3(kWideThreads), 0, s, g, cu_seqlens, cutoff_frac, bw);
     }
     return hipGetLastError();
+}
+}  // namespace
+
+SmoothFilters smooth_filters(const Geom& g, const int32_t* cu_seqlens, const int32_t* seqlens_host, int n_items,
+                             double cutoff_frac, void* workspace)
+{
+    const SmoothPlan pl = plan_smooth(g, cu_seqlens, seqlens_host, n_items, cutoff_frac, workspace);
+    SmoothFilters f;
+    f.long_work = (pl.max_log > 0 && g.cutoff_mode != AUDIOKV_CUTOFF_FRACTION) || pl.conv.spec;
+    if (!f.long_work) f.taps = pl.conv.job;
+    return f;
+}
+
+hipError_t launch_smooth_filters(const Geom& g, const int32_t* cu_seqlens, const int32_t* seqlens_host, int n_items,
+                                 double cutoff_frac, void* workspace, hipStream_t s)
+{
+    return launch_filters(g, plan_smooth(g, cu_seqlens, seqlens_host, n_items, cutoff_frac, workspace), cu_seqlens, n_items,
+                          cutoff_frac, workspace, s);
 }
 
 hipError_t launch_smooth(const Geom& g, const float* in, bool pool_on_load, const int32_t* cu_seqlens,
@@ -1500,13 +1345,13 @@ hipError_t launch_smooth(const Geom& g, const float* in, bool pool_on_load, cons
 {
     if (cutoffs_only && !kstar_out) return hipErrorInvalidValue;
     const size_t extra = g.cutoff_mode != AUDIOKV_CUTOFF_FRACTION ? sizeof(EnergyScratch) + 2 * sizeof(cf) : 0;
-    const SmoothPlan pl = plan_smooth(g, seqlens_host, n_items, cutoff_frac);
+    // (alpha = 0 copies, and a fixed cutoff is known without a transform: nothing to convolve)
+    const bool transforms = alpha != 0.0 && !(cutoffs_only && g.cutoff_mode == AUDIOKV_CUTOFF_FRACTION);
+    const SmoothPlan pl = plan_smooth(g, cu_seqlens, seqlens_host, n_items, cutoff_frac, transforms ? workspace : nullptr);
     const int max_pow2 = pl.max_pow2, max_log = pl.max_log;
     const int n_heads = g.n_items * g.H_kv;
-    {
-        const hipError_t e = smooth_kernel_attributes();
-        if (e != hipSuccess) return e;
-    }
+    hipError_t e = smooth_kernel_attributes();
+    if (e != hipSuccess) return e;
     // power-of-two heads of a call with few heads go over several workgroups each (fixed cutoff only)
     const int dec_L = (alpha != 0.0 && !cutoffs_only && g.cutoff_mode == AUDIOKV_CUTOFF_FRACTION && workspace &&
                        workspace_bytes >= smooth_workspace_bytes(seqlens_host, n_items, g.H_kv))
@@ -1539,41 +1384,29 @@ hipError_t launch_smooth(const Geom& g, const float* in, bool pool_on_load, cons
         hipLaunchKernelGGL(dec_inverse_kernel, pairs, dim3(kDecThreads), smem, s, g, in, pool_on_load ? 1 : 0, cu_seqlens,
                            cutoff_frac, (float)alpha, out, dw);
     }
-    if (max_log > 0 && alpha != 0.0) {
-        if (!workspace) return hipErrorInvalidValue;
-        if (!filters_ready) {
-            const hipError_t e = launch_smooth_filters(g, cu_seqlens, seqlens_host, n_items, cutoff_frac, workspace, s);
-            if (e != hipSuccess) return e;
-        }
+    if (max_log == 0 || alpha == 0.0) return hipGetLastError();
+    if (!workspace) return hipErrorInvalidValue;
+    if (transforms && !filters_ready) {
+        e = launch_filters(g, pl, cu_seqlens, n_items, cutoff_frac, workspace, s);
+        if (e != hipSuccess) return e;
+    }
+    if (pl.one_wg_other || cutoffs_only) {
         const size_t M = (size_t)1 << max_log;
         const BluesteinWs bw{static_cast<cf*>(workspace), M, n_heads};
-        // transforms wider than one LDS chunk go to the multi-workgroup sequence, unless the cutoff has to be found
-        // from the whole spectrum first
-        const bool wide = pl.any_wide && g.cutoff_mode == AUDIOKV_CUTOFF_FRACTION && !cutoffs_only;
         hipLaunchKernelGGL(smooth_bluestein_kernel, dim3(n_heads), dim3(kFftThreads), bluestein_smem(g, M), s, g, in,
                            pool_on_load ? 1 : 0, cu_seqlens, cutoff_frac, (float)alpha, out, bw, kstar_out,
-                           cutoffs_only ? 1 : 0, wide ? 1 : 0);
-        if (wide) {
-            const int extra_stages = max_log - kChunkLog > 2 ? max_log - kChunkLog : 2;      // of the largest transform
-            const unsigned q = (unsigned)(M >> extra_stages);
-            const dim3 ew((q + kWideThreads - 1) / kWideThreads, (unsigned)n_heads);
-            const dim3 cw((unsigned)1 << extra_stages, (unsigned)n_heads);
-            const size_t csm = bluestein_smem(g, M);
-            // instantiated for at most 4 chunks per transform (the usual case: everything in registers is small) and for 16
-            auto sequence = [&](auto maxr) {
-                constexpr int MAXR = decltype(maxr)::value;
-                hipLaunchKernelGGL(wide_first_kernel<MAXR>, ew, dim3(kWideThreads), 0, s, g, in, pool_on_load ? 1 : 0,
-                                   cu_seqlens, cutoff_frac, bw);
-                hipLaunchKernelGGL(wide_chunk_kernel, cw, dim3(kFftThreads), csm, s, g, cu_seqlens, cutoff_frac, bw, 0);
-                hipLaunchKernelGGL(wide_middle_kernel<MAXR>, ew, dim3(kWideThreads), 0, s, g, cu_seqlens, cutoff_frac, bw,
-                                   kstar_out);
-                hipLaunchKernelGGL(wide_chunk_kernel, cw, dim3(kFftThreads), csm, s, g, cu_seqlens, cutoff_frac, bw, 1);
-                hipLaunchKernelGGL(wide_last_kernel<MAXR>, ew, dim3(kWideThreads), 0, s, g, in, pool_on_load ? 1 : 0,
-                                   cu_seqlens, cutoff_frac, (float)alpha, out, bw);
-            };
-            if (extra_stages <= 2) sequence(std::integral_constant<int, 4>{});
-            else sequence(std::integral_constant<int, kWideMaxR>{});
+                           cutoffs_only ? 1 : 0, pl.conv.job);
+    }
+    if (pl.conv.any) {
+        if (pool_on_load && g.pool_kernel > kConvMaxPool) {
+            // a kernel wider than the convolution's loads can apply: pooled first, into the result (only the heads that
+            // are convolved: the others are done), and smoothed in place
+            hipLaunchKernelGGL(pool_kernel, dim3(64, n_heads), dim3(256), 0, s, g, in, cu_seqlens, out, pl.conv.job);
+            e = launch_conv(g, pl.conv, out, false, (float)alpha, out, s);
+        } else {
+            e = launch_conv(g, pl.conv, in, pool_on_load, (float)alpha, out, s);
         }
+        if (e != hipSuccess) return e;
     }
     return hipGetLastError();
 }
