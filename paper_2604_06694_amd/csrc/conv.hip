@@ -18,149 +18,20 @@
 // of in a launch of its own.
 //
 // What bounds all of this is latency: the chain of LDS exchanges of a transform (a thread keeps eight points, three
-// radix-2 stages per exchange) and, for a launch whose every wave runs through the code once, fetching the
-// instructions. So there is one copy of everything that repeats: one forward transform for filter and samples, rolled
-// loops over a head's blocks and over the twiddle table, loads without branches. (Unrolled, with a sincospi per twiddle,
-// the kernel had 63 KB of code and took 36 us per launch at any chunk size.)
+// radix-2 stages per exchange) and the gathers, whose loads go without branches around them, four blocks at a time (with
+// the edges of the sequence handled in branches the loads waited for each other and a launch took 36 us at any chunk size).
 // Pool + smooth of one layer of four heads inside evict, chirp-z path before -> this: L = 13577 41 us in six launches beside
 // 50 us of filter preparation on another stream -> 19 us in two (chunks 14, join 5) and nothing beside; a smooth call on 24
 // sequences of two heads, 1500 to 30000 samples, 147 -> 41 us (taps 8, chunks 31, join 4); one layer of 30011 alone 78 -> 22,
 // 28 layers 144 -> 68. Error against 64 bits 5.2e-7 -> 1.5e-7 (2-norm, relative).
 #include <atomic>
 
-#include "smooth_common.h"
 #include "conv_filter.h"
 #include "conv.h"
-
-// Every fused multiply-add is written out: the kernels below exist in several instantiations (pooling on load or not, a
-// filter formed here or there) that have to agree to the last bit, and what the compiler contracts is up to each.
-#pragma clang fp contract(off)
+#include "fft_regs.h"
 
 namespace audiokv {
 namespace {
-
-__device__ __forceinline__ cf mul(cf a, cf b) {
-    return {fmaf(a.re, b.re, -(a.im * b.im)), fmaf(a.re, b.im, a.im * b.re)};
-}
-__device__ __forceinline__ float mix(float s0, float smoothed, float alpha) { return fmaf(alpha, smoothed, (1.f - alpha) * s0); }
-
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));    // any head start: heads are L floats apart
-
-// exp(i pi x), |x| <= 2^16: x - k/2 is exact, and on [-1/4, 1/4] the Taylor series of cos and sin (remainders below
-// 3e-9 and 3e-10)
-__device__ __forceinline__ cf cis_pi(float x) {
-    const float k = rintf(2.f * x), r = fmaf(-0.5f, k, x), s = r * r;
-    const int q = (int)k;
-    constexpr float P2 = 9.86960440108935862f, P1 = 3.14159265358979324f;         // pi^2, pi
-    const float u = s * P2;
-    const float c = fmaf(u, fmaf(u, fmaf(u, fmaf(u, 1.f / 40320.f, -1.f / 720.f), 1.f / 24.f), -0.5f), 1.f);
-    const float v = P1 * r * fmaf(u, fmaf(u, fmaf(u, fmaf(u, 1.f / 362880.f, -1.f / 5040.f), 1.f / 120.f), -1.f / 6.f), 1.f);
-    const float a = q & 1 ? v : c, b = q & 1 ? c : v;                               // quarter turns: swap, then signs
-    return {(q + 1) & 2 ? -a : a, q & 2 ? -b : b};
-}
-
-// 4- and 8-point DFTs in registers, natural order in and out; S = -1 forwards (exp(-2 pi i / n)), +1 backwards
-template <int S>
-__device__ __forceinline__ cf mul_i(cf a) { return S < 0 ? cf{a.im, -a.re} : cf{-a.im, a.re}; }     // times S * i
-template <int S>
-__device__ __forceinline__ void dft4(cf& a, cf& b, cf& c, cf& d) {
-    const cf s0 = cadd(a, c), s1 = csub(a, c), s2 = cadd(b, d), s3 = mul_i<S>(csub(b, d));
-    a = cadd(s0, s2); b = cadd(s1, s3); c = csub(s0, s2); d = csub(s1, s3);
-}
-template <int S>
-__device__ __forceinline__ void dft8(cf (&v)[8]) {
-    constexpr float H = 0.70710678118654752f;
-    cf e0 = cadd(v[0], v[4]), e1 = cadd(v[1], v[5]), e2 = cadd(v[2], v[6]), e3 = cadd(v[3], v[7]);
-    cf o0 = csub(v[0], v[4]), o1 = csub(v[1], v[5]), o2 = csub(v[2], v[6]), o3 = csub(v[3], v[7]);
-    o1 = S < 0 ? cf{H * (o1.re + o1.im), H * (o1.im - o1.re)} : cf{H * (o1.re - o1.im), H * (o1.im + o1.re)};
-    o2 = mul_i<S>(o2);
-    o3 = S < 0 ? cf{H * (o3.im - o3.re), -H * (o3.re + o3.im)} : cf{-H * (o3.re + o3.im), H * (o3.re - o3.im)};
-    dft4<S>(e0, e1, e2, e3);
-    dft4<S>(o0, o1, o2, o3);
-    v[0] = e0; v[2] = e1; v[4] = e2; v[6] = e3;
-    v[1] = o0; v[3] = o1; v[5] = o2; v[7] = o3;
-}
-
-// In-place transforms of C = 2^LOGC points by C / 8 threads. Forwards the passes take the index bits from the top,
-// three at a time, and leave every group's outputs where its inputs were, so the bins end in a digit-reversed order
-// that nobody has to know: the filter's bins are in the same order, and backwards the passes mirror it.
-//   first layout: thread t holds points t + (C/8) q;  last layout: thread t holds slots 8 t + e  (e, q = 0..7)
-template <int LOGC>
-struct Fft {
-    static constexpr int C = 1 << LOGC, THREADS = C / 8;
-    static constexpr int P8 = LOGC / 3;                       // radix-8 passes
-    static constexpr int REM = LOGC - 3 * P8;                 // bits left for a pass of radix 2 or 4 on the last layout
-    static constexpr int TW = REM ? P8 : P8 - 1;              // passes with twiddles
-    struct Twiddles { cf w1[TW], w2[TW], w4[TW]; };           // root_{8m}^(j0 {1, 2, 4}) of this thread, per pass
-    static constexpr int low_bit(int p) { return LOGC - 3 * (p + 1); }
-
-    __device__ __forceinline__ static int base(int p, int t) {
-        const int sb = low_bit(p);
-        return ((t >> sb) << (sb + 3)) | (t & ((1 << sb) - 1));
-    }
-    // roots of unity exp(-2 pi i e / C), e < C/2, four per thread
-    __device__ __forceinline__ static void fill_table(cf* table, int t) {
-#pragma unroll 1
-        for (int e = t; e < C / 2; e += THREADS) table[e] = cis_pi(-(float)e / (float)(C / 2));
-    }
-    __device__ __forceinline__ static void init(Twiddles& tw, const cf* table, int t) {
-#pragma unroll
-        for (int p = 0; p < TW; ++p) {
-            const int e = (t & ((1 << low_bit(p)) - 1)) << (3 * p);      // j0 / 8m in units of 1 / C; 4 e < C / 2
-            tw.w1[p] = table[e]; tw.w2[p] = table[2 * e]; tw.w4[p] = table[4 * e];
-        }
-    }
-    template <bool CONJ>
-    __device__ __forceinline__ static void twist(cf (&v)[8], const Twiddles& tw, int p) {
-        const cf w1 = CONJ ? cconj(tw.w1[p]) : tw.w1[p], w2 = CONJ ? cconj(tw.w2[p]) : tw.w2[p];
-        const cf w4 = CONJ ? cconj(tw.w4[p]) : tw.w4[p], w3 = mul(w1, w2);
-        v[1] = mul(v[1], w1); v[2] = mul(v[2], w2); v[3] = mul(v[3], w3); v[4] = mul(v[4], w4);
-        v[5] = mul(v[5], mul(w1, w4)); v[6] = mul(v[6], mul(w2, w4)); v[7] = mul(v[7], mul(w3, w4));
-    }
-    template <int S>
-    __device__ __forceinline__ static void small_dfts(cf (&v)[8]) {
-        if constexpr (REM == 1) {
-#pragma unroll
-            for (int e = 0; e < 8; e += 2) { const cf a = v[e], b = v[e + 1]; v[e] = cadd(a, b); v[e + 1] = csub(a, b); }
-        } else if constexpr (REM == 2) {
-            dft4<S>(v[0], v[1], v[2], v[3]);
-            dft4<S>(v[4], v[5], v[6], v[7]);
-        }
-    }
-    __device__ __forceinline__ static void put(cf* z, const cf (&v)[8], int b, int sb) {
-#pragma unroll
-        for (int q = 0; q < 8; ++q) z[pad(b + (q << sb))] = v[q];
-    }
-    __device__ __forceinline__ static void get(const cf* z, cf (&v)[8], int b, int sb) {
-#pragma unroll
-        for (int q = 0; q < 8; ++q) v[q] = z[pad(b + (q << sb))];
-    }
-    // first layout in, last layout out; every thread's own first-layout slots are free
-    __device__ __forceinline__ static void forward(cf (&v)[8], cf* z, const Twiddles& tw, int t) {
-#pragma unroll
-        for (int p = 0; p < P8; ++p) {
-            const int sb = low_bit(p), b = base(p, t);
-            if (p) get(z, v, b, sb);
-            dft8<-1>(v);
-            if (p < TW) twist<false>(v, tw, p);
-            if (p + 1 < P8 || REM) { put(z, v, b, sb); __syncthreads(); }
-        }
-        if (REM) { get(z, v, 8 * t, 0); small_dfts<-1>(v); }
-    }
-    // last layout in, first layout out, unnormalised
-    __device__ __forceinline__ static void backward(cf (&v)[8], cf* z, const Twiddles& tw, int t) {
-        if (REM) { small_dfts<1>(v); put(z, v, 8 * t, 0); __syncthreads(); }
-#pragma unroll
-        for (int p = P8 - 1; p >= 0; --p) {
-            const int sb = low_bit(p), b = base(p, t);
-            if (p + 1 < P8 || REM) get(z, v, b, sb);
-            if (p < TW) twist<true>(v, tw, p);
-            dft8<1>(v);
-            if (p) { put(z, v, b, sb); __syncthreads(); }
-        }
-    }
-};
 
 // Pooled values around samples 4 .. 11 of a window of 16. Same taps, order of additions and reciprocal as pooled_at
 // (which is what makes the fused path equal the staged one): POOL = 7, the usual size, spelled out; POOL = 9 for any
@@ -337,7 +208,7 @@ __device__ __forceinline__ void to_bins(ConvLds<LOGC>& m, const typename Fft<LOG
     Fft<LOGC>::put(m.z, v, 8 * t, 0);
     __syncthreads();
     Fft<LOGC>::get(m.z, v, t, LOGC - 3);
-    Fft<LOGC>::forward(v, m.z, tw, t);
+    Fft<LOGC>::forward(reinterpret_cast<cf(&)[1][8]>(v), m.z, tw, t);
 }
 
 // the filter's bins of every distinct length, for calls in which many heads share them
@@ -403,7 +274,7 @@ __global__ __launch_bounds__(Fft<LOGC>::THREADS) void conv_chunk_kernel(
     }
 #pragma unroll
     for (int e = 0; e < 8; ++e) v[e] = mul(v[e], f[e]);
-    Fft<LOGC>::backward(v, m.z, tw, t);
+    Fft<LOGC>::backward(reinterpret_cast<cf(&)[1][8]>(v), m.z, tw, t);
 
     // twisted back: point n = t + T q of residue r by exp(i pi n (4 r - 1) / 2N); 1/N completes the inverse transform
     const float inv_n = 1.0f / (float)(1 << w.log_n);

@@ -23,6 +23,7 @@
 #include <algorithm>
 #include "smooth_common.h"
 #include "conv.h"
+#include "smooth_real.h"
 
 namespace audiokv {
 
@@ -241,6 +242,13 @@ __device__ __forceinline__ int energy_cutoff(EnergyFn&& energy, int n_bins, int 
 
 __device__ __forceinline__ bool dec_owns(const Geom& g, int L, double cutoff_frac);   // heads of the several-workgroups path
 
+// heads of smooth_real.hip (unless dec_owns them): long enough, and a mask that needs a transform or comes from one
+__host__ __device__ inline bool real_item(const Geom& g, int L, double cutoff_frac, int cutoffs_only) {
+    if (!real_length(L)) return false;
+    if (g.cutoff_mode != AUDIOKV_CUTOFF_FRACTION) return L < kMaxPow2L;
+    return !cutoffs_only && degenerate_mask(L, (int)floor(cutoff_frac * (double)(L >> 1)), g.taper_bins) != 2;
+}
+
 __global__ __launch_bounds__(kFftThreads) void smooth_pow2_kernel(
     Geom g, const float* __restrict__ in, int pool_on_load, const int32_t* __restrict__ cu_seq,
     double cutoff_frac, float alpha,
@@ -264,6 +272,7 @@ __global__ __launch_bounds__(kFftThreads) void smooth_pow2_kernel(
     }
     if (!pow2_length(L)) return;                      // other kernels own this head
     if (skip_dec && dec_owns(g, L, cutoff_frac)) return;   // spread over several workgroups by the dec_* kernels
+    if (real_item(g, L, cutoff_frac, cutoffs_only)) return;   // smooth_real.hip
     const int T = g.taper_bins;
     if (g.cutoff_mode == AUDIOKV_CUTOFF_FRACTION && cutoffs_only) {
         if (tid == 0) kstar_out[head] = (int)floor(cutoff_frac * (double)(L >> 1));
@@ -434,7 +443,7 @@ __device__ __forceinline__ void fill_tables(cf* lo, cf* hi, int n_hi, int M) {
 
 // ------------------------ power-of-two lengths, few heads: one head on several workgroups ------------------------
 // A call with few heads (one layer of a prefill: four) leaves all but a handful of CUs idle while each head's
-// transform runs in one workgroup. For those calls a head of L = 2^p >= 16384 samples is cut into D = 16 interleaved
+// transform runs in one workgroup. For those calls a head of 32768 samples is cut into D = 16 interleaved
 // sub-sequences x_{16 m + r} of M = L / 16 samples, the first stage of a decimation-in-time FFT taken out of the
 // workgroup:
 //   dec_forward   per pair (r, r + 1): one complex M-point FFT in LDS gives the spectra G_r, G_{r+1} of the two
@@ -448,7 +457,7 @@ __device__ __forceinline__ void fill_tables(cf* lo, cf* hi, int n_hi, int M) {
 // in one place first.
 constexpr int kDecLog = 4, kDec = 1 << kDecLog;      // D
 constexpr int kDecThreads = 1024;    // the strided (and, inside evict, pooled) loads want many waves in flight
-constexpr int kDecMinL = 16384;   // below this one workgroup per head is as fast (measured: 8192 19 us alone, 21 us spread; 16384 33 and 21)
+constexpr int kDecMinL = 32768;   // below this one workgroup per head is faster (a smooth call on 4 heads: 16384 18 us spread, 14 alone; 32768 20 and 29)
 constexpr int kDecMaxHeads = 64;                     // beyond this the heads fill the chip by themselves
 
 __host__ __device__ inline bool dec_length(int L) { return pow2_length(L) && L >= kDecMinL; }
@@ -1204,7 +1213,7 @@ size_t smooth_workspace_required(const int32_t* seqlens_host, int n_items, int H
 
 namespace {
 struct SmoothPlan {
-    int max_pow2 = 0, max_log = 0;        // longest power of two, log2 of the largest chirp-z transform
+    int max_log = 0;                      // log2 of the largest chirp-z transform
     bool any_wide = false;
     bool one_wg_other = false;            // lengths that are not powers of two and run in one workgroup per head
     ConvCall conv;                        // the convolution path's share of them
@@ -1228,7 +1237,7 @@ SmoothPlan plan_smooth(const Geom& g, const int32_t* cu_seqlens, const int32_t* 
     int longest = 0;                      // of the convolution path's heads
     for (int i = 0; i < n_items; ++i) {
         const int L = seqlens_host[i];
-        if (pow2_length(L)) { p.max_pow2 = max(p.max_pow2, L); continue; }
+        if (pow2_length(L)) continue;
         const int lg = bluestein_log(L, wanted_bins(L, cutoff_frac, g.cutoff_mode, g.taper_bins));
         p.max_log = max(p.max_log, lg);
         p.any_wide = p.any_wide || wide_size(lg);
@@ -1348,7 +1357,7 @@ hipError_t launch_smooth(const Geom& g, const float* in, bool pool_on_load, cons
     // (alpha = 0 copies, and a fixed cutoff is known without a transform: nothing to convolve)
     const bool transforms = alpha != 0.0 && !(cutoffs_only && g.cutoff_mode == AUDIOKV_CUTOFF_FRACTION);
     const SmoothPlan pl = plan_smooth(g, cu_seqlens, seqlens_host, n_items, cutoff_frac, transforms ? workspace : nullptr);
-    const int max_pow2 = pl.max_pow2, max_log = pl.max_log;
+    const int max_log = pl.max_log;
     const int n_heads = g.n_items * g.H_kv;
     hipError_t e = smooth_kernel_attributes();
     if (e != hipSuccess) return e;
@@ -1359,19 +1368,30 @@ hipError_t launch_smooth(const Geom& g, const float* in, bool pool_on_load, cons
     const DecWs dw{reinterpret_cast<cf*>(static_cast<char*>(workspace) + bluestein_bytes(seqlens_host, n_items, g.H_kv)),
                    dec_L ? dec_head_elems(dec_L) : 0};
     // every head is handled by exactly one path (alpha = 0 copies: the single-workgroup kernel)
-    bool all_dec = dec_L > 0;
-    for (int i = 0; i < n_items && all_dec; ++i)
-        all_dec = dec_length(seqlens_host[i]) &&
-                  degenerate_mask(seqlens_host[i], (int)floor(cutoff_frac * (double)(seqlens_host[i] >> 1)), g.taper_bins) != 2;
-    if (!all_dec && (max_pow2 > 0 || alpha == 0.0 || max_log == 0)) {
-        const int n_hi = (max_pow2 >> 8) + 1;
+    // which of the single-workgroup kernels have heads, by length
+    int max_small = 0;                                   // longest head left to smooth_pow2_kernel
+    unsigned real_lengths = 0;                           // bit l: heads of 2^l samples for smooth_real_kernel
+    for (int i = 0; i < n_items && alpha != 0.0; ++i) {
+        const int L = seqlens_host[i];
+        if (!pow2_length(L)) continue;
+        if (dec_L && dec_length(L) && degenerate_mask(L, (int)floor(cutoff_frac * (double)(L >> 1)), g.taper_bins) != 2) continue;
+        if (real_item(g, L, cutoff_frac, cutoffs_only ? 1 : 0)) real_lengths |= 1u << (31 - __builtin_clz((unsigned)L));
+        else max_small = max(max_small, L);
+    }
+    if (max_small > 0 || alpha == 0.0) {
+        const int n_hi = (max_small >> 8) + 1;
         // (at least the kFftThreads doubles that the no-transform paths reduce in)
-        const size_t smem = std::max((padded_len((size_t)max_pow2 >> 1) + kTwLo + n_hi) * sizeof(cf) + extra,
+        const size_t smem = std::max((padded_len((size_t)max_small >> 1) + kTwLo + n_hi) * sizeof(cf) + extra,
                                      (size_t)kFftThreads * sizeof(double));
         hipLaunchKernelGGL(smooth_pow2_kernel, dim3(n_heads), dim3(kFftThreads), smem, s, g, in,
                            pool_on_load ? 1 : 0, cu_seqlens, cutoff_frac, (float)alpha, out, kstar_out, cutoffs_only ? 1 : 0,
                            dec_L ? 1 : 0);
     }
+    for (int l = 0; l < 31; ++l)
+        if (real_lengths >> l & 1) {
+            e = launch_smooth_real(1 << l, g, in, pool_on_load, cu_seqlens, cutoff_frac, (float)alpha, out, kstar_out, cutoffs_only, s);
+            if (e != hipSuccess) return e;
+        }
     if (dec_L) {
         const int M = dec_L >> kDecLog;
         const size_t smem = (padded_len(M) + kTwLo + (M >> 8) + 1) * sizeof(cf);

@@ -1,0 +1,299 @@
+// Spectral Score Smoothing of power-of-two lengths, 1024 .. 32768 samples, one workgroup per head (paper Sec. 3.3, Eqs.
+// 13-20).
+//
+// The real sequence is viewed as N = L/2 complex points, transformed in registers and LDS (fft_regs.h), turned into the
+// real spectrum bin by bin, masked, turned back and transformed back. A bin k needs its partner N - k; the spectrum goes
+// to LDS once for that, every thread reads the partners of its own eight bins and forms its own results (both threads of
+// a pair do the pair's arithmetic, and bins whose pair is masked altogether are skipped).
+//
+// What bounds it is latency: a pass is an LDS round trip of eight points per thread, a radix-8 butterfly and a barrier.
+// Three radix-2 stages per pass with the twiddles of the whole transform held in registers (looked up per pass at
+// N = 16384, where a thread has sixteen points) take about half the vector instructions of the four stages per
+// pass with two complex multiplications per butterfly of smooth_pow2_kernel, which keeps the shorter heads (as fast
+// there) and 32768 samples with an energy-adaptive cutoff (52 us for 112 heads there, 54 here). Pool + smooth
+// inside evict, before -> now: 4 heads of 2048 12.0 -> 8.0 us, 112 heads of 8192 23 -> 13.2, of 32768 55 -> 42; smooth calls:
+// 112 heads of 16384 22.4 -> 15.7 us, with an energy-adaptive cutoff 4 heads of 8192 19.8 -> 14.6.
+#include <atomic>
+
+#include "fft_regs.h"
+#include "smooth_real.h"
+
+namespace audiokv {
+namespace {
+
+// N = 16384: 1024 threads with two groups of eight points each
+template <int LOGC> constexpr int kRealGroups = LOGC == 14 ? 2 : 1;
+template <int LOGC> constexpr int kRealThreads = (1 << LOGC) / (8 * kRealGroups<LOGC>);
+
+template <int LOGC>
+struct RealLds {
+    static constexpr bool kTable = LOGC <= 13;               // the whole root table fits beside the points
+    cf z[padded_len((size_t)1 << LOGC)];                     // also: raw samples, bin energies
+    cf roots[kTable ? 1 << (LOGC - 1) : 128 + (1 << LOGC) / 256];
+    double part[32];                                         // partial sums of the energy search, one per wave
+    int cross_wave, kstar;
+};
+
+__device__ __forceinline__ double wave_scan(double v, int lane) {       // inclusive
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const double u = __shfl_up(v, o, 64);
+        if (lane >= o) v += u;
+    }
+    return v;
+}
+
+// Adaptive cutoff (Eqs. 14-16): the smallest k >= first with sum_{first<=i<=k} e[i] >= rho * sum_{first<=i<n_bins} e[i].
+// Bin energies fp32, sums float64: every thread adds a run of consecutive bins, the runs' totals are scanned, and the
+// thread whose run crosses the target walks it again. Uniform result.
+template <int T, class Lds>
+__device__ __forceinline__ int energy_search(const float* e, int n_bins, int first, double rho, Lds& m) {
+    constexpr int kWaves = (T + 63) / 64;
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    const int per = (n_bins + T - 1) / T;
+    const int k0 = max(min(t * per, n_bins), first), k1 = max(min(t * per + per, n_bins), k0);
+    double mine = 0.0;
+    for (int k = k0; k < k1; ++k) mine += (double)e[k];
+    double incl = wave_scan(mine, lane);
+    if (lane == 63) m.part[wave] = incl;
+    if (t == 0) { m.cross_wave = T; m.kstar = min(first, n_bins - 1); }
+    __syncthreads();
+    double total = 0.0, before = 0.0;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+        if (w == wave) before = total;
+        total += m.part[w];
+    }
+    incl += before;
+    const double target = rho * total;
+    if (target > 0.0 && k1 > k0 && incl >= target) atomicMin(&m.cross_wave, t);
+    __syncthreads();
+    if (t == m.cross_wave) {
+        double acc = incl - mine;
+        int ks = k1 - 1;                                     // (rounding between the two summation orders)
+        for (int k = k0; k < k1; ++k) {
+            acc += (double)e[k];
+            if (acc >= target) { ks = k; break; }
+        }
+        m.kstar = ks;
+    }
+    __syncthreads();
+    return m.kstar;
+}
+
+// weight of bin k (Eqs. 17-18)
+__device__ __forceinline__ float bin_weight(int k, int kstar, int T) {
+    if (k <= kstar) return 1.f;
+    if (k > kstar + T) return 0.f;
+    return 0.5f * (1.f + cis_pi((float)(k - kstar) / (float)(T + 1)).re);
+}
+
+// POOL: 0 none, 7 the usual size, 1 any size
+template <int LOGC, int POOL>
+__global__ __launch_bounds__(kRealThreads<LOGC>) void smooth_real_kernel(
+    Geom g, const float* __restrict__ in, const int32_t* __restrict__ cu_seq, double cutoff_frac, float alpha,
+    float* __restrict__ out, int32_t* __restrict__ kstar_out, int cutoffs_only)
+{
+    constexpr int VT = kRealGroups<LOGC>;
+    using F = Fft<LOGC, VT>;
+    constexpr int N = 1 << LOGC, L = 2 * N, T = F::THREADS;
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    RealLds<LOGC>& m = *reinterpret_cast<RealLds<LOGC>*>(smem);
+    const int head = blockIdx.x, t = threadIdx.x;
+    const int item = head / g.H_kv, h = head - item * g.H_kv;
+    const int tok0 = cu_seq[item];
+    if (cu_seq[item + 1] - tok0 != L) return;                // another launch's head
+    const size_t off = (size_t)tok0 * g.H_kv + (size_t)h * L;
+    const float* src = in + off;
+    float* dst = out + off;
+
+    // ---- samples 2 n, 2 n + 1 of the points n of the first layout ----
+    cf v[VT][8];
+    if constexpr (POOL != 0) {
+        // one coalesced read of the raw scores into LDS, pooled from there
+        float* raw = reinterpret_cast<float*>(m.z);
+        float x[L / T];
+#pragma unroll
+        for (int u = 0; u < L / T; ++u) x[u] = src[t + u * T];
+#pragma unroll
+        for (int u = 0; u < L / T; ++u) raw[t + u * T] = x[u];
+    } else {
+#pragma unroll
+        for (int vt = 0; vt < VT; ++vt)
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                const int n = t + vt * T + (N / 8) * q;
+                v[vt][q] = {src[2 * n], src[2 * n + 1]};
+            }
+    }
+    if constexpr (RealLds<LOGC>::kTable) F::fill_table(m.roots, t);
+    else F::fill_hi_lo(m.roots, m.roots + 128, t);
+    __syncthreads();
+    if constexpr (POOL != 0) {
+        const float* raw = reinterpret_cast<const float*>(m.z);
+#pragma unroll
+        for (int vt = 0; vt < VT; ++vt)
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                const int n = t + vt * T + (N / 8) * q;
+                if constexpr (POOL == 7) pooled_pair_lds<7>(raw, L, 2 * n, g.pool_mode, v[vt][q].re, v[vt][q].im);
+                else pooled_pair(raw, L, 2 * n, g.pool_kernel, g.pool_mode, v[vt][q].re, v[vt][q].im);
+            }
+        __syncthreads();
+    }
+    auto transforms = [&](const auto& tw) {
+        F::forward(v, m.z, tw, t);
+
+        // ---- real spectrum, mask, and back ----
+        // X_k = E + w^k O with E, O the transforms of the even and odd samples, both read off Z[k] and conj(Z[N-k])
+        F::put_last(m.z, v, t);
+        __syncthreads();
+        const int Tb = g.taper_bins;
+        const int first = g.cutoff_mode == AUDIOKV_CUTOFF_ENERGY_NO_DC ? 1 : 0;
+        int kstar = (int)floor(cutoff_frac * (double)N);     // N = floor(L/2) = bins - 1
+        const cf z0 = m.z[0];
+        auto partner = [&](int k) { return cconj(m.z[pad(F::slot_of((N - k) & (N - 1)))]); };
+        auto even_odd = [&](cf A, cf B, cf& E, cf& O) {
+            E = {0.5f * (A.re + B.re), 0.5f * (A.im + B.im)};
+            const cf d = csub(A, B);
+            O = {0.5f * d.im, -0.5f * d.re};                 // -i (A - B) / 2
+        };
+        // (N = 16384 is not launched with an energy-adaptive cutoff: sixteen points and sixteen partners per thread do not
+        // fit 128 registers)
+        cf other[VT][8];                                     // (filled where the energies need every bin)
+        const bool energy = LOGC < 14 && g.cutoff_mode != AUDIOKV_CUTOFF_FRACTION;
+        if (energy) {
+            float en[VT][8];
+#pragma unroll
+            for (int vt = 0; vt < VT; ++vt)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const int k = F::bin_of(8 * (t + vt * T) + e);
+                    other[vt][e] = partner(k);
+                    cf E, O;
+                    even_odd(v[vt][e], other[vt][e], E, O);
+                    const cf X = cadd(E, mul(cis_pi(-(float)k / (float)N), O));
+                    en[vt][e] = fmaf(X.re, X.re, X.im * X.im);
+                    if (k == 0) { const float x = z0.re + z0.im; en[vt][e] = x * x; }
+                }
+            __syncthreads();                                 // all partners are read
+            float* ek = reinterpret_cast<float*>(m.z);
+#pragma unroll
+            for (int vt = 0; vt < VT; ++vt)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) ek[F::bin_of(8 * (t + vt * T) + e)] = en[vt][e];
+            if (t == 0) { const float x = z0.re - z0.im; ek[N] = x * x; }
+            __syncthreads();
+            kstar = energy_search<T>(ek, N + 1, first, cutoff_frac, m);
+            __syncthreads();
+        }
+        if (kstar_out && t == 0) kstar_out[head] = kstar;
+        if (cutoffs_only) return;
+        if (degenerate_mask(L, kstar, Tb) == 2) {
+            // every bin kept: the samples themselves (a fixed cutoff that says so never gets here)
+            for (int n = t; n < L; n += T) dst[n] = POOL ? pooled_at(src, L, n, g.pool_kernel, g.pool_mode) : src[n];
+            return;
+        }
+        const int ktop = kstar + Tb;                         // last bin with a non-zero weight
+#pragma unroll
+        for (int vt = 0; vt < VT; ++vt)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const int k = F::bin_of(8 * (t + vt * T) + e);
+                cf o = {0.f, 0.f};
+                if (k <= ktop || N - k <= ktop) {
+                    if (k == 0) {                            // the DC bin, always kept, with the Nyquist bin folded in
+                        const float X0 = z0.re + z0.im, XN = (z0.re - z0.im) * bin_weight(N, kstar, Tb);
+                        o = {0.5f * (X0 + XN), 0.5f * (X0 - XN)};
+                    } else {
+                        cf E, O;
+                        even_odd(v[vt][e], energy ? other[vt][e] : partner(k), E, O);
+                        const cf Wk = cis_pi(-(float)k / (float)N), WO = mul(Wk, O);
+                        const float wk = bin_weight(k, kstar, Tb), wn = bin_weight(N - k, kstar, Tb);
+                        const cf X = cadd(E, WO), Y = csub(E, WO);           // bin k; conjugate of bin N - k
+                        const cf Xk = {X.re * wk, X.im * wk}, Xn = {Y.re * wn, Y.im * wn};
+                        const cf E2 = {0.5f * (Xk.re + Xn.re), 0.5f * (Xk.im + Xn.im)};
+                        const cf O2 = mul({0.5f * (Xk.re - Xn.re), 0.5f * (Xk.im - Xn.im)}, cconj(Wk));
+                        o = {E2.re - O2.im, E2.im + O2.re};
+                    }
+                }
+                v[vt][e] = o;
+            }
+        __syncthreads();                                     // all partners are read: the slots are free
+        F::backward(v, m.z, tw, t);
+
+        // residual mix (Eq. 20); 1/N completes the inverse transform
+        const float inv = 1.0f / (float)N;
+#pragma unroll
+        for (int vt = 0; vt < VT; ++vt)
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                const int n = t + vt * T + (N / 8) * q;
+                float o0 = v[vt][q].re * inv, o1 = v[vt][q].im * inv;
+                if (alpha != 1.f) {
+                    float a0, a1;
+                    if constexpr (POOL != 0) {
+                        a0 = pooled_at(src, L, 2 * n, g.pool_kernel, g.pool_mode);
+                        a1 = pooled_at(src, L, 2 * n + 1, g.pool_kernel, g.pool_mode);
+                    } else {
+                        a0 = src[2 * n]; a1 = src[2 * n + 1];
+                    }
+                    o0 = mix(a0, o0, alpha);
+                    o1 = mix(a1, o1, alpha);
+                }
+                dst[2 * n] = o0;
+                dst[2 * n + 1] = o1;
+            }
+    };
+    if constexpr (RealLds<LOGC>::kTable) {
+        typename F::Twiddles tw;
+        F::init(tw, m.roots, t);
+        transforms(tw);
+    } else {
+        transforms(typename F::HiLo{m.roots, m.roots + 128, t});
+    }
+}
+
+template <int LOGC, int POOL>
+hipError_t launch(const Geom& g, const float* in, const int32_t* cu_seqlens, double cutoff_frac, float alpha, float* out,
+                  int32_t* kstar_out, bool cutoffs_only, hipStream_t s) {
+    constexpr int T = kRealThreads<LOGC>;
+    const int lds = (int)sizeof(RealLds<LOGC>);
+    if (lds > 48 * 1024) {
+        static std::atomic<bool> attr_set{false};
+        if (!attr_set) {
+            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(smooth_real_kernel<LOGC, POOL>),
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+            if (e != hipSuccess) return e;
+            attr_set = true;
+        }
+    }
+    hipLaunchKernelGGL((smooth_real_kernel<LOGC, POOL>), dim3((unsigned)(g.n_items * g.H_kv)), dim3(T), lds, s, g, in, cu_seqlens,
+                       cutoff_frac, alpha, out, kstar_out, cutoffs_only ? 1 : 0);
+    return hipGetLastError();
+}
+
+template <int LOGC>
+hipError_t launch(const Geom& g, const float* in, bool pool_on_load, const int32_t* cu_seqlens, double cutoff_frac, float alpha,
+                  float* out, int32_t* kstar_out, bool cutoffs_only, hipStream_t s) {
+    if (!pool_on_load) return launch<LOGC, 0>(g, in, cu_seqlens, cutoff_frac, alpha, out, kstar_out, cutoffs_only, s);
+    if (g.pool_kernel == 7) return launch<LOGC, 7>(g, in, cu_seqlens, cutoff_frac, alpha, out, kstar_out, cutoffs_only, s);
+    return launch<LOGC, 1>(g, in, cu_seqlens, cutoff_frac, alpha, out, kstar_out, cutoffs_only, s);
+}
+
+}  // namespace
+
+hipError_t launch_smooth_real(int L, const Geom& g, const float* in, bool pool_on_load, const int32_t* cu_seqlens, double cutoff_frac,
+                              float alpha, float* out, int32_t* kstar_out, bool cutoffs_only, hipStream_t s) {
+    switch (L) {
+        case 1024:  return launch<9>(g, in, pool_on_load, cu_seqlens, cutoff_frac, alpha, out, kstar_out, cutoffs_only, s);
+        case 2048:  return launch<10>(g, in, pool_on_load, cu_seqlens, cutoff_frac, alpha, out, kstar_out, cutoffs_only, s);
+        case 4096:  return launch<11>(g, in, pool_on_load, cu_seqlens, cutoff_frac, alpha, out, kstar_out, cutoffs_only, s);
+        case 8192:  return launch<12>(g, in, pool_on_load, cu_seqlens, cutoff_frac, alpha, out, kstar_out, cutoffs_only, s);
+        case 16384: return launch<13>(g, in, pool_on_load, cu_seqlens, cutoff_frac, alpha, out, kstar_out, cutoffs_only, s);
+        case 32768: return launch<14>(g, in, pool_on_load, cu_seqlens, cutoff_frac, alpha, out, kstar_out, cutoffs_only, s);
+    }
+    return hipErrorInvalidValue;
+}
+
+}  // namespace audiokv

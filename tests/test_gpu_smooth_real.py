@@ -1,0 +1,85 @@
+"""Power-of-two lengths, one workgroup per head, every transform size: masks at both ends of the spectrum and with a taper,
+the energy-adaptive cutoff, in place, fused pooling against the staged calls, several lengths in one call."""
+import numpy as np
+import pytest
+import torch
+
+from workloads import f64_to_bf16_bits
+
+from gpu_util import bf16_tensor
+from test_gpu_conv import ATOL, reference, sequences
+
+pytestmark = pytest.mark.gpu
+
+LENGTHS = [512, 1024, 2048, 4096, 8192, 16384, 32768]      # 512: the first length of the kernel for shorter heads
+
+
+@pytest.fixture(scope="module")
+def A():
+    import paper_2604_06694_amd as A
+    return A
+
+
+def smooth(A, x, cutoff, alpha, heads, **params):
+    """`x` [n, L] in a call of `heads` heads (more than 64: no head is spread over several workgroups)."""
+    n, L = x.shape
+    reps = -(-heads // n)
+    t = torch.from_numpy(x.reshape(-1)).cuda().repeat(reps)
+    out = A.smooth(A.Params(n, n, 128, 1, **params), t, [L] * reps, cutoff, alpha)
+    assert torch.equal(out, out[:n * L].repeat(reps))
+    A.smooth(A.Params(n, n, 128, 1, **params), t, [L] * reps, cutoff, alpha, out=t)
+    assert torch.equal(t, out)
+    return out[:n * L].cpu().numpy().reshape(n, L)
+
+
+@pytest.mark.parametrize("L", LENGTHS)
+@pytest.mark.parametrize("cutoff,alpha,T", [(0.125, 1.0, 0), (0.0, 1.0, 0), (0.0, 0.5, 3), (0.5, 1.0, 100), (0.999, 0.25, 0),
+                                            (0.97, 1.0, 1_000_000)])
+def test_every_transform_size(A, L, cutoff, alpha, T):
+    x = sequences(np.random.default_rng(L + T), 2, L)
+    got = smooth(A, x, cutoff, alpha, 66, taper_bins=T)
+    for h in range(2):
+        ref = reference(x[h].astype(np.float64), cutoff, alpha, T)
+        assert np.abs(got[h] - ref).max() <= ATOL * np.abs(x[h]).max()
+        if cutoff == 0.0 and T == 0:
+            assert np.all(got[h] == got[h, 0])              # the mean, everywhere the same
+
+
+@pytest.mark.parametrize("L", LENGTHS)
+@pytest.mark.parametrize("rho", [0.2, 0.9, 0.999])
+@pytest.mark.parametrize("no_dc", [False, True])
+def test_energy_cutoff(A, L, rho, no_dc):
+    x = sequences(np.random.default_rng(L), 3, L)
+    x -= x.mean(axis=1, keepdims=True) * np.float32(0.8)     # little enough DC for the rule to look beyond it
+    mode = A.CUTOFF_ENERGY_NO_DC if no_dc else A.CUTOFF_ENERGY
+    p = A.Params(3, 3, 128, 1, cutoff_mode=mode)
+    t = torch.from_numpy(x.reshape(-1)).cuda()
+    ks = A.smooth_cutoffs(p, t, [L], rho).cpu().numpy()
+    out = A.smooth(p, t, [L], rho, 1.0).cpu().numpy().reshape(3, L)
+    for h in range(3):
+        f = np.fft.rfft(x[h].astype(np.float64))
+        e = np.abs(f) ** 2
+        if no_dc:
+            e[0] = 0.0
+        c, k = np.cumsum(e), int(ks[h])
+        tol = 2e-5 * c[-1]                                  # fp32 bin energies: either neighbour of a near tie is right
+        assert k >= int(no_dc) and c[k] >= rho * c[-1] - tol and (k == int(no_dc) or c[k - 1] < rho * c[-1] + tol)
+        f[k + 1:] = 0
+        assert np.abs(out[h] - np.fft.irfft(f, n=L)).max() <= ATOL * np.abs(x[h]).max()
+
+
+@pytest.mark.parametrize("kernel,mode", [(3, 0), (7, 0), (7, 1), (9, 1), (21, 0)])
+def test_pooling_on_load_equals_the_stages_composed(A, kernel, mode):
+    rng = np.random.default_rng(kernel)
+    lens, H_q, H_kv, d, W = [1024, 8192, 512, 1024, 700, 16384, 32768], 4, 10, 64, 8
+    H_q = 20
+    q = bf16_tensor(f64_to_bf16_bits(rng.standard_normal(len(lens) * H_q * W * d)))
+    k = bf16_tensor(f64_to_bf16_bits(rng.standard_normal(sum(lens) * H_kv * d)))
+    w = torch.rand(len(lens) * H_kv, device="cuda") + 0.1
+    for cutoff_mode, cutoff in ((A.CUTOFF_FRACTION, 0.2), (A.CUTOFF_ENERGY_NO_DC, 0.9)):
+        p = A.Params(H_q, H_kv, d, W, pool_kernel=kernel, pool_mode=mode, cutoff_mode=cutoff_mode)
+        for alpha in (1.0, 0.5):
+            out = A.evict(p, q, k, k, w, lens, 0.4, cutoff, alpha, alloc_scope=A.SCOPE_ITEM)
+            b, cu = A.allocate(p, w, len(lens), H_kv, lens, 0.4)
+            idx = A.select(p, A.smooth(p, A.score(p, q, k, lens), lens, cutoff, alpha), b, cu, lens, out["total_rows"])
+            assert torch.equal(idx, out["indices"][:out["total_rows"]])
