@@ -45,6 +45,7 @@ __device__ __forceinline__ int64_t kv_row_offset(const Geom& g, int item, int64_
 
 // ---- launchers (defined in the .hip files, called from api.hip) ------------
 
+constexpr int kAllocateWaveHeads = 128;    // pools up to this size are allocated by one wave
 // Arguments of launch_allocate, for callers that let the allocation ride along with another small launch.
 struct AllocateJob {
     const float* weights; int n_segments, heads_per_segment, weight_group; const int32_t* cu_seqlens;
@@ -76,6 +77,7 @@ hipError_t launch_score(const Geom& g, const void* q_win, const void* k, const i
 // More than 448 window rows (d <= 128): sweep 2 runs as two launches and needs a second buffer of the size of the
 // scores (raw_second, raw_elems floats).
 bool score_needs_second_raw(int rows, int D);
+// raw: inside a workspace that extends 16 floats to either side of every head
 hipError_t launch_pool(const Geom& g, const float* raw, const int32_t* cu_seqlens, int max_L,
                        float* pooled, hipStream_t s);
 

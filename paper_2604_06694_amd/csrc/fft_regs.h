@@ -16,8 +16,6 @@ __device__ __forceinline__ cf mul(cf a, cf b) {
 // Eq. 20
 __device__ __forceinline__ float mix(float s0, float smoothed, float alpha) { return fmaf(alpha, smoothed, (1.f - alpha) * s0); }
 
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));    // any head start: heads are L floats apart
 
 // exp(i pi x), |x| <= 2^16: x - k/2 is exact, and on [-1/4, 1/4] the Taylor series of cos and sin (remainders below
 // 3e-9 and 3e-10)

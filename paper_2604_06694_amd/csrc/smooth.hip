@@ -31,6 +31,10 @@ namespace {
 
 // ----------------------------- pooling --------------------------------------
 
+// A thread pools eight neighbours from one window of 16 samples (POOL = 7 or any size up to 9: pooled_window; 0: any size,
+// tap by tap). The raw scores lie inside a workspace that extends at least 16 floats to either side of every head: what a
+// window reads outside its head is replaced by the padding. Per-tap loads of every output cost 23 us for 192 heads of 16384.
+template <int POOL>
 __global__ __launch_bounds__(256) void pool_kernel(Geom g, const float* __restrict__ raw,
                                                    const int32_t* __restrict__ cu_seq,
                                                    float* __restrict__ pooled,
@@ -42,8 +46,30 @@ __global__ __launch_bounds__(256) void pool_kernel(Geom g, const float* __restri
     const int L = cu_seq[item + 1] - tok0;
     if (only.h && !conv_item(only, L)) return;
     const size_t off = (size_t)tok0 * g.H_kv + (size_t)h * L;
-    for (int j = blockIdx.x * blockDim.x + threadIdx.x; j < L; j += gridDim.x * blockDim.x)
-        pooled[off + j] = pooled_at(raw + off, L, j, g.pool_kernel, g.pool_mode);
+    const float* src = raw + off;
+    float* dst = pooled + off;
+    if constexpr (POOL == 0) {
+        for (int j = blockIdx.x * blockDim.x + threadIdx.x; j < L; j += gridDim.x * blockDim.x)
+            dst[j] = pooled_at(src, L, j, g.pool_kernel, g.pool_mode);
+    } else {
+        const float fill = g.pool_mode == AUDIOKV_POOL_MAX ? -INFINITY : 0.f;
+        const int j0 = (blockIdx.x * 256 + threadIdx.x) * 8;
+        if (j0 >= L) return;
+        float x[16], o[8];
+        window_load(src + j0 - 4, x);
+        if (j0 < 4 || j0 + 12 > L) {
+#pragma unroll
+            for (int u = 0; u < 16; ++u) x[u] = j0 - 4 + u >= 0 && j0 - 4 + u < L ? x[u] : fill;
+        }
+        pooled_window<POOL>(x, g.pool_kernel, g.pool_mode, o);
+        if (j0 + 8 <= L) {
+            *reinterpret_cast<f32x4u*>(dst + j0) = f32x4{o[0], o[1], o[2], o[3]};
+            *reinterpret_cast<f32x4u*>(dst + j0 + 4) = f32x4{o[4], o[5], o[6], o[7]};
+        } else {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) if (j0 + e < L) dst[j0 + e] = o[e];
+        }
+    }
 }
 
 // ------------------------ LDS-resident real FFT ------------------------------
@@ -660,7 +686,6 @@ __device__ __forceinline__ cf tw_m(const cf* lo, const cf* hi, int e) { return c
 // the one or two wider stages ("top" stages) run on global memory, fused into a single radix-4 pass when there are
 // two. `z` is the padded LDS chunk; lo/hi are the twiddle tables of root M.
 
-typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ cf mul_neg_i(cf a) { return {a.im, -a.re}; }
 __device__ __forceinline__ cf mul_pos_i(cf a) { return {-a.im, a.re}; }
@@ -1168,9 +1193,15 @@ hipError_t launch_pool(const Geom& g, const float* raw, const int32_t* cu_seqlen
                        float* pooled, hipStream_t s)
 {
     const int n_heads = g.n_items * g.H_kv;
-    const int bx = max(1, min(64, (max_L + 255) / 256));
-    hipLaunchKernelGGL(pool_kernel, dim3(bx, n_heads), dim3(256), 0, s, g, raw, cu_seqlens, pooled,
-                       ConvFilterJob{});
+    const ConvFilterJob every{};
+    if (g.pool_kernel <= kConvMaxPool) {
+        const dim3 grid((unsigned)((max_L + 2047) / 2048), (unsigned)n_heads);
+        if (g.pool_kernel == 7) hipLaunchKernelGGL(pool_kernel<7>, grid, dim3(256), 0, s, g, raw, cu_seqlens, pooled, every);
+        else hipLaunchKernelGGL(pool_kernel<9>, grid, dim3(256), 0, s, g, raw, cu_seqlens, pooled, every);
+    } else {
+        hipLaunchKernelGGL(pool_kernel<0>, dim3(max(1, min(64, (max_L + 255) / 256)), n_heads), dim3(256), 0, s, g, raw, cu_seqlens,
+                           pooled, every);
+    }
     return hipGetLastError();
 }
 
@@ -1421,7 +1452,7 @@ hipError_t launch_smooth(const Geom& g, const float* in, bool pool_on_load, cons
         if (pool_on_load && g.pool_kernel > kConvMaxPool) {
             // a kernel wider than the convolution's loads can apply: pooled first, into the result (only the heads that
             // are convolved: the others are done), and smoothed in place
-            hipLaunchKernelGGL(pool_kernel, dim3(64, n_heads), dim3(256), 0, s, g, in, cu_seqlens, out, pl.conv.job);
+            hipLaunchKernelGGL(pool_kernel<0>, dim3(64, n_heads), dim3(256), 0, s, g, in, cu_seqlens, out, pl.conv.job);
             e = launch_conv(g, pl.conv, out, false, (float)alpha, out, s);
         } else {
             e = launch_conv(g, pl.conv, in, pool_on_load, (float)alpha, out, s);

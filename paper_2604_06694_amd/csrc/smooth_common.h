@@ -75,6 +75,46 @@ __device__ __forceinline__ void pooled_pair(const float* x, int L, int j0, int k
     }
 }
 
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));    // any head start: heads are L floats apart
+
+// Pooled values around samples 4 .. 11 of a window of 16. Same taps, order of additions and reciprocal as pooled_at
+// (which is what makes the fused path equal the staged one): POOL = 7, the usual size, spelled out; POOL = 9 for any
+// size up to 9, where the taps outside the kernel are replaced by the padding's neutral value.
+template <int POOL>
+__device__ __forceinline__ void pooled_window(const float (&w)[16], int kernel, int mode, float (&o)[8]) {
+    const int half = POOL == 7 ? 3 : kernel >> 1;
+    if (mode == AUDIOKV_POOL_AVG) {
+        const float inv = POOL == 7 ? 1.0f / 7.0f : 1.0f / (float)kernel;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            float a = 0.f;
+#pragma unroll
+            for (int u = -(POOL / 2); u <= POOL / 2; ++u) a += POOL == 7 || (u < 0 ? -u : u) <= half ? w[4 + e + u] : 0.f;
+            o[e] = a * inv;
+        }
+    } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            float a = -INFINITY;
+#pragma unroll
+            for (int u = -(POOL / 2); u <= POOL / 2; ++u)
+                a = fmaxf(a, POOL == 7 || (u < 0 ? -u : u) <= half ? w[4 + e + u] : -INFINITY);
+            o[e] = a;
+        }
+    }
+}
+// N consecutive floats from `at` (any alignment)
+template <int N>
+__device__ __forceinline__ void window_load(const float* __restrict__ at, float (&w)[N]) {
+#pragma unroll
+    for (int u = 0; u < N / 4; ++u) {
+        const f32x4 a = *reinterpret_cast<const f32x4u*>(at + 4 * u);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) w[4 * u + e] = a[e];
+    }
+}
+
 struct cf { float re, im; };
 __device__ __forceinline__ cf cmul(cf a, cf b) { return {a.re * b.re - a.im * b.im, a.re * b.im + a.im * b.re}; }
 __device__ __forceinline__ cf cadd(cf a, cf b) { return {a.re + b.re, a.im + b.im}; }

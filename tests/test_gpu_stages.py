@@ -115,6 +115,16 @@ def test_allocate_random_and_edge_cases(A):
     _alloc_case(A, rng.gamma(1.0, size=56), 2, 4, [2048, 777], 0.4, 32, 0.1, group=7)   # query-head weights
 
 
+@pytest.mark.parametrize("n", [1, 2, 63, 64, 65, 127, 128, 129])
+def test_allocate_pool_sizes_around_the_wave(A, n):
+    # pools that one wave allocates (one or two heads per lane) and the first that a workgroup does: capping in several
+    # rounds, ties in the remainders, several pools in one call
+    rng = np.random.default_rng(n)
+    _alloc_case(A, rng.gamma(0.1, size=n) + 1e-9, 1, n, [3000], 0.6, 16, 0.0)
+    _alloc_case(A, np.ones(n), 1, n, [1001], 0.3331, 8, 0.1)
+    _alloc_case(A, rng.gamma(0.3, size=3 * n) + 1e-9, 3, n, [700, 5000, 64], 0.45, 8, 0.2)
+
+
 # ------------------------------------------------------------------- select
 
 def _select_case(A, scores_per_head, lens, H_kv, budgets, W):
