@@ -1,6 +1,12 @@
 // Stage 5: gather the retained K/V rows into the packed cache.
 // Pure data movement: every row is d*2 bytes (128-512 B), moved as 16-byte
 // vectors so that a row is read and written by 8-32 adjacent lanes.
+//
+// Bound by HBM, and for small caches by the chain head -> index -> row -> store.
+// A thread moves one vector of K and one of V and the waves do the rest: with
+// so few registers a CU holds 32 of them. (Eight rows per thread, the loads of
+// all in flight, is slower at every size: 3.3 k rows 6.3 us against 3.7, 22 k 9.7
+// against 6.2, 52 k 15.0 against 11.7, 1.47 M 266 against 246, 6.1 TB/s.)
 #include "common.h"
 
 namespace audiokv {
@@ -8,16 +14,21 @@ namespace audiokv {
 namespace {
 
 constexpr int kThreads = 256;
-constexpr int kRowsInFlight = 8;   // independent rows per thread: loads issued before stores
 
-// Largest g with cu_b[g] <= p (cu_b is a non-decreasing exclusive scan, cu_b[n] = total).
+// Largest g with cu_b[g] <= p (cu_b is a non-decreasing exclusive scan, cu_b[n] = total > p; p uniform). Every round
+// probes 64 heads at equal distances, one per lane: one load latency for up to 64 heads, two up to 4096.
 __device__ __forceinline__ int head_of_row(const int32_t* __restrict__ cu_b, int n_heads, int p) {
-    int lo = 0, hi = n_heads;           // invariant: cu_b[lo] <= p < cu_b[hi]
-    while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (cu_b[mid] <= p) lo = mid; else hi = mid;
+    int head = 0;
+    for (int span = n_heads; span > 1;) {
+        const int step = (span + 63) >> 6;
+        const int probe = head + (int)(threadIdx.x & 63) * step;
+        const bool at_or_before = probe < head + span && cu_b[min(probe, n_heads - 1)] <= p;
+        const int n = __builtin_popcountll(__builtin_amdgcn_ballot_w64(at_or_before));   // a prefix of the lanes
+        const int skip = n > 0 ? (n - 1) * step : 0;
+        head += skip;
+        span = min(step, span - skip);
     }
-    return lo;
+    return __builtin_amdgcn_readfirstlane(head);
 }
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));   // 16 bytes; the nontemporal builtins need a native vector
@@ -29,43 +40,25 @@ __global__ __launch_bounds__(kThreads) void compact_kernel(
     const int32_t* __restrict__ cu_seq, int n_heads, int64_t total_rows,
     u32x4* __restrict__ k_out, u32x4* __restrict__ v_out)
 {
-    constexpr int ROWS_PER_PASS = kThreads / VEC_PER_ROW;
-    const int sub = threadIdx.x / VEC_PER_ROW;     // row within a pass
+    constexpr int ROWS = kThreads / VEC_PER_ROW;   // consecutive output rows of a workgroup
     const int vec = threadIdx.x % VEC_PER_ROW;     // 16-byte piece of the row
-    const int64_t row0 = (int64_t)blockIdx.x * (ROWS_PER_PASS * kRowsInFlight);
-
-    // The block's rows are consecutive output rows: find the head of the first one once (uniform, so the
-    // search runs on scalar loads), then every row only walks forward from there.
-    const int head0 = head_of_row(cu_b, n_heads, (int)row0);
-
-    // Nothing below branches around a load: rows past the end are clamped to the last row and simply not
-    // stored, so all gathers of the block are in flight together.
-    int64_t src[kRowsInFlight];
-#pragma unroll
-    for (int r = 0; r < kRowsInFlight; ++r) {
-        const int p = (int)min(row0 + r * ROWS_PER_PASS + sub, total_rows - 1);
-        int gh = head0;
-        while (gh + 1 < n_heads && cu_b[gh + 1] <= p) ++gh;
-        const int item = gh / g.H_kv, h = gh - item * g.H_kv;
-        const int tok0 = cu_seq[item];
-        const int L = cu_seq[item + 1] - tok0;
-        // an index outside the item is a caller error; clamp so that it can never fault
-        const int j = min(max(indices[p], 0), L - 1);
-        src[r] = kv_row_offset(g, item, tok0, L, h, j) / 8 + vec;   // in u32x4 units (8 bf16; strides are multiples of 8)
-    }
-    u32x4 kk[kRowsInFlight], vv[kRowsInFlight];
-#pragma unroll
-    for (int r = 0; r < kRowsInFlight; ++r) {
-        kk[r] = __builtin_nontemporal_load(k + src[r]);
-        vv[r] = __builtin_nontemporal_load(v + src[r]);
-    }
-#pragma unroll
-    for (int r = 0; r < kRowsInFlight; ++r) {
-        const int64_t p = row0 + r * ROWS_PER_PASS + sub;
-        if (p < total_rows) {
-            __builtin_nontemporal_store(kk[r], k_out + p * VEC_PER_ROW + vec);
-            __builtin_nontemporal_store(vv[r], v_out + p * VEC_PER_ROW + vec);
-        }
+    const int64_t row0 = (int64_t)blockIdx.x * ROWS;
+    // the head of the workgroup's first row is found once; a later row walks forward from there
+    int gh = head_of_row(cu_b, n_heads, (int)row0);
+    // (a row past the end is the last row again, which is not stored: no branch around the loads)
+    const int64_t p = row0 + threadIdx.x / VEC_PER_ROW, pc = min(p, total_rows - 1);
+    const int idx = indices[pc];
+    while (gh + 1 < n_heads && cu_b[gh + 1] <= pc) ++gh;
+    const int item = gh / g.H_kv, h = gh - item * g.H_kv;
+    const int tok0 = cu_seq[item];
+    const int L = cu_seq[item + 1] - tok0;
+    // an index outside the item is a caller error; clamp so that it can never fault
+    const int64_t src = kv_row_offset(g, item, tok0, L, h, min(max(idx, 0), L - 1)) / 8 + vec;   // strides are multiples of 8
+    const u32x4 kk = __builtin_nontemporal_load(k + src);
+    const u32x4 vv = __builtin_nontemporal_load(v + src);
+    if (p < total_rows) {
+        __builtin_nontemporal_store(kk, k_out + p * VEC_PER_ROW + vec);
+        __builtin_nontemporal_store(vv, v_out + p * VEC_PER_ROW + vec);
     }
 }
 
@@ -78,7 +71,7 @@ hipError_t launch_compact(const Geom& g, const void* k, const void* v, const int
     if (total_rows <= 0) return hipSuccess;
     const int n_heads = g.n_items * g.H_kv;
     const int vec_per_row = g.D / 8;
-    const int rows_per_block = (kThreads / vec_per_row) * kRowsInFlight;
+    const int rows_per_block = kThreads / vec_per_row;
     const unsigned blocks = (unsigned)((total_rows + rows_per_block - 1) / rows_per_block);
 #define AUDIOKV_LAUNCH_COMPACT(V)                                                                   \
     hipLaunchKernelGGL((compact_kernel<V>), dim3(blocks), dim3(kThreads), 0, s, g,                  \
