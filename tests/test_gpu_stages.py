@@ -186,6 +186,26 @@ def test_select_long_heads_every_distribution(A, L, W):
         _select_case(A, heads, [L], len(heads), budgets, W)
 
 
+@pytest.mark.parametrize("L", [65, 2047, 2048, 2049, 4096, 4097, 8192, 8193, 16385])
+def test_select_block_sizes_and_histogram_rounds(A, L):
+    """Lengths on either side of each block size, with keys that take one round of the histogram, several (a wide range
+    with most keys close together), none (all equal) or rounds over the token index (more than 64 ties at the
+    threshold, alone or below a few larger keys); integers, so exact."""
+    rng = np.random.default_rng(L)
+    x = rng.random(L)
+    few = np.full(L, 0.25)
+    few[rng.integers(0, L, 5)] = 3e4
+    low = np.full(L, 0.25)
+    low[::9] = -np.inf
+    wide = 1.0 + 1e-6 * x
+    wide[0], wide[L // 2] = np.inf, -1e30
+    heads = [np.ascontiguousarray(s, dtype=np.float32)
+             for s in (x, wide, np.zeros(L), few, low, np.round(x * 3), np.arange(L) % 50, -x)]
+    for W in (0, 1, 64):
+        for budgets in ([max(W, 1)] * 8, [W + 1] * 8, [L] * 8, [L - 1] * 8, [max(W, 1) + (L - max(W, 1)) * (h + 1) // 9 for h in range(8)]):
+            _select_case(A, heads, [L], 8, budgets, W)
+
+
 def test_select_ragged_items(A):
     rng = np.random.default_rng(9)
     lens = [100, 2500, 33]
