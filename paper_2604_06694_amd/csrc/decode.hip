@@ -248,6 +248,7 @@ void decode_partial_kernel(
 // many as possible are in flight: the statistics one chunk per thread, then the accumulators with a thread on four
 // channels of every (256 / (D/4))-th chunk. Every sum has a fixed order.
 constexpr int kMergeThreads = 256;
+constexpr int kMergeEarly = 4;            // accumulators per thread requested before the statistics are known
 constexpr int kMergeLds = 2048;           // chunks whose weights fit the LDS array (more: recomputed where used)
 
 __global__ __launch_bounds__(kMergeThreads) void decode_merge_kernel(
@@ -263,6 +264,18 @@ __global__ __launch_bounds__(kMergeThreads) void decode_merge_kernel(
     __shared__ float wgt[kMergeLds];
     __shared__ float wave_m[kMergeThreads / 64], wave_l[kMergeThreads / 64];
     __shared__ __attribute__((aligned(16))) f32x4 red[kMergeThreads];
+
+    // The first accumulators are requested together with the statistics: one load latency less (112 heads of 13 chunks 6.3 ->
+    // 5.7 us, 64 heads 4.6 -> 4.0).
+    const int quads = g.D >> 2, groups = kMergeThreads / quads;  // D = 64, 128, 256: 16, 8, 4 chunks at a time
+    const int ch4 = tid % quads, grp = tid / quads;
+    const f32x4* col = reinterpret_cast<const f32x4*>(part + ((size_t)c0 * g.G + qh) * g.D) + ch4;
+    const size_t stride = (size_t)g.G * quads;
+    f32x4 early[kMergeEarly];
+    if (nc > 0) {
+#pragma unroll
+        for (int u = 0; u < kMergeEarly; ++u) early[u] = col[(size_t)min(grp + u * groups, nc - 1) * stride];
+    }
 
     const float2* st = reinterpret_cast<const float2*>(stats) + (size_t)c0 * g.G + qh;     // chunk c at st[c * G]
     float m = -INFINITY, l = 0.f;
@@ -290,13 +303,12 @@ __global__ __launch_bounds__(kMergeThreads) void decode_merge_kernel(
 #pragma unroll
     for (int w = 0; w < kMergeThreads / 64; ++w) den += wave_l[w];
 
-    const int quads = g.D >> 2, groups = kMergeThreads / quads;  // D = 64, 128, 256: 16, 8, 4 chunks at a time
-    const int ch4 = tid % quads, grp = tid / quads;
-    const f32x4* col = reinterpret_cast<const f32x4*>(part + ((size_t)c0 * g.G + qh) * g.D) + ch4;
-    const size_t stride = (size_t)g.G * quads;
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int u = 0; u < kMergeEarly; ++u)
+        if (grp + u * groups < nc) acc += early[u] * wgt[grp + u * groups];
 #pragma unroll 4
-    for (int c = grp; c < nc; c += groups) {
+    for (int c = grp + kMergeEarly * groups; c < nc; c += groups) {
         const float w = c < kMergeLds ? wgt[c] : __builtin_amdgcn_exp2f(st[(size_t)c * g.G].x - M);
         acc += col[(size_t)c * stride] * w;
     }

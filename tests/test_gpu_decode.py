@@ -151,3 +151,13 @@ def test_decode_empty_heads_between_full_ones(A):
     out = A.decode_attend(A.Params(1, 1, d, 1), q, v, v, torch.from_numpy(cu).cuda(), n, int(cu[-1])).cpu().numpy()
     want = [(np.arange(cu[g], cu[g + 1]) % 251).mean() if budgets[g] else 0.0 for g in range(n)]
     np.testing.assert_allclose(out[:, 0], np.repeat(np.array(want)[:, None], d, 1), rtol=2e-6)     # fp32 sums of <= 256 terms
+
+
+@pytest.mark.parametrize("d,groups", [(64, 16), (128, 8), (256, 4)])
+def test_decode_merge_around_the_accumulators_requested_early(A, d, groups):
+    """Chunks per head on either side of what a thread of the merge requests before it knows the statistics (four per
+    thread, `groups` threads on a channel), of one thread's share and of nothing. Chunks hold 128 rows at these sizes."""
+    rng = np.random.default_rng(d)
+    edge = 4 * groups * 128
+    run_case(A, rng, 8, 4, d, [edge, edge + 1, edge - 127, 129], 1)
+    run_case(A, rng, 4, 4, d, [groups * 128, groups * 128 + 1, 1, edge + groups * 128 + 1], 1)
