@@ -176,13 +176,13 @@ __device__ __forceinline__ void to_bins(ConvLds<LOGC>& m, const typename Fft<LOG
 
 // the filter's bins of every distinct length, for calls in which many heads share them
 template <int LOGC>
-__global__ __launch_bounds__(Fft<LOGC>::THREADS) void conv_spectrum_kernel(Geom g, ConvFilterJob job, cf* __restrict__ spec,
-                                                                           size_t spec_stride)
+__global__ __launch_bounds__(Fft<LOGC>::THREADS) void conv_spectrum_kernel(Geom g, ConvFilterJob job, int log_r,
+                                                                           cf* __restrict__ spec, size_t spec_stride)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     ConvLds<LOGC>& m = *reinterpret_cast<ConvLds<LOGC>*>(smem);
     ConvHead w;
-    const int item = blockIdx.y, r = blockIdx.x, t = threadIdx.x;
+    const int item = blockIdx.x >> log_r, r = blockIdx.x & ((1 << log_r) - 1), t = threadIdx.x;
     if (!conv_head(g, job, item * g.H_kv, LOGC, w) || w.owner != item || r >= w.R) return;
     fill_constants<LOGC>(m, w, r, t);
     typename Fft<LOGC>::Twiddles tw;
@@ -200,7 +200,7 @@ __global__ __launch_bounds__(Fft<LOGC>::THREADS) void conv_spectrum_kernel(Geom 
 
 template <int LOGC, int POOL>
 __global__ __launch_bounds__(Fft<LOGC>::THREADS) void conv_chunk_kernel(
-    Geom g, const float* __restrict__ in, ConvFilterJob job, const cf* __restrict__ spec, size_t spec_stride,
+    Geom g, const float* __restrict__ in, ConvFilterJob job, int log_r, const cf* __restrict__ spec, size_t spec_stride,
     cf* __restrict__ part, size_t part_stride, float alpha, float* __restrict__ out)
 {
     constexpr int C = 1 << LOGC, T = Fft<LOGC>::THREADS;
@@ -208,7 +208,7 @@ __global__ __launch_bounds__(Fft<LOGC>::THREADS) void conv_chunk_kernel(
     ConvLds<LOGC>& m = *reinterpret_cast<ConvLds<LOGC>*>(smem);
     constexpr int U = LOGC == 13 ? 2 : 4;                        // (1024 threads: 128 registers)
     ConvHead w;
-    const int head = blockIdx.y, r = blockIdx.x, t = threadIdx.x;
+    const int head = blockIdx.x >> log_r, r = blockIdx.x & ((1 << log_r) - 1), t = threadIdx.x;
     if (!conv_head(g, job, head, LOGC, w) || r >= w.R) return;
     fill_constants<LOGC>(m, w, r, t);
     typename Fft<LOGC>::Twiddles tw;
@@ -308,9 +308,9 @@ __global__ __launch_bounds__(kJoinThreads) void conv_join_kernel(
     size_t part_stride, float alpha, float* __restrict__ out)
 {
     ConvHead w;
-    const int head = blockIdx.y, C = 1 << log_c;
+    const int C = 1 << log_c, per_head = C / kJoinThreads, head = blockIdx.x / per_head;
     if (!conv_head(g, job, head, log_c, w) || w.R == 1) return;
-    const int n = blockIdx.x * kJoinThreads + threadIdx.x;               // grid.x * kJoinThreads = C
+    const int n = (blockIdx.x - head * per_head) * kJoinThreads + threadIdx.x;
     const cf* p = part + (size_t)head * part_stride;
     const float* src = in + w.off;
     float* dst = out + w.off;
@@ -337,6 +337,10 @@ __global__ __launch_bounds__(kJoinThreads) void conv_join_kernel(
 
 __global__ __launch_bounds__(kConvFilterThreads) void conv_filter_kernel(ConvFilterJob job) { conv_filter_block(job, blockIdx.x); }
 
+// Workgroups are numbered in one dimension, those of a head next to each other: the second and third dimension of a grid
+// end at 65535, and a batch may hold more heads than that.
+int log_residues(const ConvCall& c) { return 31 - __builtin_clz((unsigned)c.max_r); }
+
 template <int LOGC, int POOL>
 hipError_t launch_chunks(const Geom& g, const ConvCall& c, const float* in, float alpha, float* out, hipStream_t s) {
     const int lds = (int)sizeof(ConvLds<LOGC>);
@@ -349,8 +353,8 @@ hipError_t launch_chunks(const Geom& g, const ConvCall& c, const float* in, floa
             attr_set = true;
         }
     }
-    hipLaunchKernelGGL((conv_chunk_kernel<LOGC, POOL>), dim3((unsigned)c.max_r, (unsigned)(g.n_items * g.H_kv)),
-                       dim3(Fft<LOGC>::THREADS), lds, s, g, in, c.job, (const cf*)c.spec, c.points, (cf*)c.part, c.points, alpha, out);
+    hipLaunchKernelGGL((conv_chunk_kernel<LOGC, POOL>), dim3((unsigned)(g.n_items * g.H_kv) << log_residues(c)),
+                       dim3(Fft<LOGC>::THREADS), lds, s, g, in, c.job, log_residues(c), (const cf*)c.spec, c.points, (cf*)c.part, c.points, alpha, out);
     return hipGetLastError();
 }
 template <int LOGC>
@@ -371,8 +375,8 @@ hipError_t launch_spectra(const Geom& g, const ConvCall& c, hipStream_t s) {
             attr_set = true;
         }
     }
-    hipLaunchKernelGGL((conv_spectrum_kernel<LOGC>), dim3((unsigned)c.max_r, (unsigned)g.n_items), dim3(Fft<LOGC>::THREADS), lds, s,
-                       g, c.job, (cf*)c.spec, c.points);
+    hipLaunchKernelGGL((conv_spectrum_kernel<LOGC>), dim3((unsigned)g.n_items << log_residues(c)), dim3(Fft<LOGC>::THREADS), lds, s,
+                       g, c.job, log_residues(c), (cf*)c.spec, c.points);
     return hipGetLastError();
 }
 
@@ -400,7 +404,7 @@ hipError_t launch_conv(const Geom& g, const ConvCall& c, const float* in, bool p
         default: e = launch_chunks<13>(g, c, in, pool_on_load, alpha, out, s); break;
     }
     if (e != hipSuccess || c.max_r == 1) return e;
-    hipLaunchKernelGGL(conv_join_kernel, dim3((1u << c.log_c) / kJoinThreads, (unsigned)(g.n_items * g.H_kv)), dim3(kJoinThreads),
+    hipLaunchKernelGGL(conv_join_kernel, dim3((1u << c.log_c) / kJoinThreads * (unsigned)(g.n_items * g.H_kv)), dim3(kJoinThreads),
                        0, s, g, in, pool_on_load ? 1 : 0, c.job, c.log_c, (const cf*)c.part, c.points, alpha, out);
     return hipGetLastError();
 }

@@ -37,10 +37,11 @@ namespace {
 template <int POOL>
 __global__ __launch_bounds__(256) void pool_kernel(Geom g, const float* __restrict__ raw,
                                                    const int32_t* __restrict__ cu_seq,
-                                                   float* __restrict__ pooled,
+                                                   float* __restrict__ pooled, int per_head,   // workgroups
                                                    ConvFilterJob only)     // if only.h: the heads of that job
 {
-    const int head = blockIdx.y;
+    // (numbered in one dimension: the second one of a grid ends at 65535, a batch of heads need not)
+    const int head = blockIdx.x / per_head, part = blockIdx.x - head * per_head;
     const int item = head / g.H_kv, h = head - item * g.H_kv;
     const int tok0 = cu_seq[item];
     const int L = cu_seq[item + 1] - tok0;
@@ -49,11 +50,11 @@ __global__ __launch_bounds__(256) void pool_kernel(Geom g, const float* __restri
     const float* src = raw + off;
     float* dst = pooled + off;
     if constexpr (POOL == 0) {
-        for (int j = blockIdx.x * blockDim.x + threadIdx.x; j < L; j += gridDim.x * blockDim.x)
+        for (int j = part * blockDim.x + threadIdx.x; j < L; j += per_head * blockDim.x)
             dst[j] = pooled_at(src, L, j, g.pool_kernel, g.pool_mode);
     } else {
         const float fill = g.pool_mode == AUDIOKV_POOL_MAX ? -INFINITY : 0.f;
-        const int j0 = (blockIdx.x * 256 + threadIdx.x) * 8;
+        const int j0 = (part * 256 + threadIdx.x) * 8;
         if (j0 >= L) return;
         float x[16], o[8];
         window_load(src + j0 - 4, x);
@@ -1195,12 +1196,14 @@ hipError_t launch_pool(const Geom& g, const float* raw, const int32_t* cu_seqlen
     const int n_heads = g.n_items * g.H_kv;
     const ConvFilterJob every{};
     if (g.pool_kernel <= kConvMaxPool) {
-        const dim3 grid((unsigned)((max_L + 2047) / 2048), (unsigned)n_heads);
-        if (g.pool_kernel == 7) hipLaunchKernelGGL(pool_kernel<7>, grid, dim3(256), 0, s, g, raw, cu_seqlens, pooled, every);
-        else hipLaunchKernelGGL(pool_kernel<9>, grid, dim3(256), 0, s, g, raw, cu_seqlens, pooled, every);
+        const int per_head = (max_L + 2047) / 2048;
+        const dim3 grid((unsigned)per_head * (unsigned)n_heads);
+        if (g.pool_kernel == 7) hipLaunchKernelGGL(pool_kernel<7>, grid, dim3(256), 0, s, g, raw, cu_seqlens, pooled, per_head, every);
+        else hipLaunchKernelGGL(pool_kernel<9>, grid, dim3(256), 0, s, g, raw, cu_seqlens, pooled, per_head, every);
     } else {
-        hipLaunchKernelGGL(pool_kernel<0>, dim3(max(1, min(64, (max_L + 255) / 256)), n_heads), dim3(256), 0, s, g, raw, cu_seqlens,
-                           pooled, every);
+        const int per_head = max(1, min(64, (max_L + 255) / 256));
+        hipLaunchKernelGGL(pool_kernel<0>, dim3((unsigned)per_head * (unsigned)n_heads), dim3(256), 0, s, g, raw, cu_seqlens,
+                           pooled, per_head, every);
     }
     return hipGetLastError();
 }
@@ -1452,7 +1455,7 @@ hipError_t launch_smooth(const Geom& g, const float* in, bool pool_on_load, cons
         if (pool_on_load && g.pool_kernel > kConvMaxPool) {
             // a kernel wider than the convolution's loads can apply: pooled first, into the result (only the heads that
             // are convolved: the others are done), and smoothed in place
-            hipLaunchKernelGGL(pool_kernel<0>, dim3(64, n_heads), dim3(256), 0, s, g, in, cu_seqlens, out, pl.conv.job);
+            hipLaunchKernelGGL(pool_kernel<0>, dim3(64u * (unsigned)n_heads), dim3(256), 0, s, g, in, cu_seqlens, out, 64, pl.conv.job);
             e = launch_conv(g, pl.conv, out, false, (float)alpha, out, s);
         } else {
             e = launch_conv(g, pl.conv, in, pool_on_load, (float)alpha, out, s);

@@ -111,3 +111,21 @@ def test_smoothed_scores_meet_the_oracle(A):
     out = A.smooth(A.Params(2, 2, 128, 1), torch.from_numpy(x.reshape(-1)).cuda(), [L], 0.125, 1.0).cpu().numpy().reshape(2, L)
     for h in range(2):
         assert rel_err(out[h], O.smooth(x[h].astype(np.float64), 0.125, 1.0)) <= SCORE_RTOL
+
+
+def test_smooth_more_heads_than_a_grid_dimension_holds(A):
+    """70000 short sequences of one head each: beyond 65535, where the second dimension of a grid ends; the first and the
+    last ones are what they are on their own, bit for bit."""
+    L, n = 21, 70000
+    s = torch.rand(n * L, generator=torch.Generator(device="cuda").manual_seed(3), device="cuda")
+    p = A.Params(1, 1, 64, 1)
+    out = A.smooth(p, s, [L] * n, 0.25, 1.0).view(n, L)
+    some = [0, 1, 65534, 65535, 65536, n - 1]
+    alone = torch.stack([A.smooth(p, s.view(n, L)[i].contiguous(), [L], 0.25, 1.0) for i in some])
+    torch.cuda.synchronize()
+    assert torch.equal(out[some], alone)
+    spectrum = torch.fft.rfft(s.view(n, L).double(), dim=1)
+    spectrum[:, int(0.25 * (L // 2)) + 1:] = 0
+    ref = torch.fft.irfft(spectrum, n=L, dim=1)
+    # fp32 transforms of 32 points and 21 taps: a few ulps of the mean-1/2 sequence
+    assert (out.double() - ref).abs().max().item() < 5e-6
