@@ -37,12 +37,12 @@ template <int VEC_PER_ROW>   // 16-byte vectors per row = D * 2 / 16
 __global__ __launch_bounds__(kThreads) void compact_kernel(
     Geom g, const u32x4* __restrict__ k, const u32x4* __restrict__ v,
     const int32_t* __restrict__ indices, const int32_t* __restrict__ cu_b,
-    const int32_t* __restrict__ cu_seq, int n_heads, int64_t total_rows,
+    const int32_t* __restrict__ cu_seq, int n_heads, int64_t first_row, int64_t total_rows,
     u32x4* __restrict__ k_out, u32x4* __restrict__ v_out)
 {
     constexpr int ROWS = kThreads / VEC_PER_ROW;   // consecutive output rows of a workgroup
     const int vec = threadIdx.x % VEC_PER_ROW;     // 16-byte piece of the row
-    const int64_t row0 = (int64_t)blockIdx.x * ROWS;
+    const int64_t row0 = first_row + (int64_t)blockIdx.x * ROWS;
     // the head of the workgroup's first row is found once; a later row walks forward from there
     int gh = head_of_row(cu_b, n_heads, (int)row0);
     // (a row past the end is the last row again, which is not stored: no branch around the loads)
@@ -72,19 +72,26 @@ hipError_t launch_compact(const Geom& g, const void* k, const void* v, const int
     const int n_heads = g.n_items * g.H_kv;
     const int vec_per_row = g.D / 8;
     const int rows_per_block = kThreads / vec_per_row;
-    const unsigned blocks = (unsigned)((total_rows + rows_per_block - 1) / rows_per_block);
+    // a launch holds fewer than 2^32 threads: rows beyond that (60 GB and more) take further ones
+    const int64_t slab = (int64_t)rows_per_block << 23;
 #define AUDIOKV_LAUNCH_COMPACT(V)                                                                   \
     hipLaunchKernelGGL((compact_kernel<V>), dim3(blocks), dim3(kThreads), 0, s, g,                  \
                        (const u32x4*)k, (const u32x4*)v, indices, cu_budgets, cu_seqlens, n_heads, \
-                       total_rows, (u32x4*)k_out, (u32x4*)v_out)
-    switch (vec_per_row) {
-        case 8:  AUDIOKV_LAUNCH_COMPACT(8);  break;
-        case 16: AUDIOKV_LAUNCH_COMPACT(16); break;
-        case 32: AUDIOKV_LAUNCH_COMPACT(32); break;
-        default: return hipErrorInvalidValue;
+                       first, total_rows, (u32x4*)k_out, (u32x4*)v_out)
+    for (int64_t first = 0; first < total_rows; first += slab) {
+        const int64_t rows = total_rows - first < slab ? total_rows - first : slab;
+        const unsigned blocks = (unsigned)((rows + rows_per_block - 1) / rows_per_block);
+        switch (vec_per_row) {
+            case 8:  AUDIOKV_LAUNCH_COMPACT(8);  break;
+            case 16: AUDIOKV_LAUNCH_COMPACT(16); break;
+            case 32: AUDIOKV_LAUNCH_COMPACT(32); break;
+            default: return hipErrorInvalidValue;
+        }
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
     }
 #undef AUDIOKV_LAUNCH_COMPACT
-    return hipGetLastError();
+    return hipSuccess;
 }
 
 }  // namespace audiokv
