@@ -108,12 +108,13 @@ void decode_partial_kernel(
     // the first V rows of phase 3 (all of a 128-row chunk at d <= 128) are requested first: one latency for K and V
     const int c8 = tid % VPR, kq = tid / VPR;
     u32x4 vv[UN];
+    // Rows past the end carry weight 0, but 0 times an infinity is NaN: they have to read as zeros. A buffer whose size is
+    // that of the chunk's rows does that in hardware.
+    const auto vbuf = __builtin_amdgcn_make_buffer_rsrc(const_cast<__bf16*>(vrow0), 0, rows * D * 2, 0x00027000);
     auto load_v = [&](int r0) {
 #pragma unroll
-        for (int u = 0; u < UN; ++u) {
-            const int rc = min(r0 + kq + u * KQ, rows - 1);      // rows past the end carry weight 0
-            vv[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(vrow0 + (size_t)rc * D) + c8);
-        }
+        for (int u = 0; u < UN; ++u)
+            vv[u] = __builtin_amdgcn_raw_buffer_load_b128(vbuf, ((r0 + kq + u * KQ) * VPR + c8) * 16, 0, 2 /* nontemporal */);
     };
     load_v(0);
 

@@ -161,3 +161,25 @@ def test_decode_merge_around_the_accumulators_requested_early(A, d, groups):
     edge = 4 * groups * 128
     run_case(A, rng, 8, 4, d, [edge, edge + 1, edge - 127, 129], 1)
     run_case(A, rng, 4, 4, d, [groups * 128, groups * 128 + 1, 1, edge + groups * 128 + 1], 1)
+
+
+@pytest.mark.parametrize("H_q,d", [(2, 64), (7, 128), (3, 256), (12, 64), (16, 256)])
+def test_decode_infinity_in_the_last_row_of_a_head(A, H_q, d):
+    """An infinite value is what its channel becomes, whatever the budget (the rows that fill up a trip carry weight 0 and
+    must not turn it into NaN); the other channels and heads are the means of their rows (zero queries)."""
+    budgets = [1, 5, 16, 17, 127, 128, 129, 300]
+    n = len(budgets)
+    cu = np.concatenate([[0], np.cumsum(budgets)]).astype(np.int32)
+    v = (np.arange(int(cu[-1])) % 7).astype(np.float32)[:, None].repeat(d, 1)
+    last = cu[1:] - 1
+    want = np.array([v[cu[g]:cu[g + 1], 0].mean() for g in range(n)])
+    v[last, 3] = np.inf
+    v[last, d - 1] = -np.inf
+    vt = torch.from_numpy(v).to(torch.bfloat16).cuda()
+    kt = torch.zeros_like(vt)
+    q = torch.zeros(n * H_q * d, dtype=torch.bfloat16, device="cuda")
+    out = A.decode_attend(A.Params(H_q, 1, d, 1), q, kt.view(-1), vt.view(-1), torch.from_numpy(cu).cuda(), n, int(cu[-1]))
+    out = out.cpu().numpy().reshape(n, H_q, d)
+    assert np.all(out[:, :, 3] == np.inf) and np.all(out[:, :, d - 1] == -np.inf)
+    rest = np.delete(out, [3, d - 1], axis=2)
+    np.testing.assert_allclose(rest, np.broadcast_to(want[:, None, None], rest.shape), rtol=2e-6)    # fp32 sums of <= 300 terms
