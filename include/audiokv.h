@@ -311,7 +311,8 @@ int32_t audiokv_evict_noalloc(const audiokv_params* params,
  * over the budgets[g] rows of KV head g = i * n_kv_heads + j / (n_q_heads /
  * n_kv_heads). total_rows (host) is the sum of all budgets
  * (audiokv_total_kept): it sizes the launch and the workspace
- * (audiokv_decode_workspace_bytes); cache rows at or beyond total_rows are
+ * (audiokv_decode_workspace_bytes, which never falls as total_rows grows: one
+ * workspace sized for the largest cache serves the smaller ones); cache rows at or beyond total_rows are
  * never read. A head with budget 0 yields zeros. n_q_heads / n_kv_heads <= 16. */
 int32_t audiokv_decode_workspace_bytes(const audiokv_params* params, int32_t n_items, int64_t total_rows,
                                        size_t* out_bytes);

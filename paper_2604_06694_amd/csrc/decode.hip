@@ -32,7 +32,7 @@ constexpr int kThreads = 256;
 // Rows per workgroup at most: what the weights' LDS buffer (4 bytes per row and padded query head, 32 KiB) holds, four
 // workgroups per CU. At least one trip of phase 1 (128 rows).
 __host__ __device__ constexpr int max_chunk_rows(int GP) { return GP <= 8 ? 1024 : 512; }
-constexpr int kMinChunkRows = 128;
+constexpr int kMinLogChunk = 7, kMinChunkRows = 1 << kMinLogChunk;
 
 __device__ __forceinline__ float bf16_lo(unsigned int w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf16_hi(unsigned int w) { return __uint_as_float(w & 0xffff0000u); }
@@ -335,8 +335,7 @@ bool decode_supported(int G) { return G >= 1 && G <= 16; }
 // with one workgroup per CU instead of four 367 k rows take 47 us and 734 k rows 86 instead of 78.
 constexpr int kChunksPerCu = 4;
 static int log_chunk_rows(const Geom& g, long long total_rows) {
-    int lg = 7;                                                   // kMinChunkRows
-    static_assert((1 << 7) == kMinChunkRows, "log2 of the smallest chunk");
+    int lg = kMinLogChunk;
     while ((2 << lg) <= max_chunk_rows(g.G) && (total_rows >> (lg + 1)) >= 256 * kChunksPerCu) ++lg;
     return lg;
 }
@@ -346,8 +345,12 @@ static size_t slot_bound(const Geom& g, long long total_rows) {
 }
 static size_t stats_bytes(const Geom& g, size_t bound) { return (bound * g.G * 2 * sizeof(float) + 255) & ~(size_t)255; }
 
+// A workspace sized for one cache serves every smaller one. Where the chunks double, the number of slots halves: every call
+// beyond the first such line is charged the most that calls below a line need.
 size_t decode_workspace_bytes(const Geom& g, long long total_rows) {
-    const size_t bound = slot_bound(g, total_rows);
+    size_t bound = slot_bound(g, total_rows);
+    const size_t peak = 2 * 256 * kChunksPerCu - 1 + (size_t)g.n_items * g.H_kv;
+    if (log_chunk_rows(g, total_rows) > kMinLogChunk && bound < peak) bound = peak;
     return stats_bytes(g, bound) + bound * g.G * g.D * sizeof(float);
 }
 

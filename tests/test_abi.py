@@ -56,6 +56,15 @@ def test_total_kept_and_workspace(A):
     assert big >= 2 * 28 * 4 * 32768 * 4          # raw + smoothed scores
 
 
+def test_decode_workspace_never_falls_as_rows_grow(A):
+    rows = sorted({max(0, (m << s) + d) for s in range(7, 24) for m in (1, 3, 1024, 2047, 2048) for d in (-1, 0, 1)}
+                  | set(range(0, 3_000_000, 9973)))
+    rows = [r for r in rows if r < 2**31]
+    for hq, hkv, d, n in [(28, 4, 128, 28), (28, 4, 128, 1), (8, 8, 64, 3), (16, 1, 256, 2), (9, 1, 64, 1)]:
+        sizes = [A.decode_workspace_bytes(A.Params(hq, hkv, d, 1), n, r) for r in rows]
+        assert all(a <= b for a, b in zip(sizes, sizes[1:]))
+
+
 def test_validation_errors_are_codes_not_crashes(A):
     good = A.Params(28, 4, 128, 32)
     cases = [

@@ -183,3 +183,22 @@ def test_decode_infinity_in_the_last_row_of_a_head(A, H_q, d):
     assert np.all(out[:, :, 3] == np.inf) and np.all(out[:, :, d - 1] == -np.inf)
     rest = np.delete(out, [3, d - 1], axis=2)
     np.testing.assert_allclose(rest, np.broadcast_to(want[:, None, None], rest.shape), rtol=2e-6)    # fp32 sums of <= 300 terms
+
+
+def test_decode_workspace_of_the_largest_call_serves_smaller_ones(A):
+    """One workspace sized for the largest cache, calls on either side of the sizes at which the chunks double; the bytes
+    behind what such a call asks for stay untouched."""
+    H_q, H_kv, d, n = 4, 4, 64, 1
+    p = A.Params(H_q, H_kv, d, 1)
+    most = 600_000
+    ws = torch.empty(A.decode_workspace_bytes(p, n, most), dtype=torch.uint8, device="cuda")
+    gen = torch.Generator(device="cuda").manual_seed(1)
+    k, v = (torch.randn(most * d, generator=gen, device="cuda").to(torch.bfloat16) for _ in range(2))
+    q = torch.randn(H_q * d, generator=gen, device="cuda").to(torch.bfloat16)
+    for rows in (most, 524_288, 524_287, 262_144, 262_143, 200_000, 1000, 3):
+        cu = torch.tensor([0, rows // 3, rows // 2, rows - 1, rows], dtype=torch.int32, device="cuda")
+        need = A.decode_workspace_bytes(p, n, rows)
+        ws.fill_(7)
+        got = A.decode_attend(p, q, k, v, cu, n, rows, workspace=ws)
+        assert torch.equal(got, A.decode_attend(p, q, k, v, cu, n, rows))
+        assert bool((ws[need:] == 7).all())
