@@ -23,7 +23,8 @@
 // Pool + smooth of one layer of four heads inside evict, chirp-z path before -> this: L = 13577 41 us in six launches beside
 // 50 us of filter preparation on another stream -> 19 us in two (chunks 14, join 5) and nothing beside; a smooth call on 24
 // sequences of two heads, 1500 to 30000 samples, 147 -> 41 us (taps 8, chunks 31, join 4); one layer of 30011 alone 78 -> 22,
-// 28 layers 144 -> 68. Error against 64 bits 5.2e-7 -> 1.5e-7 (2-norm, relative).
+// 28 layers 144 -> 68. Error against 64 bits (2-norm, relative, mean of 36 sequences): L = 3000 4.4e-7 -> 1.2e-7, 13577 3.5e-7 -> 1.3e-7,
+// 30011 3.1e-7 -> 1.5e-7; most of it is the filter's own transform, a gain that differs from length to length.
 #include <atomic>
 
 #include "conv_filter.h"
@@ -146,7 +147,8 @@ template <int LOGC>
 struct ConvLds {
     cf z[padded_len((size_t)1 << LOGC)];
     cf table[1 << (LOGC - 1)];
-    cf c[16], step[8], back[8];
+    cf c[16];
+    alignas(16) cd step[8], back[8];         // (factors of products: these are rounded, not their factors)
 };
 template <int LOGC>
 __device__ __forceinline__ void fill_constants(ConvLds<LOGC>& m, const ConvHead& w, int r, int t) {
@@ -155,8 +157,8 @@ __device__ __forceinline__ void fill_constants(ConvLds<LOGC>& m, const ConvHead&
         const float a = (float)(1 - 4 * r);
         const float x = t < 16 ? (float)(t & (w.R - 1)) * a / (float)(2 * w.R)
                       : t < 24 ? (float)(t - 16) * a / (float)(2 << w.log_n) : -(float)(t - 24) * a / (float)(16 * w.R);
-        const cf v = cis_pi(x);
-        if (t < 16) m.c[t] = v;
+        const cd v = cis_pi_f64(x);
+        if (t < 16) m.c[t] = rounded(v);
         else if (t < 24) m.step[t - 16] = v;
         else m.back[t - 24] = v;
     }
@@ -164,10 +166,10 @@ __device__ __forceinline__ void fill_constants(ConvLds<LOGC>& m, const ConvHead&
 }
 // acc, points 8 t + e, twisted and transformed: the bins of residue r in the last layout
 template <int LOGC>
-__device__ __forceinline__ void to_bins(ConvLds<LOGC>& m, const typename Fft<LOGC>::Twiddles& tw, cf tw0, int t, const cf (&acc)[8],
+__device__ __forceinline__ void to_bins(ConvLds<LOGC>& m, const typename Fft<LOGC>::Twiddles& tw, cd tw0, int t, const cf (&acc)[8],
                                         cf (&v)[8]) {
 #pragma unroll
-    for (int e = 0; e < 8; ++e) v[e] = mul(acc[e], mul(tw0, m.step[e]));
+    for (int e = 0; e < 8; ++e) v[e] = mul(acc[e], mul_rounded(tw0, m.step[e]));
     Fft<LOGC>::put(m.z, v, 8 * t, 0);
     __syncthreads();
     Fft<LOGC>::get(m.z, v, t, LOGC - 3);
@@ -191,7 +193,7 @@ __global__ __launch_bounds__(Fft<LOGC>::THREADS) void conv_spectrum_kernel(Geom 
 #pragma unroll
     for (int e = 0; e < 8; ++e) acc[e] = {0.f, 0.f};
     gather_taps<4>(job.h + item * job.item_stride, w, 1 << LOGC, m.c, t, acc);
-    to_bins<LOGC>(m, tw, cis_pi((float)(8 * t) * (float)(1 - 4 * r) / (float)(2 << w.log_n)), t, acc, v);
+    to_bins<LOGC>(m, tw, cis_pi_f64((float)(8 * t) * (float)(1 - 4 * r) / (float)(2 << w.log_n)), t, acc, v);
     cf* out = spec + (size_t)item * spec_stride + ((size_t)r << LOGC) + 8 * t;
 #pragma unroll
     for (int e = 0; e < 8; e += 2)
@@ -214,7 +216,7 @@ __global__ __launch_bounds__(Fft<LOGC>::THREADS) void conv_chunk_kernel(
     typename Fft<LOGC>::Twiddles tw;
     Fft<LOGC>::init(tw, m.table, t);
     const float a = (float)(1 - 4 * r);
-    const cf tw0 = cis_pi((float)(8 * t) * a / (float)(2 << w.log_n));
+    const cd tw0 = cis_pi_f64((float)(8 * t) * a / (float)(2 << w.log_n));
     const float* src = in + w.off;
 
     cf f[8], v[8];
@@ -240,13 +242,13 @@ __global__ __launch_bounds__(Fft<LOGC>::THREADS) void conv_chunk_kernel(
     Fft<LOGC>::backward(reinterpret_cast<cf(&)[1][8]>(v), m.z, tw, t);
 
     // twisted back: point n = t + T q of residue r by exp(i pi n (4 r - 1) / 2N); 1/N completes the inverse transform
-    const float inv_n = 1.0f / (float)(1 << w.log_n);
-    cf back0 = cis_pi(-(float)t * a / (float)(2 << w.log_n));
+    const double inv_n = 1.0 / (double)(1 << w.log_n);
+    cd back0 = cis_pi_f64(-(float)t * a / (float)(2 << w.log_n));
     back0 = {back0.re * inv_n, back0.im * inv_n};
     cf* dst = part + (size_t)head * part_stride + (size_t)r * C;
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
-        const cf u = mul(v[q], mul(back0, m.back[q]));
+        const cf u = mul(v[q], mul_rounded(back0, m.back[q]));
         const int n = t + T * q;
         if (w.R > 1) dst[n] = u;
         else if (n < w.L) {                                      // a head of one workgroup is done

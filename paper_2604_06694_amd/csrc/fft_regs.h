@@ -10,24 +10,43 @@
 namespace audiokv {
 namespace {
 
-__device__ __forceinline__ cf mul(cf a, cf b) {
+__host__ __device__ __forceinline__ cf mul(cf a, cf b) {
     return {fmaf(a.re, b.re, -(a.im * b.im)), fmaf(a.re, b.im, a.im * b.re)};
 }
 // Eq. 20
 __device__ __forceinline__ float mix(float s0, float smoothed, float alpha) { return fmaf(alpha, smoothed, (1.f - alpha) * s0); }
 
 
-// exp(i pi x), |x| <= 2^16: x - k/2 is exact, and on [-1/4, 1/4] the Taylor series of cos and sin (remainders below
-// 3e-9 and 3e-10)
-__device__ __forceinline__ cf cis_pi(float x) {
-    const float k = rintf(2.f * x), r = fmaf(-0.5f, k, x), s = r * r;
+// exp(i pi x), |x| <= 2^16: x - k/2 is exact, and on [-1/4, 1/4] the Taylor series of cos and sin in float64 (remainders
+// below 4e-13 and, relative, 9.8e-12; a float64 multiply-add issues as fast as a float32 one here). Roots, twists and what splits
+// and merges real spectra are float64 values rounded to float32 once, products among them; only the roots that a radix-8
+// butterfly derives from its three (twist) are float32 products.
+struct cd { double re, im; };
+__host__ __device__ __forceinline__ cd cis_pi_f64(float x) {
+    const float k = rintf(2.f * x), r = fmaf(-0.5f, k, x);
     const int q = (int)k;
-    constexpr float P2 = 9.86960440108935862f, P1 = 3.14159265358979324f;         // pi^2, pi
-    const float u = s * P2;
-    const float c = fmaf(u, fmaf(u, fmaf(u, fmaf(u, 1.f / 40320.f, -1.f / 720.f), 1.f / 24.f), -0.5f), 1.f);
-    const float v = P1 * r * fmaf(u, fmaf(u, fmaf(u, fmaf(u, 1.f / 362880.f, -1.f / 5040.f), 1.f / 120.f), -1.f / 6.f), 1.f);
-    const float a = q & 1 ? v : c, b = q & 1 ? c : v;                               // quarter turns: swap, then signs
+    const double t = 3.14159265358979324 * (double)r, u = t * t;
+    const double c = fma(u, fma(u, fma(u, fma(u, fma(u, fma(u, 1. / 479001600., -1. / 3628800.), 1. / 40320.), -1. / 720.), 1. / 24.), -0.5), 1.);
+    const double v = t * fma(u, fma(u, fma(u, fma(u, fma(u, -1. / 39916800., 1. / 362880.), -1. / 5040.), 1. / 120.), -1. / 6.), 1.);
+    const double a = q & 1 ? v : c, b = q & 1 ? c : v;                              // quarter turns: swap, then signs
     return {(q + 1) & 2 ? -a : a, q & 2 ? -b : b};
+}
+__host__ __device__ __forceinline__ cf rounded(cd a) { return {(float)a.re, (float)a.im}; }
+__host__ __device__ __forceinline__ cf cis_pi(float x) { return rounded(cis_pi_f64(x)); }
+__host__ __device__ __forceinline__ cf mul_rounded(cd a, cd b) {
+    return {(float)fma(a.re, b.re, -(a.im * b.im)), (float)fma(a.re, b.im, a.im * b.re)};
+}
+
+// exp(-i pi k / n), 0 <= k < n, in constants
+constexpr cd unit_root(int k, int n) {
+    const double x = 3.14159265358979324 * k / n;
+    double c = 0., s = 0., term = 1.;
+    for (int j = 0; j < 30; j += 2) {                        // pi^30 / 30! < 4e-18
+        c += term;
+        s -= term * x / (j + 1);
+        term *= -x * x / ((j + 1) * (j + 2));
+    }
+    return {c, s};
 }
 
 // 4- and 8-point DFTs in registers, natural order in and out; S = -1 forwards (exp(-2 pi i / n)), +1 backwards
@@ -63,7 +82,7 @@ struct Fft {
     static constexpr int P8 = LOGC / 3;                       // radix-8 passes
     static constexpr int REM = LOGC - 3 * P8;                 // bits left for a pass of radix 2 or 4 on the last layout
     static constexpr int TW = REM ? P8 : P8 - 1;              // passes with twiddles
-    static constexpr int low_bit(int p) { return LOGC - 3 * (p + 1); }
+    __host__ __device__ static constexpr int low_bit(int p) { return LOGC - 3 * (p + 1); }
 
     struct W3 { cf w1, w2, w4; };
     // root_{8m}^(j0 {1, 2, 4}) per pass, in registers, from a table of exp(-2 pi i e / C), e < C/2
@@ -71,22 +90,32 @@ struct Fft {
         W3 w[VT][TW];
         __device__ __forceinline__ W3 operator()(int p, int vt) const { return w[vt][p]; }
     };
-    // the same looked up where they are used, from exp(-2 pi i e / C) = hi[e >> 7] lo[e & 127]
-    struct HiLo {
-        const cf* lo; const cf* hi; int t;
-        __device__ __forceinline__ cf root(int e) const { return mul(hi[e >> 7], lo[e & 127]); }
-        __device__ __forceinline__ W3 operator()(int p, int vt) const {
+    // The same looked up where they are used, from a table of every fourth root, exp(-2 pi i 4 j / C) at pad(j). Only the first
+    // pass has exponents between them: w + w (root - 1), whose second term is too small for its roundings to matter.
+    struct EveryFourth {
+        const cf* table; int t; cf m1, m2;
+        __host__ __device__ __forceinline__ EveryFourth(const cf* table_, int t_) : table(table_), t(t_) {
+            const cd a = cis_pi_f64(-(float)(t & 3) / (float)(C / 2)), b = cis_pi_f64(-(float)(2 * (t & 1)) / (float)(C / 2));
+            m1 = rounded({a.re - 1., a.im});
+            m2 = rounded({b.re - 1., b.im});
+        }
+        __host__ __device__ __forceinline__ cf near(int e, cf m) const {
+            const cf w = table[pad(e >> 2)], d = mul(w, m);
+            return cadd(w, d);
+        }
+        __host__ __device__ __forceinline__ W3 operator()(int p, int vt) const {
             const int e = exponent(p, t + vt * THREADS);
-            return {root(e), root(2 * e), root(4 * e)};
+            if (p == 0) return {near(e, m1), near(2 * e, m2), table[pad(e)]};
+            return {table[pad(e >> 2)], table[pad(e >> 1)], table[pad(e)]};
         }
     };
-    __device__ __forceinline__ static int exponent(int p, int t) { return (t & ((1 << low_bit(p)) - 1)) << (3 * p); }   // 4 e < C/2
+    __host__ __device__ __forceinline__ static int exponent(int p, int t) { return (t & ((1 << low_bit(p)) - 1)) << (3 * p); }   // 4 e < C/2
 
     __device__ __forceinline__ static int base(int p, int t) {
         const int sb = low_bit(p);
         return ((t >> sb) << (sb + 3)) | (t & ((1 << sb) - 1));
     }
-    __device__ __forceinline__ static int bin_of(int slot) {
+    __host__ __device__ __forceinline__ static constexpr int bin_of(int slot) {
         int k = (slot & ((1 << REM) - 1)) << (3 * P8);
 #pragma unroll
         for (int p = 0; p < P8; ++p) k |= ((slot >> low_bit(p)) & 7) << (3 * p);
@@ -98,18 +127,33 @@ struct Fft {
         for (int p = 0; p < P8; ++p) s |= ((bin >> (3 * p)) & 7) << low_bit(p);
         return s;
     }
-    __device__ __forceinline__ static void fill_table(cf* table, int t) {
-#pragma unroll 1
-        for (int e = t; e < C / 2; e += THREADS) table[e] = cis_pi(-(float)e / (float)(C / 2));
+    // exp(-2 pi i e / C) for e = t + (C/8) u, u < 4: eighth turns apart
+    __host__ __device__ __forceinline__ static void fill_table(cf* table, int t) {
+        static_assert(VT == 1, "four entries per thread");
+        const cd w = cis_pi_f64(-(float)t / (float)(C / 2));
+        const double H = 0.70710678118654752, p = H * (w.re + w.im), q = H * (w.im - w.re);
+        table[t] = rounded(w);
+        table[t + C / 8] = {(float)p, (float)q};
+        table[t + C / 4] = {(float)w.im, (float)-w.re};
+        table[t + 3 * C / 8] = {(float)q, (float)-p};
     }
-    // lo: 128 entries, hi: C / 256
-    __device__ __forceinline__ static void fill_hi_lo(cf* lo, cf* hi, int t) {
-#pragma unroll 1
-        for (int e = t; e < 128 + C / 256; e += THREADS) {
-            const int n = e < 128 ? e : (e - 128) * 128;
-            (e < 128 ? lo[e] : hi[e - 128]) = cis_pi(-(float)n / (float)(C / 2));
+    // exp(-2 pi i 4 j / C) for j = t, t + C/16: a quarter turn apart
+    __host__ __device__ __forceinline__ static void fill_every_fourth(cf* table, int t) {
+        static_assert(VT == 2, "two entries per thread");
+        const cf w = cis_pi(-(float)t / (float)(C / 8));
+        table[pad(t)] = w;
+        table[pad(t + C / 16)] = {w.im, -w.re};
+    }
+    // exp(-i pi k / C) for the bins k of slots 8 t + e: from that of e = 0 and eight constants
+    struct BinRoots {
+        cd base;
+        __host__ __device__ __forceinline__ explicit BinRoots(int t) : base(cis_pi_f64(-(float)bin_of(8 * t) / (float)C)) {}
+        __host__ __device__ __forceinline__ cf operator()(int e) const {
+            constexpr cd step[8] = {unit_root(bin_of(0), C), unit_root(bin_of(1), C), unit_root(bin_of(2), C), unit_root(bin_of(3), C),
+                                    unit_root(bin_of(4), C), unit_root(bin_of(5), C), unit_root(bin_of(6), C), unit_root(bin_of(7), C)};
+            return mul_rounded(base, step[e]);
         }
-    }
+    };
     __device__ __forceinline__ static void init(Twiddles& tw, const cf* table, int t) {
 #pragma unroll
         for (int vt = 0; vt < VT; ++vt)

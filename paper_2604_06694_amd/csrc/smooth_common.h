@@ -117,13 +117,13 @@ __device__ __forceinline__ void window_load(const float* __restrict__ at, float 
 
 struct cf { float re, im; };
 __device__ __forceinline__ cf cmul(cf a, cf b) { return {a.re * b.re - a.im * b.im, a.re * b.im + a.im * b.re}; }
-__device__ __forceinline__ cf cadd(cf a, cf b) { return {a.re + b.re, a.im + b.im}; }
+__host__ __device__ __forceinline__ cf cadd(cf a, cf b) { return {a.re + b.re, a.im + b.im}; }
 __device__ __forceinline__ cf csub(cf a, cf b) { return {a.re - b.re, a.im - b.im}; }
 __device__ __forceinline__ cf cconj(cf a) { return {a.re, -a.im}; }
 
 // LDS slot of complex element i. One spare slot per 16 elements: a thread's 16-point group at stride 1 or 4 would
 // otherwise sit in a single bank.
-__device__ __forceinline__ int pad(int i) { return i + (i >> 4); }
+__host__ __device__ __forceinline__ int pad(int i) { return i + (i >> 4); }
 __host__ __device__ constexpr size_t padded_len(size_t n) { return n + (n >> 4) + 1; }
 
 // Masks for which the filter needs no transform at all, and for which a transform would only add rounding noise to

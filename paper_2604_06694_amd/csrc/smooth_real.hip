@@ -12,7 +12,9 @@
 // pass with two complex multiplications per butterfly of smooth_pow2_kernel, which keeps the shorter heads (as fast
 // there) and 32768 samples with an energy-adaptive cutoff (52 us for 112 heads there, 54 here). Pool + smooth
 // inside evict, before -> now: 4 heads of 2048 12.0 -> 8.0 us, 112 heads of 8192 23 -> 13.2, of 32768 55 -> 42; smooth calls:
-// 112 heads of 16384 22.4 -> 15.7 us, with an energy-adaptive cutoff 4 heads of 8192 19.8 -> 14.6.
+// 112 heads of 16384 22.4 -> 15.7 us, with an energy-adaptive cutoff 4 heads of 8192 19.8 -> 14.1. Error against 64 bits
+// (2-norm, relative, mean of 36 sequences), smooth_pow2_kernel -> this: 2048 1.21e-7 -> 0.99e-7, 8192 1.24e-7 -> 1.05e-7, 32768
+// 1.17e-7 -> 1.14e-7 (1.26e-7 with roots from a float32 polynomial, 1.18e-7 with float32 products of two table entries).
 #include <atomic>
 
 #include "fft_regs.h"
@@ -27,9 +29,9 @@ template <int LOGC> constexpr int kRealThreads = (1 << LOGC) / (8 * kRealGroups<
 
 template <int LOGC>
 struct RealLds {
-    static constexpr bool kTable = LOGC <= 13;               // the whole root table fits beside the points
+    static constexpr bool kTable = LOGC <= 13;               // the whole root table fits beside the points, otherwise a quarter
     cf z[padded_len((size_t)1 << LOGC)];                     // also: raw samples, bin energies
-    cf roots[kTable ? 1 << (LOGC - 1) : 128 + (1 << LOGC) / 256];
+    cf roots[kTable ? (size_t)1 << (LOGC - 1) : padded_len((size_t)1 << (LOGC - 3))];
     double part[32];                                         // partial sums of the energy search, one per wave
     int cross_wave, kstar;
 };
@@ -127,7 +129,7 @@ __global__ __launch_bounds__(kRealThreads<LOGC>) void smooth_real_kernel(
             }
     }
     if constexpr (RealLds<LOGC>::kTable) F::fill_table(m.roots, t);
-    else F::fill_hi_lo(m.roots, m.roots + 128, t);
+    else F::fill_every_fourth(m.roots, t);
     __syncthreads();
     if constexpr (POOL != 0) {
         const float* raw = reinterpret_cast<const float*>(m.z);
@@ -165,17 +167,19 @@ __global__ __launch_bounds__(kRealThreads<LOGC>) void smooth_real_kernel(
         if (energy) {
             float en[VT][8];
 #pragma unroll
-            for (int vt = 0; vt < VT; ++vt)
+            for (int vt = 0; vt < VT; ++vt) {
+                const typename F::BinRoots root(t + vt * T);
 #pragma unroll
                 for (int e = 0; e < 8; ++e) {
                     const int k = F::bin_of(8 * (t + vt * T) + e);
                     other[vt][e] = partner(k);
                     cf E, O;
                     even_odd(v[vt][e], other[vt][e], E, O);
-                    const cf X = cadd(E, mul(cis_pi(-(float)k / (float)N), O));
+                    const cf X = cadd(E, mul(root(e), O));
                     en[vt][e] = fmaf(X.re, X.re, X.im * X.im);
                     if (k == 0) { const float x = z0.re + z0.im; en[vt][e] = x * x; }
                 }
+            }
             __syncthreads();                                 // all partners are read
             float* ek = reinterpret_cast<float*>(m.z);
 #pragma unroll
@@ -196,7 +200,8 @@ __global__ __launch_bounds__(kRealThreads<LOGC>) void smooth_real_kernel(
         }
         const int ktop = kstar + Tb;                         // last bin with a non-zero weight
 #pragma unroll
-        for (int vt = 0; vt < VT; ++vt)
+        for (int vt = 0; vt < VT; ++vt) {
+            const typename F::BinRoots root(t + vt * T);
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
                 const int k = F::bin_of(8 * (t + vt * T) + e);
@@ -208,7 +213,7 @@ __global__ __launch_bounds__(kRealThreads<LOGC>) void smooth_real_kernel(
                     } else {
                         cf E, O;
                         even_odd(v[vt][e], energy ? other[vt][e] : partner(k), E, O);
-                        const cf Wk = cis_pi(-(float)k / (float)N), WO = mul(Wk, O);
+                        const cf Wk = root(e), WO = mul(Wk, O);
                         const float wk = bin_weight(k, kstar, Tb), wn = bin_weight(N - k, kstar, Tb);
                         const cf X = cadd(E, WO), Y = csub(E, WO);           // bin k; conjugate of bin N - k
                         const cf Xk = {X.re * wk, X.im * wk}, Xn = {Y.re * wn, Y.im * wn};
@@ -219,6 +224,7 @@ __global__ __launch_bounds__(kRealThreads<LOGC>) void smooth_real_kernel(
                 }
                 v[vt][e] = o;
             }
+        }
         __syncthreads();                                     // all partners are read: the slots are free
         F::backward(v, m.z, tw, t);
 
@@ -250,7 +256,7 @@ __global__ __launch_bounds__(kRealThreads<LOGC>) void smooth_real_kernel(
         F::init(tw, m.roots, t);
         transforms(tw);
     } else {
-        transforms(typename F::HiLo{m.roots, m.roots + 128, t});
+        transforms(typename F::EveryFourth(m.roots, t));
     }
 }
 
