@@ -28,6 +28,7 @@ namespace {
 
 // sin(pi n x) / sin(pi x), x = p / (2 q) with |x| < 3/4
 __device__ __forceinline__ double sine_ratio(long long p, long long q, int n) {
+#pragma clang fp contract(off)
     if (p == 0) return (double)n;
     const double x = (double)p / (double)(2 * q);
     return sinpi((double)n * x) / sinpi(x);
@@ -36,7 +37,10 @@ __device__ __forceinline__ double sine_ratio(long long p, long long q, int n) {
 // One tap of the circular filter whose frequency response is the mask (Eqs. 17-18): h[n] = (1/L) sum over all L bins
 // of mask * cos(2 pi k n / L). The bins up to k* add up to a ratio of sines with an exactly reduced angle. The
 // taper's weights are (1 + cos(pi j / (T+1))) / 2, so its bins are three geometric series; a Nyquist bin counts once.
+// Compiled into several sources whose settings differ: nothing is contracted, so that the taps are the same bits wherever
+// they are evaluated.
 __device__ __forceinline__ float low_pass_tap(int n, int L, int kstar, int T) {
+#pragma clang fp contract(off)
     n = min(n, L - n);                              // h is even: 0 <= n <= L/2
     const long long r = ((long long)(2 * kstar + 1) * n) % (2LL * L);
     double v = n == 0 ? (double)(2 * kstar + 1) : sinpi((double)r / (double)L) / sinpi((double)n / (double)L);

@@ -105,6 +105,48 @@ def test_pooling_on_load_equals_the_stages_composed(A, lens, kernel, mode):
         assert torch.equal(idx, out["indices"][:out["total_rows"]])
 
 
+def found(ws, close_to):
+    """The run of floats in a workspace that lies within 1e-6 of the sequence `close_to`, as bits; runs start at multiples of 256
+    bytes."""
+    w, x = ws[:ws.numel() // 4 * 4].view(torch.float32), torch.from_numpy(close_to).cuda()
+    head = w[:w.numel() - x.numel() + 1][::64]
+    for i in ((head - x[0]).abs() <= 1e-6).nonzero().view(-1).tolist():
+        if bool(((w[64 * i:64 * i + x.numel()] - x).abs() <= 1e-6).all()):
+            return w[64 * i:64 * i + x.numel()].view(torch.int32).clone()
+    raise AssertionError("no such run of floats")
+
+
+@pytest.mark.parametrize("T", [0, 1, 1000])
+@pytest.mark.parametrize("lens,H_kv", [([13577], 2), ([5003] * 20, 2), ([3000, 700], 2)])
+def test_taps_are_the_same_bits_wherever_they_are_evaluated(A, T, lens, H_kv):
+    """The filter's taps are evaluated in the launch that merges the statistics, on the helper stream, or by smooth itself; evict
+    equals the calls composed only if they are the same bits from all of them, with a taper as well."""
+    rng = np.random.default_rng(T + len(lens))
+    H_q, d, W, n, L, cutoff = 2 * H_kv, 64, 8, len(lens), lens[0], 0.25
+    q = bf16_tensor(f64_to_bf16_bits(rng.standard_normal(n * H_q * W * d)))
+    k = bf16_tensor(f64_to_bf16_bits(rng.standard_normal(sum(lens) * H_kv * d)))
+    w = torch.rand(n * H_kv, device="cuda") + 0.1
+    p = A.Params(H_q, H_kv, d, W, taper_bins=T)
+    impulse = np.zeros(L)
+    impulse[0] = 1.0
+    taps = reference(impulse, cutoff, 1.0, T).astype(np.float32)
+    ws = torch.zeros(A.workspace_bytes(p, lens), dtype=torch.uint8, device="cuda")
+    smoothed = A.smooth(p, A.score(p, q, k, lens), lens, cutoff, 1.0, workspace=ws)
+    h = found(ws, taps)
+    for scope in (A.SCOPE_ITEM, A.SCOPE_GLOBAL):
+        if scope == A.SCOPE_GLOBAL and len(set(lens)) > 1:
+            continue
+        for timed in (False, True):
+            ws.zero_()
+            A.profile_enable(timed)
+            try:
+                A.evict(p, q, k, k, w, lens, 0.4, cutoff, 1.0, alloc_scope=scope, workspace=ws)
+            finally:
+                A.profile_enable(False)
+            assert torch.equal(found(ws, taps), h)
+            assert torch.equal(found(ws, smoothed.cpu().numpy()), smoothed.view(torch.int32))
+
+
 def test_smoothed_scores_meet_the_oracle(A):
     L = 2500
     x = sequences(np.random.default_rng(3), 2, L)
