@@ -398,6 +398,9 @@ hipError_t launch_conv_filter(const Geom& g, const ConvCall& c, hipStream_t s) {
 
 hipError_t launch_conv(const Geom& g, const ConvCall& c, const float* in, bool pool_on_load, float alpha, float* out, hipStream_t s) {
     if (pool_on_load && g.pool_kernel > kConvMaxPool) return hipErrorInvalidValue;      // (pooled beforehand)
+    // a launch of 2^32 threads or more would drop workgroups without an error
+    const long long points = (long long)g.n_items * g.H_kv << c.log_c;
+    if (points >= 1LL << 32 || points * c.max_r / 8 >= 1LL << 32) return hipErrorInvalidConfiguration;
     hipError_t e;
     switch (c.log_c) {
         case 10: e = launch_chunks<10>(g, c, in, pool_on_load, alpha, out, s); break;

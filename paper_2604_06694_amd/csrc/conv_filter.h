@@ -14,7 +14,7 @@ struct ConvFilterJob {
     int n_items;
     double cutoff_frac;
     int taper_bins;
-    int blocks_per_item;      // workgroups of kConvFilterThreads, one tap per thread
+    int blocks_per_item;      // workgroups of kConvFilterThreads, one tap per thread (in a call of very many items more)
 };
 constexpr int kConvFilterThreads = 256;
 

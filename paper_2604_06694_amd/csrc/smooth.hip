@@ -50,25 +50,26 @@ __global__ __launch_bounds__(256) void pool_kernel(Geom g, const float* __restri
     const float* src = raw + off;
     float* dst = pooled + off;
     if constexpr (POOL == 0) {
-        for (int j = part * blockDim.x + threadIdx.x; j < L; j += per_head * blockDim.x)
+        for (int64_t j = part * 256 + (int)threadIdx.x; j < L; j += per_head * 256)
             dst[j] = pooled_at(src, L, j, g.pool_kernel, g.pool_mode);
     } else {
         const float fill = g.pool_mode == AUDIOKV_POOL_MAX ? -INFINITY : 0.f;
-        const int j0 = (part * 256 + threadIdx.x) * 8;
-        if (j0 >= L) return;
-        float x[16], o[8];
-        window_load(src + j0 - 4, x);
-        if (j0 < 4 || j0 + 12 > L) {
+        for (int64_t j = (int64_t)(part * 256 + (int)threadIdx.x) * 8; j < L; j += (int64_t)per_head * 2048) {
+            const int j0 = (int)j;
+            float x[16], o[8];
+            window_load(src + j0 - 4, x);
+            if (j0 < 4 || j0 > L - 12) {
 #pragma unroll
-            for (int u = 0; u < 16; ++u) x[u] = j0 - 4 + u >= 0 && j0 - 4 + u < L ? x[u] : fill;
-        }
-        pooled_window<POOL>(x, g.pool_kernel, g.pool_mode, o);
-        if (j0 + 8 <= L) {
-            *reinterpret_cast<f32x4u*>(dst + j0) = f32x4{o[0], o[1], o[2], o[3]};
-            *reinterpret_cast<f32x4u*>(dst + j0 + 4) = f32x4{o[4], o[5], o[6], o[7]};
-        } else {
+                for (int u = 0; u < 16; ++u) x[u] = j0 >= 4 - u && j0 - 4 < L - u ? x[u] : fill;
+            }
+            pooled_window<POOL>(x, g.pool_kernel, g.pool_mode, o);
+            if (j0 <= L - 8) {
+                *reinterpret_cast<f32x4u*>(dst + j0) = f32x4{o[0], o[1], o[2], o[3]};
+                *reinterpret_cast<f32x4u*>(dst + j0 + 4) = f32x4{o[4], o[5], o[6], o[7]};
+            } else {
 #pragma unroll
-            for (int e = 0; e < 8; ++e) if (j0 + e < L) dst[j0 + e] = o[e];
+                for (int e = 0; e < 8; ++e) if (j0 < L - e) dst[j0 + e] = o[e];
+            }
         }
     }
 }
@@ -1196,12 +1197,12 @@ hipError_t launch_pool(const Geom& g, const float* raw, const int32_t* cu_seqlen
     const int n_heads = g.n_items * g.H_kv;
     const ConvFilterJob every{};
     if (g.pool_kernel <= kConvMaxPool) {
-        const int per_head = (max_L + 2047) / 2048;
+        const int per_head = blocks_per_part(std::min(1024LL, (max_L + 2047LL) / 2048), n_heads);
         const dim3 grid((unsigned)per_head * (unsigned)n_heads);
         if (g.pool_kernel == 7) hipLaunchKernelGGL(pool_kernel<7>, grid, dim3(256), 0, s, g, raw, cu_seqlens, pooled, per_head, every);
         else hipLaunchKernelGGL(pool_kernel<9>, grid, dim3(256), 0, s, g, raw, cu_seqlens, pooled, per_head, every);
     } else {
-        const int per_head = max(1, min(64, (max_L + 255) / 256));
+        const int per_head = blocks_per_part(std::min(64LL, (max_L + 255LL) / 256), n_heads);
         hipLaunchKernelGGL(pool_kernel<0>, dim3((unsigned)per_head * (unsigned)n_heads), dim3(256), 0, s, g, raw, cu_seqlens,
                            pooled, per_head, every);
     }
@@ -1294,7 +1295,7 @@ SmoothPlan plan_smooth(const Geom& g, const int32_t* cu_seqlens, const int32_t* 
     c.job.n_items = n_items;
     c.job.cutoff_frac = cutoff_frac;
     c.job.taper_bins = g.taper_bins;
-    c.job.blocks_per_item = (longest + kConvFilterThreads - 1) / kConvFilterThreads;
+    c.job.blocks_per_item = blocks_per_part((longest + kConvFilterThreads - 1) / kConvFilterThreads, n_items);
     // Lengths shared by more than eight heads: their filter is transformed once, by a launch of its own, instead of by
     // every workgroup for itself (a third transform beside the two that it runs anyway).
     bool equal = true;
@@ -1455,7 +1456,9 @@ hipError_t launch_smooth(const Geom& g, const float* in, bool pool_on_load, cons
         if (pool_on_load && g.pool_kernel > kConvMaxPool) {
             // a kernel wider than the convolution's loads can apply: pooled first, into the result (only the heads that
             // are convolved: the others are done), and smoothed in place
-            hipLaunchKernelGGL(pool_kernel<0>, dim3(64u * (unsigned)n_heads), dim3(256), 0, s, g, in, cu_seqlens, out, 64, pl.conv.job);
+            const int per_head = blocks_per_part(64, n_heads);
+            hipLaunchKernelGGL(pool_kernel<0>, dim3((unsigned)per_head * (unsigned)n_heads), dim3(256), 0, s, g, in, cu_seqlens, out,
+                               per_head, pl.conv.job);
             e = launch_conv(g, pl.conv, out, false, (float)alpha, out, s);
         } else {
             e = launch_conv(g, pl.conv, in, pool_on_load, (float)alpha, out, s);
