@@ -265,7 +265,8 @@ __device__ __forceinline__ int energy_cutoff(EnergyFn&& energy, int n_bins, int 
         sc->kstar = ks;
     }
     __syncthreads();
-    return sc->kstar;
+    // (prefixes of different threads are added up in different orders: at rho = 1 all may stay an ulp below the total)
+    return target > 0.0 && sc->cross == kFftThreads ? n_bins - 1 : sc->kstar;
 }
 
 __device__ __forceinline__ bool dec_owns(const Geom& g, int L, double cutoff_frac);   // heads of the several-workgroups path

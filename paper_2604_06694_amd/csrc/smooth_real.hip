@@ -80,7 +80,8 @@ __device__ __forceinline__ int energy_search(const float* e, int n_bins, int fir
         m.kstar = ks;
     }
     __syncthreads();
-    return m.kstar;
+    // (the total is added up in another order than the prefixes: at rho = 1 all of them may stay an ulp below it)
+    return target > 0.0 && m.cross_wave == T ? n_bins - 1 : m.kstar;
 }
 
 // weight of bin k (Eqs. 17-18)

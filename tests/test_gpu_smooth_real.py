@@ -68,6 +68,36 @@ def test_energy_cutoff(A, L, rho, no_dc):
         assert np.abs(out[h] - np.fft.irfft(f, n=L)).max() <= ATOL * np.abs(x[h]).max()
 
 
+@pytest.mark.parametrize("L", [256, 512, 1000, 1024, 2048, 5003, 16384, 32768])
+@pytest.mark.parametrize("no_dc", [False, True])
+def test_energy_cutoff_keeps_everything_at_rho_one(A, L, no_dc):
+    """rho = 1 is allowed: k* captures the whole energy up to what fp32 energies resolve, and the result is the input. Smooth
+    and peaked sequences: the bins at the end hold next to nothing, so that the last prefix sums are all about the total."""
+    rng = np.random.default_rng(L)
+    n = 96 if L <= 5003 else 24
+    t = np.arange(L) / L
+    x = np.empty((n, L))
+    for i in range(n):
+        if i % 3 == 0:
+            x[i] = np.convolve(rng.random(L + 40), np.hanning(41) / 20, "valid")
+        elif i % 3 == 1:
+            x[i] = 0.1 + np.exp(-0.5 * ((t - rng.random()) / rng.uniform(0.002, 0.2)) ** 2)
+        else:
+            x[i] = 1 + sum(rng.standard_normal() / k ** 2 * np.cos(2 * np.pi * k * t + rng.random() * 6) for k in range(1, 40))
+    x = x.astype(np.float32)
+    mode = A.CUTOFF_ENERGY_NO_DC if no_dc else A.CUTOFF_ENERGY
+    p = A.Params(n, n, 128, 1, cutoff_mode=mode)
+    f = torch.from_numpy(x.reshape(-1)).cuda()
+    ks = A.smooth_cutoffs(p, f, [L], 1.0).cpu().numpy()
+    out = A.smooth(p, f, [L], 1.0, 1.0).cpu().numpy().reshape(n, L)
+    e = np.abs(np.fft.rfft(x.astype(np.float64), axis=1)) ** 2
+    e[:, 0] *= not no_dc
+    c = np.cumsum(e, axis=1)
+    kept = c[np.arange(n), ks] / c[:, -1]
+    assert kept.min() >= 1 - 1e-6, (kept.min(), int((kept < 1 - 1e-6).sum()))     # what fp32 bin energies can hide
+    assert np.abs(out - x).max() <= 2e-3 * np.abs(x).max()                       # sqrt(1e-6), plus fp32 transforms
+
+
 @pytest.mark.parametrize("kernel,mode", [(3, 0), (7, 0), (7, 1), (9, 1), (21, 0)])
 def test_pooling_on_load_equals_the_stages_composed(A, kernel, mode):
     rng = np.random.default_rng(kernel)
