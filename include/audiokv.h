@@ -168,7 +168,8 @@ int32_t audiokv_score_lse(const audiokv_params* params,
  * cu_seqlens_dev[s]). Per-sequence budgets: n_segments = n_items,
  * heads_per_segment = n_kv_heads. The paper's global form over all layers of
  * one sequence: n_segments = 1, heads_per_segment = layers * n_kv_heads.
- * weights_dev: fp32 >= 0, [n_segments * heads_per_segment * weight_group];
+ * weights_dev: fp32 >= 0, [n_segments * heads_per_segment * weight_group]
+ * (a pool whose sum is zero, infinite or NaN is shared out equally);
  * weight_group > 1 means weights are per query head and are summed within
  * each group of `weight_group` consecutive entries first.
  * Per pool (float64 on the device, same operation order as the reference

@@ -49,6 +49,10 @@ __device__ __forceinline__ int n_keep_dev(double ratio, int L) {
     return (int)floor(__dadd_rn(__dmul_rn(ratio, (double)L), 0.5));
 }
 
+// Whether the weights' sum defines shares: without one (all weights zero, a NaN, an infinity) the heads share equally. A share
+// that is NaN would not compare with the others, and the hand-out of the remainder below would never end.
+__device__ __forceinline__ bool has_shares(double sum) { return sum > 0.0 && sum < (double)INFINITY; }
+
 // the whole allocation of pool `seg` by one workgroup of kThreads threads; smem_raw: alloc_smem_bytes(n) bytes
 __device__ __forceinline__ void allocate_pool(
     unsigned char* smem_raw, const int seg,
@@ -118,7 +122,7 @@ __device__ __forceinline__ void allocate_pool(
         int over = 0;
         for (int h = tid; h < n; h += kThreads) {
             if (!(flag[h] & 1)) {
-                const double xh = tot > 0.0 ? __ddiv_rn(__dmul_rn(T, S[h]), tot) : __ddiv_rn(T, (double)nfree);
+                const double xh = has_shares(tot) ? __ddiv_rn(__dmul_rn(T, S[h]), tot) : __ddiv_rn(T, (double)nfree);
                 x[h] = xh;
                 if (xh > (double)cap) over = 1;
             }
@@ -286,7 +290,7 @@ __device__ __forceinline__ void allocate_wave(
 #pragma unroll
         for (int j = 0; j < PER; ++j)
             if (live[j] && !capped[j]) {
-                x[j] = tot > 0.0 ? __ddiv_rn(__dmul_rn(T, S[j]), tot) : __ddiv_rn(T, (double)(n - ncap));
+                x[j] = has_shares(tot) ? __ddiv_rn(__dmul_rn(T, S[j]), tot) : __ddiv_rn(T, (double)(n - ncap));
                 over = over || x[j] > (double)cap;
             }
         if (__builtin_amdgcn_ballot_w64(over) == 0) break;

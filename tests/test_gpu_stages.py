@@ -115,6 +115,20 @@ def test_allocate_random_and_edge_cases(A):
     _alloc_case(A, rng.gamma(1.0, size=56), 2, 4, [2048, 777], 0.4, 32, 0.1, group=7)   # query-head weights
 
 
+@pytest.mark.parametrize("n", [2, 3, 64, 65, 128, 129, 300])
+@pytest.mark.parametrize("bad", [np.inf, np.nan])
+def test_allocate_weights_without_a_finite_sum_are_shared_equally(A, n, bad):
+    p = A.Params(8, 8, 128, 4)
+    w = torch.rand(2 * n, generator=torch.Generator().manual_seed(n))
+    w[n // 2] = bad                                   # the second pool is sound
+    lens, ratio = [1001, 2048], 0.37
+    b, cu = A.allocate(p, w.cuda(), 2, n, lens, ratio)
+    b, cu = b.cpu().numpy(), cu.cpu().numpy()
+    assert np.all(b[:n] == A.n_keep(ratio, lens[0]))
+    ref, _ = O.allocate(w[n:].numpy().astype(np.float64), lens[1], ratio, window=4, floor_frac=float(np.float32(p.floor_frac)))
+    assert np.array_equal(b[n:], ref) and np.array_equal(np.diff(cu), b) and cu[0] == 0
+
+
 @pytest.mark.parametrize("n", [1, 2, 63, 64, 65, 127, 128, 129])
 def test_allocate_pool_sizes_around_the_wave(A, n):
     # pools that one wave allocates (one or two heads per lane) and the first that a workgroup does: capping in several
