@@ -117,7 +117,8 @@ Geom make_geom(const audiokv_params* p, int n_items) {
     const float scale = p->softmax_scale > 0.f ? p->softmax_scale : 1.0f / std::sqrt((float)p->head_dim);
     g.c_log2 = scale * 1.44269504088896340736f;
     g.cutoff_mode = p->cutoff_mode;
-    g.taper_bins = p->taper_bins;
+    // k* + T is added up in 32 bits; from 2^30 bins on, every weight that a spectrum of 65537 bins meets is 1 in fp32
+    g.taper_bins = p->taper_bins < (1 << 30) ? p->taper_bins : 1 << 30;
     g.s_item = p->kv_stride_item;
     g.s_head = p->kv_stride_head;
     g.s_tok = p->kv_stride_tok;

@@ -70,6 +70,13 @@ def test_masks(A, L, cutoff, alpha, T):
     check(A, np.random.default_rng(L + T), [L], 3, cutoff, alpha, T)
 
 
+@pytest.mark.parametrize("L", [5, 64, 999, 1024, 5000, 32768, 40000])
+@pytest.mark.parametrize("T", [2**30, 2**31 - 1])
+def test_tapers_as_long_as_the_argument_allows(A, L, T):
+    check(A, np.random.default_rng(L), [L], 2, 0.3, 1.0, T)
+    check(A, np.random.default_rng(L), [L] * 40, 2, 0.3, 1.0, T)
+
+
 def test_ragged_batch_with_equal_and_short_lengths(A):
     check(A, np.random.default_rng(2), [5000, 30, 1024, 5000, 20000, 700, 9, 4097, 20000], 2, 0.2)
 
