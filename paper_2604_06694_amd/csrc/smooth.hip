@@ -37,15 +37,13 @@ namespace {
 template <int POOL>
 __global__ __launch_bounds__(256) void pool_kernel(Geom g, const float* __restrict__ raw,
                                                    const int32_t* __restrict__ cu_seq,
-                                                   float* __restrict__ pooled, int per_head,   // workgroups
-                                                   ConvFilterJob only)     // if only.h: the heads of that job
+                                                   float* __restrict__ pooled, int per_head)   // workgroups
 {
     // (numbered in one dimension: the second one of a grid ends at 65535, a batch of heads need not)
     const int head = blockIdx.x / per_head, part = blockIdx.x - head * per_head;
     const int item = head / g.H_kv, h = head - item * g.H_kv;
     const int tok0 = cu_seq[item];
     const int L = cu_seq[item + 1] - tok0;
-    if (only.h && !conv_item(only, L)) return;
     const size_t off = (size_t)tok0 * g.H_kv + (size_t)h * L;
     const float* src = raw + off;
     float* dst = pooled + off;
@@ -1196,16 +1194,15 @@ hipError_t launch_pool(const Geom& g, const float* raw, const int32_t* cu_seqlen
                        float* pooled, hipStream_t s)
 {
     const int n_heads = g.n_items * g.H_kv;
-    const ConvFilterJob every{};
     if (g.pool_kernel <= kConvMaxPool) {
         const int per_head = blocks_per_part(std::min(1024LL, (max_L + 2047LL) / 2048), n_heads);
         const dim3 grid((unsigned)per_head * (unsigned)n_heads);
-        if (g.pool_kernel == 7) hipLaunchKernelGGL(pool_kernel<7>, grid, dim3(256), 0, s, g, raw, cu_seqlens, pooled, per_head, every);
-        else hipLaunchKernelGGL(pool_kernel<9>, grid, dim3(256), 0, s, g, raw, cu_seqlens, pooled, per_head, every);
+        if (g.pool_kernel == 7) hipLaunchKernelGGL(pool_kernel<7>, grid, dim3(256), 0, s, g, raw, cu_seqlens, pooled, per_head);
+        else hipLaunchKernelGGL(pool_kernel<9>, grid, dim3(256), 0, s, g, raw, cu_seqlens, pooled, per_head);
     } else {
         const int per_head = blocks_per_part(std::min(64LL, (max_L + 255LL) / 256), n_heads);
         hipLaunchKernelGGL(pool_kernel<0>, dim3((unsigned)per_head * (unsigned)n_heads), dim3(256), 0, s, g, raw, cu_seqlens,
-                           pooled, per_head, every);
+                           pooled, per_head);
     }
     return hipGetLastError();
 }
@@ -1389,6 +1386,17 @@ hipError_t launch_smooth(const Geom& g, const float* in, bool pool_on_load, cons
                          hipStream_t s, bool filters_ready)
 {
     if (cutoffs_only && !kstar_out) return hipErrorInvalidValue;
+    // A kernel wider than the windows that the transforms load: pooled first, into the result, and smoothed in place. Tap by tap
+    // inside the transforms it was as slow as the transform has few threads: one layer of 2048 tokens inside evict, kernel of 31 /
+    // 63 / 255, 51.8 / 75 / 214 us; on 1024 threads per head (smooth_pow2_kernel) 47 / 50 / 70; like this 34 / 37 / 53.
+    if (pool_on_load && g.pool_kernel > kConvMaxPool) {
+        int max_L = 0;
+        for (int i = 0; i < n_items; ++i) max_L = max(max_L, seqlens_host[i]);
+        const hipError_t pooled = launch_pool(g, in, cu_seqlens, max_L, out, s);
+        if (pooled != hipSuccess) return pooled;
+        in = out;
+        pool_on_load = false;
+    }
     const size_t extra = g.cutoff_mode != AUDIOKV_CUTOFF_FRACTION ? sizeof(EnergyScratch) + 2 * sizeof(cf) : 0;
     // (alpha = 0 copies, and a fixed cutoff is known without a transform: nothing to convolve)
     const bool transforms = alpha != 0.0 && !(cutoffs_only && g.cutoff_mode == AUDIOKV_CUTOFF_FRACTION);
@@ -1454,16 +1462,7 @@ hipError_t launch_smooth(const Geom& g, const float* in, bool pool_on_load, cons
                            cutoffs_only ? 1 : 0, pl.conv.job);
     }
     if (pl.conv.any) {
-        if (pool_on_load && g.pool_kernel > kConvMaxPool) {
-            // a kernel wider than the convolution's loads can apply: pooled first, into the result (only the heads that
-            // are convolved: the others are done), and smoothed in place
-            const int per_head = blocks_per_part(64, n_heads);
-            hipLaunchKernelGGL(pool_kernel<0>, dim3((unsigned)per_head * (unsigned)n_heads), dim3(256), 0, s, g, in, cu_seqlens, out,
-                               per_head, pl.conv.job);
-            e = launch_conv(g, pl.conv, out, false, (float)alpha, out, s);
-        } else {
-            e = launch_conv(g, pl.conv, in, pool_on_load, (float)alpha, out, s);
-        }
+        e = launch_conv(g, pl.conv, in, pool_on_load, (float)alpha, out, s);
         if (e != hipSuccess) return e;
     }
     return hipGetLastError();

@@ -61,17 +61,14 @@ __device__ __forceinline__ void pooled_pair_lds(const float* x, int L, int j0, i
     }
 }
 
-// Pooled values at positions j0 and j0 + 1 of x[0..L) (global memory or LDS): the common kernel sizes take all their
-// taps at once (independent loads), any other size goes tap by tap. Same bits either way.
+// Pooled values at positions j0 and j0 + 1 of x[0..L) (global memory or LDS), kernels of 3 to 9 (wider ones are pooled by a
+// launch of their own): all taps at once, independent loads. The bits of pooled_at.
 __device__ __forceinline__ void pooled_pair(const float* x, int L, int j0, int kernel, int mode, float& o0, float& o1) {
     switch (kernel) {
         case 3:  pooled_pair_lds<3>(x, L, j0, mode, o0, o1); break;
         case 5:  pooled_pair_lds<5>(x, L, j0, mode, o0, o1); break;
         case 7:  pooled_pair_lds<7>(x, L, j0, mode, o0, o1); break;
-        case 9:  pooled_pair_lds<9>(x, L, j0, mode, o0, o1); break;
-        default:
-            o0 = pooled_at(x, L, j0, kernel, mode);
-            o1 = pooled_at(x, L, j0 + 1, kernel, mode);
+        default: pooled_pair_lds<9>(x, L, j0, mode, o0, o1); break;
     }
 }
 

@@ -91,7 +91,7 @@ __device__ __forceinline__ float bin_weight(int k, int kstar, int T) {
     return 0.5f * (1.f + cis_pi((float)(k - kstar) / (float)(T + 1)).re);
 }
 
-// POOL: 0 none, 7 the usual size, 1 any size
+// POOL: 0 none, 7 the usual size, 1 any size up to 9
 template <int LOGC, int POOL>
 __global__ __launch_bounds__(kRealThreads<LOGC>) void smooth_real_kernel(
     Geom g, const float* __restrict__ in, const int32_t* __restrict__ cu_seq, double cutoff_frac, float alpha,

@@ -98,7 +98,7 @@ def test_energy_cutoff_keeps_everything_at_rho_one(A, L, no_dc):
     assert np.abs(out - x).max() <= 2e-3 * np.abs(x).max()                       # sqrt(1e-6), plus fp32 transforms
 
 
-@pytest.mark.parametrize("kernel,mode", [(3, 0), (7, 0), (7, 1), (9, 1), (21, 0)])
+@pytest.mark.parametrize("kernel,mode", [(3, 0), (5, 1), (7, 0), (7, 1), (9, 1), (11, 0), (21, 0), (255, 1), (1025, 0)])
 def test_pooling_on_load_equals_the_stages_composed(A, kernel, mode):
     rng = np.random.default_rng(kernel)
     lens, H_q, H_kv, d, W = [1024, 8192, 512, 1024, 700, 16384, 32768], 4, 10, 64, 8
