@@ -269,8 +269,8 @@ __device__ __forceinline__ int energy_cutoff(EnergyFn&& energy, int n_bins, int 
 
 __device__ __forceinline__ bool dec_owns(const Geom& g, int L, double cutoff_frac);   // heads of the several-workgroups path
 
-// heads of smooth_real.hip (unless dec_owns them): long enough, and a mask that needs a transform or comes from one
-__host__ __device__ inline bool real_item(const Geom& g, int L, double cutoff_frac, int cutoffs_only) {
+// heads that smooth_real.hip can take: long enough, and a mask that needs a transform or comes from one
+inline bool real_item(const Geom& g, int L, double cutoff_frac, int cutoffs_only) {
     if (!real_length(L)) return false;
     if (g.cutoff_mode != AUDIOKV_CUTOFF_FRACTION) return L < kMaxPow2L;
     return !cutoffs_only && degenerate_mask(L, (int)floor(cutoff_frac * (double)(L >> 1)), g.taper_bins) != 2;
@@ -279,7 +279,7 @@ __host__ __device__ inline bool real_item(const Geom& g, int L, double cutoff_fr
 __global__ __launch_bounds__(kFftThreads) void smooth_pow2_kernel(
     Geom g, const float* __restrict__ in, int pool_on_load, const int32_t* __restrict__ cu_seq,
     double cutoff_frac, float alpha,
-    float* __restrict__ out, int32_t* __restrict__ kstar_out, int cutoffs_only, int skip_dec)
+    float* __restrict__ out, int32_t* __restrict__ kstar_out, int cutoffs_only, int skip_dec, unsigned others)
 {
     extern __shared__ float smem[];
     const int head = blockIdx.x;
@@ -299,7 +299,7 @@ __global__ __launch_bounds__(kFftThreads) void smooth_pow2_kernel(
     }
     if (!pow2_length(L)) return;                      // other kernels own this head
     if (skip_dec && dec_owns(g, L, cutoff_frac)) return;   // spread over several workgroups by the dec_* kernels
-    if (real_item(g, L, cutoff_frac, cutoffs_only)) return;   // smooth_real.hip
+    if (others & (unsigned)L) return;                 // smooth_real.hip
     const int T = g.taper_bins;
     if (g.cutoff_mode == AUDIOKV_CUTOFF_FRACTION && cutoffs_only) {
         if (tid == 0) kstar_out[head] = (int)floor(cutoff_frac * (double)(L >> 1));
@@ -470,7 +470,7 @@ __device__ __forceinline__ void fill_tables(cf* lo, cf* hi, int n_hi, int M) {
 
 // ------------------------ power-of-two lengths, few heads: one head on several workgroups ------------------------
 // A call with few heads (one layer of a prefill: four) leaves all but a handful of CUs idle while each head's
-// transform runs in one workgroup. For those calls a head of 32768 samples is cut into D = 16 interleaved
+// transform runs in one workgroup. For those calls a head of L = 32768 (or 16384) samples is cut into D = 16 interleaved
 // sub-sequences x_{16 m + r} of M = L / 16 samples, the first stage of a decimation-in-time FFT taken out of the
 // workgroup:
 //   dec_forward   per pair (r, r + 1): one complex M-point FFT in LDS gives the spectra G_r, G_{r+1} of the two
@@ -484,7 +484,9 @@ __device__ __forceinline__ void fill_tables(cf* lo, cf* hi, int n_hi, int M) {
 // in one place first.
 constexpr int kDecLog = 4, kDec = 1 << kDecLog;      // D
 constexpr int kDecThreads = 1024;    // the strided (and, inside evict, pooled) loads want many waves in flight
-constexpr int kDecMinL = 32768;   // below this one workgroup per head is faster (a smooth call on 4 heads: 16384 18 us spread, 14 alone; 32768 20 and 29)
+// Calls that hold a head of 32768 samples take this path (a smooth call on 4 heads: 32768 20 us spread, 29 in one workgroup each;
+// 16384 18 and 14), and heads of 16384 go along with them (4 heads each of both 20.5 us, with 16384 in a launch of its own 32.8).
+constexpr int kDecMinL = 16384, kDecFromL = 32768;
 constexpr int kDecMaxHeads = 64;                     // beyond this the heads fill the chip by themselves
 
 __host__ __device__ inline bool dec_length(int L) { return pow2_length(L) && L >= kDecMinL; }
@@ -1226,8 +1228,8 @@ int dec_max_length(const int32_t* seqlens_host, int n_items, int H_kv) {
     if ((long long)n_items * H_kv > kDecMaxHeads) return 0;
     int mx = 0;
     for (int i = 0; i < n_items; ++i)
-        if (dec_length(seqlens_host[i])) mx = max(mx, seqlens_host[i]);
-    return mx;
+        if (pow2_length(seqlens_host[i])) mx = max(mx, seqlens_host[i]);
+    return mx >= kDecFromL ? mx : 0;
 }
 size_t dec_bytes(const int32_t* seqlens_host, int n_items, int H_kv) {
     const int mx = dec_max_length(seqlens_host, n_items, H_kv);
@@ -1414,13 +1416,22 @@ hipError_t launch_smooth(const Geom& g, const float* in, bool pool_on_load, cons
     // every head is handled by exactly one path (alpha = 0 copies: the single-workgroup kernel)
     // which of the single-workgroup kernels have heads, by length
     int max_small = 0;                                   // longest head left to smooth_pow2_kernel
-    unsigned real_lengths = 0;                           // bit l: heads of 2^l samples for smooth_real_kernel
+    unsigned real_lengths = 0;                           // the sum of the different lengths left to smooth_real.hip
     for (int i = 0; i < n_items && alpha != 0.0; ++i) {
         const int L = seqlens_host[i];
         if (!pow2_length(L)) continue;
         if (dec_L && dec_length(L) && degenerate_mask(L, (int)floor(cutoff_frac * (double)(L >> 1)), g.taper_bins) != 2) continue;
-        if (real_item(g, L, cutoff_frac, cutoffs_only ? 1 : 0)) real_lengths |= 1u << (31 - __builtin_clz((unsigned)L));
+        if (real_item(g, L, cutoff_frac, cutoffs_only ? 1 : 0)) real_lengths |= (unsigned)L;
         else max_small = max(max_small, L);
+    }
+    // If smooth_pow2_kernel has heads at all, it takes those of up to 16384 samples along: side by side they cost less than a second
+    // launch (4 heads each of 512 and 8192 samples 13.2 us, in two launches 16.4; 40 heads each of 512 and 16384 20.7 and 23.2; 4 heads
+    // of them with an energy cutoff 28.5 and 34.1). Where few heads of 16384 are left out of that, it is for their accuracy:
+    // 20.1 us with an error of 1.23e-7 against 22.6 us and 1.15e-7.
+    const unsigned too_long = n_heads <= kDecMaxHeads && g.cutoff_mode == AUDIOKV_CUTOFF_FRACTION ? 16384u : 32768u;
+    if (max_small > 0 && real_lengths < too_long) {
+        for (unsigned l = real_lengths; l; l &= l - 1) max_small = max(max_small, (int)(l & -l));
+        real_lengths = 0;
     }
     if (max_small > 0 || alpha == 0.0) {
         const int n_hi = (max_small >> 8) + 1;
@@ -1429,13 +1440,12 @@ hipError_t launch_smooth(const Geom& g, const float* in, bool pool_on_load, cons
                                      (size_t)kFftThreads * sizeof(double));
         hipLaunchKernelGGL(smooth_pow2_kernel, dim3(n_heads), dim3(kFftThreads), smem, s, g, in,
                            pool_on_load ? 1 : 0, cu_seqlens, cutoff_frac, (float)alpha, out, kstar_out, cutoffs_only ? 1 : 0,
-                           dec_L ? 1 : 0);
+                           dec_L ? 1 : 0, real_lengths);
     }
-    for (int l = 0; l < 31; ++l)
-        if (real_lengths >> l & 1) {
-            e = launch_smooth_real(1 << l, g, in, pool_on_load, cu_seqlens, cutoff_frac, (float)alpha, out, kstar_out, cutoffs_only, s);
-            if (e != hipSuccess) return e;
-        }
+    if (real_lengths) {
+        e = launch_smooth_real(real_lengths, g, in, pool_on_load, cu_seqlens, cutoff_frac, (float)alpha, out, kstar_out, cutoffs_only, s);
+        if (e != hipSuccess) return e;
+    }
     if (dec_L) {
         const int M = dec_L >> kDecLog;
         const size_t smem = (padded_len(M) + kTwLo + (M >> 8) + 1) * sizeof(cf);

@@ -15,6 +15,7 @@
 // 112 heads of 16384 22.4 -> 15.7 us, with an energy-adaptive cutoff 4 heads of 8192 19.8 -> 14.1. Error against 64 bits
 // (2-norm, relative, mean of 36 sequences), smooth_pow2_kernel -> this: 2048 1.21e-7 -> 0.99e-7, 8192 1.24e-7 -> 1.05e-7, 32768
 // 1.17e-7 -> 1.14e-7 (1.26e-7 with roots from a float32 polynomial, 1.18e-7 with float32 products of two table entries).
+#include <algorithm>
 #include <atomic>
 
 #include "fft_regs.h"
@@ -93,22 +94,15 @@ __device__ __forceinline__ float bin_weight(int k, int kstar, int T) {
 
 // POOL: 0 none, 7 the usual size, 1 any size up to 9
 template <int LOGC, int POOL>
-__global__ __launch_bounds__(kRealThreads<LOGC>) void smooth_real_kernel(
-    Geom g, const float* __restrict__ in, const int32_t* __restrict__ cu_seq, double cutoff_frac, float alpha,
-    float* __restrict__ out, int32_t* __restrict__ kstar_out, int cutoffs_only)
+__device__ __forceinline__ void smooth_real_head(
+    const Geom& g, const float* __restrict__ src, double cutoff_frac, float alpha, float* __restrict__ dst,
+    int32_t* __restrict__ kstar_out, int cutoffs_only, unsigned char* smem)
 {
     constexpr int VT = kRealGroups<LOGC>;
     using F = Fft<LOGC, VT>;
     constexpr int N = 1 << LOGC, L = 2 * N, T = F::THREADS;
-    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     RealLds<LOGC>& m = *reinterpret_cast<RealLds<LOGC>*>(smem);
     const int head = blockIdx.x, t = threadIdx.x;
-    const int item = head / g.H_kv, h = head - item * g.H_kv;
-    const int tok0 = cu_seq[item];
-    if (cu_seq[item + 1] - tok0 != L) return;                // another launch's head
-    const size_t off = (size_t)tok0 * g.H_kv + (size_t)h * L;
-    const float* src = in + off;
-    float* dst = out + off;
 
     // ---- samples 2 n, 2 n + 1 of the points n of the first layout ----
     cf v[VT][8];
@@ -261,6 +255,81 @@ __global__ __launch_bounds__(kRealThreads<LOGC>) void smooth_real_kernel(
     }
 }
 
+// length and place of the head of a workgroup
+__device__ __forceinline__ int head_span(const Geom& g, const int32_t* __restrict__ cu_seq, int head, size_t& off) {
+    const int item = head / g.H_kv, h = head - item * g.H_kv;
+    const int tok0 = cu_seq[item], L = cu_seq[item + 1] - tok0;
+    off = (size_t)tok0 * g.H_kv + (size_t)h * L;
+    return L;
+}
+
+template <int LOGC, int POOL>
+__global__ __launch_bounds__(kRealThreads<LOGC>) void smooth_real_kernel(
+    Geom g, const float* __restrict__ in, const int32_t* __restrict__ cu_seq, double cutoff_frac, float alpha,
+    float* __restrict__ out, int32_t* __restrict__ kstar_out, int cutoffs_only)
+{
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    size_t off;
+    if (head_span(g, cu_seq, blockIdx.x, off) != 2 << LOGC) return;      // another launch's head
+    smooth_real_head<LOGC, POOL>(g, in + off, cutoff_frac, alpha, out + off, kstar_out, cutoffs_only, smem);
+}
+
+// A call of several lengths: all heads in one launch, as many threads as the longest takes. The waves that a shorter head does
+// not need end at once (a barrier waits for the waves that are left). One launch per length instead would add up the times of
+// what runs side by side here: one call of four heads each of 1024, 2048, .. 16384 samples took 40.1 us, 13.5 in one launch (longest alone 13.8).
+template <int POOL>
+__global__ __launch_bounds__(1024) void smooth_mixed_kernel(
+    Geom g, const float* __restrict__ in, const int32_t* __restrict__ cu_seq, double cutoff_frac, float alpha,
+    float* __restrict__ out, int32_t* __restrict__ kstar_out, int cutoffs_only, unsigned lengths)
+{
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    size_t off;
+    const int L = head_span(g, cu_seq, blockIdx.x, off);
+    if ((L & (L - 1)) != 0 || !(lengths & (unsigned)L)) return;          // uniform
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+#define AUDIOKV_MIXED(LOGC)                                                                                               \
+    case 2 << LOGC:                                                                                                      \
+        if (wave < kRealThreads<LOGC> / 64)                                                                               \
+            smooth_real_head<LOGC, POOL>(g, in + off, cutoff_frac, alpha, out + off, kstar_out, cutoffs_only, smem);      \
+        break
+    switch (L) {
+        AUDIOKV_MIXED(9);
+        AUDIOKV_MIXED(10);
+        AUDIOKV_MIXED(11);
+        AUDIOKV_MIXED(12);
+        AUDIOKV_MIXED(13);
+        AUDIOKV_MIXED(14);
+    }
+#undef AUDIOKV_MIXED
+}
+
+size_t real_lds(int L) {
+    switch (L) {
+        case 1024:  return sizeof(RealLds<9>);
+        case 2048:  return sizeof(RealLds<10>);
+        case 4096:  return sizeof(RealLds<11>);
+        case 8192:  return sizeof(RealLds<12>);
+        case 16384: return sizeof(RealLds<13>);
+        default:    return sizeof(RealLds<14>);
+    }
+}
+
+template <int POOL>
+hipError_t launch_mixed(unsigned lengths, const Geom& g, const float* in, const int32_t* cu_seqlens, double cutoff_frac, float alpha,
+                        float* out, int32_t* kstar_out, bool cutoffs_only, hipStream_t s) {
+    const int longest = 1 << (31 - __builtin_clz(lengths));
+    static std::atomic<bool> attr_set{false};
+    if (!attr_set) {
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(smooth_mixed_kernel<POOL>),
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(RealLds<14>));
+        if (e != hipSuccess) return e;
+        attr_set = true;
+    }
+    hipLaunchKernelGGL((smooth_mixed_kernel<POOL>), dim3((unsigned)(g.n_items * g.H_kv)), dim3(std::min(longest / 16, 1024)),
+                       real_lds(longest), s, g, in, cu_seqlens, cutoff_frac, alpha, out, kstar_out, cutoffs_only ? 1 : 0, lengths);
+    return hipGetLastError();
+}
+
 template <int LOGC, int POOL>
 hipError_t launch(const Geom& g, const float* in, const int32_t* cu_seqlens, double cutoff_frac, float alpha, float* out,
                   int32_t* kstar_out, bool cutoffs_only, hipStream_t s) {
@@ -290,9 +359,14 @@ hipError_t launch(const Geom& g, const float* in, bool pool_on_load, const int32
 
 }  // namespace
 
-hipError_t launch_smooth_real(int L, const Geom& g, const float* in, bool pool_on_load, const int32_t* cu_seqlens, double cutoff_frac,
+hipError_t launch_smooth_real(unsigned lengths, const Geom& g, const float* in, bool pool_on_load, const int32_t* cu_seqlens, double cutoff_frac,
                               float alpha, float* out, int32_t* kstar_out, bool cutoffs_only, hipStream_t s) {
-    switch (L) {
+    if (lengths & (lengths - 1)) {
+        if (!pool_on_load) return launch_mixed<0>(lengths, g, in, cu_seqlens, cutoff_frac, alpha, out, kstar_out, cutoffs_only, s);
+        if (g.pool_kernel == 7) return launch_mixed<7>(lengths, g, in, cu_seqlens, cutoff_frac, alpha, out, kstar_out, cutoffs_only, s);
+        return launch_mixed<1>(lengths, g, in, cu_seqlens, cutoff_frac, alpha, out, kstar_out, cutoffs_only, s);
+    }
+    switch (lengths) {
         case 1024:  return launch<9>(g, in, pool_on_load, cu_seqlens, cutoff_frac, alpha, out, kstar_out, cutoffs_only, s);
         case 2048:  return launch<10>(g, in, pool_on_load, cu_seqlens, cutoff_frac, alpha, out, kstar_out, cutoffs_only, s);
         case 4096:  return launch<11>(g, in, pool_on_load, cu_seqlens, cutoff_frac, alpha, out, kstar_out, cutoffs_only, s);

@@ -45,6 +45,36 @@ def test_every_transform_size(A, L, cutoff, alpha, T):
             assert np.all(got[h] == got[h, 0])              # the mean, everywhere the same
 
 
+@pytest.mark.parametrize("lens", [[1024, 2048], [2048, 16384, 1024], [32768, 1024, 4096], [1024, 2048, 4096, 8192, 16384, 32768],
+                                  [512, 1024], [8, 16384, 1024], [4, 256, 8192, 32768], [2048, 3000, 1024, 31], [16384, 32768, 700]])
+@pytest.mark.parametrize("H", [2, 40])
+@pytest.mark.parametrize("mode,cutoff,T,alpha", [(0, 0.125, 0, 1.0), (0, 0.4, 9, 0.5), (0, 1.0, 0, 1.0), (2, 0.9, 0, 1.0)])
+def test_several_lengths_in_one_call(A, lens, H, mode, cutoff, T, alpha):
+    """Every head of a call with power-of-two lengths of different paths is smoothed, once, as the mask says: up to 80 heads share
+    launches, 40 heads of a length are too many to be spread over workgroups."""
+    rng = np.random.default_rng(sum(lens) + H)
+    s = [sequences(rng, 2, L) for L in lens]
+    flat = torch.from_numpy(np.concatenate([np.tile(x, (H // 2, 1)).reshape(-1) for x in s])).cuda()
+    p = A.Params(H, H, 128, 1, taper_bins=T, cutoff_mode=mode)
+    out = A.smooth(p, flat, lens, cutoff, alpha).cpu().numpy()
+    ks = A.smooth_cutoffs(p, flat, lens, cutoff).cpu().numpy()
+    at = 0
+    for i, x in enumerate(s):
+        L = x.shape[1]
+        got = out[at:at + H * L].reshape(H, L)
+        at += H * L
+        for h in range(2):
+            assert np.all(got[h::2] == got[h])
+            k = int(ks[i * H + h])
+            if mode == 0:
+                assert k == int(np.floor(cutoff * (L // 2)))
+            bins = np.arange(L // 2 + 1)
+            w = np.where(bins <= k, 1.0, np.where(bins <= k + T, 0.5 * (1 + np.cos(np.pi * (bins - k) / (T + 1))), 0.0))
+            x64 = x[h].astype(np.float64)
+            ref = (1 - alpha) * x64 + alpha * np.fft.irfft(np.fft.rfft(x64) * w, n=L)
+            assert np.abs(got[h] - ref).max() <= ATOL * np.abs(x[h]).max(), (L, h)
+
+
 @pytest.mark.parametrize("L", LENGTHS)
 @pytest.mark.parametrize("rho", [0.2, 0.9, 0.999])
 @pytest.mark.parametrize("no_dc", [False, True])
