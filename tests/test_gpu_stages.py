@@ -182,11 +182,11 @@ def test_select_adversarial(A):
     _select_case(A, [const, ramp, neg, ramp[::-1].copy()], [L], 4, [W, W + 1, L - 1, 77], W)   # b = W: window only
 
 
-@pytest.mark.parametrize("L,W", [(12352, 64), (16384, 32), (30000, 1), (32768, 64)])
+@pytest.mark.parametrize("L,W", [(8200, 8), (12352, 64), (16384, 32), (20000, 16), (24577, 0), (30000, 1), (32768, 64)])
 def test_select_long_heads_every_distribution(A, L, W):
-    """Long heads bracket the threshold between two pivots taken from a sample of the keys; the result must not depend
-    on how good the sample is. Distributions that defeat it (sorted, periodic in the register layout, alternating with
-    the sampled threads, plateaus, few distinct values, a narrow range, half zeros) and budgets at both extremes."""
+    """Long heads guess from a few of their keys which bin of the histogram will be crowded; the result must not depend on the
+    guess, nor on how many of the registers hold tokens. Sorted keys, keys periodic in the register layout, alternating with the
+    threads, plateaus, few distinct values, a narrow range, half zeros, and budgets at both extremes."""
     rng = np.random.default_rng(L + W)
     x = rng.standard_normal(L)
     t = np.arange(L)
