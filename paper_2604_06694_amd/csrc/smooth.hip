@@ -656,20 +656,13 @@ constexpr int kWideMaxLog = 18;                   // in chunks of at most 16384 
 constexpr int kMaxBluesteinLog = 18;              // M <= 262144: any L <= 131072 at any cutoff
 __host__ __device__ inline bool wide_size(int logM) { return logM >= kWideMinLog && logM <= kWideMaxLog; }
 
-// log2 of the transform size for L samples and K wanted bins: the smallest power of two >= L + K - 1
-__host__ __device__ inline int bluestein_log(int L, int K) {
+// All bins are wanted (the cutoff is found from the spectrum): L samples, K = floor(L/2) + 1 bins, and a transform of the smallest
+// power of two >= L + K - 1 points.
+__host__ __device__ inline int chirp_bins(int L) { return (L >> 1) + 1; }
+__host__ __device__ inline int bluestein_log(int L) {
     int lg = 1;
-    while ((1 << lg) < L + K - 1) ++lg;
+    while ((1 << lg) < L + chirp_bins(L) - 1) ++lg;
     return lg;
-}
-__host__ __device__ inline int bluestein_log_max(int L) { return bluestein_log(L, (L >> 1) + 1); }
-
-// bins 0 .. K-1 that the filter can leave non-zero (all of them when the cutoff is found from the spectrum)
-__host__ __device__ inline int wanted_bins(int L, double cutoff_frac, int cutoff_mode, int taper_bins) {
-    const int half = L >> 1;
-    if (cutoff_mode != AUDIOKV_CUTOFF_FRACTION) return half + 1;
-    const long long ktop = (long long)floor(cutoff_frac * (double)half) + taper_bins;
-    return (int)(ktop < half ? ktop : half) + 1;
 }
 
 // exp(-i*pi*n^2/L): the chirp, from an exactly reduced angle in float64
@@ -861,7 +854,6 @@ __device__ __forceinline__ int owner_item(const int32_t* __restrict__ cu_seq, in
 //   inverse transform (K bins in, L samples out): conj(chirp(m)) for m in (-K, L), which is the first one read
 //   backwards, so its spectrum is the first spectrum at the negated frequency.
 __global__ __launch_bounds__(kFftThreads) void bluestein_prepare_kernel(const int32_t* __restrict__ cu_seq, BluesteinWs ws,
-                                                                         double cutoff_frac, int cutoff_mode, int taper_bins,
                                                                          int skip_wide)
 {
     extern __shared__ float smem[];
@@ -869,8 +861,7 @@ __global__ __launch_bounds__(kFftThreads) void bluestein_prepare_kernel(const in
     const int L = cu_seq[item + 1] - cu_seq[item];
     if (pow2_length(L) || owner_item(cu_seq, item, L) != item) return;
     const int tid = threadIdx.x;
-    const int K = wanted_bins(L, cutoff_frac, cutoff_mode, taper_bins);
-    const int logM = bluestein_log(L, K);
+    const int K = chirp_bins(L), logM = bluestein_log(L);
     if (skip_wide && wide_size(logM)) return;         // prepared by the multi-workgroup kernels
     const int M = 1 << logM;
     const int C = M < (1 << kChunkLog) ? M : (1 << kChunkLog);
@@ -912,25 +903,19 @@ __global__ __launch_bounds__(kFftThreads) void smooth_bluestein_kernel(
     const int L = cu_seq[item + 1] - tok0;
     if (alpha == 0.f || pow2_length(L)) return;       // the LDS kernel owns this head
     const int T = g.taper_bins;
-    // a fixed cutoff that leaves only the mean, or everything: no transform (this kernel owns such heads whatever
-    // the transform size would have been)
-    const int fixed_kind = g.cutoff_mode == AUDIOKV_CUTOFF_FRACTION
-                               ? degenerate_mask(L, (int)floor(cutoff_frac * (double)(L >> 1)), T) : 0;
     if (conv.h && conv_item(conv, L)) return;         // smoothed by the convolution path
     const size_t off = (size_t)tok0 * g.H_kv + (size_t)h * L;
     const float* src = in + off;
     float* dst = out + off;
     const int tid = threadIdx.x;
-    if (g.cutoff_mode == AUDIOKV_CUTOFF_FRACTION && cutoffs_only) {
-        if (tid == 0) kstar_out[head] = (int)floor(cutoff_frac * (double)(L >> 1));
+    if (g.cutoff_mode == AUDIOKV_CUTOFF_FRACTION) {
+        // a fixed cutoff that is only asked for, or that leaves only the mean or everything: no transform
+        const int kstar = (int)floor(cutoff_frac * (double)(L >> 1));
+        if (!cutoffs_only) write_degenerate(degenerate_mask(L, kstar, T), g, src, dst, L, pool_on_load, alpha, reinterpret_cast<double*>(smem));
+        else if (tid == 0) kstar_out[head] = kstar;
         return;
     }
-    if (fixed_kind != 0) {
-        write_degenerate(fixed_kind, g, src, dst, L, pool_on_load, alpha, reinterpret_cast<double*>(smem));
-        return;
-    }
-    const int K = wanted_bins(L, cutoff_frac, g.cutoff_mode, T);
-    const int logM = bluestein_log(L, K);
+    const int K = chirp_bins(L), logM = bluestein_log(L);
     const int M = 1 << logM;
     const int C = M < (1 << kChunkLog) ? M : (1 << kChunkLog);
     cf* z = reinterpret_cast<cf*>(smem);
@@ -959,21 +944,18 @@ __global__ __launch_bounds__(kFftThreads) void smooth_bluestein_kernel(
     // one-sided bins: s~_n = (1/L) Re sum_{k<K} g_k F~_k e^{+2 pi i k n / L}, g_k = 1 for k = 0 and for the Nyquist
     // bin of an even L, else 2. That sum is the conjugate of a forward chirp-z transform of conj(g F~), K points
     // in and L points out, so conj(g F~) * chirp goes into the same machinery with the second filter.
-    int kstar = (int)floor(cutoff_frac * (double)(L >> 1));
     const float inv_m = 1.0f / (float)M;
-    if (g.cutoff_mode != AUDIOKV_CUTOFF_FRACTION) {
-        // |F_k| = |A[k]| / M: the chirp has unit modulus
-        auto bin_energy = [&](int k) -> float {
-            const cf a = A[k];
-            const float re = a.re * inv_m, im = a.im * inv_m;
-            return re * re + im * im;
-        };
-        EnergyScratch* sc = reinterpret_cast<EnergyScratch*>(hi + n_hi + 1);
-        kstar = energy_cutoff(bin_energy, (L >> 1) + 1, g.cutoff_mode == AUDIOKV_CUTOFF_ENERGY_NO_DC ? 1 : 0, cutoff_frac, sc);
-    }
+    // |F_k| = |A[k]| / M: the chirp has unit modulus
+    auto bin_energy = [&](int k) -> float {
+        const cf a = A[k];
+        const float re = a.re * inv_m, im = a.im * inv_m;
+        return re * re + im * im;
+    };
+    EnergyScratch* sc = reinterpret_cast<EnergyScratch*>(hi + n_hi + 1);
+    const int kstar = energy_cutoff(bin_energy, K, g.cutoff_mode == AUDIOKV_CUTOFF_ENERGY_NO_DC ? 1 : 0, cutoff_frac, sc);
     if (kstar_out && tid == 0) kstar_out[head] = kstar;
     if (cutoffs_only) return;
-    if (g.cutoff_mode != AUDIOKV_CUTOFF_FRACTION && degenerate_mask(L, kstar, T) != 0) {
+    if (degenerate_mask(L, kstar, T) != 0) {
         // the energy rule left only the mean (usual when the DC bin is counted: it holds most of the energy of a
         // non-negative sequence) or everything
         __syncthreads();
@@ -1016,28 +998,23 @@ __global__ __launch_bounds__(kFftThreads) void smooth_bluestein_kernel(
 
 constexpr int kWideThreads = 256;
 
-struct WideHead {                      // what every kernel of the sequence derives for its head
-    int L, K, logM, M, extra, R, q, owner;
-    size_t off;
+struct WideItem {                      // what every kernel of the sequence derives for its item
+    int L, K, logM, M, extra, R, q;
 };
 
-__device__ __forceinline__ bool wide_head(const Geom& g, const int32_t* __restrict__ cu_seq, int head, double cutoff_frac,
-                                          WideHead& w) {
-    const int item = head / g.H_kv, h = head - item * g.H_kv;
-    const int tok0 = cu_seq[item];
-    w.L = cu_seq[item + 1] - tok0;
+// Grids run over the items; only those that own their length work.
+__device__ __forceinline__ bool wide_owner(const int32_t* __restrict__ cu_seq, int item, WideItem& w) {
+    w.L = cu_seq[item + 1] - cu_seq[item];
     if (pow2_length(w.L)) return false;
-    w.K = wanted_bins(w.L, cutoff_frac, g.cutoff_mode, g.taper_bins);
-    w.logM = bluestein_log(w.L, w.K);
-    if (!wide_size(w.logM)) return false;              // small or very large: the single-workgroup kernel owns it
+    w.K = chirp_bins(w.L);
+    w.logM = bluestein_log(w.L);
+    if (!wide_size(w.logM) || owner_item(cu_seq, item, w.L) != item) return false;       // small: one workgroup prepares it
     w.M = 1 << w.logM;
     // two top stages and four chunks of M / 4 points up to M = 65536; beyond, as many top stages as it takes for
     // a chunk to fit the LDS (8 or 16 chunks of 16384 points)
     w.extra = w.logM - kChunkLog > 2 ? w.logM - kChunkLog : 2;
     w.R = 1 << w.extra;
     w.q = w.M >> w.extra;
-    w.owner = owner_item(cu_seq, item, w.L);
-    w.off = (size_t)tok0 * g.H_kv + (size_t)h * w.L;
     return true;
 }
 
@@ -1050,87 +1027,56 @@ __device__ __forceinline__ cf root_m(int e, int M) {
 
 constexpr int kWideMaxR = 16;          // chunks per transform at most (M = 262144)
 
-// one radix-2 stage on the register values v[r] = x[i + r*q], partners HS chunks apart; `st` counts the stages from
+// one radix-2 stage, forwards, on the register values v[r] = x[i + r*q], partners HS chunks apart; `st` counts the stages from
 // the top (half-size M >> (st + 1)), so the twiddle is root_M^(offset in the half * 2^st)
 template <int HS>
-__device__ __forceinline__ void top_stage(cf* v, int R, int q, int i, int M, int st, bool inverse) {
+__device__ __forceinline__ void top_stage(cf* v, int R, int q, int i, int M, int st) {
 #pragma unroll
     for (int r = 0; r < kWideMaxR; ++r) {
         if ((r & HS) != 0 || r + HS >= kWideMaxR) continue;      // compile-time after unrolling
         if (r + HS < R) {
             const cf w = root_m(((r & (HS - 1)) * q + i) << st, M);
-            if (!inverse) { const cf d = csub(v[r], v[r + HS]); v[r] = cadd(v[r], v[r + HS]); v[r + HS] = cmul(d, w); }
-            else { const cf cw = cmul(v[r + HS], cconj(w)); v[r + HS] = csub(v[r], cw); v[r] = cadd(v[r], cw); }
+            const cf d = csub(v[r], v[r + HS]);
+            v[r] = cadd(v[r], v[r + HS]);
+            v[r + HS] = cmul(d, w);
         }
     }
 }
 
-// the top stage(s) on the R values v[r] = x[i + r*q] held in registers (see top_stages for the index algebra)
+// the two or more top stages, forwards, on the R values v[r] = x[i + r*q] held in registers (see top_stages for the index algebra)
 template <int MAXR>
-__device__ __forceinline__ void top_butterfly(cf* v, int i, int M, int extra, bool inverse) {
+__device__ __forceinline__ void top_butterfly(cf* v, int i, int M, int extra) {
     if (MAXR > 4 && extra > 2) {
-        // 8 or 16 chunks: three or four plain radix-2 stages, largest half-size first forwards, last backwards
+        // 8 or 16 chunks: three or four plain radix-2 stages, largest half-size first
         const int R = 1 << extra, q = M >> extra;
-        if (!inverse) {
-            if (extra == 4) top_stage<8>(v, R, q, i, M, 0, false);
-            top_stage<4>(v, R, q, i, M, extra - 3, false);
-            top_stage<2>(v, R, q, i, M, extra - 2, false);
-            top_stage<1>(v, R, q, i, M, extra - 1, false);
-        } else {
-            top_stage<1>(v, R, q, i, M, extra - 1, true);
-            top_stage<2>(v, R, q, i, M, extra - 2, true);
-            top_stage<4>(v, R, q, i, M, extra - 3, true);
-            if (extra == 4) top_stage<8>(v, R, q, i, M, 0, true);
-        }
-        return;
-    }
-    if (extra == 1) {
-        const cf w = root_m(i, M);
-        if (!inverse) { const cf d = csub(v[0], v[1]); v[0] = cadd(v[0], v[1]); v[1] = cmul(d, w); }
-        else { const cf cw = cmul(v[1], cconj(w)); v[1] = csub(v[0], cw); v[0] = cadd(v[0], cw); }
+        if (extra == 4) top_stage<8>(v, R, q, i, M, 0);
+        top_stage<4>(v, R, q, i, M, extra - 3);
+        top_stage<2>(v, R, q, i, M, extra - 2);
+        top_stage<1>(v, R, q, i, M, extra - 1);
         return;
     }
     const cf w1 = root_m(i, M), w2 = root_m(2 * i, M);
-    cf a0 = v[0], a1 = v[1], a2 = v[2], a3 = v[3];
-    if (!inverse) {
-        const cf b0 = cadd(a0, a2), b2 = cmul(csub(a0, a2), w1);
-        const cf b1 = cadd(a1, a3), b3 = mul_neg_i(cmul(csub(a1, a3), w1));
-        a0 = cadd(b0, b1); a1 = cmul(csub(b0, b1), w2);
-        a2 = cadd(b2, b3); a3 = cmul(csub(b2, b3), w2);
-    } else {
-        const cf w1c = cconj(w1), w2c = cconj(w2);
-        const cf t1 = cmul(a1, w2c), t3 = cmul(a3, w2c);
-        const cf b0 = cadd(a0, t1), b1 = csub(a0, t1), b2 = cadd(a2, t3), b3 = csub(a2, t3);
-        const cf u2 = cmul(b2, w1c), u3 = mul_pos_i(cmul(b3, w1c));
-        a0 = cadd(b0, u2); a2 = csub(b0, u2);
-        a1 = cadd(b1, u3); a3 = csub(b1, u3);
-    }
-    v[0] = a0; v[1] = a1; v[2] = a2; v[3] = a3;
+    const cf b0 = cadd(v[0], v[2]), b2 = cmul(csub(v[0], v[2]), w1);
+    const cf b1 = cadd(v[1], v[3]), b3 = mul_neg_i(cmul(csub(v[1], v[3]), w1));
+    v[0] = cadd(b0, b1); v[1] = cmul(csub(b0, b1), w2);
+    v[2] = cadd(b2, b3); v[3] = cmul(csub(b2, b3), w2);
 }
 
-// Grids run over the first head of every item; only items that own their length work.
-__device__ __forceinline__ bool wide_owner(const Geom& g, const int32_t* __restrict__ cu_seq, int item, double cutoff_frac,
-                                           WideHead& w) {
-    return wide_head(g, cu_seq, item * g.H_kv, cutoff_frac, w) && w.owner == item;
-}
-
-__global__ __launch_bounds__(kWideThreads) void wide_prep_chirp_kernel(Geom g, const int32_t* __restrict__ cu_seq,
-                                                                       double cutoff_frac, BluesteinWs ws)
+__global__ __launch_bounds__(kWideThreads) void wide_prep_chirp_kernel(const int32_t* __restrict__ cu_seq, BluesteinWs ws)
 {
-    WideHead w;
+    WideItem w;
     const int item = blockIdx.y;
-    if (!wide_owner(g, cu_seq, item, cutoff_frac, w)) return;
+    if (!wide_owner(cu_seq, item, w)) return;
     cf* ch = ws.chirp_of(item);
     for (int n = blockIdx.x * kWideThreads + threadIdx.x; n < w.L; n += gridDim.x * kWideThreads) ch[n] = chirp(n, w.L);
 }
 
 template <int MAXR>
-__global__ __launch_bounds__(kWideThreads) void wide_prep_first_kernel(Geom g, const int32_t* __restrict__ cu_seq,
-                                                                       double cutoff_frac, BluesteinWs ws)
+__global__ __launch_bounds__(kWideThreads) void wide_prep_first_kernel(const int32_t* __restrict__ cu_seq, BluesteinWs ws)
 {
-    WideHead w;
+    WideItem w;
     const int item = blockIdx.y;
-    if (!wide_owner(g, cu_seq, item, cutoff_frac, w)) return;
+    if (!wide_owner(cu_seq, item, w)) return;
     if (w.R > MAXR) return;                             // (the launcher picks the instantiation that holds every head)
     const int i = blockIdx.x * kWideThreads + threadIdx.x;
     if (i >= w.q) return;
@@ -1147,18 +1093,17 @@ __global__ __launch_bounds__(kWideThreads) void wide_prep_first_kernel(Geom g, c
         }
         v[r] = b;
     }
-    top_butterfly<MAXR>(v, i, w.M, w.extra, false);
+    top_butterfly<MAXR>(v, i, w.M, w.extra);
 #pragma unroll
     for (int r = 0; r < MAXR; ++r)
         if (r < w.R) B1[i + r * w.q] = v[r];
 }
 
-__global__ __launch_bounds__(kWideThreads) void wide_prep_second_kernel(Geom g, const int32_t* __restrict__ cu_seq,
-                                                                        double cutoff_frac, BluesteinWs ws)
+__global__ __launch_bounds__(kWideThreads) void wide_prep_second_kernel(const int32_t* __restrict__ cu_seq, BluesteinWs ws)
 {
-    WideHead w;
+    WideItem w;
     const int item = blockIdx.y;
-    if (!wide_owner(g, cu_seq, item, cutoff_frac, w)) return;
+    if (!wide_owner(cu_seq, item, w)) return;
     const cf* B1 = ws.bhat_of(item, 0);
     cf* B2 = ws.bhat_of(item, 1);
     const int shift = 32 - w.logM;
@@ -1169,13 +1114,12 @@ __global__ __launch_bounds__(kWideThreads) void wide_prep_second_kernel(Geom g, 
     }
 }
 
-__global__ __launch_bounds__(kFftThreads) void wide_prep_chunk_kernel(
-    Geom g, const int32_t* __restrict__ cu_seq, double cutoff_frac, BluesteinWs ws)
+__global__ __launch_bounds__(kFftThreads) void wide_prep_chunk_kernel(const int32_t* __restrict__ cu_seq, BluesteinWs ws)
 {
     extern __shared__ float smem[];
-    WideHead w;
+    WideItem w;
     const int item = blockIdx.y;
-    if (!wide_owner(g, cu_seq, item, cutoff_frac, w)) return;
+    if (!wide_owner(cu_seq, item, w)) return;
     const int chunk = blockIdx.x;
     if (chunk >= w.R) return;
     const int logC = w.logM - w.extra;
@@ -1209,7 +1153,7 @@ hipError_t launch_pool(const Geom& g, const float* raw, const int32_t* cu_seqlen
     return hipGetLastError();
 }
 
-bool smooth_supported(int L) { return pow2_length(L) || (L >= 1 && L <= 131072 && bluestein_log_max(L) <= kMaxBluesteinLog); }
+bool smooth_supported(int L) { return pow2_length(L) || (L >= 1 && L <= 131072 && bluestein_log(L) <= kMaxBluesteinLog); }
 
 namespace {
 // scratch for lengths that are not powers of two, sized for the chirp-z transforms of an energy-adaptive cutoff (all
@@ -1218,7 +1162,7 @@ namespace {
 size_t bluestein_bytes(const int32_t* seqlens_host, int n_items, int H_kv) {
     int max_log = 0;
     for (int i = 0; i < n_items; ++i)
-        if (!pow2_length(seqlens_host[i])) max_log = max(max_log, bluestein_log_max(seqlens_host[i]));
+        if (!pow2_length(seqlens_host[i])) max_log = max(max_log, bluestein_log(seqlens_host[i]));
     if (max_log == 0) return 0;
     const size_t M = (size_t)1 << max_log;
     return ((size_t)n_items * H_kv * M + (size_t)n_items * 3 * M) * sizeof(cf);
@@ -1248,9 +1192,9 @@ size_t smooth_workspace_required(const int32_t* seqlens_host, int n_items, int H
 
 namespace {
 struct SmoothPlan {
-    int max_log = 0;                      // log2 of the largest chirp-z transform
-    bool any_wide = false;
-    bool one_wg_other = false;            // lengths that are not powers of two and run in one workgroup per head
+    int chirp_log = 0;                    // log2 of the largest chirp-z transform (energy cutoff)
+    bool others = false;                  // lengths that are not powers of two ...
+    bool one_wg_other = false;            // ... and run in one workgroup per head
     ConvCall conv;                        // the convolution path's share of them
 };
 
@@ -1273,9 +1217,8 @@ SmoothPlan plan_smooth(const Geom& g, const int32_t* cu_seqlens, const int32_t* 
     for (int i = 0; i < n_items; ++i) {
         const int L = seqlens_host[i];
         if (pow2_length(L)) continue;
-        const int lg = bluestein_log(L, wanted_bins(L, cutoff_frac, g.cutoff_mode, g.taper_bins));
-        p.max_log = max(p.max_log, lg);
-        p.any_wide = p.any_wide || wide_size(lg);
+        p.others = true;
+        if (!fixed) p.chirp_log = max(p.chirp_log, bluestein_log(L));
         if (fixed && degenerate_mask(L, (int)floor(cutoff_frac * (double)(L >> 1)), g.taper_bins) == 0) longest = max(longest, L);
         else p.one_wg_other = true;
     }
@@ -1328,38 +1271,36 @@ hipError_t smooth_kernel_attributes() {
     return e;
 }
 
-size_t bluestein_smem(const Geom& g, size_t M) {
-    const size_t extra = g.cutoff_mode != AUDIOKV_CUTOFF_FRACTION ? sizeof(EnergyScratch) + 2 * sizeof(cf) : 0;
+size_t bluestein_smem(size_t M) {
     const size_t C = M < ((size_t)1 << kChunkLog) ? M : ((size_t)1 << kChunkLog);
-    return std::max((padded_len(C) + kTwLo + (M >> 8) + 1) * sizeof(cf) + extra, (size_t)kFftThreads * sizeof(double));
+    return std::max((padded_len(C) + kTwLo + (M >> 8) + 1) * sizeof(cf) + sizeof(EnergyScratch) + 2 * sizeof(cf),
+                    (size_t)kFftThreads * sizeof(double));
 }
 
-hipError_t launch_filters(const Geom& g, const SmoothPlan& pl, const int32_t* cu_seqlens, int n_items, double cutoff_frac,
-                          void* workspace, hipStream_t s)
+hipError_t launch_filters(const Geom& g, const SmoothPlan& pl, const int32_t* cu_seqlens, int n_items, void* workspace, hipStream_t s)
 {
     hipError_t e = hipSuccess;
     if (pl.conv.any) e = launch_conv_filter(g, pl.conv, s);
-    if (e != hipSuccess || pl.max_log == 0 || g.cutoff_mode == AUDIOKV_CUTOFF_FRACTION) return e;
+    if (e != hipSuccess || pl.chirp_log == 0) return e;
     if (!workspace) return hipErrorInvalidValue;
     e = smooth_kernel_attributes();
     if (e != hipSuccess) return e;
-    const size_t M = (size_t)1 << pl.max_log;
+    const size_t M = (size_t)1 << pl.chirp_log;
     const BluesteinWs bw{static_cast<cf*>(workspace), M, g.n_items * g.H_kv};
-    const bool wide = pl.any_wide;
-    hipLaunchKernelGGL(bluestein_prepare_kernel, dim3(n_items), dim3(kFftThreads), bluestein_smem(g, M), s, cu_seqlens,
-                       bw, cutoff_frac, g.cutoff_mode, g.taper_bins, wide ? 1 : 0);
+    const bool wide = wide_size(pl.chirp_log);
+    hipLaunchKernelGGL(bluestein_prepare_kernel, dim3(n_items), dim3(kFftThreads), bluestein_smem(M), s, cu_seqlens, bw, wide ? 1 : 0);
     if (wide) {
-        const int extra_stages = pl.max_log - kChunkLog > 2 ? pl.max_log - kChunkLog : 2;    // of the largest transform
+        const int extra_stages = pl.chirp_log - kChunkLog > 2 ? pl.chirp_log - kChunkLog : 2;    // of the largest transform
         const unsigned q = (unsigned)(M >> extra_stages);
         const dim3 ew((q + kWideThreads - 1) / kWideThreads, (unsigned)n_items);
-        hipLaunchKernelGGL(wide_prep_chirp_kernel, ew, dim3(kWideThreads), 0, s, g, cu_seqlens, cutoff_frac, bw);
+        hipLaunchKernelGGL(wide_prep_chirp_kernel, ew, dim3(kWideThreads), 0, s, cu_seqlens, bw);
         if (extra_stages <= 2)
-            hipLaunchKernelGGL(wide_prep_first_kernel<4>, ew, dim3(kWideThreads), 0, s, g, cu_seqlens, cutoff_frac, bw);
+            hipLaunchKernelGGL(wide_prep_first_kernel<4>, ew, dim3(kWideThreads), 0, s, cu_seqlens, bw);
         else
-            hipLaunchKernelGGL(wide_prep_first_kernel<kWideMaxR>, ew, dim3(kWideThreads), 0, s, g, cu_seqlens, cutoff_frac, bw);
+            hipLaunchKernelGGL(wide_prep_first_kernel<kWideMaxR>, ew, dim3(kWideThreads), 0, s, cu_seqlens, bw);
         hipLaunchKernelGGL(wide_prep_chunk_kernel, dim3((unsigned)1 << extra_stages, (unsigned)n_items), dim3(kFftThreads),
-                           bluestein_smem(g, M), s, g, cu_seqlens, cutoff_frac, bw);
-        hipLaunchKernelGGL(wide_prep_second_kernel, ew, dim3(kWideThreads), 0, s, g, cu_seqlens, cutoff_frac, bw);
+                           bluestein_smem(M), s, cu_seqlens, bw);
+        hipLaunchKernelGGL(wide_prep_second_kernel, ew, dim3(kWideThreads), 0, s, cu_seqlens, bw);
     }
     return hipGetLastError();
 }
@@ -1370,7 +1311,7 @@ SmoothFilters smooth_filters(const Geom& g, const int32_t* cu_seqlens, const int
 {
     const SmoothPlan pl = plan_smooth(g, cu_seqlens, seqlens_host, n_items, cutoff_frac, workspace);
     SmoothFilters f;
-    f.long_work = (pl.max_log > 0 && g.cutoff_mode != AUDIOKV_CUTOFF_FRACTION) || pl.conv.spec;
+    f.long_work = pl.chirp_log > 0 || pl.conv.spec;
     if (!f.long_work) f.taps = pl.conv.job;
     return f;
 }
@@ -1379,7 +1320,7 @@ hipError_t launch_smooth_filters(const Geom& g, const int32_t* cu_seqlens, const
                                  double cutoff_frac, void* workspace, hipStream_t s)
 {
     return launch_filters(g, plan_smooth(g, cu_seqlens, seqlens_host, n_items, cutoff_frac, workspace), cu_seqlens, n_items,
-                          cutoff_frac, workspace, s);
+                          workspace, s);
 }
 
 hipError_t launch_smooth(const Geom& g, const float* in, bool pool_on_load, const int32_t* cu_seqlens,
@@ -1403,7 +1344,6 @@ hipError_t launch_smooth(const Geom& g, const float* in, bool pool_on_load, cons
     // (alpha = 0 copies, and a fixed cutoff is known without a transform: nothing to convolve)
     const bool transforms = alpha != 0.0 && !(cutoffs_only && g.cutoff_mode == AUDIOKV_CUTOFF_FRACTION);
     const SmoothPlan pl = plan_smooth(g, cu_seqlens, seqlens_host, n_items, cutoff_frac, transforms ? workspace : nullptr);
-    const int max_log = pl.max_log;
     const int n_heads = g.n_items * g.H_kv;
     hipError_t e = smooth_kernel_attributes();
     if (e != hipSuccess) return e;
@@ -1458,16 +1398,18 @@ hipError_t launch_smooth(const Geom& g, const float* in, bool pool_on_load, cons
         hipLaunchKernelGGL(dec_inverse_kernel, pairs, dim3(kDecThreads), smem, s, g, in, pool_on_load ? 1 : 0, cu_seqlens,
                            cutoff_frac, (float)alpha, out, dw);
     }
-    if (max_log == 0 || alpha == 0.0) return hipGetLastError();
+    if (!pl.others || alpha == 0.0) return hipGetLastError();
     if (!workspace) return hipErrorInvalidValue;
     if (transforms && !filters_ready) {
-        e = launch_filters(g, pl, cu_seqlens, n_items, cutoff_frac, workspace, s);
+        e = launch_filters(g, pl, cu_seqlens, n_items, workspace, s);
         if (e != hipSuccess) return e;
     }
     if (pl.one_wg_other || cutoffs_only) {
-        const size_t M = (size_t)1 << max_log;
+        // (a fixed cutoff needs no transform here, only the doubles that a mean is reduced in)
+        const size_t M = (size_t)1 << pl.chirp_log;
         const BluesteinWs bw{static_cast<cf*>(workspace), M, n_heads};
-        hipLaunchKernelGGL(smooth_bluestein_kernel, dim3(n_heads), dim3(kFftThreads), bluestein_smem(g, M), s, g, in,
+        const size_t smem = pl.chirp_log ? bluestein_smem(M) : (size_t)kFftThreads * sizeof(double);
+        hipLaunchKernelGGL(smooth_bluestein_kernel, dim3(n_heads), dim3(kFftThreads), smem, s, g, in,
                            pool_on_load ? 1 : 0, cu_seqlens, cutoff_frac, (float)alpha, out, bw, kstar_out,
                            cutoffs_only ? 1 : 0, pl.conv.job);
     }
