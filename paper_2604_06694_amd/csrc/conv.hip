@@ -23,8 +23,9 @@
 // Pool + smooth of one layer of four heads inside evict, chirp-z path before -> this: L = 13577 41 us in six launches beside
 // 50 us of filter preparation on another stream -> 19 us in two (chunks 14, join 5) and nothing beside; a smooth call on 24
 // sequences of two heads, 1500 to 30000 samples, 147 -> 41 us (taps 8, chunks 31, join 4); one layer of 30011 alone 78 -> 22,
-// 28 layers 144 -> 68. Error against 64 bits (2-norm, relative, mean of 36 sequences): L = 3000 4.4e-7 -> 1.2e-7, 13577 3.5e-7 -> 1.3e-7,
-// 30011 3.1e-7 -> 1.5e-7; most of it is the filter's own transform, a gain that differs from length to length.
+// 28 layers 144 -> 68. Error against 64 bits (2-norm, relative, mean of 36 sequences): L = 3000 4.4e-7 -> 1.0e-7, 13577 3.5e-7 -> 1.2e-7,
+// 30011 3.1e-7 -> 1.3e-7, 100003 4.3e-7 -> 2.1e-7; much of it is the filter's own transform, a gain that differs from length to
+// length (60 lengths and cutoffs: mean 3.9e-7 -> 1.3e-7, 1.5e-7 with three roots per butterfly instead of seven).
 #include <atomic>
 
 #include "conv_filter.h"
@@ -33,6 +34,9 @@
 
 namespace audiokv {
 namespace {
+
+// (the 1024 threads of 8192 points have 128 registers each: too few for all roots)
+template <int LOGC> using Cfft = Fft<LOGC, 1, (LOGC < 13)>;
 
 struct ConvHead { int L, log_n, R, owner; size_t off; };
 
@@ -146,13 +150,13 @@ __device__ __forceinline__ void gather_taps(const float* __restrict__ h, const C
 template <int LOGC>
 struct ConvLds {
     cf z[padded_len((size_t)1 << LOGC)];
-    cf table[1 << (LOGC - 1)];
+    cf table[padded_len((size_t)1 << (LOGC - 1))];
     cf c[16];
     alignas(16) cd step[8], back[8];         // (factors of products: these are rounded, not their factors)
 };
 template <int LOGC>
 __device__ __forceinline__ void fill_constants(ConvLds<LOGC>& m, const ConvHead& w, int r, int t) {
-    Fft<LOGC>::fill_table(m.table, t);
+    Cfft<LOGC>::fill_table(m.table, t);
     if (t < 32) {
         const float a = (float)(1 - 4 * r);
         const float x = t < 16 ? (float)(t & (w.R - 1)) * a / (float)(2 * w.R)
@@ -166,19 +170,19 @@ __device__ __forceinline__ void fill_constants(ConvLds<LOGC>& m, const ConvHead&
 }
 // acc, points 8 t + e, twisted and transformed: the bins of residue r in the last layout
 template <int LOGC>
-__device__ __forceinline__ void to_bins(ConvLds<LOGC>& m, const typename Fft<LOGC>::Twiddles& tw, cd tw0, int t, const cf (&acc)[8],
+__device__ __forceinline__ void to_bins(ConvLds<LOGC>& m, const typename Cfft<LOGC>::Twiddles& tw, cd tw0, int t, const cf (&acc)[8],
                                         cf (&v)[8]) {
 #pragma unroll
     for (int e = 0; e < 8; ++e) v[e] = mul(acc[e], mul_rounded(tw0, m.step[e]));
-    Fft<LOGC>::put(m.z, v, 8 * t, 0);
+    Cfft<LOGC>::put(m.z, v, 8 * t, 0);
     __syncthreads();
-    Fft<LOGC>::get(m.z, v, t, LOGC - 3);
-    Fft<LOGC>::forward(reinterpret_cast<cf(&)[1][8]>(v), m.z, tw, t);
+    Cfft<LOGC>::get(m.z, v, t, LOGC - 3);
+    Cfft<LOGC>::forward(reinterpret_cast<cf(&)[1][8]>(v), m.z, tw, t);
 }
 
 // the filter's bins of every distinct length, for calls in which many heads share them
 template <int LOGC>
-__global__ __launch_bounds__(Fft<LOGC>::THREADS) void conv_spectrum_kernel(Geom g, ConvFilterJob job, int log_r,
+__global__ __launch_bounds__(Cfft<LOGC>::THREADS) void conv_spectrum_kernel(Geom g, ConvFilterJob job, int log_r,
                                                                            cf* __restrict__ spec, size_t spec_stride)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -187,8 +191,8 @@ __global__ __launch_bounds__(Fft<LOGC>::THREADS) void conv_spectrum_kernel(Geom 
     const int item = blockIdx.x >> log_r, r = blockIdx.x & ((1 << log_r) - 1), t = threadIdx.x;
     if (!conv_head(g, job, item * g.H_kv, LOGC, w) || w.owner != item || r >= w.R) return;
     fill_constants<LOGC>(m, w, r, t);
-    typename Fft<LOGC>::Twiddles tw;
-    Fft<LOGC>::init(tw, m.table, t);
+    typename Cfft<LOGC>::Twiddles tw;
+    Cfft<LOGC>::init(tw, m.table, t);
     cf acc[8], v[8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) acc[e] = {0.f, 0.f};
@@ -201,11 +205,11 @@ __global__ __launch_bounds__(Fft<LOGC>::THREADS) void conv_spectrum_kernel(Geom 
 }
 
 template <int LOGC, int POOL>
-__global__ __launch_bounds__(Fft<LOGC>::THREADS) void conv_chunk_kernel(
+__global__ __launch_bounds__(Cfft<LOGC>::THREADS) void conv_chunk_kernel(
     Geom g, const float* __restrict__ in, ConvFilterJob job, int log_r, const cf* __restrict__ spec, size_t spec_stride,
     cf* __restrict__ part, size_t part_stride, float alpha, float* __restrict__ out)
 {
-    constexpr int C = 1 << LOGC, T = Fft<LOGC>::THREADS;
+    constexpr int C = 1 << LOGC, T = Cfft<LOGC>::THREADS;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     ConvLds<LOGC>& m = *reinterpret_cast<ConvLds<LOGC>*>(smem);
     constexpr int U = LOGC == 13 ? 2 : 4;                        // (1024 threads: 128 registers)
@@ -213,8 +217,8 @@ __global__ __launch_bounds__(Fft<LOGC>::THREADS) void conv_chunk_kernel(
     const int head = blockIdx.x >> log_r, r = blockIdx.x & ((1 << log_r) - 1), t = threadIdx.x;
     if (!conv_head(g, job, head, LOGC, w) || r >= w.R) return;
     fill_constants<LOGC>(m, w, r, t);
-    typename Fft<LOGC>::Twiddles tw;
-    Fft<LOGC>::init(tw, m.table, t);
+    typename Cfft<LOGC>::Twiddles tw;
+    Cfft<LOGC>::init(tw, m.table, t);
     const float a = (float)(1 - 4 * r);
     const cd tw0 = cis_pi_f64((float)(8 * t) * a / (float)(2 << w.log_n));
     const float* src = in + w.off;
@@ -239,7 +243,7 @@ __global__ __launch_bounds__(Fft<LOGC>::THREADS) void conv_chunk_kernel(
     }
 #pragma unroll
     for (int e = 0; e < 8; ++e) v[e] = mul(v[e], f[e]);
-    Fft<LOGC>::backward(reinterpret_cast<cf(&)[1][8]>(v), m.z, tw, t);
+    Cfft<LOGC>::backward(reinterpret_cast<cf(&)[1][8]>(v), m.z, tw, t);
 
     // twisted back: point n = t + T q of residue r by exp(i pi n (4 r - 1) / 2N); 1/N completes the inverse transform
     const double inv_n = 1.0 / (double)(1 << w.log_n);
@@ -356,7 +360,7 @@ hipError_t launch_chunks(const Geom& g, const ConvCall& c, const float* in, floa
         }
     }
     hipLaunchKernelGGL((conv_chunk_kernel<LOGC, POOL>), dim3((unsigned)(g.n_items * g.H_kv) << log_residues(c)),
-                       dim3(Fft<LOGC>::THREADS), lds, s, g, in, c.job, log_residues(c), (const cf*)c.spec, c.points, (cf*)c.part, c.points, alpha, out);
+                       dim3(Cfft<LOGC>::THREADS), lds, s, g, in, c.job, log_residues(c), (const cf*)c.spec, c.points, (cf*)c.part, c.points, alpha, out);
     return hipGetLastError();
 }
 template <int LOGC>
@@ -377,7 +381,7 @@ hipError_t launch_spectra(const Geom& g, const ConvCall& c, hipStream_t s) {
             attr_set = true;
         }
     }
-    hipLaunchKernelGGL((conv_spectrum_kernel<LOGC>), dim3((unsigned)g.n_items << log_residues(c)), dim3(Fft<LOGC>::THREADS), lds, s,
+    hipLaunchKernelGGL((conv_spectrum_kernel<LOGC>), dim3((unsigned)g.n_items << log_residues(c)), dim3(Cfft<LOGC>::THREADS), lds, s,
                        g, c.job, log_residues(c), (cf*)c.spec, c.points);
     return hipGetLastError();
 }

@@ -1,6 +1,8 @@
 // In-place power-of-two transforms with eight points per thread in registers, for the smoothing kernels.
 #pragma once
 
+#include <type_traits>
+
 #include "smooth_common.h"
 
 // Every fused multiply-add is written out: the kernels that use this exist in several instantiations (pooling on load or
@@ -19,8 +21,8 @@ __device__ __forceinline__ float mix(float s0, float smoothed, float alpha) { re
 
 // exp(i pi x), |x| <= 2^16: x - k/2 is exact, and on [-1/4, 1/4] the Taylor series of cos and sin in float64 (remainders
 // below 4e-13 and, relative, 9.8e-12; a float64 multiply-add issues as fast as a float32 one here). Roots, twists and what splits
-// and merges real spectra are float64 values rounded to float32 once, products among them; only the roots that a radix-8
-// butterfly derives from its three (twist) are float32 products.
+// and merges real spectra are float64 values rounded to float32 once, products among them; only a transform that keeps three
+// roots per radix-8 butterfly (ALL = false) derives the other four as float32 products.
 struct cd { double re, im; };
 __host__ __device__ __forceinline__ cd cis_pi_f64(float x) {
     const float k = rintf(2.f * x), r = fmaf(-0.5f, k, x);
@@ -76,7 +78,9 @@ __device__ __forceinline__ void dft8(cf (&v)[8]) {
 // digit-reversed order (bin_of, slot_of); backwards the passes mirror it.
 //   first layout: virtual thread t holds points t + (C/8) q;  last layout: it holds slots 8 t + e  (e, q = 0..7)
 // Virtual threads of thread x: x, x + THREADS.
-template <int LOGC, int VT = 1>
+// ALL: the seven roots of every radix-8 butterfly in registers, all of them rounded once, instead of three that the others are
+// products of.
+template <int LOGC, int VT = 1, bool ALL = false>
 struct Fft {
     static constexpr int C = 1 << LOGC, THREADS = C / (8 * VT);
     static constexpr int P8 = LOGC / 3;                       // radix-8 passes
@@ -85,10 +89,12 @@ struct Fft {
     __host__ __device__ static constexpr int low_bit(int p) { return LOGC - 3 * (p + 1); }
 
     struct W3 { cf w1, w2, w4; };
-    // root_{8m}^(j0 {1, 2, 4}) per pass, in registers, from a table of exp(-2 pi i e / C), e < C/2
+    struct W7 { cf w1, w2, w4, w3, w5, w6, w7; };
+    using W = std::conditional_t<ALL, W7, W3>;
+    // root_{8m}^(j0 {1, 2, 4}) per pass, in registers, from a table of exp(-2 pi i e / C) at pad(e), e < C/2
     struct Twiddles {
-        W3 w[VT][TW];
-        __device__ __forceinline__ W3 operator()(int p, int vt) const { return w[vt][p]; }
+        W w[VT][TW];
+        __device__ __forceinline__ W operator()(int p, int vt) const { return w[vt][p]; }
     };
     // The same looked up where they are used, from a table of every fourth root, exp(-2 pi i 4 j / C) at pad(j). Only the first
     // pass has exponents between them: w + w (root - 1), whose second term is too small for its roundings to matter.
@@ -127,15 +133,15 @@ struct Fft {
         for (int p = 0; p < P8; ++p) s |= ((bin >> (3 * p)) & 7) << low_bit(p);
         return s;
     }
-    // exp(-2 pi i e / C) for e = t + (C/8) u, u < 4: eighth turns apart
+    // exp(-2 pi i e / C) at pad(e) for e = t + (C/8) u, u < 4: eighth turns apart
     __host__ __device__ __forceinline__ static void fill_table(cf* table, int t) {
         static_assert(VT == 1, "four entries per thread");
         const cd w = cis_pi_f64(-(float)t / (float)(C / 2));
         const double H = 0.70710678118654752, p = H * (w.re + w.im), q = H * (w.im - w.re);
-        table[t] = rounded(w);
-        table[t + C / 8] = {(float)p, (float)q};
-        table[t + C / 4] = {(float)w.im, (float)-w.re};
-        table[t + 3 * C / 8] = {(float)q, (float)-p};
+        table[pad(t)] = rounded(w);
+        table[pad(t + C / 8)] = {(float)p, (float)q};
+        table[pad(t + C / 4)] = {(float)w.im, (float)-w.re};
+        table[pad(t + 3 * C / 8)] = {(float)q, (float)-p};
     }
     // exp(-2 pi i 4 j / C) for j = t, t + C/16: a quarter turn apart
     __host__ __device__ __forceinline__ static void fill_every_fourth(cf* table, int t) {
@@ -154,14 +160,32 @@ struct Fft {
             return mul_rounded(base, step[e]);
         }
     };
-    __device__ __forceinline__ static void init(Twiddles& tw, const cf* table, int t) {
+    __host__ __device__ __forceinline__ static void init(Twiddles& tw, const cf* table, int t) {
 #pragma unroll
         for (int vt = 0; vt < VT; ++vt)
 #pragma unroll
             for (int p = 0; p < TW; ++p) {
                 const int e = exponent(p, t + vt * THREADS);
-                tw.w[vt][p] = {table[e], table[2 * e], table[4 * e]};
+                tw.w[vt][p].w1 = table[pad(e)];
+                tw.w[vt][p].w2 = table[pad(2 * e)];
+                tw.w[vt][p].w4 = table[pad(4 * e)];
+                if constexpr (ALL) {
+                    auto root = [&](int k) {                 // the second half of the circle: negated
+                        const cf r = table[pad(k & (C / 2 - 1))];
+                        return k & (C / 2) ? cf{-r.re, -r.im} : r;
+                    };
+                    tw.w[vt][p].w3 = root(3 * e);
+                    tw.w[vt][p].w5 = root(5 * e);
+                    tw.w[vt][p].w6 = root(6 * e);
+                    tw.w[vt][p].w7 = root(7 * e);
+                }
             }
+    }
+    template <bool CONJ>
+    __device__ __forceinline__ static void twist(cf (&v)[8], const W7& w) {
+        auto at = [](cf r) { return CONJ ? cconj(r) : r; };
+        v[1] = mul(v[1], at(w.w1)); v[2] = mul(v[2], at(w.w2)); v[3] = mul(v[3], at(w.w3)); v[4] = mul(v[4], at(w.w4));
+        v[5] = mul(v[5], at(w.w5)); v[6] = mul(v[6], at(w.w6)); v[7] = mul(v[7], at(w.w7));
     }
     template <bool CONJ>
     __device__ __forceinline__ static void twist(cf (&v)[8], const W3& w) {

@@ -27,12 +27,18 @@ struct Worst {
 
 template <int LOGC>
 void table_of_roots() {
-    using F = Fft<LOGC>;
-    std::vector<cf> table(F::C / 2);
+    using F = Fft<LOGC, 1, true>;
+    std::vector<cf> table(padded_len(F::C / 2));
     for (int t = 0; t < F::THREADS; ++t) F::fill_table(table.data(), t);
     Worst roots{"table", kOnce}, bins{"bins", kOnce};
-    for (int e = 0; e < F::C / 2; ++e) roots.add(table[e], -(long double)e / (F::C / 2));
+    for (int e = 0; e < F::C / 2; ++e) roots.add(table[pad(e)], -(long double)e / (F::C / 2));
     for (int t = 0; t < F::THREADS; ++t) {
+        typename F::Twiddles tw;
+        F::init(tw, table.data(), t);
+        for (int p = 0; p < F::TW; ++p) {
+            const cf w[8] = {{1.f, 0.f}, tw.w[0][p].w1, tw.w[0][p].w2, tw.w[0][p].w3, tw.w[0][p].w4, tw.w[0][p].w5, tw.w[0][p].w6, tw.w[0][p].w7};
+            for (int k = 0; k < 8; ++k) roots.add(w[k], -(long double)(k * F::exponent(p, t)) / (F::C / 2));
+        }
         const typename F::BinRoots root(t);
         for (int e = 0; e < 8; ++e) bins.add(root(e), -(long double)F::bin_of(8 * t + e) / F::C);
     }
