@@ -190,7 +190,7 @@ def time_config(A, cfg, data, steps, warmup, dev):
         if dominant != "compact":
             roof["note"] = ("a chain of small per-head kernels, bound by launch and barrier latency rather than by bandwidth; "
                             "with stage timing on, work that otherwise runs beside the score sweeps on the helper stream "
-                            "(chirp-z filter preparation for lengths that are not powers of two) is in line and counted here")
+                            "(filter preparation for lengths that are not powers of two) is in line and counted here")
     roof["frac"] = roof["achieved"] / roof["peak"]
     return {"dt": dt, "stage_ms": stage_ms, "tokens": tokens, "kept": kept, "ab": ab, "score_flops": score_flops,
             "roof": roof, "p": p, "scope": scope, "cu": cu, "ws": ws, "outs": outs, "step": step}

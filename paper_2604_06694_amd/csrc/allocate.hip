@@ -246,7 +246,8 @@ __device__ __forceinline__ long long wave_sum_ll(long long v) {
 // The same for a pool of at most 64 PER heads by one wave, head 64 j + l in register j of lane l: no LDS and no barrier, the
 // chains (the weight sum in head order, the ranks) run over lane reads. Same operations in the same order, hence the
 // same bits. What this is for is latency: the launch that merges the statistics and allocates four heads 6.2 -> 3.8 us.
-// The chains grow by 0.3 us per head (112 heads 36 us here, 61 by 256 threads); beyond 128 heads the threads have it.
+// The chains grow with the heads: a call on 112 of them takes 22 us here and 24 by 256 threads (weights that cap in several
+// rounds 33 and 41), on 128 25 and 26; beyond, the threads have it. Beside the sweeps, on the helper stream, it takes 65 us.
 template <int PER>
 __device__ __forceinline__ void allocate_wave(
     const int seg, const float* __restrict__ weights, int n_segments, int n, int weight_group, int window,

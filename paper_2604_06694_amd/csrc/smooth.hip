@@ -13,8 +13,9 @@
 // that depends on the position inside the 16-point group is a constant 16th
 // root of unity.
 //
-// With a fixed cutoff any other length is convolved with the mask's taps (conv.hip). What is left for lengths that are not powers of two is the energy-adaptive cutoff, which needs the whole
-// spectrum before there is a mask: Bluestein's chirp-z identity (the transform length must be exactly L: zero-padding
+// Longer power-of-two heads are transformed in registers (smooth_real.hip). With a fixed cutoff any other length is convolved
+// with the mask's taps (conv.hip). What is left for lengths that are not powers of two is the energy-adaptive cutoff, which needs
+// the whole spectrum before there is a mask: Bluestein's chirp-z identity (the transform length must be exactly L: zero-padding
 // would be a different circular filter), a convolution with a chirp done with power-of-two FFTs in a per-head
 // global-memory workspace, M >= L + L/2 points. Stages whose span exceeds the LDS (M > 16384) run on global memory,
 // the rest on 16384-point chunks inside LDS.
@@ -1202,7 +1203,9 @@ struct SmoothPlan {
 // results). One layer of 4 heads, all launches of a smooth call, chunks of 1024 / 2048 / 4096 / 8192 points: L = 4001 19.5 /
 // 18.9 / 16.6 / 16.5 us, 13577 23.5 / 20.7 / 19.9 / 32.4, 30011 24.5 / 24.6 / 22.5 / 34.8; 28 layers: 45.8 / 41.4 / 36.9 /
 // 56.5 at 13577. Every chunk gathers from the whole head, so shorter ones repeat more of that, and 8192 points take
-// 1024 threads with too few registers each: only for transforms of 131072 points, which would be 32 chunks.
+// 1024 threads with too few registers each: only for transforms of 131072 points, which would be 32 chunks. One size for all heads of a
+// call, after the longest: a head of 500 samples beside one of 30000 runs 4096 points instead of 1024 (seven of them 26.9 us in all, 21.8
+// with one).
 int conv_chunk_log(int max_len) {
     const int log_n = conv_log_points(max_len, kConvMinLogC);
     return max(min(log_n, 12), log_n - kConvMaxLogR);

@@ -12,7 +12,7 @@
 // pass with two complex multiplications per butterfly of smooth_pow2_kernel, which keeps the shorter heads (as fast
 // there) and 32768 samples with an energy-adaptive cutoff (52 us for 112 heads there, 54 here). Pool + smooth
 // inside evict, before -> now: 4 heads of 2048 12.0 -> 8.0 us, 112 heads of 8192 23 -> 13.2, of 32768 55 -> 42; smooth calls:
-// 112 heads of 16384 22.4 -> 14.5 us, with an energy-adaptive cutoff 4 heads of 8192 19.8 -> 13.8. Error against 64 bits
+// 112 heads of 16384 21.2 -> 13.6 us, with an energy-adaptive cutoff 4 heads of 8192 19.3 -> 13.5. Error against 64 bits
 // (2-norm, relative, mean of 36 sequences), smooth_pow2_kernel -> this: 2048 1.21e-7 -> 0.99e-7, 8192 1.24e-7 -> 1.05e-7, 32768
 // 1.17e-7 -> 1.14e-7 (1.26e-7 with roots from a float32 polynomial, 1.18e-7 with float32 products of two table entries).
 #include <algorithm>

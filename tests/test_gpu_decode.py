@@ -63,7 +63,7 @@ def test_decode_long_heads_and_peaked_softmax(A):
 
 
 def test_decode_one_very_long_head(A):
-    # more chunks than the merge kernel's on-chip table holds: the path that sums straight from memory
+    # about a thousand chunks in one head, several per thread of the merge
     rng = np.random.default_rng(8)
     run_case(A, rng, 1, 1, 64, [1024 * 256 + 300], 1, k_scale=0.5)
     run_case(A, rng, 9, 1, 64, [512 * 256 + 7], 1, k_scale=0.5)          # 16-wide group padding: 512-row chunks
