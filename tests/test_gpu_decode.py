@@ -202,3 +202,17 @@ def test_decode_workspace_of_the_largest_call_serves_smaller_ones(A):
         got = A.decode_attend(p, q, k, v, cu, n, rows, workspace=ws)
         assert torch.equal(got, A.decode_attend(p, q, k, v, cu, n, rows))
         assert bool((ws[need:] == 7).all())
+
+
+@pytest.mark.parametrize("H_q,H_kv,d", [(8, 2, 64), (28, 4, 128), (8, 2, 256), (32, 2, 128)])
+def test_decode_takes_a_cache_at_any_element(A, H_q, H_kv, d):
+    """Queries and cache that start at any bf16 element, as slices of larger buffers do, give the bits of aligned copies."""
+    rows, n = 1003, 1
+    gen = torch.Generator(device="cuda").manual_seed(d)
+    bufs = [torch.randn(m + 8, generator=gen, device="cuda").to(torch.bfloat16) for m in (H_q * d, rows * d, rows * d)]
+    cu = torch.tensor([rows * i // H_kv for i in range(H_kv + 1)], dtype=torch.int32, device="cuda")
+    p = A.Params(H_q, H_kv, d, 1)
+    for off in (0, 1, 2, 3, 4, 7):
+        parts = [b[off:b.numel() - 8 + off] for b in bufs]
+        got = A.decode_attend(p, *parts, cu, n, rows)
+        assert torch.equal(got, A.decode_attend(p, *[x.clone() for x in parts], cu, n, rows))
