@@ -168,12 +168,29 @@ __device__ __forceinline__ void fill_constants(ConvLds<LOGC>& m, const ConvHead&
     }
     __syncthreads();
 }
+// exp(i pi n a / 2N) of points n = 8 t + e, a = 1 - 4 r: kept for both passes where there are registers for that
+template <int LOGC>
+struct Twists {
+    static constexpr bool kKept = LOGC < 13;
+    cd first;
+    cf kept[8];
+    __device__ __forceinline__ Twists(const ConvLds<LOGC>& m, const ConvHead& w, float a, int t)
+        : first(cis_pi_f64((float)(8 * t) * a / (float)(2 << w.log_n))) {
+        if constexpr (kKept)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) kept[e] = mul_rounded(first, m.step[e]);
+    }
+    __device__ __forceinline__ cf at(const ConvLds<LOGC>& m, int e) const {
+        if constexpr (kKept) return kept[e];
+        else return mul_rounded(first, m.step[e]);
+    }
+};
 // acc, points 8 t + e, twisted and transformed: the bins of residue r in the last layout
 template <int LOGC>
-__device__ __forceinline__ void to_bins(ConvLds<LOGC>& m, const typename Cfft<LOGC>::Twiddles& tw, cd tw0, int t, const cf (&acc)[8],
+__device__ __forceinline__ void to_bins(ConvLds<LOGC>& m, const typename Cfft<LOGC>::Twiddles& tw, const Twists<LOGC>& twist, int t, const cf (&acc)[8],
                                         cf (&v)[8]) {
 #pragma unroll
-    for (int e = 0; e < 8; ++e) v[e] = mul(acc[e], mul_rounded(tw0, m.step[e]));
+    for (int e = 0; e < 8; ++e) v[e] = mul(acc[e], twist.at(m, e));
     Cfft<LOGC>::put(m.z, v, 8 * t, 0);
     __syncthreads();
     Cfft<LOGC>::get(m.z, v, t, LOGC - 3);
@@ -197,7 +214,7 @@ __global__ __launch_bounds__(Cfft<LOGC>::THREADS) void conv_spectrum_kernel(Geom
 #pragma unroll
     for (int e = 0; e < 8; ++e) acc[e] = {0.f, 0.f};
     gather_taps<4>(job.h + item * job.item_stride, w, 1 << LOGC, m.c, t, acc);
-    to_bins<LOGC>(m, tw, cis_pi_f64((float)(8 * t) * (float)(1 - 4 * r) / (float)(2 << w.log_n)), t, acc, v);
+    to_bins<LOGC>(m, tw, Twists<LOGC>(m, w, (float)(1 - 4 * r), t), t, acc, v);
     cf* out = spec + (size_t)item * spec_stride + ((size_t)r << LOGC) + 8 * t;
 #pragma unroll
     for (int e = 0; e < 8; e += 2)
@@ -220,7 +237,7 @@ __global__ __launch_bounds__(Cfft<LOGC>::THREADS) void conv_chunk_kernel(
     typename Cfft<LOGC>::Twiddles tw;
     Cfft<LOGC>::init(tw, m.table, t);
     const float a = (float)(1 - 4 * r);
-    const cd tw0 = cis_pi_f64((float)(8 * t) * a / (float)(2 << w.log_n));
+    const Twists<LOGC> twist(m, w, a, t);
     const float* src = in + w.off;
 
     cf f[8], v[8];
@@ -239,7 +256,7 @@ __global__ __launch_bounds__(Cfft<LOGC>::THREADS) void conv_chunk_kernel(
         for (int e = 0; e < 8; ++e) { f[e] = v[e]; acc[e] = {0.f, 0.f}; }
         if (pass == 0) gather_taps<U>(job.h + w.owner * job.item_stride, w, C, m.c, t, acc);
         else gather_samples<U, POOL>(src, w, C, g.pool_kernel, g.pool_mode, m.c, t, acc);
-        to_bins<LOGC>(m, tw, tw0, t, acc, v);
+        to_bins<LOGC>(m, tw, twist, t, acc, v);
     }
 #pragma unroll
     for (int e = 0; e < 8; ++e) v[e] = mul(v[e], f[e]);
