@@ -5,14 +5,8 @@
 // definition (sum of weights accumulated in head order, share = (T*S)/sum),
 // so the integers produced are reproducible bit for bit on any IEEE machine.
 // Head-parallel steps (shares, floors, remainder ranks) are order-free.
-//
-// The merge of the score sweeps' per-range row statistics lives here too: it is
-// as small as the allocation, neither depends on the other, and inside one
-// call on one stream a launch costs more than either's work, so the
-// allocation can ride along in extra workgroups of the merge launch, and so can
-// the taps of the smoothing's filter.
 #include "common.h"
-#include "conv_filter.h"
+#include "allocate_wave.h"
 
 #pragma clang fp contract(off)
 
@@ -44,14 +38,6 @@ __device__ long long block_sum_ll(long long v, long long* scratch) {
     __syncthreads();
     return r;
 }
-
-__device__ __forceinline__ int n_keep_dev(double ratio, int L) {
-    return (int)floor(__dadd_rn(__dmul_rn(ratio, (double)L), 0.5));
-}
-
-// Whether the weights' sum defines shares: without one (all weights zero, a NaN, an infinity) the heads share equally. A share
-// that is NaN would not compare with the others, and the hand-out of the remainder below would never end.
-__device__ __forceinline__ bool has_shares(double sum) { return sum > 0.0 && sum < (double)INFINITY; }
 
 // the whole allocation of pool `seg` by one workgroup of kThreads threads; smem_raw: alloc_smem_bytes(n) bytes
 __device__ __forceinline__ void allocate_pool(
@@ -232,153 +218,6 @@ __device__ __forceinline__ void allocate_pool(
     }
 }
 
-__device__ __forceinline__ double lane_double(double v, int lane) {       // uniform lane
-    const long long b = __double_as_longlong(v);
-    const unsigned lo = __builtin_amdgcn_readlane((unsigned)b, lane), hi = __builtin_amdgcn_readlane((unsigned)(b >> 32), lane);
-    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
-}
-__device__ __forceinline__ long long wave_sum_ll(long long v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
-
-// The same for a pool of at most 64 PER heads by one wave, head 64 j + l in register j of lane l: no LDS and no barrier, the
-// chains (the weight sum in head order, the ranks) run over lane reads. Same operations in the same order, hence the
-// same bits. What this is for is latency: the launch that merges the statistics and allocates four heads 6.2 -> 3.8 us.
-// The chains grow with the heads: a call on 112 of them takes 22 us here and 24 by 256 threads (weights that cap in several
-// rounds 33 and 41), on 128 25 and 26; beyond, the threads have it. Beside the sweeps, on the helper stream, it takes 65 us.
-template <int PER>
-__device__ __forceinline__ void allocate_wave(
-    const int seg, const float* __restrict__ weights, int n_segments, int n, int weight_group, int window,
-    const int32_t* __restrict__ cu_seq, double ratio, double beta,
-    int32_t* __restrict__ budgets, int32_t* __restrict__ cu_budgets)
-{
-    const int lane = threadIdx.x & 63;
-    const int L = cu_seq[seg + 1] - cu_seq[seg];
-    const int nk = n_keep_dev(ratio, L);
-    const int r = (int)floor(__dmul_rn(beta, (double)(nk - window)));
-    const int f = window + r;                       // w + r of Eq. 1
-    const long long Bs = (long long)n * (nk - f);   // budget shared out by weight
-    const int cap = L - f;                          // no head keeps more than L tokens
-
-    double S[PER], x[PER], frac[PER];
-    int e[PER];
-    bool live[PER], capped[PER];
-#pragma unroll
-    for (int j = 0; j < PER; ++j) {
-        const int h = 64 * j + lane;
-        live[j] = h < n;
-        capped[j] = false;
-        const float* w = weights + ((size_t)seg * n + min(h, n - 1)) * weight_group;
-        S[j] = 0.0;
-        for (int q = 0; q < weight_group; ++q) S[j] = __dadd_rn(S[j], (double)w[q]);
-        x[j] = 0.0;
-    }
-    // proportional shares with the cap: heads over the cap are fixed at it and the rest is shared again among the others
-    for (;;) {
-        int ncap = 0;
-        double tot = 0.0;
-#pragma unroll
-        for (int j = 0; j < PER; ++j) {
-            ncap += __builtin_popcountll(__builtin_amdgcn_ballot_w64(live[j] && capped[j]));
-            const double add = capped[j] ? 0.0 : S[j];       // (+0.0 leaves the sum as it is, bit for bit)
-            const int m = min(64, n - 64 * j);
-            for (int l = 0; l < m; ++l) tot = __dadd_rn(tot, lane_double(add, l));
-        }
-        const double T = (double)(Bs - (long long)ncap * cap);
-        bool over = false;
-#pragma unroll
-        for (int j = 0; j < PER; ++j)
-            if (live[j] && !capped[j]) {
-                x[j] = has_shares(tot) ? __ddiv_rn(__dmul_rn(T, S[j]), tot) : __ddiv_rn(T, (double)(n - ncap));
-                over = over || x[j] > (double)cap;
-            }
-        if (__builtin_amdgcn_ballot_w64(over) == 0) break;
-#pragma unroll
-        for (int j = 0; j < PER; ++j)
-            if (live[j] && !capped[j] && x[j] > (double)cap) { capped[j] = true; x[j] = (double)cap; }
-    }
-    // floors and fractional parts
-    long long sum = 0;
-#pragma unroll
-    for (int j = 0; j < PER; ++j) {
-        const double fl = floor(x[j]);
-        e[j] = !live[j] ? 0 : capped[j] ? cap : (int)fl;
-        frac[j] = capped[j] ? 0.0 : __dsub_rn(x[j], fl);
-        sum += e[j];
-    }
-    long long left = Bs - wave_sum_ll(sum);
-    // largest remainder, rounds as in allocate_pool
-    while (left != 0) {
-        const bool give = left > 0;
-        const long long want = give ? left : -left;
-        bool el[PER];
-        double key[PER];
-        int rank[PER];
-#pragma unroll
-        for (int j = 0; j < PER; ++j) {
-            el[j] = live[j] && !capped[j] && (give ? e[j] < cap : e[j] > 0);
-            key[j] = el[j] ? frac[j] : (give ? -1.0 : 2.0);
-            rank[j] = 0;
-        }
-#pragma unroll
-        for (int j2 = 0; j2 < PER; ++j2) {
-            const int m = min(64, n - 64 * j2);
-            for (int l = 0; l < m; ++l) {
-                const double o = lane_double(key[j2], l);
-                const int oh = 64 * j2 + l;
-#pragma unroll
-                for (int j = 0; j < PER; ++j) {
-                    const int h = 64 * j + lane;
-                    const bool ahead = give ? (o > frac[j] || (o == frac[j] && oh < h)) : (o < frac[j] || (o == frac[j] && oh > h));
-                    rank[j] += ahead ? 1 : 0;
-                }
-            }
-        }
-        int granted = 0;
-#pragma unroll
-        for (int j = 0; j < PER; ++j) {
-            const bool got = el[j] && rank[j] < want;
-            if (got) e[j] += give ? 1 : -1;
-            granted += __builtin_popcountll(__builtin_amdgcn_ballot_w64(got));
-        }
-        if (granted == 0) break;                    // cannot happen for valid input (n_keep <= L)
-        left = give ? left - granted : left + granted;
-    }
-    // budgets and their exclusive scan; the scan base is the total of the pools before this one
-    long long run = 0;
-    for (int s2 = lane; s2 < seg; s2 += 64) run += (long long)n * n_keep_dev(ratio, cu_seq[s2 + 1] - cu_seq[s2]);
-    run = wave_sum_ll(run);
-#pragma unroll
-    for (int j = 0; j < PER; ++j) {
-        const int b = live[j] ? f + e[j] : 0;
-        long long incl = b;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const long long t = __shfl_up(incl, o, 64);
-            if (lane >= o) incl += t;
-        }
-        if (live[j]) {
-            budgets[(size_t)seg * n + 64 * j + lane] = b;
-            cu_budgets[(size_t)seg * n + 64 * j + lane] = (int32_t)(run + incl - b);
-        }
-        run += __shfl(incl, 63, 64);
-    }
-    if (lane == 0 && seg == n_segments - 1) cu_budgets[(size_t)n_segments * n] = (int32_t)run;
-}
-
-// pool `seg` by the first wave of the workgroup (pools of up to kAllocateWaveHeads heads)
-__device__ __forceinline__ void allocate_small(
-    const int seg, const float* __restrict__ weights, int n_segments, int n, int weight_group, int window,
-    const int32_t* __restrict__ cu_seq, double ratio, double beta,
-    int32_t* __restrict__ budgets, int32_t* __restrict__ cu_budgets)
-{
-    if (threadIdx.x >= 64) return;
-    if (n <= 64) allocate_wave<1>(seg, weights, n_segments, n, weight_group, window, cu_seq, ratio, beta, budgets, cu_budgets);
-    else allocate_wave<kAllocateWaveHeads / 64>(seg, weights, n_segments, n, weight_group, window, cu_seq, ratio, beta, budgets, cu_budgets);
-}
-
 __global__ __launch_bounds__(64) void allocate_small_kernel(
     const float* __restrict__ weights, int n_segments, int n, int weight_group, int window,
     const int32_t* __restrict__ cu_seq, double ratio, double beta,
@@ -396,93 +235,11 @@ __global__ __launch_bounds__(kThreads) void allocate_kernel(
     allocate_pool(smem_raw, blockIdx.x, weights, n_segments, n, weight_group, window, cu_seq, ratio, beta, budgets, cu_budgets);
 }
 
-// Row r of head `head`: the per-range softmax statistics (reference in base-2 units, sum of exp2) of sweep 1 merged
-// into max + log2(sum). The statistics are fetched sixteen ranges at a time, so that the loads overlap instead of
-// forming a chain of memory latencies as long as the number of ranges, and merged as they come (one pass: a running
-// reference and a sum rescaled when the reference rises). The multiply-adds are written out as fused ones: the
-// result does not depend on how this file is compiled.
-__device__ __forceinline__ void merge_row(const float* __restrict__ stats, int nsplit, int rows_pad, int R,
-                                          int head, int r, float* __restrict__ cst)
-{
-    if (r >= rows_pad) return;
-    float out = INFINITY;
-    if (r < R) {
-        const float2* hs = reinterpret_cast<const float2*>(stats) + (size_t)head * nsplit * rows_pad + r;
-        float M = -INFINITY, Z = 0.f;
-        for (int s0 = 0; s0 < nsplit; s0 += 16) {
-            float2 v[16];
-#pragma unroll
-            for (int u = 0; u < 16; ++u) v[u] = hs[(size_t)min(s0 + u, nsplit - 1) * rows_pad];
-            float Mb = M;
-#pragma unroll
-            for (int u = 0; u < 16; ++u)
-                if (s0 + u < nsplit && v[u].y > 0.f) Mb = fmaxf(Mb, v[u].x);
-            if (Mb == -INFINITY) continue;                  // nothing seen in these ranges either
-            Z *= __builtin_amdgcn_exp2f(M - Mb);            // exp2(-inf) = 0 while Z is still 0
-            M = Mb;
-#pragma unroll
-            for (int u = 0; u < 16; ++u)
-                if (s0 + u < nsplit && v[u].y > 0.f) Z = __builtin_fmaf(v[u].y, __builtin_amdgcn_exp2f(v[u].x - M), Z);
-        }
-        out = M + __log2f(Z);
-    }
-    cst[(size_t)head * rows_pad + r] = out;
-}
-
-// Workgroups [0, alloc_blocks) allocate one pool each (alloc_blocks = 0: none), the next tap_blocks evaluate kThreads
-// filter taps each, the others merge kThreads rows each.
-__global__ __launch_bounds__(kThreads) void merge_allocate_kernel(
-    const float* __restrict__ stats, int nsplit, int rows_pad, int R, float* __restrict__ cst, int alloc_blocks,
-    int tap_blocks, ConvFilterJob taps,
-    const float* __restrict__ weights, int n_segments, int n, int weight_group, int window,
-    const int32_t* __restrict__ cu_seq, double ratio, double beta,
-    int32_t* __restrict__ budgets, int32_t* __restrict__ cu_budgets)
-{
-    extern __shared__ unsigned char smem_raw[];
-    if ((int)blockIdx.x < alloc_blocks) {          // uniform over the workgroup
-        if (n <= kAllocateWaveHeads)
-            allocate_small(blockIdx.x, weights, n_segments, n, weight_group, window, cu_seq, ratio, beta, budgets, cu_budgets);
-        else
-            allocate_pool(smem_raw, blockIdx.x, weights, n_segments, n, weight_group, window, cu_seq, ratio, beta, budgets, cu_budgets);
-        return;
-    }
-    if ((int)blockIdx.x < alloc_blocks + tap_blocks) {
-        conv_filter_block(taps, blockIdx.x - alloc_blocks);
-        return;
-    }
-    const int mb = blockIdx.x - alloc_blocks - tap_blocks;
-    const int blocks_per_head = (rows_pad + kThreads - 1) / kThreads;
-    const int head = mb / blocks_per_head;
-    merge_row(stats, nsplit, rows_pad, R, head, (mb - head * blocks_per_head) * kThreads + threadIdx.x, cst);
-}
-
 size_t alloc_smem_bytes(int n) {
     return (size_t)n * (3 * sizeof(double) + 2 * sizeof(int)) + kThreads * sizeof(long long) + sizeof(AllocShared) + 16;
 }
 
 }  // namespace
-
-hipError_t launch_score_merge(const Geom& g, const float* stats, int nsplit, int rows_pad, float* cst,
-                              const AllocateJob* job, const ConvFilterJob* taps, hipStream_t s)
-{
-    static_assert(kConvFilterThreads == kThreads, "the taps share the launch's workgroup size");
-    const int n_heads = g.n_items * g.H_kv;
-    const unsigned merge_blocks = (unsigned)(n_heads * ((rows_pad + kThreads - 1) / kThreads));
-    size_t smem = 0;
-    int alloc_blocks = 0;
-    AllocateJob j{};
-    if (job) {
-        j = *job;
-        smem = j.heads_per_segment > kAllocateWaveHeads ? alloc_smem_bytes(j.heads_per_segment) : 0;
-        if (smem > 64 * 1024) return hipErrorInvalidValue;
-        alloc_blocks = j.n_segments;
-    }
-    const int tap_blocks = taps && taps->h ? taps->blocks_per_item * taps->n_items : 0;
-    hipLaunchKernelGGL(merge_allocate_kernel, dim3(merge_blocks + (unsigned)(alloc_blocks + tap_blocks)), dim3(kThreads), smem, s,
-                       stats, nsplit, rows_pad, g.G * g.W, cst, alloc_blocks, tap_blocks, taps ? *taps : ConvFilterJob{}, j.weights, j.n_segments, j.heads_per_segment,
-                       j.weight_group, g.W, j.cu_seqlens, j.ratio, j.floor_frac, j.budgets, j.cu_budgets);
-    return hipGetLastError();
-}
 
 hipError_t launch_allocate(const Geom& g, const float* weights, int n_segments, int heads_per_segment,
                            int weight_group, const int32_t* cu_seqlens, double ratio, double floor_frac,

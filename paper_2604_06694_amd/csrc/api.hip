@@ -138,8 +138,8 @@ Workspace plan_workspace(const audiokv_params* p, const Batch& b, const int32_t*
     const int nsplit = score_num_splits(p->n_kv_heads, b.n_items, seqlens_host, rows, p->head_dim);
     size_t off = 0;
     w.stats_off = off;
-    // partial row statistics [head][split][rows_pad][2], then the merged per-row constants [head][rows_pad]
-    off += align_up((size_t)n_heads * (rows_pad > 0 ? rows_pad : 1) * (2 * (size_t)nsplit + 1) * sizeof(float), 256);
+    // partial row statistics [head][split][rows_pad][2]
+    off += align_up((size_t)n_heads * (rows_pad > 0 ? rows_pad : 1) * 2 * (size_t)nsplit * sizeof(float), 256);
     w.raw_off = off;
     off += align_up((size_t)b.total_tokens * p->n_kv_heads * sizeof(float), 256);
     w.raw2 = score_needs_second_raw(rows, p->head_dim);     // second row range of a split sweep 2
@@ -496,13 +496,12 @@ int32_t evict_entry(const audiokv_params* params, const void* q_win, const void*
     if (side) helper_lock.lock();
 #define AUDIOKV_MARK(i) do { if (prof) AUDIOKV_HIP(hipEventRecord(g_prof.ev[i], s), "hipEventRecord"); } while (0)
     AUDIOKV_MARK(0);
-    // In line and without stage timing, the allocation and the taps of the smoothing's filter ride along with the launch
-    // that merges the row statistics between the two sweeps (one launch less each on the critical path of a call); with
-    // the caller's log-sum-exp there is no such launch.
+    // In line and without stage timing, the allocation of small pools and the taps of the smoothing's filter ride along with
+    // the first sweep (one launch less each on the critical path of a call).
     const AllocateJob alloc_job{weights_dev, n_seg, hps, 1, cu_seqlens_dev, ratio, (double)params->floor_frac,
                                 budgets_dev, cu_budgets_dev};
-    const bool ride = !side && !prof && !lse_dev;
-    const bool ride_taps = ride && filters.taps.h;
+    const bool ride = !side && !prof && hps <= kAllocateWaveHeads;
+    const bool ride_taps = !side && !prof && filters.taps.h;
     if (!side && !ride) {
         // (stage timing wants one kernel per interval: then, too, the allocation stays in line)
         AUDIOKV_HIP(launch_allocate(g, weights_dev, n_seg, hps, 1, cu_seqlens_dev, ratio, (double)params->floor_frac,

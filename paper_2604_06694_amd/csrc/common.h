@@ -53,18 +53,12 @@ inline int blocks_per_part(long long wanted, long long n) {
 // ---- launchers (defined in the .hip files, called from api.hip) ------------
 
 constexpr int kAllocateWaveHeads = 128;    // pools up to this size are allocated by one wave
-// Arguments of launch_allocate, for callers that let the allocation ride along with another small launch.
+// Arguments of launch_allocate, for callers that let the allocation ride along with another launch.
 struct AllocateJob {
     const float* weights; int n_segments, heads_per_segment, weight_group; const int32_t* cu_seqlens;
     double ratio, floor_frac; int32_t* budgets; int32_t* cu_budgets;
 };
 struct ConvFilterJob;      // taps of the smoothing's filter (conv_filter.h)
-// Merge of the per-range row statistics of sweep 1 (stats: [head][nsplit][rows_pad][2]) into one constant per row
-// (cst: [head][rows_pad], max + log2(sum); +inf for rows >= R). With `job` and `taps`, the same launch also runs the
-// budget allocation and evaluates the smoothing's filter in extra workgroups: none depends on another, and each launch
-// costs more than any one's work.
-hipError_t launch_score_merge(const Geom& g, const float* stats, int nsplit, int rows_pad, float* cst,
-                              const AllocateJob* job, const ConvFilterJob* taps, hipStream_t s);
 
 // Number of key-range splits per head used by the score kernels; a pure
 // function of the batch so that the workspace query and the launch agree.
@@ -74,8 +68,8 @@ int score_padded_rows(int rows, int D);
 
 // between_sweeps: optional event recorded on `s` after the first sweep (timing aid), or nullptr.
 // lse: optional fp32 [items][H_q][W] natural-log softmax denominators of the window rows; given, sweep 1 is skipped.
-// ride_along, ride_taps: optional allocation and filter taps to run in the launch that merges the row statistics
-// (ignored with lse, where there is no such launch: the caller launches them itself).
+// ride_along, ride_taps: optional allocation (pools of at most kAllocateWaveHeads heads) and filter taps to run in extra
+// workgroups of the first sweep.
 hipError_t launch_score(const Geom& g, const void* q_win, const void* k, const int32_t* cu_seqlens,
                         const int32_t* seqlens_host, float* stats_ws, float* raw_out, hipStream_t s,
                         hipEvent_t between_sweeps = nullptr, const float* lse = nullptr,

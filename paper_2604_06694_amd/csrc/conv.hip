@@ -358,7 +358,10 @@ __global__ __launch_bounds__(kJoinThreads) void conv_join_kernel(
     }
 }
 
-__global__ __launch_bounds__(kConvFilterThreads) void conv_filter_kernel(ConvFilterJob job) { conv_filter_block(job, blockIdx.x); }
+constexpr int kFilterThreads = 256;
+__global__ __launch_bounds__(kFilterThreads) void conv_filter_kernel(ConvFilterJob job, int per_item) {
+    conv_filter_block(job, blockIdx.x, per_item, kFilterThreads);
+}
 
 // Workgroups are numbered in one dimension, those of a head next to each other: the second and third dimension of a grid
 // end at 65535, and a batch may hold more heads than that.
@@ -406,8 +409,8 @@ hipError_t launch_spectra(const Geom& g, const ConvCall& c, hipStream_t s) {
 }  // namespace
 
 hipError_t launch_conv_filter(const Geom& g, const ConvCall& c, hipStream_t s) {
-    hipLaunchKernelGGL(conv_filter_kernel, dim3((unsigned)(c.job.blocks_per_item * c.job.n_items)), dim3(kConvFilterThreads),
-                       0, s, c.job);
+    const int per_item = c.job.blocks_per_item(kFilterThreads);
+    hipLaunchKernelGGL(conv_filter_kernel, dim3((unsigned)(per_item * c.job.n_items)), dim3(kFilterThreads), 0, s, c.job, per_item);
     if (!c.spec) return hipGetLastError();
     switch (c.log_c) {
         case 10: return launch_spectra<10>(g, c, s);

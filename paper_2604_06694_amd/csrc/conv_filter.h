@@ -14,9 +14,10 @@ struct ConvFilterJob {
     int n_items;
     double cutoff_frac;
     int taper_bins;
-    int blocks_per_item;      // workgroups of kConvFilterThreads, one tap per thread (in a call of very many items more)
+    int max_length;           // of the items that have taps
+    // workgroups of `threads`, one tap per thread (in a call of very many items more)
+    int blocks_per_item(int threads) const { return blocks_per_part((max_length + threads - 1) / threads, n_items); }
 };
-constexpr int kConvFilterThreads = 256;
 
 struct SmoothFilters {
     bool long_work = false;
@@ -74,14 +75,14 @@ __device__ __forceinline__ int conv_owner(const int32_t* __restrict__ cu_seq, in
     return item;
 }
 
-// workgroup `block` of blocks_per_item * n_items
-__device__ __forceinline__ void conv_filter_block(const ConvFilterJob& job, int block) {
-    const int item = block / job.blocks_per_item, part = block - item * job.blocks_per_item;
+// workgroup `block` of per_item * n_items, of `threads` threads each
+__device__ __forceinline__ void conv_filter_block(const ConvFilterJob& job, int block, int per_item, int threads) {
+    const int item = block / per_item, part = block - item * per_item;
     const int L = job.cu_seqlens[item + 1] - job.cu_seqlens[item];
     if (!conv_item(job, L) || conv_owner(job.cu_seqlens, item, L) != item) return;
     const int kstar = conv_kstar(job.cutoff_frac, L);
     float* h = job.h + item * job.item_stride;
-    for (int n = part * kConvFilterThreads + (int)threadIdx.x; n < L; n += job.blocks_per_item * kConvFilterThreads)
+    for (int n = part * threads + (int)threadIdx.x; n < L; n += per_item * threads)
         h[n] = low_pass_tap(n, L, kstar, job.taper_bins);
 }
 

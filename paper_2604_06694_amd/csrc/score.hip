@@ -121,25 +121,26 @@ hipError_t launch_score(const Geom& g, const void* q_win, const void* k, const i
     Plan p1;
     const int rows = g.G * g.W;
     if (!make_plan(rows, g.D, 1, &p1)) return hipErrorInvalidValue;
-    const int n_heads = g.n_items * g.H_kv;
     const int rows_pad = score_padded_rows(rows, g.D);
     if (rows_pad == 0) return hipErrorInvalidValue;
     const int ns1 = num_splits(p1, g.H_kv, g.n_items, seqlens_host, g.D);
-    float* cst = stats_ws + (size_t)n_heads * ns1 * rows_pad * 2;
+    score_detail::SweepArgs args{q_win, k, cu_seqlens, 0, rows_pad, 0, stats_ws, ns1, lse, raw_out, ride_along, ride_taps};
     auto sweep = [&](int which, const Plan& p, int ns, int row_base, float* raw) -> hipError_t {
+        args.nsplit = ns;
+        args.row_base = row_base;
+        args.raw = raw;
+        hipError_t e = hipErrorInvalidValue;
         switch (g.D) {
-            case 64:  return launch_score_d64(which, g, p.NB, p.WR, q_win, k, cu_seqlens, ns, rows_pad, row_base, stats_ws, cst, raw, s, lse);
-            case 128: return launch_score_d128(which, g, p.NB, p.WR, q_win, k, cu_seqlens, ns, rows_pad, row_base, stats_ws, cst, raw, s, lse);
-            case 256: return launch_score_d256(which, g, p.NB, p.WR, q_win, k, cu_seqlens, ns, rows_pad, row_base, stats_ws, cst, raw, s, lse);
+            case 64:  e = launch_score_d64(which, g, p.NB, p.WR, args, s); break;
+            case 128: e = launch_score_d128(which, g, p.NB, p.WR, args, s); break;
+            case 256: e = launch_score_d256(which, g, p.NB, p.WR, args, s); break;
         }
-        return hipErrorInvalidValue;
+        args.alloc = nullptr;                       // they have gone along
+        args.taps = nullptr;
+        return e;
     };
-    hipError_t e = sweep(1, p1, ns1, 0, raw_out);
+    hipError_t e = lse ? hipSuccess : sweep(1, p1, ns1, 0, raw_out);
     if (e != hipSuccess) return e;
-    if (!lse) {
-        e = launch_score_merge(g, stats_ws, ns1, rows_pad, cst, ride_along, ride_taps, s);
-        if (e != hipSuccess) return e;
-    }
     if (between_sweeps) {
         e = hipEventRecord(between_sweeps, s);
         if (e != hipSuccess) return e;

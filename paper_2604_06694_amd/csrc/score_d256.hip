@@ -3,16 +3,14 @@
 
 namespace audiokv {
 
-hipError_t launch_score_d256(int which, const Geom& g, int NB, int WR, const void* q_win, const void* k,
-        const int32_t* cu_seq, int nsplit, int rows_pad, int row_base, float* stats, float* cst, float* raw,
-        hipStream_t s, const float* lse)
+hipError_t launch_score_d256(int which, const Geom& g, int NB, int WR, const score_detail::SweepArgs& a, hipStream_t s)
 {
     using namespace score_detail;
-    if (NB == 1 && WR == 1) return launch_sweep<256, 1, 1>(which, g, q_win, k, cu_seq, nsplit, rows_pad, row_base, stats, cst, raw, s, lse);
-    if (NB == 1 && WR == 2) return launch_sweep<256, 1, 2>(which, g, q_win, k, cu_seq, nsplit, rows_pad, row_base, stats, cst, raw, s, lse);
-    if (NB == 1 && WR == 4) return launch_sweep<256, 1, 4>(which, g, q_win, k, cu_seq, nsplit, rows_pad, row_base, stats, cst, raw, s, lse);
-    if (NB == 1 && WR == 7) return launch_sweep<256, 1, 7>(which, g, q_win, k, cu_seq, nsplit, rows_pad, row_base, stats, cst, raw, s, lse);
-    if (NB == 1 && WR == 8) return launch_sweep<256, 1, 8>(which, g, q_win, k, cu_seq, nsplit, rows_pad, row_base, stats, cst, raw, s, lse);
+    if (NB == 1 && WR == 1) return launch_sweep<256, 1, 1>(which, g, a, s);
+    if (NB == 1 && WR == 2) return launch_sweep<256, 1, 2>(which, g, a, s);
+    if (NB == 1 && WR == 4) return launch_sweep<256, 1, 4>(which, g, a, s);
+    if (NB == 1 && WR == 7) return launch_sweep<256, 1, 7>(which, g, a, s);
+    if (NB == 1 && WR == 8) return launch_sweep<256, 1, 8>(which, g, a, s);
     return hipErrorInvalidValue;
 }
 

@@ -7,10 +7,10 @@
 // The contraction (G*W rows) x (L keys) x d is dense, so it runs on bf16 MFMA
 // (v_mfma_f32_32x32x16_bf16, fp32 accumulate). A softmax row needs its max and
 // its sum over ALL keys before any column sum can be formed, so the work is
-// two sweeps over K with the same tiling, and a tiny merge in between:
+// two sweeps over K with the same tiling:
 //   sweep 1: logits tile -> running (max, sum of exp) per row, per key range
-//   merge  : per row, max + log2(sum) over the key ranges
-//   sweep 2: logits tile -> exp2(z - max - log2 sum) summed over rows, per key
+//   sweep 2: first, per row, max + log2(sum) over the key ranges;
+//            logits tile -> exp2(z - max - log2 sum) summed over rows, per key
 // Keeping logits instead would cost G*W*4 bytes per token and head against the
 // d*2 bytes of the key itself, so recomputing is the cheaper choice.
 //
@@ -48,7 +48,9 @@
 #include <type_traits>
 #include <utility>
 
+#include "allocate_wave.h"
 #include "common.h"
+#include "conv_filter.h"
 
 #ifndef AUDIOKV_SCORE_KB
 #define AUDIOKV_SCORE_KB 2
@@ -154,16 +156,98 @@ __device__ __forceinline__ void quad_transpose(bf16x8& p0, bf16x8& p1, bf16x8& p
     p3 = __builtin_bit_cast(bf16x8, d);
 }
 
+// Work that the first sweep of a call takes along in extra workgroups after its own: nothing in it depends on the scores, and
+// a launch costs more than all of it.
+struct RideAlong {
+    int alloc_blocks = 0, tap_blocks = 0, taps_per_item = 1;    // workgroups; the latter per item
+    int window = 0;
+    AllocateJob alloc{};                                        // one wave per pool
+    ConvFilterJob taps{};
+};
+__device__ __forceinline__ void ride_along(const RideAlong& ride, int block) {
+    if (block >= ride.alloc_blocks) {
+        conv_filter_block(ride.taps, block - ride.alloc_blocks, ride.taps_per_item, blockDim.x);
+        return;
+    }
+    const AllocateJob& j = ride.alloc;
+    const int seg = block * (int)(blockDim.x >> 6) + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    if (seg < j.n_segments)
+        allocate_small(seg, j.weights, j.n_segments, j.heads_per_segment, j.weight_group, ride.window, j.cu_seqlens, j.ratio, j.floor_frac,
+                       j.budgets, j.cu_budgets);
+}
+
+// Row r of head `head`: the per-range softmax statistics (reference in base-2 units, sum of exp2) of sweep 1 merged into
+// max + log2(sum), one pass with a running reference and a sum rescaled when the reference rises, sixteen ranges at a time.
+// Every workgroup of sweep 2 merges the rows it needs for itself, N ranges' loads in flight beside those of its queries and
+// first keys, instead of reading constants that a launch in between prepared: that launch took 3.9 to 5.5 us, most of it spent on
+// starting and draining, and the host's share of it (2.4 us), where this adds 1.2 us to sweep 2 (four heads of 2048, 32 ranges of
+// 224 rows), 2.9 (13577, 54 ranges of 256) and, the most there is, 4 (32768, 64 ranges of 448). Whole calls on one layer of
+// 2048 30.8 -> 28.7 us, 13577 63.5 -> 61.1, 32768 the same; 28 layers of 8192 280 -> 277; with the log-sum-exp given, where two
+// launches fall away, 13577 53.3 -> 45.2. (64 ranges in flight spill registers: 32.2 us instead of 27.9 at 32768.)
+// HALVES: the two halves of a wave share a row (the caller's r is the same in both) and take the batches of sixteen in turn.
+template <int N, bool HALVES>
+__device__ __forceinline__ float merged_row(const float* __restrict__ stats, int nsplit, int rows_pad, int head, int r, int half) {
+    const float2* hs = reinterpret_cast<const float2*>(stats) + (size_t)head * nsplit * rows_pad + r;
+    const int first = HALVES ? half * 16 : 0;
+    constexpr int kStep = HALVES ? 2 * N : N;
+    static_assert(!HALVES || N == 16, "batches in turn");
+    float M = -INFINITY, Z = 0.f;
+    // z and its reference after one more batch, the terms added in order
+    auto add = [](float z, float from, float to, const float (&e)[16], const float2* v) {
+        z *= fast_exp2(from - to);                          // exp2(-inf) = 0 while z is still 0
+#pragma unroll
+        for (int u = 0; u < 16; ++u) z = __builtin_fmaf(v[u].y, e[u], z);
+        return z;
+    };
+    for (int s0 = 0; s0 < nsplit; s0 += kStep) {
+        float2 v[N];
+#pragma unroll
+        for (int u = 0; u < N; ++u) v[u] = hs[(size_t)min(s0 + first + u, nsplit - 1) * rows_pad];
+#pragma unroll
+        for (int b = 0; b < N; b += 16) {
+            float top = -INFINITY;
+#pragma unroll
+            for (int u = b; u < b + 16; ++u) {
+                const bool counts = s0 + first + u < nsplit && v[u].y > 0.f;   // (a term of nothing leaves the sum as it is)
+                v[u].x = counts ? v[u].x : -INFINITY;
+                v[u].y = counts ? v[u].y : 0.f;
+                top = fmaxf(top, v[u].x);
+            }
+            const float other = HALVES ? __shfl_xor(top, 32, 64) : 0.f;
+            const float M1 = fmaxf(M, HALVES && half ? other : top), M2 = HALVES ? fmaxf(M1, half ? top : other) : M1;
+            const float mine = HALVES && half ? M2 : M1, ref = mine == -INFINITY ? 0.f : mine;
+            float e[16];
+#pragma unroll
+            for (int u = 0; u < 16; ++u) e[u] = fast_exp2(v[b + u].x - ref);
+            // (nothing seen in these ranges either: the sum stays)
+            Z = M1 == -INFINITY ? Z : add(Z, M, M1, e, v + b);
+            if constexpr (HALVES) {
+                Z = __shfl(Z, (int)threadIdx.x & 31, 64);   // the lower half's
+                Z = M2 == -INFINITY ? Z : add(Z, M1, M2, e, v + b);
+                Z = __shfl(Z, ((int)threadIdx.x & 31) + 32, 64);
+            }
+            M = M2;
+        }
+    }
+    return M + __log2f(Z);
+}
+
 template <int D, int NB, int WR, bool SWEEP2>
 __global__ __launch_bounds__(64 * (WR + 1), (NB == 1 && D <= 128) ? 4 : 2) void score_kernel(
     Geom g, const __bf16* __restrict__ q_win, const __bf16* __restrict__ k,
-    const int32_t* __restrict__ cu_seq, int nsplit,
-    int rows_pad,                     // row pitch of stats / cst (>= ROWS: the two sweeps may tile the rows differently)
+    const int32_t* __restrict__ cu_seq, int n_wg, int nsplit,
+    int rows_pad,                     // row pitch of stats (>= ROWS: the two sweeps may tile the rows differently)
     int row_base,                     // first window row of this launch (sweep 2 may cover the rows in two launches)
-    float* __restrict__ stats,        // sweep 1 out: [head][split][rows_pad][2] = (max in base-2 units, sum of exp2)
-    const float* __restrict__ cst,    // sweep 2 in : [head][rows_pad] = max + log2(sum), +inf for padded rows
-    float* __restrict__ raw)          // sweep 2 out, packed like scores
+    float* __restrict__ stats,        // [head][split][rows_pad][2] = (max in base-2 units, sum of exp2): sweep 1 out, sweep 2 in
+    int stat_splits,                  // sweep 2: ranges per head in stats
+    const float* __restrict__ lse,    // sweep 2: instead of stats, [item][H_q][W] natural logs of the softmax denominators
+    float* __restrict__ raw,          // sweep 2 out, packed like scores
+    RideAlong ride)                   // in the workgroups from n_wg on
 {
+    if ((int)blockIdx.x >= n_wg) {                    // uniform
+        ride_along(ride, (int)blockIdx.x - n_wg);
+        return;
+    }
     using T = Tile<D, NB, WR>;
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     float* lds_cols = reinterpret_cast<float*>(lds + T::STAGES * T::LDS_K);
@@ -174,7 +258,7 @@ __global__ __launch_bounds__(64 * (WR + 1), (NB == 1 && D <= 128) ? 4 : 2) void 
     // shared by neighbouring splits) are fetched from HBM by one L2 only.
     int head, split;
     {
-        const int n_heads = gridDim.x / nsplit;
+        const int n_heads = n_wg / nsplit;
         const int full = n_heads & ~7;                  // heads that fill whole groups of 8
         const int bid = blockIdx.x;
         if (bid < full * nsplit) {
@@ -182,9 +266,16 @@ __global__ __launch_bounds__(64 * (WR + 1), (NB == 1 && D <= 128) ? 4 : 2) void 
             split = q % nsplit;
             head = (q / nsplit) * 8 + (bid & 7);
         } else {
-            const int r = bid - full * nsplit;
-            head = full + r / nsplit;
-            split = r - (r / nsplit) * nsplit;
+            const int r = bid - full * nsplit, rem = n_heads - full;
+            // one, two or four heads: a head on eight, four or two XCDs of its own
+            const int per = (rem & (rem - 1)) == 0 ? 8 / rem : 1;
+            if (per > 1 && nsplit % per == 0) {
+                head = full + (r & 7) / per;
+                split = (r >> 3) * per + (r & 7) % per;
+            } else {
+                head = full + r / nsplit;
+                split = r - (r / nsplit) * nsplit;
+            }
         }
     }
     const int item = head / g.H_kv, h = head - item * g.H_kv;
@@ -330,8 +421,17 @@ __global__ __launch_bounds__(64 * (WR + 1), (NB == 1 && D <= 128) ? 4 : 2) void 
             for (int kq = 0; kq < T::KK; kq += 4) quad_transpose(qf[rb][kq], qf[rb][kq + 1], qf[rb][kq + 2], qf[rb][kq + 3], lane);
     }
     if (SWEEP2)
-        for (int r = tid; r < T::ROWS; r += 64 * WR)
-            lds_rc[r] = row_base + r < rows_pad ? cst[(size_t)head * rows_pad + row_base + r] : INFINITY;
+        // row constants: max + log2(sum); +inf for padded rows, whose exp2 then vanishes
+        for (int i = NB == 1 ? l32 : lane; i < NB * 32; i += 64) {
+            const int r = min(rowg0 + i, R - 1);
+            float out;
+            if (lse)                      // rows of a head follow one another: window row r % W of query head r / W of the group
+                out = lse[((size_t)item * g.H_q + (size_t)h * g.G) * g.W + r] * 1.44269504088896340736f;
+            else if constexpr (NB == 1) out = merged_row<16, true>(stats, stat_splits, rows_pad, head, r, g2);
+            else if (stat_splits <= 16) out = merged_row<16, false>(stats, stat_splits, rows_pad, head, r, 0);
+            else out = merged_row<32, false>(stats, stat_splits, rows_pad, head, r, 0);
+            lds_rc[row0 + i] = rowg0 + i < R ? out : INFINITY;
+        }
 
     // sweep 1: reference (base-2 units: logit * c) and sum of exp2(logit * c - reference) for row
     // row0 + rb*32 + l32 over this lane's keys. The reference is a logit that the row has met, not its running
@@ -628,43 +728,32 @@ __global__ __launch_bounds__(64 * (WR + 1), (NB == 1 && D <= 128) ? 4 : 2) void 
     }
 }
 
-// per row: reference + log2(sum) over the key ranges (fixed order); +inf for padded rows, whose exp2 then vanishes.
-// Row constants from log-sum-exp values that the caller already has (natural log of the softmax denominator of
-// every window row, as an attention kernel that ran the window's queries returns them): replaces sweep 1.
-static __global__ __launch_bounds__(64) void score_cst_from_lse_kernel(Geom g, const float* __restrict__ lse,
-                                                                       int rows_pad, float* __restrict__ cst)
-{
-    const int blocks_per_head = (rows_pad + 63) / 64;
-    const int head = blockIdx.x / blocks_per_head;
-    const int r = (blockIdx.x - head * blocks_per_head) * 64 + threadIdx.x;
-    if (r >= rows_pad) return;
-    const int item = head / g.H_kv, h = head - item * g.H_kv;
-    float out = INFINITY;
-    if (r < g.G * g.W) {
-        const int qh = r / g.W, wrow = r - qh * g.W;
-        out = lse[((size_t)item * g.H_q + (size_t)h * g.G + qh) * g.W + wrow] * 1.44269504088896340736f;
-    }
-    cst[(size_t)head * rows_pad + r] = out;
-}
-
 // raw += raw_b: the column sums of the second row range of a split sweep 2 (fixed order: deterministic)
 static __global__ __launch_bounds__(256) void score_add_kernel(float* __restrict__ raw, const float* __restrict__ raw_b, size_t n)
 {
     for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256) raw[i] += raw_b[i];
 }
 
-// which = 1: per-range row statistics into stats (sweep 1; the caller merges them into cst with launch_score_merge),
-//            or the conversion of supplied log-sum-exp values straight into cst;
-// which = 2: column sums (sweep 2) from the cst at cst_in. The two may use different (NB, WR) tilings and key-range
-// counts: they only share the row pitch rows_pad of the statistics.
+// What a sweep works on. The two sweeps may use different (NB, WR) tilings and key-range counts: they only share the row pitch
+// rows_pad of the statistics.
+struct SweepArgs {
+    const void* q_win;
+    const void* k;
+    const int32_t* cu_seq;
+    int nsplit, rows_pad, row_base;
+    float* stats;
+    int stat_splits;
+    const float* lse;
+    float* raw;
+    const AllocateJob* alloc;      // these two ride along, if given
+    const ConvFilterJob* taps;
+};
+
+// which = 1: per-range row statistics into stats; which = 2: column sums from stats or lse into raw
 template <int D, int NB, int WR>
-hipError_t launch_sweep(int which, const Geom& g, const void* q_win, const void* k, const int32_t* cu_seq,
-                        int nsplit, int rows_pad, int row_base, float* stats, float* cst, float* raw, hipStream_t s,
-                        const float* lse)
+hipError_t launch_sweep(int which, const Geom& g, const SweepArgs& a, hipStream_t s)
 {
     using T = Tile<D, NB, WR>;
-    const int n_heads = g.n_items * g.H_kv;
-    const dim3 grid((unsigned)(n_heads * nsplit));
     static std::atomic<bool> attr_set{false};
     if (!attr_set && T::LDS_BYTES > 48 * 1024) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(score_kernel<D, NB, WR, false>),
@@ -675,34 +764,33 @@ hipError_t launch_sweep(int which, const Geom& g, const void* q_win, const void*
         if (e != hipSuccess) return e;
         attr_set = true;
     }
-    if (which == 1) {
-        const unsigned merge_blocks = (unsigned)(n_heads * ((rows_pad + 63) / 64));
-        if (lse) {
-            hipLaunchKernelGGL(score_cst_from_lse_kernel, dim3(merge_blocks), dim3(64), 0, s, g, lse, rows_pad, cst);
-        } else {
-            hipLaunchKernelGGL((score_kernel<D, NB, WR, false>), grid, dim3(T::THREADS), T::LDS_BYTES, s, g,
-                               (const __bf16*)q_win, (const __bf16*)k, cu_seq, nsplit, rows_pad, 0, stats,
-                               (const float*)nullptr, raw);
-        }
-    } else {
-        hipLaunchKernelGGL((score_kernel<D, NB, WR, true>), grid, dim3(T::THREADS), T::LDS_BYTES, s, g,
-                           (const __bf16*)q_win, (const __bf16*)k, cu_seq, nsplit, rows_pad, row_base, (float*)nullptr,
-                           (const float*)cst, raw);
+    RideAlong ride;
+    ride.window = g.W;
+    if (a.alloc) {
+        ride.alloc = *a.alloc;
+        ride.alloc_blocks = (ride.alloc.n_segments + WR) / (WR + 1);
     }
+    if (a.taps) {
+        ride.taps = *a.taps;
+        ride.taps_per_item = ride.taps.blocks_per_item(T::THREADS);
+        ride.tap_blocks = ride.taps_per_item * ride.taps.n_items;
+    }
+    const int n_wg = g.n_items * g.H_kv * a.nsplit;
+    const dim3 grid((unsigned)(n_wg + ride.alloc_blocks + ride.tap_blocks));
+    if (which == 1)
+        hipLaunchKernelGGL((score_kernel<D, NB, WR, false>), grid, dim3(T::THREADS), T::LDS_BYTES, s, g, (const __bf16*)a.q_win,
+                           (const __bf16*)a.k, a.cu_seq, n_wg, a.nsplit, a.rows_pad, 0, a.stats, 0, (const float*)nullptr, a.raw, ride);
+    else
+        hipLaunchKernelGGL((score_kernel<D, NB, WR, true>), grid, dim3(T::THREADS), T::LDS_BYTES, s, g, (const __bf16*)a.q_win,
+                           (const __bf16*)a.k, a.cu_seq, n_wg, a.nsplit, a.rows_pad, a.row_base, a.stats, a.stat_splits, a.lse, a.raw, ride);
     return hipGetLastError();
 }
 
 }  // namespace score_detail
 
 // one translation unit per head_dim keeps the build parallel
-hipError_t launch_score_d64(int which, const Geom& g, int NB, int WR, const void* q_win, const void* k,
-        const int32_t* cu_seq, int nsplit, int rows_pad, int row_base, float* stats, float* cst, float* raw,
-        hipStream_t s, const float* lse);
-hipError_t launch_score_d128(int which, const Geom& g, int NB, int WR, const void* q_win, const void* k,
-        const int32_t* cu_seq, int nsplit, int rows_pad, int row_base, float* stats, float* cst, float* raw,
-        hipStream_t s, const float* lse);
-hipError_t launch_score_d256(int which, const Geom& g, int NB, int WR, const void* q_win, const void* k,
-        const int32_t* cu_seq, int nsplit, int rows_pad, int row_base, float* stats, float* cst, float* raw,
-        hipStream_t s, const float* lse);
+hipError_t launch_score_d64(int which, const Geom& g, int NB, int WR, const score_detail::SweepArgs& a, hipStream_t s);
+hipError_t launch_score_d128(int which, const Geom& g, int NB, int WR, const score_detail::SweepArgs& a, hipStream_t s);
+hipError_t launch_score_d256(int which, const Geom& g, int NB, int WR, const score_detail::SweepArgs& a, hipStream_t s);
 
 }  // namespace audiokv

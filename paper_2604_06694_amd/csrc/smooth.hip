@@ -1241,7 +1241,7 @@ SmoothPlan plan_smooth(const Geom& g, const int32_t* cu_seqlens, const int32_t* 
     c.job.n_items = n_items;
     c.job.cutoff_frac = cutoff_frac;
     c.job.taper_bins = g.taper_bins;
-    c.job.blocks_per_item = blocks_per_part((longest + kConvFilterThreads - 1) / kConvFilterThreads, n_items);
+    c.job.max_length = longest;
     // Lengths shared by more than eight heads: their filter is transformed once, by a launch of its own, instead of by
     // every workgroup for itself (a third transform beside the two that it runs anyway).
     bool equal = true;
