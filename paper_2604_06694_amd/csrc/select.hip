@@ -1,29 +1,41 @@
 // Stage 4: per-head top-k with a forced window tail (paper Sec. 1, Solution 2:
 // Top-K selection on the importance scores; window w of Sec. 3.1 Eq. 1).
 //
-// One workgroup per head. Scores become order-preserving 32-bit keys held in
-// registers (token t + NT e in register e of thread t: coalesced loads). The
-// extremes of the keys give their range; a histogram of 2048 equal parts of the
-// range, counted in LDS, gives the part that the threshold lies in. If it holds
-// more than 64 candidates, it is divided in the same way again, and once its
-// keys are all equal, by token index (ties are kept in index order, so key and
-// index together order the candidates strictly). The last candidates, 64 at
-// most, are ranked against each other by every wave for itself, which gives the
-// threshold as a key T and an index X: a token stays if its key is larger than
-// T, or equal to T and its index at most X. For a fixed register the lanes of a
-// wave hold 64 consecutive tokens, so one lane mask gives every (register, wave)
-// chunk its count, a scan over the chunks their output offsets, and every kept
-// token computes its own ascending output slot from the offset and its rank in
-// the lane mask. Integer-only (counts and integer adds in any order): bit-exact.
+// One workgroup per head, token t + NT e in register e of thread t (coalesced
+// loads). A histogram counted in LDS finds the part of the scores' range that
+// the threshold lies in: parts of equal width over two standard deviations to
+// either side of the mean (to the largest or smallest score if the budget asks
+// for a few of the tokens or for nearly all), which the threshold of a share in
+// between rarely leaves and where no part holds many tokens, whatever the tails
+// are like. The candidates in that part, 64 at most, are ranked against each
+// other by every wave for itself, by score and, among equals, by index (ties
+// are kept in index order). That gives the threshold as a score T and an index
+// X: a token stays if its score is larger than T, or equal to T and its index
+// at most X. For a fixed register the lanes of a wave hold 64 consecutive
+// tokens, so one lane mask gives every (register, wave) chunk its count, a scan
+// over the chunks their output offsets, and every kept token computes its own
+// ascending output slot from the offset and its rank in the lane mask.
 //
-// What bounds it is the chain of one head: the loads of up to 128 KB by one CU
-// and six barriers. Rounds of 2048 parts over the range that is there take the
-// place of one counting pass per bit (short heads) and of pivots from a sample
-// (long ones). Four heads of 2048 tokens 10.6 -> 4.2 us, 8192 12.7 -> 6.3, 16384
-// 14.5 -> 9.0, 32768 21.9 -> 15.2; 112 heads of 16384 17.6 -> 10.9. Two, four or
-// eight workgroups per head that each find the threshold and write a part gain
-// nothing with four heads (14.8 us at 32768, 8.4 at 16384) and lose with 112
-// (11.7 and more): every one of them has to load the whole head.
+// More than 64 candidates in the part, and scores that are not finite: the
+// general search. Scores become order-preserving 32-bit keys, and the keys'
+// range is divided into 2048 parts, the part with the threshold again, and
+// once its keys are all equal, the token indices: key and index together order
+// the candidates strictly, so the rounds end. Both ways compare and count only
+// (the mean and the deviation choose where the parts lie, nothing else): the
+// result is exact, and the same whichever way it was found.
+//
+// What bounds it is the chain of one head: the loads of up to 128 KB by one CU,
+// five barriers, the adds of the histogram and the stores. Keys of float scores
+// that cross zero, as smoothed ones do, leave the bulk of the tokens few parts
+// of their range, and the general search alone took a second round for nearly
+// every head. Smoothed scores, general search -> this: four heads of 2048 tokens
+// 5.1 -> 4.4 us, 13577 12.5 -> 9.1, 32768 20.8 -> 15.5; 112 heads of 8192 10.4 ->
+// 9.7, 32768 22.9 -> 18.7; 16 ragged heads 17.0 -> 13.2. Normal scores, which need
+// one round either way: four heads of 32768 15.7 -> 13.5. Scores of a few dozen
+// values only, which go to the general search after all: 32.5 -> 35.5.
+// Two, four or eight workgroups per head that each find the threshold and write
+// a part gained nothing with four heads and lost with 112: every one of them
+// has to load the whole head.
 #include "common.h"
 
 namespace audiokv {
@@ -37,6 +49,11 @@ constexpr int kSelWaves = kSelThreads / 64;
 __device__ __forceinline__ uint32_t order_key(float f) {
     const uint32_t u = __float_as_uint(f + 0.0f);
     return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+}
+
+// its inverse
+__device__ __forceinline__ float key_value(uint32_t key) {
+    return __uint_as_float((key & 0x80000000u) ? key ^ 0x80000000u : ~key);
 }
 
 __device__ __forceinline__ int wave_sum(int v) {
@@ -74,6 +91,27 @@ __device__ __forceinline__ void block_exscan2(int a, int b, int* slots /* 2*kSel
     eb = pb + ib - b;
 }
 
+// Largest value over the lanes of a full wave, in lane 63 (the sum likewise)
+#define AUDIOKV_DPP_F(x, ctrl, rows, none) \
+    __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(none), __float_as_int(x), ctrl, rows, 0xf, false))
+#define AUDIOKV_WAVE_FOLD(op, x, none)                      \
+    do {                                                    \
+        x = op(x, AUDIOKV_DPP_F(x, 0x111, 0xf, none));      \
+        x = op(x, AUDIOKV_DPP_F(x, 0x112, 0xf, none));      \
+        x = op(x, AUDIOKV_DPP_F(x, 0x114, 0xf, none));      \
+        x = op(x, AUDIOKV_DPP_F(x, 0x118, 0xf, none));      \
+        x = op(x, AUDIOKV_DPP_F(x, 0x142, 0xa, none));      \
+        x = op(x, AUDIOKV_DPP_F(x, 0x143, 0xc, none));      \
+    } while (0)
+__device__ __forceinline__ float plus(float a, float b) { return a + b; }
+__device__ __forceinline__ float wave_sum63(float x) { AUDIOKV_WAVE_FOLD(plus, x, 0.f); return x; }
+__device__ __forceinline__ float wave_max63(float x) { AUDIOKV_WAVE_FOLD(fmaxf, x, -INFINITY); return x; }
+__device__ __forceinline__ float lane_float(float x, int lane) {           // uniform lane
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), lane));
+}
+#undef AUDIOKV_WAVE_FOLD
+#undef AUDIOKV_DPP_F
+
 constexpr int kCompact = 8;          // undecided keys per thread once the streaming kernel has narrowed the candidates down
 constexpr int kDigitBits = 11, kBins = 1 << kDigitBits;   // bins of one histogram round
 constexpr int kLast = 64;            // candidates that one wave ranks against each other
@@ -108,12 +146,17 @@ __global__ __launch_bounds__(NT) void select_kernel(
     const int32_t* __restrict__ cu_b, const int32_t* __restrict__ cu_seq, int32_t* __restrict__ indices)
 {
     constexpr int NW = NT / 64;
-    constexpr int kPer = kBins / NT;                 // bins per thread in the scan
+    constexpr int kFine = EPT * NT <= 2048 ? 2048 : EPT * NT <= 16384 ? 4096 : 8192;    // parts of the first division
+    constexpr int kFinePer = kFine / NT;             // parts per thread in the scan
+    constexpr int kPer = kBins / NT;                 // the same in the general search
     constexpr int kChunks = EPT * NW;                // chunks of 64 consecutive tokens, in token order
     constexpr int kChunkPer = (kChunks + 63) / 64;   // chunks per lane in their scan
-    __shared__ __attribute__((aligned(16))) int hist[kBins];
+    static_assert(kFinePer % 2 == 0 && kFine >= kBins, "the histograms share their memory");
+    __shared__ __attribute__((aligned(16))) int hist[kFine];
     __shared__ __attribute__((aligned(16))) int chunk_n[kChunkPer * 64];
     __shared__ __attribute__((aligned(16))) unsigned long long last[kLast];
+    __shared__ int upto_thread[NT];                  // inclusive counts within a wave
+    __shared__ float part[4 * NW];                   // per wave: sums, or extremes
     __shared__ uint32_t extreme[2 * NW];             // per wave: largest key, largest complement of a key
     __shared__ int wave_n[NW];
     __shared__ int pick[3];
@@ -124,7 +167,7 @@ __global__ __launch_bounds__(NT) void select_kernel(
     const int L = cu_seq[item + 1] - tok0;
     const float* s = scores + (size_t)tok0 * g.H_kv + (size_t)h * L;
     const int tid = threadIdx.x;
-    const int lane = tid & 63, wave = tid >> 6;
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), wave_at = wave * 64;
 
     const int W = min(g.W, L);
     const int n_cand = L - W;
@@ -140,21 +183,229 @@ __global__ __launch_bounds__(NT) void select_kernel(
     if (want <= 0) return;
     if (n_cand > EPT * NT) return;                   // launcher never allows this
 
-    // Thread t holds tokens t, t + NT, t + 2 NT, ...: the loads are coalesced straight into registers, and for a fixed
-    // register the lanes of a wave hold 64 consecutive tokens. Past the end a thread loads the last candidate again (clamped address instead of a branch around the load: all loads of a thread are in
-    // flight together), which leaves the extremes what they are.
-    auto live = [&](int e) { return tid < n_cand - e * NT; };
-    uint32_t key[EPT];
+    // (a buffer of the candidates' size reads as zero past its end: no clamped addresses, all loads of a thread in flight)
+    const auto live = [&](int e) { return tid < n_cand - e * NT; };
+    const auto full = [&](int e) { return (e + 1) * NT <= n_cand; };            // uniform
+    const auto any = [&](int e) { return e * NT + wave_at < n_cand; };          // uniform over the wave
+    const auto buf = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(s), 0, n_cand * 4, 0x00027000);
+    float x[EPT];
 #pragma unroll
-    for (int e = 0; e < EPT; ++e) key[e] = max(order_key(s[min(tid + e * NT, n_cand - 1)]), 1u);
+    for (int e = 0; e < EPT; ++e) x[e] = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(buf, tid * 4, e * NT * 4, 0));
+#pragma unroll
+    for (int u = 0; u < kFine / NT; u += 2) *reinterpret_cast<int2*>(&hist[u * NT + 2 * tid]) = make_int2(0, 0);
+    if (tid == 0) last_n = 0;
+
+    // Mean and deviation. (Sums of scores and squares: where the deviation is so small beside the mean that they cancel, the
+    // parts come out too wide or too narrow and the search takes longer.)
+    const bool few = 12 * (long long)want < n_cand, most = 12 * (long long)(n_cand - want) < n_cand;   // (uniform) below a twelfth, above eleven
+    float s1 = 0.f, s2 = 0.f, end = -INFINITY;
+#pragma unroll
+    for (int e = 0; e < EPT; ++e) {
+        s1 += x[e];
+        s2 = fmaf(x[e], x[e], s2);
+    }
+    if (few || most) {
+        const float sign = few ? 1.f : -1.f;
+#pragma unroll
+        for (int e = 0; e < EPT; ++e) end = fmaxf(end, live(e) ? sign * x[e] : -INFINITY);
+        end = wave_max63(end);
+    }
+    s1 = wave_sum63(s1);
+    s2 = wave_sum63(s2);
+    if (lane == 63) { part[wave] = s1; part[NW + wave] = s2; part[2 * NW + wave] = end; }
+    __syncthreads();
+    float hi, inv;
+    {
+        const auto of_wave = [&](int which, float none) { return lane < NW ? part[which * NW + (lane < NW ? lane : 0)] : none; };
+        const float n_inv = 1.f / (float)n_cand, mean = lane_float(wave_sum63(of_wave(0, 0.f)), 63) * n_inv;
+        const float dev = sqrtf(fmaxf(fmaf(-mean, mean, lane_float(wave_sum63(of_wave(1, 0.f)), 63) * n_inv), 0.f));
+        hi = fmaf(2.f, dev, mean);
+        float lo = fmaf(-2.f, dev, mean);
+        if (few || most) {
+            const float top = lane_float(wave_max63(of_wave(2, -INFINITY)), 63);
+            if (few) hi = fmaxf(hi, top);
+            else lo = fminf(lo, -top);
+        }
+        inv = (float)kFine / (hi - lo);
+        if (!(inv > 0.f && fabsf(hi) * inv < INFINITY)) inv = 0.f;       // no number, no end, or no width: the general search
+    }
+    // part of a score: falls as the score rises, rounded and cut off alike for all
+    const float at0 = hi * inv;
+    const auto fine = [&](int e) { return (int)__builtin_amdgcn_fmed3f(fmaf(x[e], -inv, at0), 0.f, (float)(kFine - 1)); };
+
+    // a token past the end is below everything
+#pragma unroll
+    for (int e = 0; e < EPT; ++e)
+        if (!full(e)) x[e] = live(e) ? x[e] : -INFINITY;
+
+    int rank = want, inside = n_cand;
+    // Adds to one part take their turns, which a long head with many equal scores would wait for: a wave that finds a quarter
+    // of the lanes of a register in one part counts that part from lane masks and adds it once (half zeros at 32768 tokens
+    // 30 -> 20 us, all equal but one 64 -> 39). Heads of up to eight registers finish sooner without. Registers past the end look
+    // crowded but hold no candidates (left in: half zeros at 18000 tokens 22 us instead of 17, random scores 16.2 instead of 14.5).
+    auto add_all = [&](auto part_of, auto counts) {
+        int crowded = -1, many = 15;
+        if constexpr (EPT >= 16) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int p = (int)part_of(u * (EPT / 4));
+                const int one = __builtin_amdgcn_readlane(p, 21 * u);
+                const int n = __builtin_popcountll(__builtin_amdgcn_ballot_w64(counts(u * (EPT / 4)) && p == one));
+                if (n > many) { many = n; crowded = one; }
+            }
+        }
+        if (crowded < 0) {
+#pragma unroll
+            for (int e = 0; e < EPT; ++e)
+                if (any(e) && counts(e)) atomicAdd(&hist[part_of(e)], 1);
+        } else {
+            int n = 0;
+#pragma unroll
+            for (int e = 0; e < EPT; ++e) {
+                const int p = (int)part_of(e);
+                n += __builtin_popcountll(__builtin_amdgcn_ballot_w64(counts(e) && p == crowded));
+                if (counts(e) && p != crowded) atomicAdd(&hist[p], 1);
+            }
+            if (lane == 0 && n) atomicAdd(&hist[crowded], n);
+        }
+    };
+    // The part at which the running count reaches `rank`: every wave looks for the wave, then the thread, then the part. The rank
+    // in it and what it holds follow.
+    auto locate = [&]() -> int {
+        __syncthreads();
+        int sum = 0;
+#pragma unroll
+        for (int u = 0; u < kFinePer; u += 2) {
+            const int2 n = *reinterpret_cast<const int2*>(&hist[tid * kFinePer + u]);
+            sum += n.x + n.y;
+        }
+        const int incl = wave_incl(sum);
+        upto_thread[tid] = incl;
+        if (lane == 63) wave_n[wave] = incl;
+        __syncthreads();
+        int before = 0;
+        auto first_at = [&](int upto) {              // `upto` rises with the lanes and reaches rank
+            const int l = __builtin_ctzll(__builtin_amdgcn_ballot_w64(upto >= rank) | (1ull << 63));
+            before = l > 0 ? __builtin_amdgcn_readlane(upto, l > 0 ? l - 1 : 0) : before;
+            return l;
+        };
+        const int w = first_at(wave_incl(lane < NW ? wave_n[lane < NW ? lane : 0] : 0)) & (NW - 1);
+        const int t = w * 64 + first_at(before + upto_thread[w * 64 + lane]);
+        const int n_at = lane < kFinePer ? hist[t * kFinePer + (lane < kFinePer ? lane : 0)] : 0;
+        const int u = first_at(before + wave_incl(n_at)) & (kFinePer - 1);
+        inside = __builtin_amdgcn_readlane(n_at, u);
+        rank -= before;
+        return t * kFinePer + u;
+    };
+    const bool divided = n_cand > kLast && inv > 0.f;
+    int bin = 0, bin2 = -1;
+    // a part divided in the same way
+    const auto finer = [&](int e) { return (int)__builtin_amdgcn_fmed3f((fmaf(x[e], -inv, at0) - (float)bin) * (float)kFine, 0.f, (float)(kFine - 1)); };
+    const auto in_part = [&](int e) { return fine(e) == bin && (bin2 < 0 || finer(e) == bin2); };
+    if (divided) {
+        // (tokens past the end of a wave's last register count in the last part: no harm, the part ends with them)
+        add_all(fine, any);
+        bin = locate();
+        // Too many, in a part with two ends: once more, unless the parts beside it are empty (a few values that many share)
+        if (inside > kLast && bin > 0 && bin < kFine - 1 && hist[max(bin - 1, 0)] + hist[min(bin + 1, kFine - 1)] > 0) {
+            __syncthreads();                         // (the counts are read)
+#pragma unroll
+            for (int u = 0; u < kFine / NT; u += 2) *reinterpret_cast<int2*>(&hist[u * NT + 2 * tid]) = make_int2(0, 0);
+            __syncthreads();
+#pragma unroll
+            for (int e = 0; e < EPT; ++e)
+                if (fine(e) == bin) atomicAdd(&hist[finer(e)], 1);
+            bin2 = locate();
+        }
+    }
+
+    // The 64 candidates at most that are left: every wave ranks them by (score falling, index), one per lane, against all. No
+    // two are equal, so exactly one is number `rank`.
+    // (more: others share its score and come after it)
+    auto rank_last = [&](uint32_t& at, int& index, bool& more) {
+        __syncthreads();
+        const int n_last = min(last_n, kLast);
+        const unsigned long long mine = last[min(lane, n_last - 1)];
+        int upto = 0;
+#pragma unroll 4
+        for (int i = 0; i < n_last; ++i) upto += last[i] <= mine ? 1 : 0;
+        const int winner = __builtin_ctzll(__builtin_amdgcn_ballot_w64(upto == rank) | (1ull << 63));
+        at = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(mine >> 32), winner);
+        index = __builtin_amdgcn_readlane((int)(uint32_t)mine, winner);
+        more = __builtin_amdgcn_ballot_w64((uint32_t)(mine >> 32) == at && (int)(uint32_t)mine > index) != 0;
+    };
+    auto put_last = [&](uint32_t order, int e) {
+        const int pos = atomicAdd(&last_n, 1);
+        if (pos < kLast) last[pos] = ((unsigned long long)order << 32) | (uint32_t)(tid + e * NT);
+    };
+
+    // For a fixed register e, wave w holds the 64 consecutive tokens of chunk e * NW + w.
+    auto write = [&](auto kept) {
+        // Count the chunk's kept tokens from lane masks (lane e collects register e) ...
+        int my_n = 0;
+#pragma unroll
+        for (int e = 0; e < EPT; ++e) {
+            const int c = __builtin_popcountll(__builtin_amdgcn_ballot_w64(kept(e)));
+            asm volatile("v_writelane_b32 %0, %1, %2" : "+v"(my_n) : "s"(c), "n"(e));
+        }
+        if (lane < EPT) chunk_n[lane * NW + wave] = my_n;
+        if (kChunks < 64 && tid >= kChunks && tid < 64) chunk_n[tid] = 0;
+        __syncthreads();
+        // ... every wave scans all the chunks for itself, kChunkPer per lane, and reads off the offsets of its own ...
+        int sum = 0, ahead = 0;                      // a lane's chunks; those before the one of this wave
+#pragma unroll
+        for (int u = 0; u < kChunkPer; ++u) {
+            const int c = chunk_n[lane * kChunkPer + u];
+            if (u < (wave & (kChunkPer - 1))) ahead += c;
+            sum += c;
+        }
+        ahead += wave_incl(sum) - sum;
+        // ... and every kept token writes itself to its slot: the slots of a wave's tokens are consecutive, so each store
+        // instruction writes one run of the output.
+#pragma unroll
+        for (int e = 0; e < EPT; ++e) {
+            const bool k = kept(e);
+            const unsigned long long m = __builtin_amdgcn_ballot_w64(k);
+            const int at = __builtin_amdgcn_readlane(ahead, (e * NW + wave) / kChunkPer);
+            const int pos = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, (uint32_t)at));
+            if (k && pos < want) out[pos] = tid + e * NT;
+        }
+    };
+
+    if (divided && inside <= kLast) {
+#pragma unroll
+        for (int e = 0; e < EPT; ++e)
+            if (in_part(e) && live(e)) put_last(~order_key(x[e]), e);
+        uint32_t at;
+        int X;
+        bool more;
+        rank_last(at, X, more);
+        const float T = key_value(~at);
+        if (more)                                    // (uniform) all that share a score are in its part
+#pragma unroll
+            for (int e = 0; e < EPT; ++e) x[e] = x[e] == T && tid > X - e * NT ? -INFINITY : x[e];
+        write([&](int e) { return x[e] >= T; });
+        return;
+    }
+
+    // ---- the general search, among what is in the part found so far (or all candidates) ----
+    // From here on a key is its distance below the largest one, and what is no candidate is further than all (keys are at
+    // least 1, which only the lowest NaN would not be, so no distance is 0xffffffff). The order: shorter distances first, of
+    // equal ones the smaller index.
+    __syncthreads();                                 // (the parts' counts are read)
+    uint32_t key[EPT];
+    uint32_t big = 0, small = 0;                     // (the complement of the smallest)
+#pragma unroll
+    for (int e = 0; e < EPT; ++e) {
+        const bool c = live(e) && (!divided || in_part(e));
+        key[e] = c ? max(order_key(x[e]), 1u) : 0u;
+        big = max(big, key[e]);
+        small = max(small, c ? ~key[e] : 0u);
+    }
 #pragma unroll
     for (int u = 0; u < kPer; ++u) hist[tid + u * NT] = 0;
-    if (tid == 0) last_n = 0;
-    uint32_t big = key[0], small = key[0];
-#pragma unroll
-    for (int e = 1; e < EPT; ++e) { big = max(big, key[e]); small = min(small, key[e]); }
     big = wave_max63(big);
-    small = wave_max63(~small);
+    small = wave_max63(small);
     if (lane == 63) { extreme[wave] = big; extreme[NW + wave] = small; }
     __syncthreads();
     {
@@ -162,18 +413,15 @@ __global__ __launch_bounds__(NT) void select_kernel(
         big = (uint32_t)__builtin_amdgcn_readlane((int)wave_max63(a), 63);
         small = ~(uint32_t)__builtin_amdgcn_readlane((int)wave_max63(c), 63);
     }
-
-    // From here on a key is its distance below the largest one, and what is no candidate is further than all (keys are
-    // at least 1, which only the lowest NaN would not be, so no distance is 0xffffffff). The order: shorter distances first, of equal ones the smaller index.
 #pragma unroll
-    for (int e = 0; e < EPT; ++e) key[e] = live(e) ? big - key[e] : 0xffffffffu;
+    for (int e = 0; e < EPT; ++e) key[e] = key[e] ? big - key[e] : 0xffffffffu;
+    auto cand = [&](int e) { return key[e] != 0xffffffffu; };
 
     // The bracket: candidates with distances in [d0, d0 + lim] and indices in [i0, i0 + ilim]. It holds `inside`
     // candidates, the threshold (number `rank` of them in order, from 1) among them.
     int nb = 32 - __builtin_clz((big - small) | 1u);   // distances have at most nb bits
     uint32_t d0 = 0, lim = 0xffffffffu >> (32 - nb);
     uint32_t i0 = 0, ilim = (uint32_t)n_cand - 1u;
-    int inside = n_cand, rank = want;
     auto in_indices = [&](int e) { return (uint32_t)(tid + e * NT) - i0 <= ilim; };
     // One add per candidate, but candidates that may all be equal: the lanes that share the first one's bin as one number.
     auto add_shared = [&](int bin) {
@@ -212,35 +460,7 @@ __global__ __launch_bounds__(NT) void select_kernel(
     // that are left.
     if (inside > kLast && big != small) {
         int sh = max(nb - kDigitBits, 0);
-        // Adds to one bin take their turns, which a long head with many equal scores would wait for: a wave that finds a
-        // quarter of the lanes of a register in one bin counts that bin from lane masks and adds it once (half zeros at
-        // 32768 tokens 30 -> 20 us, all equal but one 64 -> 39). Heads of up to eight registers finish sooner without. Registers
-        // past the end look crowded but hold no candidates (left in: half zeros at 18000 tokens 22 us instead of 17, random
-        // scores 16.2 instead of 14.5).
-        int crowded = -1, many = 15;
-        if constexpr (EPT >= 16) {
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int bin = (int)(key[u * (EPT / 4)] >> sh);
-                const int one = __builtin_amdgcn_readlane(bin, 21 * u);
-                const int n = __builtin_popcountll(__builtin_amdgcn_ballot_w64(live(u * (EPT / 4)) && bin == one));
-                if (n > many) { many = n; crowded = one; }
-            }
-        }
-        if (crowded < 0) {
-#pragma unroll
-            for (int e = 0; e < EPT; ++e)
-                if (live(e)) atomicAdd(&hist[key[e] >> sh], 1);
-        } else {
-            int n = 0;
-#pragma unroll
-            for (int e = 0; e < EPT; ++e) {
-                const int bin = (int)(key[e] >> sh);
-                n += __builtin_popcountll(__builtin_amdgcn_ballot_w64(live(e) && bin == crowded));
-                if (live(e) && bin != crowded) atomicAdd(&hist[bin], 1);
-            }
-            if (lane == 0 && n) atomicAdd(&hist[crowded], n);
-        }
+        add_all([&](int e) { return key[e] >> sh; }, cand);
         d0 = (uint32_t)settle() << sh;
         nb = sh;
         lim = (1u << nb) - 1u;
@@ -248,7 +468,7 @@ __global__ __launch_bounds__(NT) void select_kernel(
             sh = max(nb - kDigitBits, 0);
 #pragma unroll
             for (int e = 0; e < EPT; ++e)
-                if (key[e] - d0 <= lim && live(e)) add_shared((int)((key[e] - d0) >> sh));
+                if (key[e] - d0 <= lim && cand(e)) add_shared((int)((key[e] - d0) >> sh));
             d0 += (uint32_t)settle() << sh;
             nb = sh;
             lim = (1u << nb) - 1u;
@@ -270,55 +490,18 @@ __global__ __launch_bounds__(NT) void select_kernel(
         }
     }
 
-    // At most 64 candidates are left: every wave ranks them by (distance, index), one per lane, against all. No two are
-    // equal, so exactly one is number `rank`.
 #pragma unroll
     for (int e = 0; e < EPT; ++e)
-        if (key[e] - d0 <= lim && in_indices(e)) {
-            const int pos = atomicAdd(&last_n, 1);
-            if (pos < kLast) last[pos] = ((unsigned long long)key[e] << 32) | (uint32_t)(tid + e * NT);
-        }
-    __syncthreads();
-    const int n_last = min(last_n, kLast);
-    const unsigned long long mine = last[min(lane, n_last - 1)];
-    int upto = 0;
-#pragma unroll 4
-    for (int i = 0; i < n_last; ++i) upto += last[i] <= mine ? 1 : 0;
-    const int winner = __builtin_ctzll(__builtin_amdgcn_ballot_w64(upto == rank) | (1ull << 63));
-    const uint32_t T = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(mine >> 32), winner);
-    const int X = __builtin_amdgcn_readlane((int)(uint32_t)mine, winner);   // at distance T, tokens up to X stay
-
-    // For a fixed register e, wave w holds the 64 consecutive tokens of chunk e * NW + w. Count the chunk's kept tokens
-    // from lane masks (lane e collects register e) ...
-    auto kept = [&](int e) { return key[e] < T + (tid <= X - e * NT ? 1u : 0u); };
-    int my_n = 0;
-#pragma unroll
-    for (int e = 0; e < EPT; ++e) {
-        const int c = __builtin_popcountll(__builtin_amdgcn_ballot_w64(kept(e)));
-        asm volatile("v_writelane_b32 %0, %1, %2" : "+v"(my_n) : "s"(c), "n"(e));
-    }
-    if (lane < EPT) chunk_n[lane * NW + wave] = my_n;
-    if (kChunks < 64 && tid >= kChunks && tid < 64) chunk_n[tid] = 0;
-    __syncthreads();
-    // ... every wave scans all the chunks for itself, kChunkPer per lane, and reads off the offsets of its own ...
-    int sum = 0, ahead = 0;                          // a lane's chunks; those before the one of this wave
-#pragma unroll
-    for (int u = 0; u < kChunkPer; ++u) {
-        const int c = chunk_n[lane * kChunkPer + u];
-        if (u < (wave & (kChunkPer - 1))) ahead += c;
-        sum += c;
-    }
-    ahead += wave_incl(sum) - sum;
-    // ... and every kept token writes itself to its slot: the slots of a wave's tokens are consecutive, so each store
-    // instruction writes one run of the output.
-#pragma unroll
-    for (int e = 0; e < EPT; ++e) {
-        const bool k = kept(e);
-        const unsigned long long m = __builtin_amdgcn_ballot_w64(k);
-        const int base = __builtin_amdgcn_readlane(ahead, (e * NW + wave) / kChunkPer);
-        const int pos = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, (uint32_t)base));
-        if (k && pos < want) out[pos] = tid + e * NT;
-    }
+        if (key[e] - d0 <= lim && cand(e) && in_indices(e)) put_last(key[e], e);
+    uint32_t at;
+    int X;
+    bool more;
+    rank_last(at, X, more);
+    const uint32_t T = big - at;
+    write([&](int e) {
+        const uint32_t k = live(e) ? max(order_key(x[e]), 1u) : 0u;
+        return k > T || (k == T && tid <= X - e * NT);
+    });
 }
 
 // Heads longer than 32 * 1024 tokens: the keys do not fit the registers of one workgroup, so every counting pass

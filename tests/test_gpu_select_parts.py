@@ -1,0 +1,68 @@
+"""Selection where its division of the scores' range can go wrong: budgets of a few tokens and of nearly all, parts that hold too
+many, scores that share values, that lie close together far from zero, drift along the head, or are not finite; all register counts."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import audiokv_oracle as O
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def A():
+    import paper_2604_06694_amd as A
+    return A
+
+
+def _scores(kind, rng, L):
+    x = rng.standard_normal(L)
+    if kind == "normal":     return x
+    if kind == "skewed":     return np.exp(2.0 * x) - 0.5
+    if kind == "outlier":    return np.where(np.arange(L) == L // 3, 1e6, x)
+    if kind == "clusters":   return np.where(rng.random(L) < 0.55, 1e-3 * x, 5.0 + 1e-4 * x)
+    if kind == "close":      return 1000.0 + 1e-4 * x
+    if kind == "levels":     return np.floor(4 * np.abs(x)) / 4
+    if kind == "zeros":      return np.where(rng.random(L) < 0.5, np.where(rng.random(L) < 0.5, -0.0, 0.0), x)
+    if kind == "equal":      return np.full(L, 0.25)
+    if kind == "drift":      return np.cumsum(x)
+    if kind == "tiny":       return 1e-42 * x
+    if kind == "huge":       return 1e30 * x
+    if kind == "infinite":   return np.where(rng.random(L) < 0.02, np.inf, np.where(rng.random(L) < 0.02, -np.inf, x))
+    raise ValueError(kind)
+
+
+KINDS = ["normal", "skewed", "outlier", "clusters", "close", "levels", "zeros", "equal", "drift", "tiny", "huge", "infinite"]
+
+
+@pytest.mark.parametrize("L", [17, 80, 81, 500, 2048, 2049, 4096, 5000, 8208, 16384, 16400, 20001, 32768])
+@pytest.mark.parametrize("kind", KINDS)
+def test_selection_is_exact(A, kind, L):
+    W, shares = 16, [0.0, 0.002, 0.07, 0.09, 0.4, 0.9, 0.93, 0.999, 1.0]
+    rng = np.random.default_rng(L + KINDS.index(kind))
+    s = np.stack([_scores(kind, rng, L) for _ in shares]).astype(np.float32)
+    b = np.array([W + int(r * (L - W)) for r in shares], dtype=np.int32)
+    cu = np.concatenate([[0], np.cumsum(b)]).astype(np.int32)
+    p = A.Params(len(shares), len(shares), 64, W)
+    got = A.select(p, torch.from_numpy(s).cuda().reshape(-1), torch.from_numpy(b).cuda(), torch.from_numpy(cu).cuda(), [L], int(cu[-1]))
+    got = got.cpu().numpy()
+    for h in range(len(shares)):
+        order = np.lexsort((np.arange(L - W), -s[h, :L - W].astype(np.float64)))
+        want = np.concatenate([np.sort(order[:b[h] - W]), np.arange(L - W, L)])
+        assert np.array_equal(got[cu[h]:cu[h + 1]], want), (kind, L, shares[h])
+
+
+def test_scores_that_are_no_numbers_keep_their_place(A):
+    """NaN of either sign among ordinary scores: positive ones first of all, negative ones last."""
+    L, W = 3000, 8
+    rng = np.random.default_rng(5)
+    s = rng.standard_normal(L).astype(np.float32)
+    s[[10, 700, 2900]] = np.nan
+    s[[11, 1500]] = -np.nan
+    b = np.array([W + 1000], dtype=np.int32)
+    got = A.select(A.Params(1, 1, 64, W), torch.from_numpy(s).cuda(), torch.from_numpy(b).cuda(),
+                   torch.from_numpy(np.array([0, b[0]], dtype=np.int32)).cuda(), [L], int(b[0])).cpu().numpy()
+    key = s.view(np.uint32).astype(np.int64)
+    key = np.where(key & 0x80000000, 0xffffffff - key, key | 0x80000000)
+    want = np.sort(np.lexsort((np.arange(L - W), -key[:L - W]))[:1000])
+    assert np.array_equal(got, np.concatenate([want, np.arange(L - W, L)]))
