@@ -6,39 +6,40 @@ namespace audiokv {
 
 namespace {
 
-struct Plan { int NB, WR, rows_pad, tile_keys; };
+struct Plan { int NB, WR, rows_pad, tile_keys, per_cu; };      // per_cu: resident workgroups
 
 // Instantiated (32-row blocks per wave, waves per workgroup) pairs in order of preference per sweep: the first
-// that holds the rows is taken (all must exist in score_d*.hip). The sweeps differ where their register needs do:
-// three row tiles per wave fit the registers of sweep 1 (and let two 4-wave workgroups share a CU at 256 rows),
-// but spill in sweep 2, which also carries the row constants.
+// that holds the rows is taken (all must exist in score_d*.hip). More than 448 rows take three row tiles per wave in sweep 1;
+// they would spill in sweep 2, which also carries the row constants and covers those rows in two launches. 256 rows in
+// sweep 1 with three tiles on three waves, the ninth tile padding: 48 items of 16384 535 us for the whole score call, with two
+// tiles on four waves, two workgroups per CU 530; 8 x 32768 183 and 179, 1 x 32768 37.2 and 35.1, ragged 8 x 2000-20000 76.7 and 72.1.
 struct Combo { int NB, WR; };
-const Combo kSweep1_128[] = {{1, 1}, {1, 2}, {1, 4}, {1, 7}, {3, 3}, {2, 7}, {3, 6}};   // d = 64, 128
-const Combo kSweep2_128[] = {{1, 1}, {1, 2}, {1, 4}, {1, 7}, {2, 4}, {2, 7}, {2, 8}};
+const Combo kSweep1_128[] = {{1, 1}, {1, 2}, {1, 4}, {1, 7}, {2, 4}, {2, 7}, {3, 6}};   // d = 64, 128
+const Combo kSweep2_128[] = {{1, 1}, {1, 2}, {1, 4}, {1, 7}, {2, 4}, {2, 7}};
 const Combo kCombos256[] = {{1, 1}, {1, 2}, {1, 4}, {1, 7}, {1, 8}};                    // d = 256, both sweeps
 
 bool make_plan(int rows, int D, int sweep, Plan* out) {
     const Combo* cs; int n;
-    if (D == 64 || D == 128) { cs = sweep == 1 ? kSweep1_128 : kSweep2_128; n = 7; }
+    if (D == 64 || D == 128) { cs = sweep == 1 ? kSweep1_128 : kSweep2_128; n = sweep == 1 ? 7 : 6; }
     else if (D == 256) { cs = kCombos256; n = 5; }
     else return false;
     for (int i = 0; i < n; ++i) {
         const int pad = cs[i].NB * 32 * cs[i].WR;
         if (pad >= rows) {
-            *out = Plan{cs[i].NB, cs[i].WR, pad, (D == 256) ? 32 : 32 * AUDIOKV_SCORE_KB};
+            // two when the waves are few or hold one row tile each (128 registers), or when the workgroup is four waves of two
+            // row tiles without constants (168 registers: three waves per SIMD); one when eight waves take all the registers
+            const bool two = (cs[i].NB == 1 && D <= 128) || cs[i].WR < 4 || (cs[i].NB == 2 && cs[i].WR == 4 && sweep == 1);
+            *out = Plan{cs[i].NB, cs[i].WR, pad, (D == 256) ? 32 : 32 * AUDIOKV_SCORE_KB, two ? 2 : 1};
             return true;
         }
     }
     return false;
 }
 
-int num_splits(const Plan& p, int H_kv, int n_items, const int32_t* seqlens_host, int D) {
+int num_splits(const Plan& p, int H_kv, int n_items, const int32_t* seqlens_host) {
     // A head is cut into key ranges so that the grid fills the 256 CUs evenly: the split count minimises the time of
     // the launch in units of one tile, with a fixed prologue cost per workgroup (in tiles).
-    // resident workgroups per CU: two when the waves are few or hold one row tile each (128 registers), or when
-    // the workgroup is four waves of three row tiles; one when eight waves take all the registers
-    const bool two = (p.NB == 1 && D <= 128) || p.WR < 4 || (p.NB == 3 && p.WR == 3);
-    const int slots = 256 * (two ? 2 : 1);
+    const int slots = 256 * p.per_cu;
     // what a workgroup costs before its first and after its last tile (query fragments, filling the ring, the row
     // statistics or constants), in tiles: about 200 keys' worth, fitted to measured launches
     const int overhead = p.tile_keys >= 64 ? 3 : 7;
@@ -110,7 +111,7 @@ bool score_needs_second_raw(int rows, int D) { return sweep2_is_split(rows, D); 
 int score_num_splits(int H_kv, int n_items, const int32_t* seqlens_host, int rows, int D) {
     Plan p;
     if (!make_plan(rows, D, 1, &p) || n_items <= 0 || H_kv <= 0) return 1;
-    return num_splits(p, H_kv, n_items, seqlens_host, D);
+    return num_splits(p, H_kv, n_items, seqlens_host);
 }
 
 hipError_t launch_score(const Geom& g, const void* q_win, const void* k, const int32_t* cu_seqlens,
@@ -123,7 +124,7 @@ hipError_t launch_score(const Geom& g, const void* q_win, const void* k, const i
     if (!make_plan(rows, g.D, 1, &p1)) return hipErrorInvalidValue;
     const int rows_pad = score_padded_rows(rows, g.D);
     if (rows_pad == 0) return hipErrorInvalidValue;
-    const int ns1 = num_splits(p1, g.H_kv, g.n_items, seqlens_host, g.D);
+    const int ns1 = num_splits(p1, g.H_kv, g.n_items, seqlens_host);
     score_detail::SweepArgs args{q_win, k, cu_seqlens, 0, rows_pad, 0, stats_ws, ns1, lse, raw_out, ride_along, ride_taps};
     auto sweep = [&](int which, const Plan& p, int ns, int row_base, float* raw) -> hipError_t {
         args.nsplit = ns;
@@ -148,14 +149,14 @@ hipError_t launch_score(const Geom& g, const void* q_win, const void* k, const i
     Plan p2;
     if (!sweep2_is_split(rows, g.D)) {
         if (!make_plan(rows, g.D, 2, &p2)) return hipErrorInvalidValue;
-        return sweep(2, p2, num_splits(p2, g.H_kv, g.n_items, seqlens_host, g.D), 0, raw_out);
+        return sweep(2, p2, num_splits(p2, g.H_kv, g.n_items, seqlens_host), 0, raw_out);
     }
     if (!raw_second) return hipErrorInvalidValue;
     Plan p2b;
     if (!make_plan(kSweep2MaxRows, g.D, 2, &p2) || !make_plan(rows - kSweep2MaxRows, g.D, 2, &p2b)) return hipErrorInvalidValue;
-    e = sweep(2, p2, num_splits(p2, g.H_kv, g.n_items, seqlens_host, g.D), 0, raw_out);
+    e = sweep(2, p2, num_splits(p2, g.H_kv, g.n_items, seqlens_host), 0, raw_out);
     if (e != hipSuccess) return e;
-    e = sweep(2, p2b, num_splits(p2b, g.H_kv, g.n_items, seqlens_host, g.D), kSweep2MaxRows, raw_second);
+    e = sweep(2, p2b, num_splits(p2b, g.H_kv, g.n_items, seqlens_host), kSweep2MaxRows, raw_second);
     if (e != hipSuccess) return e;
     const unsigned blocks = (unsigned)((raw_elems + 256 * 8 - 1) / (256 * 8));
     hipLaunchKernelGGL(score_detail::score_add_kernel, dim3(blocks > 0 ? blocks : 1), dim3(256), 0, s, raw_out,

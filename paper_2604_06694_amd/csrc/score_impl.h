@@ -754,8 +754,9 @@ struct SweepArgs {
     const ConvFilterJob* taps;
 };
 
-// which = 1: per-range row statistics into stats; which = 2: column sums from stats or lse into raw
-template <int D, int NB, int WR>
+// which = 1: per-range row statistics into stats; which = 2: column sums from stats or lse into raw (of a tiling that is not
+// for sweep 1 only)
+template <int D, int NB, int WR, bool BOTH = true>
 hipError_t launch_sweep(int which, const Geom& g, const SweepArgs& a, hipStream_t s)
 {
     using T = Tile<D, NB, WR>;
@@ -763,9 +764,10 @@ hipError_t launch_sweep(int which, const Geom& g, const SweepArgs& a, hipStream_
     if (!attr_set && T::LDS_BYTES > 48 * 1024) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(score_kernel<D, NB, WR, false>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, T::LDS_BYTES);
-        if (e == hipSuccess)
-            e = hipFuncSetAttribute(reinterpret_cast<const void*>(score_kernel<D, NB, WR, true>),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, T::LDS_BYTES);
+        if constexpr (BOTH)
+            if (e == hipSuccess)
+                e = hipFuncSetAttribute(reinterpret_cast<const void*>(score_kernel<D, NB, WR, true>),
+                                        hipFuncAttributeMaxDynamicSharedMemorySize, T::LDS_BYTES);
         if (e != hipSuccess) return e;
         attr_set = true;
     }
@@ -785,9 +787,11 @@ hipError_t launch_sweep(int which, const Geom& g, const SweepArgs& a, hipStream_
     if (which == 1)
         hipLaunchKernelGGL((score_kernel<D, NB, WR, false>), grid, dim3(T::THREADS), T::LDS_BYTES, s, g, (const __bf16*)a.q_win,
                            (const __bf16*)a.k, a.cu_seq, n_wg, a.nsplit, a.rows_pad, 0, a.stats, 0, (const float*)nullptr, a.raw, ride);
-    else
+    else if constexpr (BOTH)
         hipLaunchKernelGGL((score_kernel<D, NB, WR, true>), grid, dim3(T::THREADS), T::LDS_BYTES, s, g, (const __bf16*)a.q_win,
                            (const __bf16*)a.k, a.cu_seq, n_wg, a.nsplit, a.rows_pad, a.row_base, a.stats, a.stat_splits, a.lse, a.raw, ride);
+    else
+        return hipErrorInvalidValue;
     return hipGetLastError();
 }
 
