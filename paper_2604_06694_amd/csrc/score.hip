@@ -125,7 +125,13 @@ hipError_t launch_score(const Geom& g, const void* q_win, const void* k, const i
     const int rows_pad = score_padded_rows(rows, g.D);
     if (rows_pad == 0) return hipErrorInvalidValue;
     const int ns1 = num_splits(p1, g.H_kv, g.n_items, seqlens_host);
-    score_detail::SweepArgs args{q_win, k, cu_seqlens, 0, rows_pad, 0, stats_ws, ns1, lse, raw_out, ride_along, ride_taps};
+    // What the memory-side cache (256 MB) holds of K after sweep 1 is its end: where K does not fit, sweep 2 begins there. Score
+    // calls, forwards and backwards: 28 x 32768, 448 rows 929 and 915 us, 13 x 32768 452 and 442; 224 rows 30 x 9000 (276 MB) 169 and 165,
+    // 48 x 10000 297 and 289; K that fits: 28 x 9000, 256 rows (258 MB) 352 and 356 with the eviction around it.
+    long long k_bytes = 0;
+    for (int i = 0; i < g.n_items; ++i) k_bytes += (long long)seqlens_host[i] * g.H_kv * g.D * 2;
+    const bool backwards = k_bytes > (1LL << 28);
+    score_detail::SweepArgs args{q_win, k, cu_seqlens, 0, rows_pad, 0, stats_ws, ns1, lse, raw_out, backwards, ride_along, ride_taps};
     auto sweep = [&](int which, const Plan& p, int ns, int row_base, float* raw) -> hipError_t {
         args.nsplit = ns;
         args.row_base = row_base;

@@ -236,6 +236,7 @@ template <int D, int NB, int WR, bool SWEEP2>
 __global__ __launch_bounds__(64 * (WR + 1), (NB == 1 && D <= 128) ? 4 : 2) void score_kernel(
     Geom g, const __bf16* __restrict__ q_win, const __bf16* __restrict__ k,
     const int32_t* __restrict__ cu_seq, int n_wg, int nsplit,
+    int backwards,                    // sweep 2 begins with the heads that sweep 1 ended with
     int rows_pad,                     // row pitch of stats (>= ROWS: the two sweeps may tile the rows differently)
     int row_base,                     // first window row of this launch (sweep 2 may cover the rows in two launches)
     float* __restrict__ stats,        // [head][split][rows_pad][2] = (max in base-2 units, sum of exp2): sweep 1 out, sweep 2 in
@@ -262,7 +263,7 @@ __global__ __launch_bounds__(64 * (WR + 1), (NB == 1 && D <= 128) ? 4 : 2) void 
         const int full = n_heads & ~7;                  // heads that fill whole groups of 8
         const int bid = blockIdx.x;
         if (bid < full * nsplit) {
-            const int q = bid >> 3;
+            const int q = SWEEP2 && backwards ? (full * nsplit >> 3) - 1 - (bid >> 3) : bid >> 3;
             split = q % nsplit;
             head = (q / nsplit) * 8 + (bid & 7);
         } else {
@@ -750,6 +751,7 @@ struct SweepArgs {
     int stat_splits;
     const float* lse;
     float* raw;
+    bool backwards;
     const AllocateJob* alloc;      // these two ride along, if given
     const ConvFilterJob* taps;
 };
@@ -786,10 +788,10 @@ hipError_t launch_sweep(int which, const Geom& g, const SweepArgs& a, hipStream_
     const dim3 grid((unsigned)(n_wg + ride.alloc_blocks + ride.tap_blocks));
     if (which == 1)
         hipLaunchKernelGGL((score_kernel<D, NB, WR, false>), grid, dim3(T::THREADS), T::LDS_BYTES, s, g, (const __bf16*)a.q_win,
-                           (const __bf16*)a.k, a.cu_seq, n_wg, a.nsplit, a.rows_pad, 0, a.stats, 0, (const float*)nullptr, a.raw, ride);
+                           (const __bf16*)a.k, a.cu_seq, n_wg, a.nsplit, 0, a.rows_pad, 0, a.stats, 0, (const float*)nullptr, a.raw, ride);
     else if constexpr (BOTH)
         hipLaunchKernelGGL((score_kernel<D, NB, WR, true>), grid, dim3(T::THREADS), T::LDS_BYTES, s, g, (const __bf16*)a.q_win,
-                           (const __bf16*)a.k, a.cu_seq, n_wg, a.nsplit, a.rows_pad, a.row_base, a.stats, a.stat_splits, a.lse, a.raw, ride);
+                           (const __bf16*)a.k, a.cu_seq, n_wg, a.nsplit, a.backwards ? 1 : 0, a.rows_pad, a.row_base, a.stats, a.stat_splits, a.lse, a.raw, ride);
     else
         return hipErrorInvalidValue;
     return hipGetLastError();
