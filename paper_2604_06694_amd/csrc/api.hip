@@ -433,7 +433,7 @@ int32_t audiokv_compact(const audiokv_params* params, const void* k, const void*
     if (total_rows < 0 || total_rows > b.total_tokens * params->n_kv_heads)
         return fail(AUDIOKV_E_INVALID_ARG, "total_rows %lld outside [0, tokens x heads]", (long long)total_rows);
     const Geom g = make_geom(params, n_items);
-    AUDIOKV_HIP(launch_compact(g, k, v, indices_dev, cu_budgets_dev, cu_seqlens_dev, total_rows, k_out, v_out,
+    AUDIOKV_HIP(launch_compact(g, k, v, indices_dev, cu_budgets_dev, cu_seqlens_dev, b.total_tokens, total_rows, k_out, v_out,
                                static_cast<hipStream_t>(stream)),
                 "compact kernel");
     return AUDIOKV_OK;
@@ -536,7 +536,7 @@ int32_t evict_entry(const audiokv_params* params, const void* q_win, const void*
     AUDIOKV_HIP(launch_select(g, smoothed, budgets_dev, cu_budgets_dev, cu_seqlens_dev, b.max_L, indices_dev, s),
                 "select kernel");
     AUDIOKV_MARK(4);
-    AUDIOKV_HIP(launch_compact(g, k, v, indices_dev, cu_budgets_dev, cu_seqlens_dev, total_rows, k_out, v_out, s),
+    AUDIOKV_HIP(launch_compact(g, k, v, indices_dev, cu_budgets_dev, cu_seqlens_dev, b.total_tokens, total_rows, k_out, v_out, s),
                 "compact kernel");
     AUDIOKV_MARK(5);
 #undef AUDIOKV_MARK

@@ -119,8 +119,9 @@ bool select_supported(int L);
 hipError_t launch_select(const Geom& g, const float* scores, const int32_t* budgets, const int32_t* cu_budgets,
                          const int32_t* cu_seqlens, int max_L, int32_t* indices, hipStream_t s);
 
+// total_tokens: of all items, total_rows: kept, of all heads
 hipError_t launch_compact(const Geom& g, const void* k, const void* v, const int32_t* indices,
-                          const int32_t* cu_budgets, const int32_t* cu_seqlens, int64_t total_rows,
+                          const int32_t* cu_budgets, const int32_t* cu_seqlens, int64_t total_tokens, int64_t total_rows,
                           void* k_out, void* v_out, hipStream_t s);
 
 }  // namespace audiokv

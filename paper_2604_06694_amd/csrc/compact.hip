@@ -33,7 +33,11 @@ __device__ __forceinline__ int head_of_row(const int32_t* __restrict__ cu_b, int
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));   // 16 bytes; the nontemporal builtins need a native vector
 
-template <int VEC_PER_ROW>   // 16-byte vectors per row = D * 2 / 16
+// VEC_PER_ROW: 16-byte vectors per row = D * 2 / 16. STREAM: what is read and written is too much for the memory-side cache.
+// Rows of a small cache stay there for the decoding step that follows, and K may still be there from the scoring: evict and
+// a decoding step with nontemporal accesses and without, 4 layers of 8192 (67 MB of K and V) 80.4 and 77.1 us, 8 of 5000 (82 MB) 113 and 109;
+// 16 of 5000 (164 MB) 147 and 149, 28 of 8192 274 and 278; the gather alone the same up to 164 MB, 28 of 10000 75.7 and 85.0.
+template <int VEC_PER_ROW, bool STREAM>
 __global__ __launch_bounds__(kThreads) void compact_kernel(
     Geom g, const u32x4* __restrict__ k, const u32x4* __restrict__ v,
     const int32_t* __restrict__ indices, const int32_t* __restrict__ cu_b,
@@ -54,37 +58,44 @@ __global__ __launch_bounds__(kThreads) void compact_kernel(
     const int L = cu_seq[item + 1] - tok0;
     // an index outside the item is a caller error; clamp so that it can never fault
     const int64_t src = kv_row_offset(g, item, tok0, L, h, min(max(idx, 0), L - 1)) / 8 + vec;   // strides are multiples of 8
-    const u32x4 kk = __builtin_nontemporal_load(k + src);
-    const u32x4 vv = __builtin_nontemporal_load(v + src);
+    const u32x4 kk = STREAM ? __builtin_nontemporal_load(k + src) : k[src];
+    const u32x4 vv = STREAM ? __builtin_nontemporal_load(v + src) : v[src];
     if (p < total_rows) {
-        __builtin_nontemporal_store(kk, k_out + p * VEC_PER_ROW + vec);
-        __builtin_nontemporal_store(vv, v_out + p * VEC_PER_ROW + vec);
+        if constexpr (STREAM) {
+            __builtin_nontemporal_store(kk, k_out + p * VEC_PER_ROW + vec);
+            __builtin_nontemporal_store(vv, v_out + p * VEC_PER_ROW + vec);
+        } else {
+            k_out[p * VEC_PER_ROW + vec] = kk;
+            v_out[p * VEC_PER_ROW + vec] = vv;
+        }
     }
 }
 
 }  // namespace
 
 hipError_t launch_compact(const Geom& g, const void* k, const void* v, const int32_t* indices,
-                          const int32_t* cu_budgets, const int32_t* cu_seqlens, int64_t total_rows,
+                          const int32_t* cu_budgets, const int32_t* cu_seqlens, int64_t total_tokens, int64_t total_rows,
                           void* k_out, void* v_out, hipStream_t s)
 {
     if (total_rows <= 0) return hipSuccess;
+    const int64_t all = (total_tokens * g.H_kv + total_rows) * g.D * 4;      // bytes of K and V, whole and kept
+    const bool stream = all > (192LL << 20);
     const int n_heads = g.n_items * g.H_kv;
     const int vec_per_row = g.D / 8;
     const int rows_per_block = kThreads / vec_per_row;
     // a launch holds fewer than 2^32 threads: rows beyond that (60 GB and more) take further ones
     const int64_t slab = (int64_t)rows_per_block << 23;
-#define AUDIOKV_LAUNCH_COMPACT(V)                                                                   \
-    hipLaunchKernelGGL((compact_kernel<V>), dim3(blocks), dim3(kThreads), 0, s, g,                  \
+#define AUDIOKV_LAUNCH_COMPACT(V, S)                                                                \
+    hipLaunchKernelGGL((compact_kernel<V, S>), dim3(blocks), dim3(kThreads), 0, s, g,               \
                        (const u32x4*)k, (const u32x4*)v, indices, cu_budgets, cu_seqlens, n_heads, \
                        first, total_rows, (u32x4*)k_out, (u32x4*)v_out)
     for (int64_t first = 0; first < total_rows; first += slab) {
         const int64_t rows = total_rows - first < slab ? total_rows - first : slab;
         const unsigned blocks = (unsigned)((rows + rows_per_block - 1) / rows_per_block);
         switch (vec_per_row) {
-            case 8:  AUDIOKV_LAUNCH_COMPACT(8);  break;
-            case 16: AUDIOKV_LAUNCH_COMPACT(16); break;
-            case 32: AUDIOKV_LAUNCH_COMPACT(32); break;
+            case 8:  if (stream) AUDIOKV_LAUNCH_COMPACT(8, true); else AUDIOKV_LAUNCH_COMPACT(8, false);  break;
+            case 16: if (stream) AUDIOKV_LAUNCH_COMPACT(16, true); else AUDIOKV_LAUNCH_COMPACT(16, false); break;
+            case 32: if (stream) AUDIOKV_LAUNCH_COMPACT(32, true); else AUDIOKV_LAUNCH_COMPACT(32, false); break;
             default: return hipErrorInvalidValue;
         }
         const hipError_t e = hipGetLastError();

@@ -49,3 +49,31 @@ def test_pooling_of_a_head_longer_than_its_workgroups(A, kernel, mode):
         assert torch.equal(got.double(), ref)
     else:
         assert ((got.double() - ref).abs() <= 1e-6 * ref).all()       # up to fifteen fp32 additions of positive scores
+
+
+@pytest.mark.parametrize("d", [64, 128, 256])
+@pytest.mark.parametrize("megabytes", [150, 260])          # of K, V and the kept rows: what the memory-side cache holds, and more
+def test_gather_on_either_side_of_the_cache(A, d, megabytes):
+    H, L = 2, megabytes * (1 << 20) * 5 // 7 // (2 * 2 * d * 2)      # 0.4 of the rows kept
+    gen = torch.Generator(device="cuda").manual_seed(d)
+    k = torch.randn(H * L * d, generator=gen, device="cuda").to(torch.bfloat16)
+    v = torch.randn(H * L * d, generator=gen, device="cuda").to(torch.bfloat16)
+    keep = [torch.sort(torch.randperm(L, generator=gen, device="cuda")[:int(0.4 * L) + h])[0] for h in range(H)]
+    cu_b = torch.tensor(np.concatenate([[0], np.cumsum([len(x) for x in keep])]), dtype=torch.int32, device="cuda")
+    ko, vo = A.compact(A.Params(H, H, d, 1), k, v, torch.cat(keep).to(torch.int32), cu_b, [L], int(cu_b[-1]))
+    for got, src in ((ko, k), (vo, v)):
+        assert torch.equal(got, torch.cat([src.view(H, L, d)[h][keep[h]] for h in range(H)]))
+
+
+def test_scores_of_keys_that_do_not_fit_the_cache(A):
+    """Beyond 256 MB of keys the second sweep takes the heads from the last to the first, whole groups of eight; here 17 of them."""
+    n, L, d, W = 17, 130_000, 64, 4
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    k = torch.randn(n * L * d, generator=gen, device="cuda").to(torch.bfloat16)
+    q = torch.randn(n * W * d, generator=gen, device="cuda").to(torch.bfloat16)
+    p = A.Params(1, 1, d, W)
+    got = A.score(p, q, k, [L] * n).view(n, L)
+    for i in (0, 7, 8, 15, 16):
+        one = A.score(p, q.view(n, -1)[i].contiguous(), k.view(n, -1)[i].contiguous(), [L])
+        # the same logits; the row sums are added over other ranges
+        assert ((got[i] - one).abs() <= 2e-6 * one).all()
