@@ -129,7 +129,8 @@ def _check(rc: int) -> None:
 
 
 def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    """The current stream's handle (torch.cuda.current_stream() builds an object around it: 2.8 us of a call, this 0.2)."""
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 _LENS_CACHE: dict = {}
@@ -203,10 +204,9 @@ def workspace_bytes(p: Params, seqlens: Sequence[int]) -> int:
 
 
 def _workspace(p: Params, seqlens: Sequence[int], device, workspace: Optional[torch.Tensor]) -> torch.Tensor:
-    need = workspace_bytes(p, seqlens)
-    if workspace is None:
-        workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=device)
-    return workspace
+    if workspace is not None:         # (its size is checked by the call that it is handed to)
+        return workspace
+    return torch.empty(max(workspace_bytes(p, seqlens), 256), dtype=torch.uint8, device=device)
 
 
 def score(p: Params, q_win: torch.Tensor, k: torch.Tensor, seqlens: Sequence[int], *,
@@ -255,7 +255,7 @@ def smooth(p: Params, scores: torch.Tensor, seqlens: Sequence[int], cutoff_frac:
     cu = cu_seqlens if cu_seqlens is not None else _cu(seqlens, dev)
     if out is None:
         out = torch.empty_like(scores)
-    ws = _workspace(dataclasses.replace(p, window=0), seqlens, dev, workspace)
+    ws = workspace if workspace is not None else _workspace(dataclasses.replace(p, window=0), seqlens, dev, None)
     cp = p.c()
     _check(_lib.audiokv_smooth(C.byref(cp), _ptr(scores), _ptr(cu), _host_lens(seqlens), len(seqlens),
                                float(cutoff_frac), float(alpha), _ptr(out), _ptr(ws), ws.numel(), _stream()))
@@ -269,7 +269,7 @@ def smooth_cutoffs(p: Params, scores: torch.Tensor, seqlens: Sequence[int], cuto
     dev = scores.device
     cu = cu_seqlens if cu_seqlens is not None else _cu(seqlens, dev)
     out = torch.empty(len(seqlens) * p.n_kv_heads, dtype=torch.int32, device=dev)
-    ws = _workspace(dataclasses.replace(p, window=0), seqlens, dev, workspace)
+    ws = workspace if workspace is not None else _workspace(dataclasses.replace(p, window=0), seqlens, dev, None)
     cp = p.c()
     _check(_lib.audiokv_smooth_cutoffs(C.byref(cp), _ptr(scores), _ptr(cu), _host_lens(seqlens), len(seqlens),
                                        float(cutoff_frac), _ptr(out), _ptr(ws), ws.numel(), _stream()))
@@ -285,7 +285,7 @@ def select(p: Params, scores: torch.Tensor, budgets: torch.Tensor, cu_budgets: t
     cp = p.c()
     _check(_lib.audiokv_select(C.byref(cp), _ptr(scores), _ptr(budgets), _ptr(cu_budgets), _ptr(cu),
                                _host_lens(seqlens), len(seqlens), _ptr(idx), None, 0, _stream()))
-    return idx[:int(total_rows)]
+    return idx if idx.shape[0] == int(total_rows) else idx[:int(total_rows)]
 
 
 def compact(p: Params, k: torch.Tensor, v: torch.Tensor, indices: torch.Tensor, cu_budgets: torch.Tensor,
@@ -300,6 +300,8 @@ def compact(p: Params, k: torch.Tensor, v: torch.Tensor, indices: torch.Tensor, 
     _check(_lib.audiokv_compact(C.byref(cp), _ptr(k), _ptr(v), _ptr(indices), _ptr(cu_budgets), _ptr(cu),
                                 _host_lens(seqlens), len(seqlens), int(total_rows), _ptr(k_out), _ptr(v_out),
                                 _stream()))
+    if k_out.shape[0] == int(total_rows):
+        return k_out, v_out
     return k_out[:int(total_rows)], v_out[:int(total_rows)]
 
 
@@ -377,8 +379,9 @@ def decode_attend(p: Params, q: torch.Tensor, k_cache: torch.Tensor, v_cache: to
     dev = q.device
     if out is None:
         out = torch.empty((n_items, p.n_q_heads, p.head_dim), dtype=torch.float32, device=dev)
-    need = decode_workspace_bytes(p, n_items, total_rows)
-    ws = workspace if workspace is not None else torch.empty(max(need, 256), dtype=torch.uint8, device=dev)
+    ws = workspace
+    if ws is None:
+        ws = torch.empty(max(decode_workspace_bytes(p, n_items, total_rows), 256), dtype=torch.uint8, device=dev)
     cp = p.c()
     _check(_lib.audiokv_decode_attend(C.byref(cp), _ptr(q), _ptr(k_cache), _ptr(v_cache), _ptr(cu_budgets),
                                       int(n_items), int(total_rows), _ptr(out), _ptr(ws), ws.numel(), _stream()))

@@ -66,12 +66,13 @@ int score_num_splits(int H_kv, int n_items, const int32_t* seqlens_host, int row
 // Padded row count (multiple of the MFMA row tiling) for G*W window rows; 0 if unsupported.
 int score_padded_rows(int rows, int D);
 
+// stat_splits: score_num_splits() of the batch.
 // between_sweeps: optional event recorded on `s` after the first sweep (timing aid), or nullptr.
 // lse: optional fp32 [items][H_q][W] natural-log softmax denominators of the window rows; given, sweep 1 is skipped.
 // ride_along, ride_taps: optional allocation (pools of at most kAllocateWaveHeads heads) and filter taps to run in extra
 // workgroups of the first sweep.
 hipError_t launch_score(const Geom& g, const void* q_win, const void* k, const int32_t* cu_seqlens,
-                        const int32_t* seqlens_host, float* stats_ws, float* raw_out, hipStream_t s,
+                        const int32_t* seqlens_host, int stat_splits, float* stats_ws, float* raw_out, hipStream_t s,
                         hipEvent_t between_sweeps = nullptr, const float* lse = nullptr,
                         float* raw_second = nullptr, size_t raw_elems = 0, const AllocateJob* ride_along = nullptr,
                         const ConvFilterJob* ride_taps = nullptr);

@@ -1,5 +1,7 @@
 // Host-side planning for the score kernels: which (row blocks per wave, row-splitting waves) instantiation
 // covers G*W window rows in each of the two sweeps, and into how many key ranges a head is cut.
+#include <vector>
+
 #include "score_impl.h"
 
 namespace audiokv {
@@ -50,6 +52,12 @@ int num_splits(const Plan& p, int H_kv, int n_items, const int32_t* seqlens_host
         if (t > max_tiles) max_tiles = t;
         if (seqlens_host[i] != seqlens_host[0]) uniform = false;
     }
+    // (for ragged batches, in which every count is tried with every length: quotients rounded up, in float64 and off the whole
+    // numbers, so that they are exact. 48 lengths took 25 us with integer divisions.)
+    std::vector<double> tiles;
+    if (!uniform)
+        for (int i = 0; i < n_items; ++i)
+            if (seqlens_host[i] > 0) tiles.push_back((double)((seqlens_host[i] + p.tile_keys - 1) / p.tile_keys));
     int best = 1;
     long long best_cost = -1;
     const int ns_max = max_tiles < 64 ? max_tiles : 64;
@@ -65,16 +73,16 @@ int num_splits(const Plan& p, int H_kv, int n_items, const int32_t* seqlens_host
             // start as others end. The launch takes about the average load of a slot, plus part of the longest
             // workgroup for the ones that start last, plus, when the last round of workgroups fills only part of the
             // slots, that round's average workgroup for the slots left idle (all in twice the unit, to keep halves).
-            long long total = 0, longest = 0;
             const long long groups = (long long)n_items * H_kv * ns;   // launched, whether or not they hold tiles
-            for (int i = 0; i < n_items; ++i) {
-                const int t = (seqlens_host[i] + p.tile_keys - 1) / p.tile_keys;
-                if (t <= 0) continue;
-                const int tps = (t + ns - 1) / ns;
-                const int used = (t + tps - 1) / tps;          // ranges of this head that hold tiles
-                total += (long long)H_kv * (t + (long long)used * overhead);
-                if (tps + overhead > longest) longest = tps + overhead;
+            double sum = 0., most = 0.;
+            const double per_range = 1. / ns;
+            for (const double t : tiles) {
+                const double tps = (double)(int)((t + ns - 0.5) * per_range);
+                const double used = (double)(int)((t + tps - 0.5) / tps);       // ranges of this head that hold tiles
+                sum += t + used * overhead;
+                most = tps > most ? tps : most;
             }
+            const long long total = (long long)sum * H_kv, longest = tiles.empty() ? 0 : (long long)most + overhead;
             cost = 2 * ((total + slots - 1) / slots) + longest;
             const long long rem = groups % slots;
             if (groups > slots && rem) cost += 2 * (total / groups) * (slots - rem) / slots;
@@ -115,7 +123,7 @@ int score_num_splits(int H_kv, int n_items, const int32_t* seqlens_host, int row
 }
 
 hipError_t launch_score(const Geom& g, const void* q_win, const void* k, const int32_t* cu_seqlens,
-                        const int32_t* seqlens_host, float* stats_ws, float* raw_out, hipStream_t s, hipEvent_t between_sweeps,
+                        const int32_t* seqlens_host, int ns1, float* stats_ws, float* raw_out, hipStream_t s, hipEvent_t between_sweeps,
                         const float* lse, float* raw_second, size_t raw_elems, const AllocateJob* ride_along,
                         const ConvFilterJob* ride_taps)
 {
@@ -124,7 +132,6 @@ hipError_t launch_score(const Geom& g, const void* q_win, const void* k, const i
     if (!make_plan(rows, g.D, 1, &p1)) return hipErrorInvalidValue;
     const int rows_pad = score_padded_rows(rows, g.D);
     if (rows_pad == 0) return hipErrorInvalidValue;
-    const int ns1 = num_splits(p1, g.H_kv, g.n_items, seqlens_host);
     // What the memory-side cache (256 MB) holds of K after sweep 1 is its end: where K does not fit, sweep 2 begins there. Score
     // calls, forwards and backwards: 28 x 32768, 448 rows 929 and 915 us, 13 x 32768 452 and 442; 224 rows 30 x 9000 (276 MB) 169 and 165,
     // 48 x 10000 297 and 289; K that fits: 28 x 9000, 256 rows (258 MB) 352 and 356 with the eviction around it.
