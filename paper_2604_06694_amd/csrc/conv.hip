@@ -57,15 +57,12 @@ __device__ __forceinline__ bool conv_head(const Geom& g, const ConvFilterJob& jo
 // is read and masked where the memory around it is known to be there, and clamped where it is not.
 
 // sum_k s[8 t + e + C k] c[k], zero from L on. POOL != 0: samples pooled; they lie inside a workspace that extends at
-// least 16 floats to either side of every head.
+// least 16 floats to either side of every head. The first U blocks can be requested ahead of everything else (load).
 template <int U, int POOL>
-__device__ __forceinline__ void gather_samples(const float* __restrict__ src, const ConvHead& w, int C, int kernel, int mode,
-                                               const cf* __restrict__ c, int t, cf (&acc)[8]) {
-    constexpr int LEN = POOL ? 16 : 8, AT = POOL ? 4 : 0;
-    const float fill = POOL && mode == AUDIOKV_POOL_MAX ? -INFINITY : 0.f;
-#pragma unroll 1
-    for (int k0 = 0; k0 < w.R; k0 += U) {
-        float x[U][LEN];
+struct SampleBlocks {
+    static constexpr int LEN = POOL ? 16 : 8, AT = POOL ? 4 : 0;
+    float x[U][LEN];
+    __device__ __forceinline__ void load(const float* __restrict__ src, const ConvHead& w, int C, int t, int k0) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int n0 = (k0 + u) * C + 8 * t;
@@ -77,6 +74,9 @@ __device__ __forceinline__ void gather_samples(const float* __restrict__ src, co
                 for (int j = 0; j < LEN; ++j) x[u][j] = src[min(j, w.L - 1)];
             }
         }
+    }
+    __device__ __forceinline__ void add(const ConvHead& w, int C, int kernel, int mode, const cf* __restrict__ c, int t, int k0, cf (&acc)[8]) {
+        const float fill = POOL && mode == AUDIOKV_POOL_MAX ? -INFINITY : 0.f;
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int n0 = (k0 + u) * C + 8 * t;
@@ -112,23 +112,35 @@ __device__ __forceinline__ void gather_samples(const float* __restrict__ src, co
             for (int e = 0; e < 8; ++e) { acc[e].re = fmaf(o[e], ck.re, acc[e].re); acc[e].im = fmaf(o[e], ck.im, acc[e].im); }
         }
     }
-}
+    // all blocks; LOADED: the first of them are here already
+    template <bool LOADED>
+    __device__ __forceinline__ void sum(const float* __restrict__ src, const ConvHead& w, int C, int kernel, int mode, const cf* __restrict__ c,
+                                        int t, cf (&acc)[8]) {
+        if constexpr (LOADED) add(w, C, kernel, mode, c, t, 0, acc);
+#pragma unroll 1
+        for (int k0 = LOADED ? U : 0; k0 < w.R; k0 += U) {
+            load(src, w, C, t, k0);
+            add(w, C, kernel, mode, c, t, k0, acc);
+        }
+    }
+};
 
 // sum_k (h[n] - i h[N - n]) c[k], n = 8 t + e + C k; taps from L on are zero, and so is h[N] for n = 0 (a negacyclic
 // sequence has no element N). Memory past the taps is there for 8 floats.
 template <int U>
-__device__ __forceinline__ void gather_taps(const float* __restrict__ h, const ConvHead& w, int C, const cf* __restrict__ c,
-                                            int t, cf (&acc)[8]) {
-    const int N = 1 << w.log_n;
-#pragma unroll 1
-    for (int k0 = 0; k0 < w.R; k0 += U) {
-        float a[U][8], b[U][8];                              // b holds h[low .. low + 7], low = N - n0 - 7, read forwards
+struct TapBlocks {
+    float a[U][8], b[U][8];                                  // b holds h[low .. low + 7], low = N - n0 - 7, read forwards
+    __device__ __forceinline__ void load(const float* __restrict__ h, const ConvHead& w, int C, int t, int k0) {
+        const int N = 1 << w.log_n;
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int n0 = (k0 + u) * C + 8 * t;
             window_load(h + min(n0, w.L), a[u]);
             window_load(h + min(max(N - n0 - 7, 0), w.L), b[u]);
         }
+    }
+    __device__ __forceinline__ void add(const ConvHead& w, int C, const cf* __restrict__ c, int t, int k0, cf (&acc)[8]) {
+        const int N = 1 << w.log_n;
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int n0 = (k0 + u) * C + 8 * t, low = N - n0 - 7;       // low >= 1, or <= -7 past the last block
@@ -142,7 +154,16 @@ __device__ __forceinline__ void gather_taps(const float* __restrict__ h, const C
             }
         }
     }
-}
+    template <bool LOADED>
+    __device__ __forceinline__ void sum(const float* __restrict__ h, const ConvHead& w, int C, const cf* __restrict__ c, int t, cf (&acc)[8]) {
+        if constexpr (LOADED) add(w, C, c, t, 0, acc);
+#pragma unroll 1
+        for (int k0 = LOADED ? U : 0; k0 < w.R; k0 += U) {
+            load(h, w, C, t, k0);
+            add(w, C, c, t, k0, acc);
+        }
+    }
+};
 
 // LDS of a workgroup: the padded points, the roots of unity, and the constants of residue r:
 //   c[k] = exp(i pi k (1 - 4 r) / 2R), k < R;  step[e] = exp(i pi e (1 - 4 r) / 2N) and
@@ -185,6 +206,37 @@ struct Twists {
         else return mul_rounded(first, m.step[e]);
     }
 };
+// The same for two sequences side by side: half the barriers, and each one's work in the shadow of the other's (with the first
+// blocks of both requested ahead of the tables: evict on one layer of 13577 55.8 -> 54.5 us, smooth on 24 ragged sequences
+// 41.2 -> 39.3, on 30 of 500-32000 74.6 -> 69.9, on one of 1500 13.7 -> 12.3).
+// z2: padded_len(C) points
+template <int LOGC>
+__device__ __forceinline__ void to_bins_of_two(ConvLds<LOGC>& m, cf* z2, const typename Cfft<LOGC>::Twiddles& tw, const Twists<LOGC>& twist, int t,
+                                               cf (&a)[8], cf (&b)[8]) {
+    using F = Cfft<LOGC>;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) { const cf w = twist.at(m, e); a[e] = mul(a[e], w); b[e] = mul(b[e], w); }
+    F::put(m.z, a, 8 * t, 0);
+    F::put(z2, b, 8 * t, 0);
+    __syncthreads();
+    F::get(m.z, a, t, LOGC - 3);
+    F::get(z2, b, t, LOGC - 3);
+#pragma unroll
+    for (int p = 0; p < F::P8; ++p) {                        // Fft::forward
+        const int sb = F::low_bit(p), at = F::base(p, t);
+        if (p) { F::get(m.z, a, at, sb); F::get(z2, b, at, sb); }
+        dft8<-1>(a);
+        dft8<-1>(b);
+        if (p < F::TW) { F::template twist<false>(a, tw(p, 0)); F::template twist<false>(b, tw(p, 0)); }
+        if (p + 1 < F::P8 || F::REM) { F::put(m.z, a, at, sb); F::put(z2, b, at, sb); __syncthreads(); }
+    }
+    if (F::REM) {
+        F::get(m.z, a, 8 * t, 0);
+        F::get(z2, b, 8 * t, 0);
+        F::template small_dfts<-1>(a);
+        F::template small_dfts<-1>(b);
+    }
+}
 // acc, points 8 t + e, twisted and transformed: the bins of residue r in the last layout
 template <int LOGC>
 __device__ __forceinline__ void to_bins(ConvLds<LOGC>& m, const typename Cfft<LOGC>::Twiddles& tw, const Twists<LOGC>& twist, int t, const cf (&acc)[8],
@@ -207,13 +259,16 @@ __global__ __launch_bounds__(Cfft<LOGC>::THREADS) void conv_spectrum_kernel(Geom
     ConvHead w;
     const int item = blockIdx.x >> log_r, r = blockIdx.x & ((1 << log_r) - 1), t = threadIdx.x;
     if (!conv_head(g, job, item * g.H_kv, LOGC, w) || w.owner != item || r >= w.R) return;
+    TapBlocks<LOGC == 13 ? 2 : 4> taps;
+    constexpr bool kEarly = LOGC < 13;
+    if constexpr (kEarly) taps.load(job.h + item * job.item_stride, w, 1 << LOGC, t, 0);
     fill_constants<LOGC>(m, w, r, t);
     typename Cfft<LOGC>::Twiddles tw;
     Cfft<LOGC>::init(tw, m.table, t);
     cf acc[8], v[8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) acc[e] = {0.f, 0.f};
-    gather_taps<4>(job.h + item * job.item_stride, w, 1 << LOGC, m.c, t, acc);
+    taps.template sum<kEarly>(job.h + item * job.item_stride, w, 1 << LOGC, m.c, t, acc);
     to_bins<LOGC>(m, tw, Twists<LOGC>(m, w, (float)(1 - 4 * r), t), t, acc, v);
     cf* out = spec + (size_t)item * spec_stride + ((size_t)r << LOGC) + 8 * t;
 #pragma unroll
@@ -221,7 +276,9 @@ __global__ __launch_bounds__(Cfft<LOGC>::THREADS) void conv_spectrum_kernel(Geom
         *reinterpret_cast<f32x4*>(out + e) = f32x4{v[e].re, v[e].im, v[e + 1].re, v[e + 1].im};
 }
 
-template <int LOGC, int POOL>
+// SPEC: the filter's bins come from conv_spectrum_kernel; otherwise the workgroup transforms its share of the filter beside its
+// share of the samples (8192 points, whose 1024 threads have 128 registers each: before it).
+template <int LOGC, int POOL, bool SPEC>
 __global__ __launch_bounds__(Cfft<LOGC>::THREADS) void conv_chunk_kernel(
     Geom g, const float* __restrict__ in, ConvFilterJob job, int log_r, const cf* __restrict__ spec, size_t spec_stride,
     cf* __restrict__ part, size_t part_stride, float alpha, float* __restrict__ out)
@@ -233,29 +290,47 @@ __global__ __launch_bounds__(Cfft<LOGC>::THREADS) void conv_chunk_kernel(
     ConvHead w;
     const int head = blockIdx.x >> log_r, r = blockIdx.x & ((1 << log_r) - 1), t = threadIdx.x;
     if (!conv_head(g, job, head, LOGC, w) || r >= w.R) return;
+    const float* src = in + w.off;
+    const float* h = job.h + w.owner * job.item_stride;
+    // Without spectra few heads are at work and a CU has one workgroup: the first blocks are on their way while the tables are
+    // filled. With them two share a CU, with 128 registers each.
+    constexpr bool kEarly = !SPEC && LOGC < 13;
+    SampleBlocks<U, POOL> samples;
+    TapBlocks<U> taps;
+    if constexpr (kEarly) {
+        taps.load(h, w, C, t, 0);
+        samples.load(src, w, C, t, 0);
+    }
     fill_constants<LOGC>(m, w, r, t);
     typename Cfft<LOGC>::Twiddles tw;
     Cfft<LOGC>::init(tw, m.table, t);
     const float a = (float)(1 - 4 * r);
     const Twists<LOGC> twist(m, w, a, t);
-    const float* src = in + w.off;
 
-    cf f[8], v[8];
-    if (spec) {
+    cf f[8], v[8], acc[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) { f[e] = {0.f, 0.f}; acc[e] = {0.f, 0.f}; }
+    if constexpr (SPEC) {
         const cf* b = spec + (size_t)w.owner * spec_stride + ((size_t)r << LOGC) + 8 * t;
 #pragma unroll
         for (int e = 0; e < 8; e += 2) {
             const f32x4 p = *reinterpret_cast<const f32x4*>(b + e);
-            v[e] = {p[0], p[1]}; v[e + 1] = {p[2], p[3]};
+            f[e] = {p[0], p[1]}; f[e + 1] = {p[2], p[3]};
         }
-    }
-#pragma unroll 1
-    for (int pass = spec ? 1 : 0; pass < 2; ++pass) {
-        cf acc[8];
+        samples.template sum<false>(src, w, C, g.pool_kernel, g.pool_mode, m.c, t, acc);
+        to_bins<LOGC>(m, tw, twist, t, acc, v);
+    } else if constexpr (kEarly) {
+        taps.template sum<true>(h, w, C, m.c, t, f);
+        samples.template sum<true>(src, w, C, g.pool_kernel, g.pool_mode, m.c, t, acc);
+        to_bins_of_two<LOGC>(m, reinterpret_cast<cf*>(smem + sizeof(m)), tw, twist, t, acc, f);
 #pragma unroll
-        for (int e = 0; e < 8; ++e) { f[e] = v[e]; acc[e] = {0.f, 0.f}; }
-        if (pass == 0) gather_taps<U>(job.h + w.owner * job.item_stride, w, C, m.c, t, acc);
-        else gather_samples<U, POOL>(src, w, C, g.pool_kernel, g.pool_mode, m.c, t, acc);
+        for (int e = 0; e < 8; ++e) v[e] = acc[e];
+    } else {
+        taps.template sum<false>(h, w, C, m.c, t, acc);
+        to_bins<LOGC>(m, tw, twist, t, acc, f);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) acc[e] = {0.f, 0.f};
+        samples.template sum<false>(src, w, C, g.pool_kernel, g.pool_mode, m.c, t, acc);
         to_bins<LOGC>(m, tw, twist, t, acc, v);
     }
 #pragma unroll
@@ -367,21 +442,25 @@ __global__ __launch_bounds__(kFilterThreads) void conv_filter_kernel(ConvFilterJ
 // end at 65535, and a batch may hold more heads than that.
 int log_residues(const ConvCall& c) { return 31 - __builtin_clz((unsigned)c.max_r); }
 
-template <int LOGC, int POOL>
+template <int LOGC, int POOL, bool SPEC>
 hipError_t launch_chunks(const Geom& g, const ConvCall& c, const float* in, float alpha, float* out, hipStream_t s) {
-    const int lds = (int)sizeof(ConvLds<LOGC>);
+    const int lds = (int)(sizeof(ConvLds<LOGC>) + (SPEC || LOGC == 13 ? 0 : padded_len((size_t)1 << LOGC) * sizeof(cf)));
     if (lds > 48 * 1024) {
         static std::atomic<bool> attr_set{false};
         if (!attr_set) {
-            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(conv_chunk_kernel<LOGC, POOL>),
+            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(conv_chunk_kernel<LOGC, POOL, SPEC>),
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, lds);
             if (e != hipSuccess) return e;
             attr_set = true;
         }
     }
-    hipLaunchKernelGGL((conv_chunk_kernel<LOGC, POOL>), dim3((unsigned)(g.n_items * g.H_kv) << log_residues(c)),
+    hipLaunchKernelGGL((conv_chunk_kernel<LOGC, POOL, SPEC>), dim3((unsigned)(g.n_items * g.H_kv) << log_residues(c)),
                        dim3(Cfft<LOGC>::THREADS), lds, s, g, in, c.job, log_residues(c), (const cf*)c.spec, c.points, (cf*)c.part, c.points, alpha, out);
     return hipGetLastError();
+}
+template <int LOGC, int POOL>
+hipError_t launch_chunks(const Geom& g, const ConvCall& c, const float* in, float alpha, float* out, hipStream_t s) {
+    return c.spec ? launch_chunks<LOGC, POOL, true>(g, c, in, alpha, out, s) : launch_chunks<LOGC, POOL, false>(g, c, in, alpha, out, s);
 }
 template <int LOGC>
 hipError_t launch_chunks(const Geom& g, const ConvCall& c, const float* in, bool pool_on_load, float alpha, float* out, hipStream_t s) {
