@@ -15,8 +15,8 @@ struct ConvFilterJob {
     double cutoff_frac;
     int taper_bins;
     int max_length;           // of the items that have taps
-    // workgroups of `threads`, one tap per thread (in a call of very many items more)
-    int blocks_per_item(int threads) const { return blocks_per_part((max_length + threads - 1) / threads, n_items); }
+    // workgroups of `threads`, a tap and its mirror image per thread (in a call of very many items more)
+    int blocks_per_item(int threads) const { return blocks_per_part((max_length / 2 + threads) / threads, n_items); }
 };
 
 struct SmoothFilters {
@@ -40,11 +40,15 @@ __device__ __forceinline__ double sine_ratio(long long p, long long q, int n) {
 // taper's weights are (1 + cos(pi j / (T+1))) / 2, so its bins are three geometric series; a Nyquist bin counts once.
 // Compiled into several sources whose settings differ: nothing is contracted, so that the taps are the same bits wherever
 // they are evaluated.
+// 0 <= n <= L/2
 __device__ __forceinline__ float low_pass_tap(int n, int L, int kstar, int T) {
 #pragma clang fp contract(off)
-    n = min(n, L - n);                              // h is even: 0 <= n <= L/2
-    const long long r = ((long long)(2 * kstar + 1) * n) % (2LL * L);
-    double v = n == 0 ? (double)(2 * kstar + 1) : sinpi((double)r / (double)L) / sinpi((double)n / (double)L);
+    // (2 k* + 1) n mod 2 L, 0 <= n <= L/2: in float64, where all of it is exact (a 64-bit integer remainder takes as long as a
+    // sine), from a quotient that may be off by one
+    const double all = (double)(2 * kstar + 1) * (double)n, turn = 2.0 * (double)L;
+    double r = fma(-floor(all / turn), turn, all);
+    r = r < 0.0 ? r + turn : r >= turn ? r - turn : r;
+    double v = n == 0 ? (double)(2 * kstar + 1) : sinpi(r / (double)L) / sinpi((double)n / (double)L);
     const int half = L >> 1, J = min(T, half - kstar);
     if (J > 0) {
         const double phi = 2.0 * (double)((long long)kstar * n % L) / (double)L;        // angle of bin k*, in units of pi
@@ -82,8 +86,11 @@ __device__ __forceinline__ void conv_filter_block(const ConvFilterJob& job, int 
     if (!conv_item(job, L) || conv_owner(job.cu_seqlens, item, L) != item) return;
     const int kstar = conv_kstar(job.cutoff_frac, L);
     float* h = job.h + item * job.item_stride;
-    for (int n = part * threads + (int)threadIdx.x; n < L; n += per_item * threads)
-        h[n] = low_pass_tap(n, L, kstar, job.taper_bins);
+    for (int n = part * threads + (int)threadIdx.x; n <= L >> 1; n += per_item * threads) {
+        const float v = low_pass_tap(n, L, kstar, job.taper_bins);
+        h[n] = v;
+        if (n > 0) h[L - n] = v;                    // h is even
+    }
 }
 
 }  // namespace
