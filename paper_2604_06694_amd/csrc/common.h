@@ -96,10 +96,12 @@ size_t smooth_workspace_bytes(const int32_t* seqlens_host, int n_items, int H_kv
 size_t smooth_workspace_required(const int32_t* seqlens_host, int n_items, int H_kv);
 // kstar_out (may be null): the cutoff bin of every head; cutoffs_only stops after writing it. workspace_bytes: what
 // `workspace` holds (at least _required; with less than _bytes every power-of-two head runs in one workgroup).
+// join (conv.h): if given, the last step of some heads may be left to launch_select, and `out` without their result.
+struct ConvJoin;
 hipError_t launch_smooth(const Geom& g, const float* in, bool pool_on_load, const int32_t* cu_seqlens,
                          const int32_t* seqlens_host, int n_items, double cutoff_frac, double alpha,
                          float* out, void* workspace, size_t workspace_bytes, int32_t* kstar_out, bool cutoffs_only,
-                         hipStream_t s, bool filters_ready = false);
+                         hipStream_t s, bool filters_ready = false, ConvJoin* join = nullptr);
 // What lengths that are not powers of two need that depends on the lengths and the cutoff only: launch_smooth_filters
 // prepares it in the workspace (launch_smooth does it itself unless told that it is ready). smooth_filters says how much
 // that is: several launches (long_work, worth a stream of its own), or the taps alone, which can ride along elsewhere,
@@ -117,8 +119,10 @@ hipError_t launch_decode(const Geom& g, const void* q, const void* k_cache, cons
                          const int32_t* cu_budgets, long long total_rows, float* out, void* workspace, hipStream_t s);
 
 bool select_supported(int L);
+// whether launch_select can combine what smoothing left
+bool select_joins(int max_L);
 hipError_t launch_select(const Geom& g, const float* scores, const int32_t* budgets, const int32_t* cu_budgets,
-                         const int32_t* cu_seqlens, int max_L, int32_t* indices, hipStream_t s);
+                         const int32_t* cu_seqlens, int max_L, int32_t* indices, hipStream_t s, const ConvJoin* join = nullptr);
 
 // total_tokens: of all items, total_rows: kept, of all heads
 hipError_t launch_compact(const Geom& g, const void* k, const void* v, const int32_t* indices,

@@ -27,9 +27,25 @@ struct ConvCall {
     void* spec = nullptr;     // the filters' bins, or null: every workgroup transforms its own share of the filter
 };
 
+// The chunks of a run that are left to be combined by whoever reads the result (conv_join.h): heads of kJoinMaxR chunks of
+// 2^kJoinLogC points at most, which is 16384 samples. (Of eight chunks a workgroup would read 256 KB: one layer of 30000 tokens
+// 71.9 us with a launch that combines them, 73.5 without.)
+constexpr int kJoinLogC = 12, kJoinMaxR = 4;
+struct ConvJoin {
+    ConvFilterJob job{};
+    const float* in = nullptr;          // the samples, for alpha < 1
+    int pool_on_load = 0;
+    float alpha = 1.f;
+    const void* part = nullptr;         // null: nothing is left
+    size_t part_stride = 0;             // complex values per head
+    float* out = nullptr;               // where the result goes
+};
+
 // taps and, if c.spec is set, the filters' bins
 hipError_t launch_conv_filter(const Geom& g, const ConvCall& c, hipStream_t s);
 // pool_on_load: `in` lies inside a workspace that extends 16 floats to either side of every head
-hipError_t launch_conv(const Geom& g, const ConvCall& c, const float* in, bool pool_on_load, float alpha, float* out, hipStream_t s);
+// join: if given and the chunks are of that kind, they are left uncombined
+hipError_t launch_conv(const Geom& g, const ConvCall& c, const float* in, bool pool_on_load, float alpha, float* out, hipStream_t s,
+                       ConvJoin* join = nullptr);
 
 }  // namespace audiokv

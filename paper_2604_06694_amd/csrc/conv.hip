@@ -30,6 +30,7 @@
 
 #include "conv_filter.h"
 #include "conv.h"
+#include "conv_join.h"
 #include "fft_regs.h"
 
 namespace audiokv {
@@ -37,20 +38,6 @@ namespace {
 
 // (the 1024 threads of 8192 points have 128 registers each: too few for all roots)
 template <int LOGC> using Cfft = Fft<LOGC, 1, (LOGC < 13)>;
-
-struct ConvHead { int L, log_n, R, owner; size_t off; };
-
-__device__ __forceinline__ bool conv_head(const Geom& g, const ConvFilterJob& job, int head, int log_c, ConvHead& w) {
-    const int item = head / g.H_kv, h = head - item * g.H_kv;
-    const int tok0 = job.cu_seqlens[item];
-    w.L = job.cu_seqlens[item + 1] - tok0;
-    if (!conv_item(job, w.L)) return false;
-    w.log_n = conv_log_points(w.L, log_c);
-    w.R = 1 << (w.log_n - log_c);
-    w.owner = conv_owner(job.cu_seqlens, item, w.L);
-    w.off = (size_t)tok0 * g.H_kv + (size_t)h * w.L;
-    return true;
-}
 
 // What both transforms of a workgroup start from: points n = 8 t + e + C k of all R blocks k, weighted by the constants
 // c[k], summed over k. U blocks' loads are in flight together, none behind a branch: what lies outside the sequence
@@ -358,47 +345,6 @@ __global__ __launch_bounds__(Cfft<LOGC>::THREADS) void conv_chunk_kernel(
     }
 }
 
-// out[n + C t] = Re sum_r part_r[n] exp(i pi (4 r - 1) t / 2R), t = 0..R-1: an R-point inverse DFT and a rotation
-template <int R>
-__device__ __forceinline__ void join(const cf* __restrict__ p, int C, int n, float* o) {
-    cf v[16];
-#pragma unroll
-    for (int r = 0; r < R; ++r) v[r] = p[(size_t)r * C + n];
-    if constexpr (R == 2) { const cf a = v[0]; v[0] = cadd(a, v[1]); v[1] = csub(a, v[1]); }
-    else if constexpr (R == 4) dft4<1>(v[0], v[1], v[2], v[3]);
-    else if constexpr (R == 8) dft8<1>(reinterpret_cast<cf(&)[8]>(v));
-    else {
-        // sixteen points as two of eight: even and odd residues
-        cf e[8], d[8];
-#pragma unroll
-        for (int k = 0; k < 8; ++k) { e[k] = v[2 * k]; d[k] = v[2 * k + 1]; }
-        dft8<1>(e);
-        dft8<1>(d);
-        constexpr float C1 = 0.92387953251128674f, S1 = 0.38268343236508977f, H = 0.70710678118654752f;
-        constexpr cf root[8] = {{1.f, 0.f}, {C1, S1}, {H, H}, {S1, C1}, {0.f, 1.f}, {-S1, C1}, {-H, H}, {-C1, S1}};
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            const cf x = mul(d[k], root[k]);
-            v[k] = cadd(e[k], x);
-            v[k + 8] = csub(e[k], x);
-        }
-    }
-    // exp(-i pi t / 2R)
-    constexpr cf unit[16] = {{1.f, 0.f}, {0.99518472667219689f, 0.098017140329560602f}, {0.98078528040323045f, 0.19509032201612827f},
-                             {0.95694033573220887f, 0.29028467725446237f}, {0.92387953251128676f, 0.38268343236508977f},
-                             {0.88192126434835503f, 0.47139673682599764f}, {0.83146961230254524f, 0.55557023301960222f},
-                             {0.77301045336273696f, 0.63439328416364549f}, {0.70710678118654752f, 0.70710678118654752f},
-                             {0.63439328416364549f, 0.77301045336273696f}, {0.55557023301960222f, 0.83146961230254524f},
-                             {0.47139673682599764f, 0.88192126434835503f}, {0.38268343236508977f, 0.92387953251128676f},
-                             {0.29028467725446237f, 0.95694033573220887f}, {0.19509032201612827f, 0.98078528040323045f},
-                             {0.098017140329560602f, 0.99518472667219689f}};      // cos, sin of pi t / 32
-#pragma unroll
-    for (int t = 0; t < R; ++t) {
-        const cf c = unit[t * (16 / R)];
-        o[t] = fmaf(v[t].re, c.re, v[t].im * c.im);
-    }
-}
-
 constexpr int kJoinThreads = 64;
 
 __global__ __launch_bounds__(kJoinThreads) void conv_join_kernel(
@@ -413,11 +359,15 @@ __global__ __launch_bounds__(kJoinThreads) void conv_join_kernel(
     const float* src = in + w.off;
     float* dst = out + w.off;
     float o[16];
+    cf v[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r)
+        if (r < w.R) v[r] = p[(size_t)r * C + n];
     switch (w.R) {
-        case 2:  join<2>(p, C, n, o); break;
-        case 4:  join<4>(p, C, n, o); break;
-        case 8:  join<8>(p, C, n, o); break;
-        default: join<16>(p, C, n, o); break;
+        case 2:  join<2>(v, o); break;
+        case 4:  join<4>(v, o); break;
+        case 8:  join<8>(v, o); break;
+        default: join<16>(v, o); break;
     }
 #pragma unroll
     for (int t = 0; t < 16; ++t) {
@@ -499,7 +449,8 @@ hipError_t launch_conv_filter(const Geom& g, const ConvCall& c, hipStream_t s) {
     }
 }
 
-hipError_t launch_conv(const Geom& g, const ConvCall& c, const float* in, bool pool_on_load, float alpha, float* out, hipStream_t s) {
+hipError_t launch_conv(const Geom& g, const ConvCall& c, const float* in, bool pool_on_load, float alpha, float* out, hipStream_t s,
+                       ConvJoin* join) {
     if (pool_on_load && g.pool_kernel > kConvMaxPool) return hipErrorInvalidValue;      // (pooled beforehand)
     // a launch of 2^32 threads or more would drop workgroups without an error
     const long long points = (long long)g.n_items * g.H_kv << c.log_c;
@@ -512,6 +463,10 @@ hipError_t launch_conv(const Geom& g, const ConvCall& c, const float* in, bool p
         default: e = launch_chunks<13>(g, c, in, pool_on_load, alpha, out, s); break;
     }
     if (e != hipSuccess || c.max_r == 1) return e;
+    if (join && c.log_c == kJoinLogC && c.max_r <= kJoinMaxR) {
+        *join = ConvJoin{c.job, in, pool_on_load ? 1 : 0, alpha, c.part, c.points, out};
+        return hipSuccess;
+    }
     hipLaunchKernelGGL(conv_join_kernel, dim3((1u << c.log_c) / kJoinThreads * (unsigned)(g.n_items * g.H_kv)), dim3(kJoinThreads),
                        0, s, g, in, pool_on_load ? 1 : 0, c.job, c.log_c, (const cf*)c.part, c.points, alpha, out);
     return hipGetLastError();

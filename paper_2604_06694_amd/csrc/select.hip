@@ -37,6 +37,7 @@
 // a part gained nothing with four heads and lost with 112: every one of them
 // has to load the whole head.
 #include "common.h"
+#include "conv_join.h"
 
 namespace audiokv {
 
@@ -91,6 +92,14 @@ __device__ __forceinline__ void block_exscan2(int a, int b, int* slots /* 2*kSel
     eb = pb + ib - b;
 }
 
+// Workgroup barrier that orders LDS traffic only: nothing is exchanged through memory, and the stores on their way (the window's
+// indices, scores combined from chunks) are no reason to wait.
+__device__ __forceinline__ void lds_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
 // Largest value over the lanes of a full wave, in lane 63 (the sum likewise)
 #define AUDIOKV_DPP_F(x, ctrl, rows, none) \
     __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(none), __float_as_int(x), ctrl, rows, 0xf, false))
@@ -140,10 +149,49 @@ __device__ __forceinline__ uint32_t wave_max63(uint32_t x) {
     return x;
 }
 
-template <int EPT, int NT>   // tokens per thread, threads; the head must have at most EPT * NT candidates
+// Scores of tokens tid + NT e that a convolution left in chunks: token n + C t from points n of all chunks, and every thread's
+// points are those of its own tokens. They go to `smoothed` as well; from n_cand on they are zero here. In place of a launch that combined them: evict
+// on one layer of 5000 tokens 40.2 -> 38.8 us, 13577 54.9 -> 52.9, 28 layers of 13577 439 -> 433.
+template <int EPT, int NT, int R>
+__device__ __forceinline__ void joined_scores(const Geom& g, const ConvJoin& j, const ConvHead& w, int head, int n_cand, float* smoothed,
+                                              float (&x)[EPT]) {
+    constexpr int C = 1 << kJoinLogC, PER = C / NT;          // points per thread
+    const int tid = threadIdx.x;
+    const cf* p = reinterpret_cast<const cf*>(j.part) + (size_t)head * j.part_stride;
+    cf v[PER][16];
+#pragma unroll
+    for (int i = 0; i < PER; ++i)
+#pragma unroll
+        for (int r = 0; r < R; ++r) v[i][r] = p[(size_t)r * C + tid + i * NT];
+    __builtin_amdgcn_sched_barrier(0);                       // all loads before the first result is worked on
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        float o[16];
+        join<R>(v[i], o);
+#pragma unroll
+        for (int t = 0; t < R; ++t) x[i + PER * t] = o[t];
+    }
+    if (j.alpha != 1.f) {
+        const float* src = j.in + w.off;
+#pragma unroll
+        for (int e = 0; e < PER * R; ++e) {
+            const int n = tid + e * NT;
+            if (n < w.L) x[e] = mix(j.pool_on_load ? pooled_at(src, w.L, n, g.pool_kernel, g.pool_mode) : src[n], x[e], j.alpha);
+        }
+    }
+    // (a buffer of the head's size: what lies past its end is not stored)
+    const auto buf = __builtin_amdgcn_make_buffer_rsrc(smoothed, 0, w.L * 4, 0x00027000);
+#pragma unroll
+    for (int e = 0; e < PER * R; ++e) __builtin_amdgcn_raw_buffer_store_b32(__float_as_int(x[e]), buf, tid * 4, e * NT * 4, 0);
+#pragma unroll
+    for (int e = 0; e < EPT; ++e) x[e] = e < PER * R && tid + e * NT < n_cand ? x[e] : 0.f;
+}
+
+// EPT, NT: tokens per thread, threads; the head must have at most EPT * NT candidates. JOIN: some heads' scores are left in chunks.
+template <int EPT, int NT, bool JOIN>
 __global__ __launch_bounds__(NT) void select_kernel(
     Geom g, const float* __restrict__ scores, const int32_t* __restrict__ budgets,
-    const int32_t* __restrict__ cu_b, const int32_t* __restrict__ cu_seq, int32_t* __restrict__ indices)
+    const int32_t* __restrict__ cu_b, const int32_t* __restrict__ cu_seq, int32_t* __restrict__ indices, ConvJoin chunks, float* smoothed)
 {
     constexpr int NW = NT / 64;
     constexpr int kFine = EPT * NT <= 2048 ? 2048 : EPT * NT <= 16384 ? 4096 : 8192;    // parts of the first division
@@ -189,8 +237,21 @@ __global__ __launch_bounds__(NT) void select_kernel(
     const auto any = [&](int e) { return e * NT + wave_at < n_cand; };          // uniform over the wave
     const auto buf = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(s), 0, n_cand * 4, 0x00027000);
     float x[EPT];
+    const auto load = [&]() {
 #pragma unroll
-    for (int e = 0; e < EPT; ++e) x[e] = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(buf, tid * 4, e * NT * 4, 0));
+        for (int e = 0; e < EPT; ++e) x[e] = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(buf, tid * 4, e * NT * 4, 0));
+    };
+    if constexpr (JOIN) {
+        constexpr int kMaxR = EPT * NT >> kJoinLogC;
+        static_assert(kMaxR == 2 || kMaxR == 4, "the cases below");
+        ConvHead w;
+        const int R = conv_head(g, chunks.job, head, kJoinLogC, w) ? w.R : 1;     // (a head of one chunk is done)
+        if (R == 2) joined_scores<EPT, NT, 2>(g, chunks, w, head, n_cand, smoothed + w.off, x);
+        else if (R == 4) joined_scores<EPT, NT, kMaxR>(g, chunks, w, head, n_cand, smoothed + w.off, x);
+        else load();
+    } else {
+        load();
+    }
 #pragma unroll
     for (int u = 0; u < kFine / NT; u += 2) *reinterpret_cast<int2*>(&hist[u * NT + 2 * tid]) = make_int2(0, 0);
     if (tid == 0) last_n = 0;
@@ -213,7 +274,7 @@ __global__ __launch_bounds__(NT) void select_kernel(
     s1 = wave_sum63(s1);
     s2 = wave_sum63(s2);
     if (lane == 63) { part[wave] = s1; part[NW + wave] = s2; part[2 * NW + wave] = end; }
-    __syncthreads();
+    lds_barrier();
     float hi, inv;
     {
         const auto of_wave = [&](int which, float none) { return lane < NW ? part[which * NW + (lane < NW ? lane : 0)] : none; };
@@ -272,7 +333,7 @@ __global__ __launch_bounds__(NT) void select_kernel(
     // The part at which the running count reaches `rank`: every wave looks for the wave, then the thread, then the part. The rank
     // in it and what it holds follow.
     auto locate = [&]() -> int {
-        __syncthreads();
+        lds_barrier();
         int sum = 0;
 #pragma unroll
         for (int u = 0; u < kFinePer; u += 2) {
@@ -282,7 +343,7 @@ __global__ __launch_bounds__(NT) void select_kernel(
         const int incl = wave_incl(sum);
         upto_thread[tid] = incl;
         if (lane == 63) wave_n[wave] = incl;
-        __syncthreads();
+        lds_barrier();
         int before = 0;
         auto first_at = [&](int upto) {              // `upto` rises with the lanes and reaches rank
             const int l = __builtin_ctzll(__builtin_amdgcn_ballot_w64(upto >= rank) | (1ull << 63));
@@ -308,10 +369,10 @@ __global__ __launch_bounds__(NT) void select_kernel(
         bin = locate();
         // Too many, in a part with two ends: once more, unless the parts beside it are empty (a few values that many share)
         if (inside > kLast && bin > 0 && bin < kFine - 1 && hist[max(bin - 1, 0)] + hist[min(bin + 1, kFine - 1)] > 0) {
-            __syncthreads();                         // (the counts are read)
+            lds_barrier();                         // (the counts are read)
 #pragma unroll
             for (int u = 0; u < kFine / NT; u += 2) *reinterpret_cast<int2*>(&hist[u * NT + 2 * tid]) = make_int2(0, 0);
-            __syncthreads();
+            lds_barrier();
 #pragma unroll
             for (int e = 0; e < EPT; ++e)
                 if (fine(e) == bin) atomicAdd(&hist[finer(e)], 1);
@@ -323,7 +384,7 @@ __global__ __launch_bounds__(NT) void select_kernel(
     // two are equal, so exactly one is number `rank`.
     // (more: others share its score and come after it)
     auto rank_last = [&](uint32_t& at, int& index, bool& more) {
-        __syncthreads();
+        lds_barrier();
         const int n_last = min(last_n, kLast);
         const unsigned long long mine = last[min(lane, n_last - 1)];
         int upto = 0;
@@ -350,7 +411,7 @@ __global__ __launch_bounds__(NT) void select_kernel(
         }
         if (lane < EPT) chunk_n[lane * NW + wave] = my_n;
         if (kChunks < 64 && tid >= kChunks && tid < 64) chunk_n[tid] = 0;
-        __syncthreads();
+        lds_barrier();
         // ... every wave scans all the chunks for itself, kChunkPer per lane, and reads off the offsets of its own ...
         int sum = 0, ahead = 0;                      // a lane's chunks; those before the one of this wave
 #pragma unroll
@@ -392,7 +453,7 @@ __global__ __launch_bounds__(NT) void select_kernel(
     // From here on a key is its distance below the largest one, and what is no candidate is further than all (keys are at
     // least 1, which only the lowest NaN would not be, so no distance is 0xffffffff). The order: shorter distances first, of
     // equal ones the smaller index.
-    __syncthreads();                                 // (the parts' counts are read)
+    lds_barrier();                                 // (the parts' counts are read)
     uint32_t key[EPT];
     uint32_t big = 0, small = 0;                     // (the complement of the smallest)
 #pragma unroll
@@ -407,7 +468,7 @@ __global__ __launch_bounds__(NT) void select_kernel(
     big = wave_max63(big);
     small = wave_max63(small);
     if (lane == 63) { extreme[wave] = big; extreme[NW + wave] = small; }
-    __syncthreads();
+    lds_barrier();
     {
         const uint32_t a = extreme[lane & (NW - 1)], c = extreme[NW + (lane & (NW - 1))];
         big = (uint32_t)__builtin_amdgcn_readlane((int)wave_max63(a), 63);
@@ -433,7 +494,7 @@ __global__ __launch_bounds__(NT) void select_kernel(
 
     // After the bins of a round are counted: the first bin at which the running count reaches `rank`.
     auto settle = [&]() -> int {
-        __syncthreads();
+        lds_barrier();
         int n[kPer], sum = 0;
 #pragma unroll
         for (int u = 0; u < kPer; ++u) { n[u] = hist[tid * kPer + u]; sum += n[u]; }
@@ -441,7 +502,7 @@ __global__ __launch_bounds__(NT) void select_kernel(
         for (int u = 0; u < kPer; ++u) hist[tid * kPer + u] = 0;      // for the next round
         int incl = wave_incl(sum);
         if (lane == 63) wave_n[wave] = incl;
-        __syncthreads();
+        lds_barrier();
         const int wn = lane < NW ? wave_n[lane < NW ? lane : 0] : 0;
         const int before = wave == 0 ? 0 : __builtin_amdgcn_readlane(wave_incl(wn), wave - 1);
         int c = before + incl - sum;
@@ -450,7 +511,7 @@ __global__ __launch_bounds__(NT) void select_kernel(
             if (c < rank && rank <= c + n[u]) { pick[0] = tid * kPer + u; pick[1] = c; pick[2] = n[u]; }   // exactly one bin
             c += n[u];
         }
-        __syncthreads();
+        lds_barrier();
         rank -= pick[1];
         inside = pick[2];
         return pick[0];
@@ -640,24 +701,32 @@ __global__ __launch_bounds__(kSelThreads) void select_stream_kernel(
 }  // namespace
 
 bool select_supported(int L) { return L >= 1; }
+bool select_joins(int max_L) { return max_L <= kJoinMaxR << kJoinLogC; }
 
 hipError_t launch_select(const Geom& g, const float* scores, const int32_t* budgets, const int32_t* cu_budgets,
-                         const int32_t* cu_seqlens, int max_L, int32_t* indices, hipStream_t s)
+                         const int32_t* cu_seqlens, int max_L, int32_t* indices, hipStream_t s, const ConvJoin* join)
 {
     const int n_heads = g.n_items * g.H_kv;
-#define AUDIOKV_LAUNCH_SELECT(E, NT)                                                                    \
+#define AUDIOKV_LAUNCH_SELECT(E, NT, J)                                                                 \
     do {                                                                                                \
-        hipLaunchKernelGGL((select_kernel<E, NT>), dim3(n_heads), dim3(NT), 0, s, g, scores, budgets,    \
-                           cu_budgets, cu_seqlens, indices);                                            \
+        hipLaunchKernelGGL((select_kernel<E, NT, J>), dim3(n_heads), dim3(NT), 0, s, g, scores, budgets, \
+                           cu_budgets, cu_seqlens, indices, join ? *join : ConvJoin{}, join ? join->out : nullptr); \
     } while (0)
+    if (join) {
+        // (a head in chunks has more than 4096 tokens)
+        if (max_L <= 8192) AUDIOKV_LAUNCH_SELECT(8, 1024, true);
+        else if (select_joins(max_L)) AUDIOKV_LAUNCH_SELECT(16, 1024, true);
+        else return hipErrorInvalidValue;
+        return hipGetLastError();
+    }
     // Four tokens per thread while the head lasts: fewer waves make the barriers cheaper (512 threads against 1024 at
     // 2048 tokens 4.2 us against 4.9), more tokens per thread make every pass longer (256 threads of eight 5.6 us, 512 of
     // eight at 4096 tokens 5.8 us against 4.9, 512 of sixteen at 8192 tokens 8.2 us against 7.1).
-    if (max_L <= 2048) AUDIOKV_LAUNCH_SELECT(4, 512);
-    else if (max_L <= 4096) AUDIOKV_LAUNCH_SELECT(4, 1024);
-    else if (max_L <= 8192) AUDIOKV_LAUNCH_SELECT(8, 1024);
-    else if (max_L <= 16384) AUDIOKV_LAUNCH_SELECT(16, 1024);
-    else if (max_L <= 32768) AUDIOKV_LAUNCH_SELECT(32, 1024);
+    if (max_L <= 2048) AUDIOKV_LAUNCH_SELECT(4, 512, false);
+    else if (max_L <= 4096) AUDIOKV_LAUNCH_SELECT(4, 1024, false);
+    else if (max_L <= 8192) AUDIOKV_LAUNCH_SELECT(8, 1024, false);
+    else if (max_L <= 16384) AUDIOKV_LAUNCH_SELECT(16, 1024, false);
+    else if (max_L <= 32768) AUDIOKV_LAUNCH_SELECT(32, 1024, false);
     else   // longer heads than the registers and the LDS staging of one workgroup hold
         hipLaunchKernelGGL(select_stream_kernel, dim3(n_heads), dim3(kSelThreads), 0, s, g, scores, budgets, cu_budgets,
                            cu_seqlens, indices);

@@ -1329,7 +1329,7 @@ hipError_t launch_smooth_filters(const Geom& g, const int32_t* cu_seqlens, const
 hipError_t launch_smooth(const Geom& g, const float* in, bool pool_on_load, const int32_t* cu_seqlens,
                          const int32_t* seqlens_host, int n_items, double cutoff_frac, double alpha,
                          float* out, void* workspace, size_t workspace_bytes, int32_t* kstar_out, bool cutoffs_only,
-                         hipStream_t s, bool filters_ready)
+                         hipStream_t s, bool filters_ready, ConvJoin* join)
 {
     if (cutoffs_only && !kstar_out) return hipErrorInvalidValue;
     // A kernel wider than the windows that the transforms load: pooled first, into the result, and smoothed in place. Tap by tap
@@ -1417,7 +1417,7 @@ hipError_t launch_smooth(const Geom& g, const float* in, bool pool_on_load, cons
                            cutoffs_only ? 1 : 0, pl.conv.job);
     }
     if (pl.conv.any) {
-        e = launch_conv(g, pl.conv, in, pool_on_load, (float)alpha, out, s);
+        e = launch_conv(g, pl.conv, in, pool_on_load, (float)alpha, out, s, join);
         if (e != hipSuccess) return e;
     }
     return hipGetLastError();

@@ -66,3 +66,19 @@ def test_scores_that_are_no_numbers_keep_their_place(A):
     key = np.where(key & 0x80000000, 0xffffffff - key, key | 0x80000000)
     want = np.sort(np.lexsort((np.arange(L - W), -key[:L - W]))[:1000])
     assert np.array_equal(got, np.concatenate([want, np.arange(L - W, L)]))
+
+
+@pytest.mark.parametrize("lens", [[4097], [5000, 700], [8191, 4096], [9001, 2048], [16001], [16385, 32768, 600], [32767, 5001], [40000, 9000]])
+@pytest.mark.parametrize("alpha,kernel,mode", [(1.0, 7, 0), (0.5, 7, 0), (0.5, 1, 0), (0.75, 15, 1), (1.0, 5, 1)])
+def test_selection_combines_the_chunks_of_a_convolution(A, lens, alpha, kernel, mode):
+    """evict, whose selection reads heads of several chunks uncombined, against its stages one by one."""
+    H, d, W = 2, 64, 8
+    gen = torch.Generator(device="cuda").manual_seed(sum(lens))
+    q = torch.randn(len(lens) * H * W * d, generator=gen, device="cuda").to(torch.bfloat16)
+    k = torch.randn(sum(lens) * H * d, generator=gen, device="cuda").to(torch.bfloat16)
+    w = torch.rand(len(lens) * H, generator=gen, device="cuda")
+    p = A.Params(H, H, d, W, pool_kernel=kernel, pool_mode=mode)
+    out = A.evict(p, q, k, k, w, lens, 0.3, 0.125, alpha, alloc_scope=A.SCOPE_ITEM)
+    smoothed = A.smooth(p, A.score(p, q, k, lens), lens, 0.125, alpha)
+    staged = A.select(p, smoothed, out["budgets"], out["cu_budgets"], lens, out["total_rows"])
+    assert torch.equal(out["indices"], staged)
