@@ -258,8 +258,8 @@ int32_t audiokv_compact(const audiokv_params* params,
  * length shared by more than eight heads, an energy-adaptive cutoff), they are
  * forked onto a helper stream owned by the library (created on first use,
  * default priority) and joined back into `stream` with events after the scoring
- * (otherwise they stay on `stream`, in the launch that merges the softmax
- * statistics between the two scoring sweeps); everything is ordered after prior
+ * (otherwise they stay on `stream`, in extra workgroups of the first scoring
+ * sweep); everything is ordered after prior
  * work on `stream` and before later work on it. Calls on different streams may be in
  * flight together (separate workspaces and outputs), also from several host
  * threads: the helper stream and its two events are shared, so the part of a
