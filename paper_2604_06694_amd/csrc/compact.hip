@@ -34,9 +34,10 @@ __device__ __forceinline__ int head_of_row(const int32_t* __restrict__ cu_b, int
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));   // 16 bytes; the nontemporal builtins need a native vector
 
 // VEC_PER_ROW: 16-byte vectors per row = D * 2 / 16. STREAM: what is read and written is too much for the memory-side cache.
-// Rows of a small cache stay there for the decoding step that follows, and K may still be there from the scoring: evict and
-// a decoding step with nontemporal accesses and without, 4 layers of 8192 (67 MB of K and V) 80.4 and 77.1 us, 8 of 5000 (82 MB) 113 and 109;
-// 16 of 5000 (164 MB) 147 and 149, 28 of 8192 274 and 278; the gather alone the same up to 164 MB, 28 of 10000 75.7 and 85.0.
+// Rows of a small cache stay there for the decoding step that follows, and K may still be there from the scoring. With nontemporal
+// accesses and without (K, V and kept rows together): the gather of 8 ragged items (110 MB) 12.6 and 11.4 us, evict on one layer of
+// 32768 (47 MB) 96.4 and 94.4; with a decoding step 4 layers of 8192 (94 MB) 80.4 and 77.1, 8 of 5000 (115 MB) 113 and 109;
+// 8 ragged items at d = 256 (178 MB, other inputs each time) 128.1 and 131.9, 28 layers of 8192 274 and 278.
 template <int VEC_PER_ROW, bool STREAM>
 __global__ __launch_bounds__(kThreads) void compact_kernel(
     Geom g, const u32x4* __restrict__ k, const u32x4* __restrict__ v,
@@ -79,7 +80,7 @@ hipError_t launch_compact(const Geom& g, const void* k, const void* v, const int
 {
     if (total_rows <= 0) return hipSuccess;
     const int64_t all = (total_tokens * g.H_kv + total_rows) * g.D * 4;      // bytes of K and V, whole and kept
-    const bool stream = all > (192LL << 20);
+    const bool stream = all > (128LL << 20);
     const int n_heads = g.n_items * g.H_kv;
     const int vec_per_row = g.D / 8;
     const int rows_per_block = kThreads / vec_per_row;
