@@ -179,10 +179,11 @@ __device__ __forceinline__ void joined_scores(const Geom& g, const ConvJoin& j, 
             if (n < w.L) x[e] = mix(j.pool_on_load ? pooled_at(src, w.L, n, g.pool_kernel, g.pool_mode) : src[n], x[e], j.alpha);
         }
     }
-    // (a buffer of the head's size: what lies past its end is not stored)
+    // (a buffer of the head's size: what lies past its end is not stored. The whole offset goes into the operand that is checked
+    // against that size; the scalar one is not.)
     const auto buf = __builtin_amdgcn_make_buffer_rsrc(smoothed, 0, w.L * 4, 0x00027000);
 #pragma unroll
-    for (int e = 0; e < PER * R; ++e) __builtin_amdgcn_raw_buffer_store_b32(__float_as_int(x[e]), buf, tid * 4, e * NT * 4, 0);
+    for (int e = 0; e < PER * R; ++e) __builtin_amdgcn_raw_buffer_store_b32(__float_as_int(x[e]), buf, (tid + e * NT) * 4, 0, 0);
 #pragma unroll
     for (int e = 0; e < EPT; ++e) x[e] = e < PER * R && tid + e * NT < n_cand ? x[e] : 0.f;
 }
@@ -231,7 +232,8 @@ __global__ __launch_bounds__(NT) void select_kernel(
     if (want <= 0) return;
     if (n_cand > EPT * NT) return;                   // launcher never allows this
 
-    // (a buffer of the candidates' size reads as zero past its end: no clamped addresses, all loads of a thread in flight)
+    // (a buffer of the candidates' size reads as zero past its end: no clamped addresses, all loads of a thread in flight. As with
+    // the stores above, the whole offset is in the operand that is checked.)
     const auto live = [&](int e) { return tid < n_cand - e * NT; };
     const auto full = [&](int e) { return (e + 1) * NT <= n_cand; };            // uniform
     const auto any = [&](int e) { return e * NT + wave_at < n_cand; };          // uniform over the wave
@@ -239,7 +241,7 @@ __global__ __launch_bounds__(NT) void select_kernel(
     float x[EPT];
     const auto load = [&]() {
 #pragma unroll
-        for (int e = 0; e < EPT; ++e) x[e] = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(buf, tid * 4, e * NT * 4, 0));
+        for (int e = 0; e < EPT; ++e) x[e] = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(buf, (tid + e * NT) * 4, 0, 0));
     };
     if constexpr (JOIN) {
         constexpr int kMaxR = EPT * NT >> kJoinLogC;
