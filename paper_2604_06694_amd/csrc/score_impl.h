@@ -28,7 +28,8 @@
 // the whole kernel. K tiles (64 keys, or 32 at d = 256) are read from HBM once
 // per sweep by the loader wave (16-byte load-to-LDS instructions that go from
 // HBM straight into a ring of three or four LDS buffers, two or three tiles
-// ahead of the compute waves, one barrier per tile), so the HBM latency is paid
+// ahead of the compute waves, one barrier per tile at which all that was
+// requested has landed), so the HBM latency is paid
 // by a wave that has nothing else to do and no wave holds staging registers.
 // Every compute wave pulls all 32-key x 16-channel fragments of the tile.
 // Sweep 1 keeps no running maximum: its exponentials are taken against a fixed
@@ -51,6 +52,7 @@
 #include "allocate_wave.h"
 #include "common.h"
 #include "conv_filter.h"
+#include "score_ring.h"
 
 #ifndef AUDIOKV_SCORE_KB
 #define AUDIOKV_SCORE_KB 2
@@ -83,12 +85,12 @@ struct Tile {
     static constexpr int CHUNKS = TK * D / 8;         // 16-byte pieces per tile
     static constexpr int CH = CHUNKS / 64;            // load instructions per tile
     static_assert(CHUNKS % 64 == 0, "a tile is a whole number of wave-wide 16-byte loads");
-    // LDS ring: the loader wave requests tile t + AHEAD while tile t is consumed, straight from HBM into the ring
-    // (no staging registers), so AHEAD - 1 whole tiles are in flight across every barrier. Workgroups of one or two
-    // compute waves keep a shorter ring: there the number of resident workgroups matters more.
+    // LDS ring: the loader wave requests tile t + STAGES - 1 while tile t is consumed, straight from HBM into the ring (no
+    // staging registers), and enters the barrier that ends tile t when all it has requested is there (score_ring.h): the loads
+    // of a tile overlap with the work on one tile, and none is on its way across a barrier. Workgroups of one or two compute
+    // waves keep a shorter ring: there the number of resident workgroups matters more.
     static constexpr int STAGES = (WR >= 4) ? 4 : 3;
-    static constexpr int AHEAD = STAGES - 1;
-    static_assert((AHEAD - 1) * CH <= 63, "the outstanding loads must fit the vmcnt field");
+    static_assert(kInFlight * CH <= 63, "the outstanding loads must fit the vmcnt field");
     static constexpr int LDS_K = TK * ROW_BYTES;      // one K buffer
     static constexpr int LDS_COLS = WR * TK * 4;      // one column-sum exchange buffer
     static constexpr int LDS_RC = ROWS * 4;           // sweep 2: per-row normalisation constants
@@ -338,7 +340,7 @@ __global__ __launch_bounds__(64 * (WR + 1), (NB == 1 && D <= 128) ? 4 : 2) void 
     };
 
     if (wave == WR) {
-        // ================= loader wave: HBM -> LDS ring, AHEAD tiles ahead =================
+        // ================= loader wave: HBM -> LDS ring =================
         // Every instruction moves 64 x 16 bytes from per-lane global addresses to 1 KiB of consecutive LDS bytes
         // (global_load_lds_dwordx4): lane l fills chunk slot l % CPR of row l / CPR of the instruction's RPI rows,
         // so it fetches the chunk that belongs in that slot. Rows past the end are clamped to the last
@@ -374,29 +376,14 @@ __global__ __launch_bounds__(64 * (WR + 1), (NB == 1 && D <= 128) ? 4 : 2) void 
                 }
             }
         };
-        // Loads complete in the order they were issued, so "at most n tiles' worth outstanding" means that all tiles but the
-        // last n requested have landed; the barrier then hands them to the compute waves. (These are the only vector-memory
-        // operations of this wave. Ranges of one tile are common, so nothing is requested past the end: with the last tile
-        // requested again instead, a score call on four heads of 1000 tokens and 448 rows took 23.4 us, now 19.9.)
-        auto landed_then_barrier = [&](int outstanding) {   // tiles; uniform
-            if (outstanding >= T::AHEAD - 1)               __builtin_amdgcn_s_waitcnt(vmcnt_only((T::AHEAD - 1) * T::CH));
-            else if (T::AHEAD == 3 && outstanding == 1)    __builtin_amdgcn_s_waitcnt(vmcnt_only(T::CH));
-            else                                           __builtin_amdgcn_s_waitcnt(vmcnt_only(0));
+        // (These are the only vector-memory operations of this wave. Ranges of one tile are common, so nothing is requested past
+        // the end: with the last tile requested again instead, a score call on four heads of 1000 tokens and 448 rows took 23.4 us,
+        // now 19.9.)
+        fill_ring<T::STAGES>(n_loc, issue_tile, [&]() {
+            __builtin_amdgcn_s_waitcnt(vmcnt_only(kInFlight * T::CH));
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
             __builtin_amdgcn_s_barrier();
-        };
-        static_assert(T::AHEAD == 2 || T::AHEAD == 3, "the waits above");
-#pragma unroll
-        for (int a = 0; a < T::AHEAD; ++a)
-            if (a < n_loc) issue_tile(a);
-        landed_then_barrier(n_loc - 1);                 // tile 0 is in the ring
-#pragma unroll 1
-        for (int lt = 0; lt < n_loc; ++lt) {
-            // slot (lt + AHEAD) % STAGES held tile lt - 1, which every wave left at the barrier that ended it
-            if (lt + T::AHEAD < n_loc) issue_tile(lt + T::AHEAD);
-            landed_then_barrier(n_loc - 2 - lt);        // tile lt + 1 is in the ring; ends iteration lt
-        }
-        __builtin_amdgcn_s_waitcnt(vmcnt_only(0));      // nothing may still be writing LDS when the wave ends
+        });
         return;
     }
 
@@ -538,7 +525,8 @@ __global__ __launch_bounds__(64 * (WR + 1), (NB == 1 && D <= 128) ? 4 : 2) void 
     };
     auto reduce_end = [&](f32x16 (&a)[NB], int cbuf, int kb) {
         if (SWEEP2) {
-            // rows held by the other half of the wave; the other waves' rows are added by the loader wave
+            // rows held by the other half of the wave; the other waves' rows are added by wave FLUSH_WAVE
+            // between the barrier that ends the tile and the next one, while the waves fill another buffer.
             // v_permlane32_swap trades lanes 32..63 of its first operand with lanes 0..31 of its second: afterwards
             // one register holds the lower-half sums in both halves, the other the upper-half sums. (Written as asm
             // because the two-result builtin got its results merged; the wait states in front cover the vector
@@ -636,7 +624,7 @@ __global__ __launch_bounds__(64 * (WR + 1), (NB == 1 && D <= 128) ? 4 : 2) void 
     const int t_plain_end = min(max(t_first_masked, t_begin), t_end);
     auto slot_of = [&](int t) { return (t - t_begin) % T::STAGES; };
 
-    wg_barrier();                                       // the first tile is in the ring (and lds_rc is filled)
+    wg_barrier();                                       // the first tiles are in the ring (and lds_rc is filled)
     if (SWEEP2) {
 #pragma unroll
         for (int rb = 0; rb < NB; ++rb)

@@ -1,0 +1,45 @@
+// When the loader wave of a score workgroup requests a tile of keys, and what has landed at each barrier. A header of its own
+// because the order is checked on the host as well (tests/score_ring_check.cpp).
+#pragma once
+
+#if !defined(__HIPCC__)
+#define __host__
+#define __device__
+#define __forceinline__ inline
+#endif
+
+namespace audiokv {
+namespace score_detail {
+
+// Iteration t of the compute waves lies between the barrier that ended tile t - 1 (for the first tile the one in front of the
+// loop) and the one that ends tile t. In it they reduce tile t and already multiply the first block of the next one, so at the
+// barrier that opens iteration t the tiles up to t + kLookAhead have to have landed.
+constexpr int kLookAhead = 1;
+// Tiles that may still be on their way when the loader enters a barrier.
+constexpr int kInFlight = 0;
+
+// STAGES slots, tile t in slot t % STAGES. issue(t) requests tile t, barrier() waits until at most kInFlight tiles' requests
+// are outstanding (they complete in the order in which they were issued) and enters the workgroup's barrier.
+template <int STAGES, class Issue, class Barrier>
+__host__ __device__ __forceinline__ void fill_ring(int n_tiles, Issue issue, Barrier barrier) {
+    constexpr int AHEAD = STAGES - 1;
+    // At the barrier that ends tile t, tiles up to t + AHEAD are requested and t + 1 is opened.
+    static_assert(AHEAD - kInFlight >= 1 + kLookAhead, "what an iteration reads has landed when it opens");
+#if defined(__clang__)
+#pragma unroll
+#endif
+    for (int a = 0; a < AHEAD; ++a)
+        if (a < n_tiles) issue(a);
+    barrier();                                      // opens iteration 0
+#if defined(__clang__)
+#pragma unroll 1
+#endif
+    for (int t = 0; t < n_tiles; ++t) {
+        // its slot held tile t - 1, which every wave left at the barrier that ended it
+        if (t + AHEAD < n_tiles) issue(t + AHEAD);
+        barrier();                                  // ends tile t
+    }
+}
+
+}  // namespace score_detail
+}  // namespace audiokv
