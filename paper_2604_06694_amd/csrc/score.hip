@@ -29,7 +29,9 @@ bool make_plan(int rows, int D, int sweep, Plan* out) {
         const int pad = cs[i].NB * 32 * cs[i].WR;
         if (pad >= rows) {
             // two when the waves are few or hold one row tile each (128 registers), or when the workgroup is four waves of two
-            // row tiles without constants (168 registers: three waves per SIMD); one when eight waves take all the registers
+            // row tiles without constants (168 registers: three waves per SIMD); one when eight waves take all the registers.
+            // At d = 256, four waves and, in sweep 1, seven are resident twice but planned as if they were not: planned with two, 128
+            // rows 28 x 8192 take 113.5 us instead of 125.4, but 4 x 8192 29.7 instead of 24.0 and 8 of 2048-32768 56.7 instead of 55.3.
             const bool two = (cs[i].NB == 1 && D <= 128) || cs[i].WR < 4 || (cs[i].NB == 2 && cs[i].WR == 4 && sweep == 1);
             *out = Plan{cs[i].NB, cs[i].WR, pad, (D == 256) ? 32 : 32 * AUDIOKV_SCORE_KB, two ? 2 : 1};
             return true;

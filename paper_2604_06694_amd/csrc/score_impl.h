@@ -388,6 +388,27 @@ __global__ __launch_bounds__(64 * (WR + 1), (NB == 1 && D <= 128) ? 4 : 2) void 
     }
 
     // ================= compute waves =================
+    // sweep 2, row constants: max + log2(sum); +inf for padded rows, whose exp2 then vanishes
+    auto row_constants = [&]() {
+        for (int i = NB == 1 ? l32 : lane; i < NB * 32; i += 64) {
+            const int r = min(rowg0 + i, R - 1);
+            float out;
+            if (lse)                      // rows of a head follow one another: window row r % W of query head r / W of the group
+                out = lse[((size_t)item * g.H_q + (size_t)h * g.G) * g.W + r] * 1.44269504088896340736f;
+            else if constexpr (NB == 1) out = merged_row<16, true>(stats, stat_splits, rows_pad, head, r, g2);
+            else if (stat_splits <= 16) out = merged_row<16, false>(stats, stat_splits, rows_pad, head, r, 0);
+            else out = merged_row<32, false>(stats, stat_splits, rows_pad, head, r, 0);
+            lds_rc[row0 + i] = rowg0 + i < R ? out : INFINITY;
+        }
+    };
+    // At d = 256 the queries take 64 registers, and a merge beside them 195 in all where the tile loop needs 154: two waves per
+    // SIMD instead of three, which is one workgroup per CU instead of two at 128 rows, two instead of three at 64, and spills at 256,
+    // whose nine waves leave 168. The constants come first there, although their loads and those of the queries then wait for each
+    // other (score calls, constants last and first: 256 rows 8 of 2048-32768 83.8 and 77.8 us, 28 x 8192 167 and 163; 128 rows 28 x
+    // 8192 127.3 and 125.4, 1 x 4000 15.1 and 15.7). The eight waves of 224 rows are one workgroup per CU either way (28 x 8192 135.6
+    // and 138.4).
+    constexpr bool kConstantsFirst = SWEEP2 && D == 256 && WR != 7;
+    if constexpr (kConstantsFirst) row_constants();
     // stationary operand: this wave's window queries, as MFMA fragments
     // fragment (rb, kk): lane holds row row0 + rb*32 + l32, channels kk*16 + g2*8 .. +8
     //
@@ -413,18 +434,7 @@ __global__ __launch_bounds__(64 * (WR + 1), (NB == 1 && D <= 128) ? 4 : 2) void 
 #pragma unroll
             for (int kq = 0; kq < T::KK; kq += 4) quad_transpose(qf[rb][kq], qf[rb][kq + 1], qf[rb][kq + 2], qf[rb][kq + 3], lane);
     }
-    if (SWEEP2)
-        // row constants: max + log2(sum); +inf for padded rows, whose exp2 then vanishes
-        for (int i = NB == 1 ? l32 : lane; i < NB * 32; i += 64) {
-            const int r = min(rowg0 + i, R - 1);
-            float out;
-            if (lse)                      // rows of a head follow one another: window row r % W of query head r / W of the group
-                out = lse[((size_t)item * g.H_q + (size_t)h * g.G) * g.W + r] * 1.44269504088896340736f;
-            else if constexpr (NB == 1) out = merged_row<16, true>(stats, stat_splits, rows_pad, head, r, g2);
-            else if (stat_splits <= 16) out = merged_row<16, false>(stats, stat_splits, rows_pad, head, r, 0);
-            else out = merged_row<32, false>(stats, stat_splits, rows_pad, head, r, 0);
-            lds_rc[row0 + i] = rowg0 + i < R ? out : INFINITY;
-        }
+    if constexpr (SWEEP2 && !kConstantsFirst) row_constants();
 
     // sweep 1: reference (base-2 units: logit * c) and sum of exp2(logit * c - reference) for row
     // row0 + rb*32 + l32 over this lane's keys. The reference is a logit that the row has met, not its running

@@ -55,3 +55,25 @@ def test_buffer_offsets_are_range_checked(assembly):
                 operands = line.split("s[", 1)[1]                  # resource, scalar offset, modifiers
                 assert re.match(r"\d+:\d+\], 0( |$)", operands), (name, line)
     assert seen > 0
+
+
+@pytest.fixture(scope="module")
+def resources(code_objects):
+    """Kernel -> (vector registers, spilled vector registers, threads of its largest workgroup)."""
+    out = {}
+    for f in code_objects:
+        notes = subprocess.run([f"{LLVM}/llvm-readelf", "--notes", f], check=True, capture_output=True, text=True).stdout
+        for kernel in re.split(r"\n  - (?=\.)", notes)[1:]:
+            def value(key):
+                return re.search(rf"^\s*{re.escape(key)}:\s+(\S+)", kernel, re.M).group(1)
+            name = subprocess.run(["c++filt", value(".name").strip("'")], check=True, capture_output=True, text=True).stdout.strip()
+            out[name] = int(value(".vgpr_count")), int(value(".vgpr_spill_count")), int(value(".max_flat_workgroup_size"))
+    return out
+
+
+def test_score_kernels_keep_their_registers(resources):
+    """No spills, and at head_dim 256 three waves per SIMD (512 registers) where that decides how many workgroups share a CU."""
+    for name, (vgprs, spills, _) in named(resources, "score_kernel<").items():
+        assert spills == 0, (name, spills)
+        if re.search(r"<256, 1, [124], true>", name):
+            assert vgprs <= 168, (name, vgprs)
