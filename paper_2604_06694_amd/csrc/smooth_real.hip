@@ -55,22 +55,24 @@ __device__ __forceinline__ double wave_scan(double v) {      // inclusive, over 
 }
 
 // Adaptive cutoff (Eqs. 14-16): the smallest k >= first with sum_{first<=i<=k} e[i] >= rho * sum_{first<=i<n_bins} e[i].
-// Bin energies fp32, sums float64: every thread adds a run of PER consecutive bins, which it keeps, the runs' totals are scanned,
-// and the thread whose run crosses the target walks it again. Uniform result. (Runs read twice from LDS, one bin after the other,
-// and a scan by LDS permutes: smooth calls on four heads of 8192 13.2 -> 12.6 us,
-// of 2048 10.0 -> 9.1.)
+// Bin energies fp32, sums float64: every thread adds a run of PER consecutive bins, all requested at once, the runs' totals are
+// scanned, and the thread whose run crosses the target walks it again. Uniform result. (Runs read one bin after the other and a
+// scan by LDS permutes: smooth calls on four heads of 8192 13.2 -> 12.6 us, of 2048 10.0 -> 9.1. Runs kept in registers for the second
+// walk cost all threads what one reads in a moment.)
 template <int T, int PER, class Lds>
 __device__ __forceinline__ int energy_search(const float* e, int n_bins, int first, double rho, Lds& m) {
     constexpr int kWaves = (T + 63) / 64;
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
     const int k0 = t * PER;                                  // (the last threads may have no bins)
-    float run[PER];
-#pragma unroll
-    for (int u = 0; u < PER; ++u) run[u] = e[min(k0 + u, n_bins - 1)];
     const auto counts = [&](int u) { return k0 + u >= first && k0 + u < n_bins; };
     double mine = 0.0;
+    {
+        float run[PER];
 #pragma unroll
-    for (int u = 0; u < PER; ++u) mine += counts(u) ? (double)run[u] : 0.0;
+        for (int u = 0; u < PER; ++u) run[u] = e[min(k0 + u, n_bins - 1)];
+#pragma unroll
+        for (int u = 0; u < PER; ++u) mine += counts(u) ? (double)run[u] : 0.0;
+    }
     double incl = wave_scan(mine);
     if (lane == 63) m.part[wave] = incl;
     if (t == 0) { m.cross_wave = T; m.kstar = min(first, n_bins - 1); }
@@ -88,6 +90,9 @@ __device__ __forceinline__ int energy_search(const float* e, int n_bins, int fir
     if (t == m.cross_wave) {
         double acc = incl - mine;
         int ks = min(k0 + PER, n_bins) - 1;                  // (rounding between the two summation orders)
+        float run[PER];
+#pragma unroll
+        for (int u = 0; u < PER; ++u) run[u] = e[min(k0 + u, n_bins - 1)];
         bool found = false;
 #pragma unroll
         for (int u = 0; u < PER; ++u) {
@@ -109,7 +114,7 @@ __device__ __forceinline__ float bin_weight(int k, int kstar, int T) {
 }
 
 // POOL: 0 none, 7 the usual size, 1 any size up to 9
-template <int LOGC, int POOL>
+template <int LOGC, int POOL, bool ENERGY>
 __device__ __forceinline__ void smooth_real_head(
     const Geom& g, const float* __restrict__ src, double cutoff_frac, float alpha, float* __restrict__ dst,
     int32_t* __restrict__ kstar_out, int cutoffs_only, unsigned char* smem)
@@ -118,7 +123,8 @@ __device__ __forceinline__ void smooth_real_head(
     using F = Fft<LOGC, VT>;
     constexpr int N = 1 << LOGC, L = 2 * N, T = F::THREADS;
     RealLds<LOGC>& m = *reinterpret_cast<RealLds<LOGC>*>(smem);
-    const int head = blockIdx.x, t = threadIdx.x;
+    const int head = blockIdx.x;
+    int t = threadIdx.x;
 
     // ---- samples 2 n, 2 n + 1 of the points n of the first layout ----
     cf v[VT][8];
@@ -171,36 +177,35 @@ __device__ __forceinline__ void smooth_real_head(
             const cf d = csub(A, B);
             O = {0.5f * d.im, -0.5f * d.re};                 // -i (A - B) / 2
         };
-        // (N = 16384 is not launched with an energy-adaptive cutoff: sixteen points and sixteen partners per thread do not
-        // fit 128 registers)
+        static_assert(!ENERGY || VT == 1, "sixteen points and sixteen partners per thread do not fit 128 registers");
         cf other[VT][8];                                     // (filled where the energies need every bin)
-        const bool energy = LOGC < 14 && g.cutoff_mode != AUDIOKV_CUTOFF_FRACTION;
-        if (energy) {
-            float en[VT][8];
+        typename F::BinRoots roots_of_bins(t);
+        if constexpr (ENERGY) {
+            float en[8];
 #pragma unroll
-            for (int vt = 0; vt < VT; ++vt) {
-                const typename F::BinRoots root(t + vt * T);
-#pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    const int k = F::bin_of(8 * (t + vt * T) + e);
-                    other[vt][e] = partner(k);
-                    cf E, O;
-                    even_odd(v[vt][e], other[vt][e], E, O);
-                    const cf X = cadd(E, mul(root(e), O));
-                    en[vt][e] = fmaf(X.re, X.re, X.im * X.im);
-                    if (k == 0) { const float x = z0.re + z0.im; en[vt][e] = x * x; }
-                }
+            for (int e = 0; e < 8; ++e) {
+                const int k = F::bin_of(8 * t + e);
+                other[0][e] = partner(k);
+                cf E, O;
+                even_odd(v[0][e], other[0][e], E, O);
+                const cf X = cadd(E, mul(roots_of_bins(e), O));
+                en[e] = fmaf(X.re, X.re, X.im * X.im);
+                if (k == 0) { const float x = z0.re + z0.im; en[e] = x * x; }
             }
             __syncthreads();                                 // all partners are read
             float* ek = reinterpret_cast<float*>(m.z);
 #pragma unroll
-            for (int vt = 0; vt < VT; ++vt)
-#pragma unroll
-                for (int e = 0; e < 8; ++e) ek[F::bin_of(8 * (t + vt * T) + e)] = en[vt][e];
+            for (int e = 0; e < 8; ++e) ek[F::bin_of(8 * t + e)] = en[e];
             if (t == 0) { const float x = z0.re - z0.im; ek[N] = x * x; }
             __syncthreads();
             kstar = energy_search<T, N / T + 1>(ek, N + 1, first, cutoff_frac, m);
             __syncthreads();
+#if defined(__HIP_DEVICE_COMPILE__)
+            // (what the energies were made of is formed again below: kept across the search it takes 40 registers)
+            asm volatile("" : "+v"(roots_of_bins.base.re), "+v"(roots_of_bins.base.im), "+v"(t));
+#pragma unroll
+            for (int e = 0; e < 8; ++e) asm volatile("" : "+v"(other[0][e].re), "+v"(other[0][e].im));
+#endif
         }
         if (kstar_out && t == 0) kstar_out[head] = kstar;
         if (cutoffs_only) return;
@@ -212,7 +217,7 @@ __device__ __forceinline__ void smooth_real_head(
         const int ktop = kstar + Tb;                         // last bin with a non-zero weight
 #pragma unroll
         for (int vt = 0; vt < VT; ++vt) {
-            const typename F::BinRoots root(t + vt * T);
+            const typename F::BinRoots root = ENERGY ? roots_of_bins : typename F::BinRoots(t + vt * T);
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
                 const int k = F::bin_of(8 * (t + vt * T) + e);
@@ -223,7 +228,7 @@ __device__ __forceinline__ void smooth_real_head(
                         o = {0.5f * (X0 + XN), 0.5f * (X0 - XN)};
                     } else {
                         cf E, O;
-                        even_odd(v[vt][e], energy ? other[vt][e] : partner(k), E, O);
+                        even_odd(v[vt][e], ENERGY ? other[vt][e] : partner(k), E, O);
                         const cf Wk = root(e), WO = mul(Wk, O);
                         const float wk = bin_weight(k, kstar, Tb), wn = bin_weight(N - k, kstar, Tb);
                         const cf X = cadd(E, WO), Y = csub(E, WO);           // bin k; conjugate of bin N - k
@@ -279,7 +284,11 @@ __device__ __forceinline__ int head_span(const Geom& g, const int32_t* __restric
     return L;
 }
 
-template <int LOGC, int POOL>
+// ENERGY: the cutoff is energy-adaptive. As a branch in one kernel its bins and partners cost the fixed cutoff registers too: with
+// 16384 samples it spilled, with 8192 a CU held one workgroup instead of two. Smooth calls, in one kernel and apart: fixed cutoff 192
+// heads of 16384 15.4 and 14.3 us, 320 of 8192 15.0 and 11.3; energy-adaptive 320 of 8192 25.3 and 18.4, 192 of 16384 23.0 and 21.6.
+// (N = 16384 is not built with an energy-adaptive cutoff: sixteen points and sixteen partners per thread do not fit 128 registers)
+template <int LOGC, int POOL, bool ENERGY>
 __global__ __launch_bounds__(kRealThreads<LOGC>) void smooth_real_kernel(
     Geom g, const float* __restrict__ in, const int32_t* __restrict__ cu_seq, double cutoff_frac, float alpha,
     float* __restrict__ out, int32_t* __restrict__ kstar_out, int cutoffs_only)
@@ -287,13 +296,13 @@ __global__ __launch_bounds__(kRealThreads<LOGC>) void smooth_real_kernel(
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     size_t off;
     if (head_span(g, cu_seq, blockIdx.x, off) != 2 << LOGC) return;      // another launch's head
-    smooth_real_head<LOGC, POOL>(g, in + off, cutoff_frac, alpha, out + off, kstar_out, cutoffs_only, smem);
+    smooth_real_head<LOGC, POOL, ENERGY>(g, in + off, cutoff_frac, alpha, out + off, kstar_out, cutoffs_only, smem);
 }
 
 // A call of several lengths: all heads in one launch, as many threads as the longest takes. The waves that a shorter head does
 // not need end at once (a barrier waits for the waves that are left). One launch per length instead would add up the times of
 // what runs side by side here: one call of four heads each of 1024, 2048, .. 16384 samples took 40.1 us, 13.5 in one launch (longest alone 13.8).
-template <int POOL>
+template <int POOL, bool ENERGY>
 __global__ __launch_bounds__(1024) void smooth_mixed_kernel(
     Geom g, const float* __restrict__ in, const int32_t* __restrict__ cu_seq, double cutoff_frac, float alpha,
     float* __restrict__ out, int32_t* __restrict__ kstar_out, int cutoffs_only, unsigned lengths)
@@ -306,7 +315,7 @@ __global__ __launch_bounds__(1024) void smooth_mixed_kernel(
 #define AUDIOKV_MIXED(LOGC)                                                                                               \
     case 2 << LOGC:                                                                                                      \
         if (wave < kRealThreads<LOGC> / 64)                                                                               \
-            smooth_real_head<LOGC, POOL>(g, in + off, cutoff_frac, alpha, out + off, kstar_out, cutoffs_only, smem);      \
+            smooth_real_head<LOGC, POOL, ENERGY>(g, in + off, cutoff_frac, alpha, out + off, kstar_out, cutoffs_only, smem); \
         break
     switch (L) {
         AUDIOKV_MIXED(9);
@@ -314,7 +323,10 @@ __global__ __launch_bounds__(1024) void smooth_mixed_kernel(
         AUDIOKV_MIXED(11);
         AUDIOKV_MIXED(12);
         AUDIOKV_MIXED(13);
-        AUDIOKV_MIXED(14);
+        case 2 << 14:
+            if constexpr (!ENERGY)
+                smooth_real_head<14, POOL, false>(g, in + off, cutoff_frac, alpha, out + off, kstar_out, cutoffs_only, smem);
+            break;
     }
 #undef AUDIOKV_MIXED
 }
@@ -330,23 +342,23 @@ size_t real_lds(int L) {
     }
 }
 
-template <int POOL>
+template <int POOL, bool ENERGY>
 hipError_t launch_mixed(unsigned lengths, const Geom& g, const float* in, const int32_t* cu_seqlens, double cutoff_frac, float alpha,
                         float* out, int32_t* kstar_out, bool cutoffs_only, hipStream_t s) {
     const int longest = 1 << (31 - __builtin_clz(lengths));
     static std::atomic<bool> attr_set{false};
     if (!attr_set) {
-        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(smooth_mixed_kernel<POOL>),
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(smooth_mixed_kernel<POOL, ENERGY>),
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(RealLds<14>));
         if (e != hipSuccess) return e;
         attr_set = true;
     }
-    hipLaunchKernelGGL((smooth_mixed_kernel<POOL>), dim3((unsigned)(g.n_items * g.H_kv)), dim3(std::min(longest / 16, 1024)),
+    hipLaunchKernelGGL((smooth_mixed_kernel<POOL, ENERGY>), dim3((unsigned)(g.n_items * g.H_kv)), dim3(std::min(longest / 16, 1024)),
                        real_lds(longest), s, g, in, cu_seqlens, cutoff_frac, alpha, out, kstar_out, cutoffs_only ? 1 : 0, lengths);
     return hipGetLastError();
 }
 
-template <int LOGC, int POOL>
+template <int LOGC, int POOL, bool ENERGY>
 hipError_t launch(const Geom& g, const float* in, const int32_t* cu_seqlens, double cutoff_frac, float alpha, float* out,
                   int32_t* kstar_out, bool cutoffs_only, hipStream_t s) {
     constexpr int T = kRealThreads<LOGC>;
@@ -354,43 +366,53 @@ hipError_t launch(const Geom& g, const float* in, const int32_t* cu_seqlens, dou
     if (lds > 48 * 1024) {
         static std::atomic<bool> attr_set{false};
         if (!attr_set) {
-            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(smooth_real_kernel<LOGC, POOL>),
+            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(smooth_real_kernel<LOGC, POOL, ENERGY>),
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, lds);
             if (e != hipSuccess) return e;
             attr_set = true;
         }
     }
-    hipLaunchKernelGGL((smooth_real_kernel<LOGC, POOL>), dim3((unsigned)(g.n_items * g.H_kv)), dim3(T), lds, s, g, in, cu_seqlens,
+    hipLaunchKernelGGL((smooth_real_kernel<LOGC, POOL, ENERGY>), dim3((unsigned)(g.n_items * g.H_kv)), dim3(T), lds, s, g, in, cu_seqlens,
                        cutoff_frac, alpha, out, kstar_out, cutoffs_only ? 1 : 0);
     return hipGetLastError();
 }
 
-template <int LOGC>
+template <int LOGC, bool ENERGY>
 hipError_t launch(const Geom& g, const float* in, bool pool_on_load, const int32_t* cu_seqlens, double cutoff_frac, float alpha,
                   float* out, int32_t* kstar_out, bool cutoffs_only, hipStream_t s) {
-    if (!pool_on_load) return launch<LOGC, 0>(g, in, cu_seqlens, cutoff_frac, alpha, out, kstar_out, cutoffs_only, s);
-    if (g.pool_kernel == 7) return launch<LOGC, 7>(g, in, cu_seqlens, cutoff_frac, alpha, out, kstar_out, cutoffs_only, s);
-    return launch<LOGC, 1>(g, in, cu_seqlens, cutoff_frac, alpha, out, kstar_out, cutoffs_only, s);
+    if (!pool_on_load) return launch<LOGC, 0, ENERGY>(g, in, cu_seqlens, cutoff_frac, alpha, out, kstar_out, cutoffs_only, s);
+    if (g.pool_kernel == 7) return launch<LOGC, 7, ENERGY>(g, in, cu_seqlens, cutoff_frac, alpha, out, kstar_out, cutoffs_only, s);
+    return launch<LOGC, 1, ENERGY>(g, in, cu_seqlens, cutoff_frac, alpha, out, kstar_out, cutoffs_only, s);
+}
+
+template <bool ENERGY>
+hipError_t launch_lengths(unsigned lengths, const Geom& g, const float* in, bool pool_on_load, const int32_t* cu_seqlens, double cutoff_frac,
+                          float alpha, float* out, int32_t* kstar_out, bool cutoffs_only, hipStream_t s) {
+    if (ENERGY && lengths >= 32768) return hipErrorInvalidValue;
+    if (lengths & (lengths - 1)) {
+        if (!pool_on_load) return launch_mixed<0, ENERGY>(lengths, g, in, cu_seqlens, cutoff_frac, alpha, out, kstar_out, cutoffs_only, s);
+        if (g.pool_kernel == 7) return launch_mixed<7, ENERGY>(lengths, g, in, cu_seqlens, cutoff_frac, alpha, out, kstar_out, cutoffs_only, s);
+        return launch_mixed<1, ENERGY>(lengths, g, in, cu_seqlens, cutoff_frac, alpha, out, kstar_out, cutoffs_only, s);
+    }
+    switch (lengths) {
+        case 1024:  return launch<9, ENERGY>(g, in, pool_on_load, cu_seqlens, cutoff_frac, alpha, out, kstar_out, cutoffs_only, s);
+        case 2048:  return launch<10, ENERGY>(g, in, pool_on_load, cu_seqlens, cutoff_frac, alpha, out, kstar_out, cutoffs_only, s);
+        case 4096:  return launch<11, ENERGY>(g, in, pool_on_load, cu_seqlens, cutoff_frac, alpha, out, kstar_out, cutoffs_only, s);
+        case 8192:  return launch<12, ENERGY>(g, in, pool_on_load, cu_seqlens, cutoff_frac, alpha, out, kstar_out, cutoffs_only, s);
+        case 16384: return launch<13, ENERGY>(g, in, pool_on_load, cu_seqlens, cutoff_frac, alpha, out, kstar_out, cutoffs_only, s);
+        case 32768:
+            if constexpr (!ENERGY) return launch<14, false>(g, in, pool_on_load, cu_seqlens, cutoff_frac, alpha, out, kstar_out, cutoffs_only, s);
+    }
+    return hipErrorInvalidValue;
 }
 
 }  // namespace
 
 hipError_t launch_smooth_real(unsigned lengths, const Geom& g, const float* in, bool pool_on_load, const int32_t* cu_seqlens, double cutoff_frac,
                               float alpha, float* out, int32_t* kstar_out, bool cutoffs_only, hipStream_t s) {
-    if (lengths & (lengths - 1)) {
-        if (!pool_on_load) return launch_mixed<0>(lengths, g, in, cu_seqlens, cutoff_frac, alpha, out, kstar_out, cutoffs_only, s);
-        if (g.pool_kernel == 7) return launch_mixed<7>(lengths, g, in, cu_seqlens, cutoff_frac, alpha, out, kstar_out, cutoffs_only, s);
-        return launch_mixed<1>(lengths, g, in, cu_seqlens, cutoff_frac, alpha, out, kstar_out, cutoffs_only, s);
-    }
-    switch (lengths) {
-        case 1024:  return launch<9>(g, in, pool_on_load, cu_seqlens, cutoff_frac, alpha, out, kstar_out, cutoffs_only, s);
-        case 2048:  return launch<10>(g, in, pool_on_load, cu_seqlens, cutoff_frac, alpha, out, kstar_out, cutoffs_only, s);
-        case 4096:  return launch<11>(g, in, pool_on_load, cu_seqlens, cutoff_frac, alpha, out, kstar_out, cutoffs_only, s);
-        case 8192:  return launch<12>(g, in, pool_on_load, cu_seqlens, cutoff_frac, alpha, out, kstar_out, cutoffs_only, s);
-        case 16384: return launch<13>(g, in, pool_on_load, cu_seqlens, cutoff_frac, alpha, out, kstar_out, cutoffs_only, s);
-        case 32768: return launch<14>(g, in, pool_on_load, cu_seqlens, cutoff_frac, alpha, out, kstar_out, cutoffs_only, s);
-    }
-    return hipErrorInvalidValue;
+    if (g.cutoff_mode == AUDIOKV_CUTOFF_FRACTION)
+        return launch_lengths<false>(lengths, g, in, pool_on_load, cu_seqlens, cutoff_frac, alpha, out, kstar_out, cutoffs_only, s);
+    return launch_lengths<true>(lengths, g, in, pool_on_load, cu_seqlens, cutoff_frac, alpha, out, kstar_out, cutoffs_only, s);
 }
 
 }  // namespace audiokv

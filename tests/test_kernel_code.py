@@ -77,3 +77,11 @@ def test_score_kernels_keep_their_registers(resources):
         assert spills == 0, (name, spills)
         if re.search(r"<256, 1, [124], true>", name):
             assert vgprs <= 168, (name, vgprs)
+
+
+def test_smoothing_kernels_keep_their_registers(resources):
+    """Power-of-two heads up to 16384 samples: no spills, and never more than 128 registers, with which the workgroups of up to 512
+    threads fill a CU twice. (32768 samples, sixteen points per thread, spill.)"""
+    for name, (vgprs, spills, _) in named(resources, "smooth_real_kernel<").items():
+        if not re.search(r"smooth_real_kernel<14, ", name):
+            assert spills == 0 and vgprs <= 128, (name, vgprs, spills)
