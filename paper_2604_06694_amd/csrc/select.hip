@@ -9,18 +9,18 @@
 // between rarely leaves and where no part holds many tokens, whatever the tails
 // are like. The candidates in that part, 64 at most, are ranked against each
 // other by every wave for itself, by score and, among equals, by index (ties
-// are kept in index order). That gives the threshold as a score T and an index
-// X: a token stays if its score is larger than T, or equal to T and its index
-// at most X. For a fixed register the lanes of a wave hold 64 consecutive
-// tokens, so one lane mask gives every (register, wave) chunk its count, a scan
-// over the chunks their output offsets, and every kept token computes its own
-// ascending output slot from the offset and its rank in the lane mask.
+// are kept in index order). That gives the threshold as a score T and the
+// number of tokens to keep that equal it: a token stays if its score is larger
+// than T, or equal to T and the token among the first that many. For a fixed
+// register the lanes of a wave hold 64 consecutive tokens, so one lane mask
+// gives every (register, wave) chunk its count, a scan over the chunks their
+// output offsets, and every kept token computes its own ascending output slot
+// from the offset and its rank in the lane mask; equal ones are counted along.
 //
 // More than 64 candidates in the part, and scores that are not finite: the
 // general search. Scores become order-preserving 32-bit keys, and the keys'
-// range is divided into 2048 parts, the part with the threshold again, and
-// once its keys are all equal, the token indices: key and index together order
-// the candidates strictly, so the rounds end. Both ways compare and count only
+// range is divided into 2048 parts, and the part with the threshold again,
+// until it holds few or one value only. Both ways compare and count only
 // (the mean and the deviation choose where the parts lie, nothing else): the
 // result is exact, and the same whichever way it was found.
 //
@@ -32,7 +32,14 @@
 // 5.1 -> 4.4 us, 13577 12.5 -> 9.1, 32768 20.8 -> 15.5; 112 heads of 8192 10.4 ->
 // 9.7, 32768 22.9 -> 18.7; 16 ragged heads 17.0 -> 13.2. Normal scores, which need
 // one round either way: four heads of 32768 15.7 -> 13.5. Scores of a few dozen
-// values only, which go to the general search after all: 32.5 -> 35.5.
+// values crowd the threshold's part with one value: then that value is the
+// threshold, and rounds over the indices of its tokens are not needed. Calls,
+// general search with those rounds -> the division with them -> this: four heads
+// of 32768 32.8 -> 35.2 -> 22.9 us, of 16385 23.9 -> 28.9 -> 19.4, 800 of 9000 56 ->
+// 61 -> 44, 8000 of 500 39 -> 41 -> 39.
+// Short heads in large numbers are bound by the instructions of a wave (sums
+// over 8 or 16 lanes in three or four steps, reciprocals and roots as one
+// instruction: 8000 heads of 500 32.8 -> 30.3 us, general search 31.8).
 // Two, four or eight workgroups per head that each find the threshold and write
 // a part gained nothing with four heads and lost with 112: every one of them
 // has to load the whole head.
@@ -112,12 +119,23 @@ __device__ __forceinline__ void lds_barrier() {
         x = op(x, AUDIOKV_DPP_F(x, 0x142, 0xa, none));      \
         x = op(x, AUDIOKV_DPP_F(x, 0x143, 0xc, none));      \
     } while (0)
+// the same over the first N lanes, a power of two up to 16: in lane N - 1
+#define AUDIOKV_ROW_FOLD(op, x, none, N)                    \
+    do {                                                    \
+        x = op(x, AUDIOKV_DPP_F(x, 0x111, 0xf, none));      \
+        if (N > 2) x = op(x, AUDIOKV_DPP_F(x, 0x112, 0xf, none)); \
+        if (N > 4) x = op(x, AUDIOKV_DPP_F(x, 0x114, 0xf, none)); \
+        if (N > 8) x = op(x, AUDIOKV_DPP_F(x, 0x118, 0xf, none)); \
+    } while (0)
 __device__ __forceinline__ float plus(float a, float b) { return a + b; }
 __device__ __forceinline__ float wave_sum63(float x) { AUDIOKV_WAVE_FOLD(plus, x, 0.f); return x; }
 __device__ __forceinline__ float wave_max63(float x) { AUDIOKV_WAVE_FOLD(fmaxf, x, -INFINITY); return x; }
+template <int N> __device__ __forceinline__ float row_sum(float x) { AUDIOKV_ROW_FOLD(plus, x, 0.f, N); return x; }
+template <int N> __device__ __forceinline__ float row_max(float x) { AUDIOKV_ROW_FOLD(fmaxf, x, -INFINITY, N); return x; }
 __device__ __forceinline__ float lane_float(float x, int lane) {           // uniform lane
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), lane));
 }
+#undef AUDIOKV_ROW_FOLD
 #undef AUDIOKV_WAVE_FOLD
 #undef AUDIOKV_DPP_F
 
@@ -133,6 +151,16 @@ __device__ __forceinline__ int wave_incl(int x) {
     x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);
     x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);   // row_bcast 15 into rows 1 and 3
     x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);   // row_bcast 31 into rows 2 and 3
+    return x;
+}
+
+// the same over the first N lanes, a power of two up to 16
+template <int N>
+__device__ __forceinline__ int row_incl(int x) {
+    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);
+    if (N > 2) x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);
+    if (N > 4) x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);
+    if (N > 8) x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);
     return x;
 }
 
@@ -234,7 +262,15 @@ __global__ __launch_bounds__(NT) void select_kernel(
 
     // (a buffer of the candidates' size reads as zero past its end: no clamped addresses, all loads of a thread in flight. As with
     // the stores above, the whole offset is in the operand that is checked.)
-    const auto live = [&](int e) { return tid < n_cand - e * NT; };
+    // A value that the compiler is to take for another one from here on: lane masks of comparisons with it are formed again
+    // where they are needed again, instead of 32 pairs of scalar registers being kept (and spilled).
+    auto renewed = [](auto& v) {
+#if defined(__HIP_DEVICE_COMPILE__)
+        asm volatile("" : "+s"(v));
+#endif
+    };
+    int n_live = n_cand;
+    const auto live = [&](int e) { return tid < n_live - e * NT; };
     const auto full = [&](int e) { return (e + 1) * NT <= n_cand; };            // uniform
     const auto any = [&](int e) { return e * NT + wave_at < n_cand; };          // uniform over the wave
     const auto buf = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(s), 0, n_cand * 4, 0x00027000);
@@ -280,16 +316,16 @@ __global__ __launch_bounds__(NT) void select_kernel(
     float hi, inv;
     {
         const auto of_wave = [&](int which, float none) { return lane < NW ? part[which * NW + (lane < NW ? lane : 0)] : none; };
-        const float n_inv = 1.f / (float)n_cand, mean = lane_float(wave_sum63(of_wave(0, 0.f)), 63) * n_inv;
-        const float dev = sqrtf(fmaxf(fmaf(-mean, mean, lane_float(wave_sum63(of_wave(1, 0.f)), 63) * n_inv), 0.f));
+        const float n_inv = __builtin_amdgcn_rcpf((float)n_cand), mean = lane_float(row_sum<NW>(of_wave(0, 0.f)), NW - 1) * n_inv;
+        const float dev = __builtin_amdgcn_sqrtf(fmaxf(fmaf(-mean, mean, lane_float(row_sum<NW>(of_wave(1, 0.f)), NW - 1) * n_inv), 0.f));
         hi = fmaf(2.f, dev, mean);
         float lo = fmaf(-2.f, dev, mean);
         if (few || most) {
-            const float top = lane_float(wave_max63(of_wave(2, -INFINITY)), 63);
+            const float top = lane_float(row_max<NW>(of_wave(2, -INFINITY)), NW - 1);
             if (few) hi = fmaxf(hi, top);
             else lo = fminf(lo, -top);
         }
-        inv = (float)kFine / (hi - lo);
+        inv = (float)kFine * __builtin_amdgcn_rcpf(hi - lo);
         if (!(inv > 0.f && fabsf(hi) * inv < INFINITY)) inv = 0.f;       // no number, no end, or no width: the general search
     }
     // part of a score: falls as the score rises, rounded and cut off alike for all
@@ -301,6 +337,7 @@ __global__ __launch_bounds__(NT) void select_kernel(
     for (int e = 0; e < EPT; ++e)
         if (!full(e)) x[e] = live(e) ? x[e] : -INFINITY;
 
+    renewed(n_live);
     int rank = want, inside = n_cand;
     // Adds to one part take their turns, which a long head with many equal scores would wait for: a wave that finds a quarter
     // of the lanes of a register in one part counts that part from lane masks and adds it once (half zeros at 32768 tokens
@@ -352,10 +389,10 @@ __global__ __launch_bounds__(NT) void select_kernel(
             before = l > 0 ? __builtin_amdgcn_readlane(upto, l > 0 ? l - 1 : 0) : before;
             return l;
         };
-        const int w = first_at(wave_incl(lane < NW ? wave_n[lane < NW ? lane : 0] : 0)) & (NW - 1);
+        const int w = first_at(row_incl<NW>(lane < NW ? wave_n[lane < NW ? lane : 0] : 0)) & (NW - 1);
         const int t = w * 64 + first_at(before + upto_thread[w * 64 + lane]);
         const int n_at = lane < kFinePer ? hist[t * kFinePer + (lane < kFinePer ? lane : 0)] : 0;
-        const int u = first_at(before + wave_incl(n_at)) & (kFinePer - 1);
+        const int u = first_at(before + row_incl<kFinePer>(n_at)) & (kFinePer - 1);
         inside = __builtin_amdgcn_readlane(n_at, u);
         rank -= before;
         return t * kFinePer + u;
@@ -384,8 +421,8 @@ __global__ __launch_bounds__(NT) void select_kernel(
 
     // The 64 candidates at most that are left: every wave ranks them by (score falling, index), one per lane, against all. No
     // two are equal, so exactly one is number `rank`.
-    // (more: others share its score and come after it)
-    auto rank_last = [&](uint32_t& at, int& index, bool& more) {
+    // (rank: afterwards among those that share its score; more: some of them come after it)
+    auto rank_last = [&](uint32_t& at, bool& more) {
         lds_barrier();
         const int n_last = min(last_n, kLast);
         const unsigned long long mine = last[min(lane, n_last - 1)];
@@ -394,27 +431,21 @@ __global__ __launch_bounds__(NT) void select_kernel(
         for (int i = 0; i < n_last; ++i) upto += last[i] <= mine ? 1 : 0;
         const int winner = __builtin_ctzll(__builtin_amdgcn_ballot_w64(upto == rank) | (1ull << 63));
         at = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(mine >> 32), winner);
-        index = __builtin_amdgcn_readlane((int)(uint32_t)mine, winner);
-        more = __builtin_amdgcn_ballot_w64((uint32_t)(mine >> 32) == at && (int)(uint32_t)mine > index) != 0;
+        more = __builtin_amdgcn_ballot_w64((uint32_t)(mine >> 32) == at && upto > rank) != 0;
+        rank -= __builtin_popcountll(__builtin_amdgcn_ballot_w64(lane < n_last && (uint32_t)(mine >> 32) < at));
     };
     auto put_last = [&](uint32_t order, int e) {
         const int pos = atomicAdd(&last_n, 1);
         if (pos < kLast) last[pos] = ((unsigned long long)order << 32) | (uint32_t)(tid + e * NT);
     };
 
-    // For a fixed register e, wave w holds the 64 consecutive tokens of chunk e * NW + w.
-    auto write = [&](auto kept) {
-        // Count the chunk's kept tokens from lane masks (lane e collects register e) ...
-        int my_n = 0;
-#pragma unroll
-        for (int e = 0; e < EPT; ++e) {
-            const int c = __builtin_popcountll(__builtin_amdgcn_ballot_w64(kept(e)));
-            asm volatile("v_writelane_b32 %0, %1, %2" : "+v"(my_n) : "s"(c), "n"(e));
-        }
+    // For a fixed register e, wave w holds the 64 consecutive tokens of chunk e * NW + w. Counts of the chunks (lane e has that of
+    // register e), scanned: every wave scans all the chunks for itself, kChunkPer per lane, and has those ahead of its own in
+    // lane (e * NW + wave) / kChunkPer.
+    auto scan_chunks = [&](int my_n) {
         if (lane < EPT) chunk_n[lane * NW + wave] = my_n;
         if (kChunks < 64 && tid >= kChunks && tid < 64) chunk_n[tid] = 0;
         lds_barrier();
-        // ... every wave scans all the chunks for itself, kChunkPer per lane, and reads off the offsets of its own ...
         int sum = 0, ahead = 0;                      // a lane's chunks; those before the one of this wave
 #pragma unroll
         for (int u = 0; u < kChunkPer; ++u) {
@@ -422,149 +453,169 @@ __global__ __launch_bounds__(NT) void select_kernel(
             if (u < (wave & (kChunkPer - 1))) ahead += c;
             sum += c;
         }
-        ahead += wave_incl(sum) - sum;
-        // ... and every kept token writes itself to its slot: the slots of a wave's tokens are consecutive, so each store
-        // instruction writes one run of the output.
+        return ahead + (wave_incl(sum) - sum);
+    };
+    const auto lanes_before = [&](unsigned long long m, int from) {
+        return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, (uint32_t)from));
+    };
+
+    // Writes the tokens that are larger than the threshold, and the first `rank` of those equal to it. Both are counted per
+    // chunk, in two halves of a number (32768 tokens at most).
+    auto write_first = [&](uint32_t threshold, auto larger, auto equal) {
+        int my_n = 0;
 #pragma unroll
         for (int e = 0; e < EPT; ++e) {
-            const bool k = kept(e);
-            const unsigned long long m = __builtin_amdgcn_ballot_w64(k);
-            const int at = __builtin_amdgcn_readlane(ahead, (e * NW + wave) / kChunkPer);
-            const int pos = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, (uint32_t)at));
+            if (EPT <= 4 && !any(e)) continue;       // (four registers are what the shortest heads have: most of them empty)
+            const int c = __builtin_popcountll(__builtin_amdgcn_ballot_w64(larger(e, threshold))) |
+                          __builtin_popcountll(__builtin_amdgcn_ballot_w64(equal(e, threshold))) << 16;
+            asm volatile("v_writelane_b32 %0, %1, %2" : "+v"(my_n) : "s"(c), "n"(e));
+        }
+        const int ahead = scan_chunks(my_n);
+        renewed(threshold);
+#pragma unroll
+        for (int e = 0; e < EPT; ++e) {
+            if (EPT <= 4 && !any(e)) continue;
+            const uint32_t at = (uint32_t)__builtin_amdgcn_readlane(ahead, (e * NW + wave) / kChunkPer);
+            const int equal_before = (int)(at >> 16), first = (int)(at & 0xffffu) + min(equal_before, rank);
+            const bool same = equal(e, threshold);
+            const bool k = larger(e, threshold) || (same && lanes_before(__builtin_amdgcn_ballot_w64(same), equal_before) < rank);
+            const int pos = lanes_before(__builtin_amdgcn_ballot_w64(k), first);
             if (k && pos < want) out[pos] = tid + e * NT;
         }
     };
 
+    uint32_t T;                                      // the threshold's order key
     if (divided && inside <= kLast) {
 #pragma unroll
         for (int e = 0; e < EPT; ++e)
             if (in_part(e) && live(e)) put_last(~order_key(x[e]), e);
-        uint32_t at;
-        int X;
         bool more;
-        rank_last(at, X, more);
-        const float T = key_value(~at);
-        if (more)                                    // (uniform) all that share a score are in its part
+        rank_last(T, more);
+        T = ~T;
+        if (!more) {                                 // (uniform) all that share the threshold's score stay
+            uint32_t least = __float_as_uint(key_value(T));
+            int my_n = 0;
 #pragma unroll
-            for (int e = 0; e < EPT; ++e) x[e] = x[e] == T && tid > X - e * NT ? -INFINITY : x[e];
-        write([&](int e) { return x[e] >= T; });
-        return;
-    }
-
-    // ---- the general search, among what is in the part found so far (or all candidates) ----
-    // From here on a key is its distance below the largest one, and what is no candidate is further than all (keys are at
-    // least 1, which only the lowest NaN would not be, so no distance is 0xffffffff). The order: shorter distances first, of
-    // equal ones the smaller index.
-    lds_barrier();                                 // (the parts' counts are read)
-    uint32_t key[EPT];
-    uint32_t big = 0, small = 0;                     // (the complement of the smallest)
+            for (int e = 0; e < EPT; ++e) {
+                const int c = __builtin_popcountll(__builtin_amdgcn_ballot_w64(x[e] >= __uint_as_float(least)));
+                asm volatile("v_writelane_b32 %0, %1, %2" : "+v"(my_n) : "s"(c), "n"(e));
+            }
+            const int ahead = scan_chunks(my_n);
+            renewed(least);
+            // every kept token writes itself to its slot: the slots of a wave's tokens are consecutive, so each store
+            // instruction writes one run of the output
 #pragma unroll
-    for (int e = 0; e < EPT; ++e) {
-        const bool c = live(e) && (!divided || in_part(e));
-        key[e] = c ? max(order_key(x[e]), 1u) : 0u;
-        big = max(big, key[e]);
-        small = max(small, c ? ~key[e] : 0u);
-    }
-#pragma unroll
-    for (int u = 0; u < kPer; ++u) hist[tid + u * NT] = 0;
-    big = wave_max63(big);
-    small = wave_max63(small);
-    if (lane == 63) { extreme[wave] = big; extreme[NW + wave] = small; }
-    lds_barrier();
-    {
-        const uint32_t a = extreme[lane & (NW - 1)], c = extreme[NW + (lane & (NW - 1))];
-        big = (uint32_t)__builtin_amdgcn_readlane((int)wave_max63(a), 63);
-        small = ~(uint32_t)__builtin_amdgcn_readlane((int)wave_max63(c), 63);
-    }
-#pragma unroll
-    for (int e = 0; e < EPT; ++e) key[e] = key[e] ? big - key[e] : 0xffffffffu;
-    auto cand = [&](int e) { return key[e] != 0xffffffffu; };
-
-    // The bracket: candidates with distances in [d0, d0 + lim] and indices in [i0, i0 + ilim]. It holds `inside`
-    // candidates, the threshold (number `rank` of them in order, from 1) among them.
-    int nb = 32 - __builtin_clz((big - small) | 1u);   // distances have at most nb bits
-    uint32_t d0 = 0, lim = 0xffffffffu >> (32 - nb);
-    uint32_t i0 = 0, ilim = (uint32_t)n_cand - 1u;
-    auto in_indices = [&](int e) { return (uint32_t)(tid + e * NT) - i0 <= ilim; };
-    // One add per candidate, but candidates that may all be equal: the lanes that share the first one's bin as one number.
-    auto add_shared = [&](int bin) {
-        const int b0 = __builtin_amdgcn_readfirstlane(bin);
-        const unsigned long long m = __builtin_amdgcn_ballot_w64(bin == b0);
-        if (bin != b0) atomicAdd(&hist[bin], 1);
-        else if (lane == __builtin_ctzll(m)) atomicAdd(&hist[bin], __builtin_popcountll(m));
-    };
-
-    // After the bins of a round are counted: the first bin at which the running count reaches `rank`.
-    auto settle = [&]() -> int {
-        lds_barrier();
-        int n[kPer], sum = 0;
-#pragma unroll
-        for (int u = 0; u < kPer; ++u) { n[u] = hist[tid * kPer + u]; sum += n[u]; }
-#pragma unroll
-        for (int u = 0; u < kPer; ++u) hist[tid * kPer + u] = 0;      // for the next round
-        int incl = wave_incl(sum);
-        if (lane == 63) wave_n[wave] = incl;
-        lds_barrier();
-        const int wn = lane < NW ? wave_n[lane < NW ? lane : 0] : 0;
-        const int before = wave == 0 ? 0 : __builtin_amdgcn_readlane(wave_incl(wn), wave - 1);
-        int c = before + incl - sum;
-#pragma unroll
-        for (int u = 0; u < kPer; ++u) {
-            if (c < rank && rank <= c + n[u]) { pick[0] = tid * kPer + u; pick[1] = c; pick[2] = n[u]; }   // exactly one bin
-            c += n[u];
+            for (int e = 0; e < EPT; ++e) {
+                const bool k = x[e] >= __uint_as_float(least);
+                const int pos = lanes_before(__builtin_amdgcn_ballot_w64(k), __builtin_amdgcn_readlane(ahead, (e * NW + wave) / kChunkPer));
+                if (k && pos < want) out[pos] = tid + e * NT;
+            }
+            return;
         }
-        lds_barrier();
-        rank -= pick[1];
-        inside = pick[2];
-        return pick[0];
-    };
-
-    // Rounds over the bits of the distance, eleven at a time. The first one counts every candidate, later ones, rare, those
-    // that are left.
-    if (inside > kLast && big != small) {
-        int sh = max(nb - kDigitBits, 0);
-        add_all([&](int e) { return key[e] >> sh; }, cand);
-        d0 = (uint32_t)settle() << sh;
-        nb = sh;
-        lim = (1u << nb) - 1u;
-        while (inside > kLast && nb > 0) {           // uniform
-            sh = max(nb - kDigitBits, 0);
+    } else {
+        // ---- the general search, among what is in the part found so far (or all candidates) ----
+        // From here on a key is its distance below the largest one, and what is no candidate is further than all (keys are at
+        // least 1, which only the lowest NaN would not be, so no distance is 0xffffffff). Shorter distances come first.
+        lds_barrier();                                 // (the parts' counts are read)
+        renewed(n_live);
+        uint32_t key[EPT];
+        uint32_t big = 0, small = 0;                     // (the complement of the smallest)
 #pragma unroll
-            for (int e = 0; e < EPT; ++e)
-                if (key[e] - d0 <= lim && cand(e)) add_shared((int)((key[e] - d0) >> sh));
-            d0 += (uint32_t)settle() << sh;
+        for (int e = 0; e < EPT; ++e) {
+            const bool c = live(e) && (!divided || in_part(e));
+            key[e] = c ? max(order_key(x[e]), 1u) : 0u;
+            big = max(big, key[e]);
+            small = max(small, c ? ~key[e] : 0u);
+        }
+#pragma unroll
+        for (int u = 0; u < kPer; ++u) hist[tid + u * NT] = 0;
+        big = wave_max63(big);
+        small = wave_max63(small);
+        if (lane == 63) { extreme[wave] = big; extreme[NW + wave] = small; }
+        lds_barrier();
+        {
+            const uint32_t a = extreme[lane & (NW - 1)], c = extreme[NW + (lane & (NW - 1))];
+            big = (uint32_t)__builtin_amdgcn_readlane((int)wave_max63(a), 63);
+            small = ~(uint32_t)__builtin_amdgcn_readlane((int)wave_max63(c), 63);
+        }
+#pragma unroll
+        for (int e = 0; e < EPT; ++e) key[e] = key[e] ? big - key[e] : 0xffffffffu;
+        auto cand = [&](int e) { return key[e] != 0xffffffffu; };
+
+        // The bracket: candidates with distances in [d0, d0 + lim]. It holds `inside` candidates, the threshold (number `rank` of
+        // them in order, from 1) among them.
+        int nb = 32 - __builtin_clz((big - small) | 1u);   // distances have at most nb bits
+        uint32_t d0 = 0, lim = 0xffffffffu >> (32 - nb);
+        // One add per candidate, but candidates that may all be equal: the lanes that share the first one's bin as one number.
+        auto add_shared = [&](int bin) {
+            const int b0 = __builtin_amdgcn_readfirstlane(bin);
+            const unsigned long long m = __builtin_amdgcn_ballot_w64(bin == b0);
+            if (bin != b0) atomicAdd(&hist[bin], 1);
+            else if (lane == __builtin_ctzll(m)) atomicAdd(&hist[bin], __builtin_popcountll(m));
+        };
+
+        // After the bins of a round are counted: the first bin at which the running count reaches `rank`.
+        auto settle = [&]() -> int {
+            lds_barrier();
+            int n[kPer], sum = 0;
+#pragma unroll
+            for (int u = 0; u < kPer; ++u) { n[u] = hist[tid * kPer + u]; sum += n[u]; }
+#pragma unroll
+            for (int u = 0; u < kPer; ++u) hist[tid * kPer + u] = 0;      // for the next round
+            int incl = wave_incl(sum);
+            if (lane == 63) wave_n[wave] = incl;
+            lds_barrier();
+            const int wn = lane < NW ? wave_n[lane < NW ? lane : 0] : 0;
+            const int before = wave == 0 ? 0 : __builtin_amdgcn_readlane(row_incl<NW>(wn), wave - 1);
+            int c = before + incl - sum;
+#pragma unroll
+            for (int u = 0; u < kPer; ++u) {
+                if (c < rank && rank <= c + n[u]) { pick[0] = tid * kPer + u; pick[1] = c; pick[2] = n[u]; }   // exactly one bin
+                c += n[u];
+            }
+            lds_barrier();
+            rank -= pick[1];
+            inside = pick[2];
+            return pick[0];
+        };
+
+        // Rounds over the bits of the distance, eleven at a time. The first one counts every candidate, later ones, rare, those
+        // that are left.
+        if (inside > kLast && big != small) {
+            int sh = max(nb - kDigitBits, 0);
+            add_all([&](int e) { return key[e] >> sh; }, cand);
+            d0 = (uint32_t)settle() << sh;
             nb = sh;
             lim = (1u << nb) - 1u;
+            while (inside > kLast && nb > 0) {           // uniform
+                sh = max(nb - kDigitBits, 0);
+#pragma unroll
+                for (int e = 0; e < EPT; ++e)
+                    if (key[e] - d0 <= lim && cand(e)) add_shared((int)((key[e] - d0) >> sh));
+                d0 += (uint32_t)settle() << sh;
+                nb = sh;
+                lim = (1u << nb) - 1u;
+            }
         }
-    } else if (big == small) {
-        lim = 0;
-    }
-    // More than 64 candidates tie with the threshold: the same rounds over the bits of their indices.
-    if (inside > kLast) {
-        nb = 32 - __builtin_clz((uint32_t)n_cand);
-        while (inside > kLast) {                     // a bracket of one index holds one candidate: ends
-            const int sh = max(nb - kDigitBits, 0);
+        if (inside > kLast || big == small) {          // all that are left share the threshold's score
+            T = big - d0;
+        } else {
 #pragma unroll
             for (int e = 0; e < EPT; ++e)
-                if (key[e] == d0 && in_indices(e)) add_shared((int)(((uint32_t)(tid + e * NT) - i0) >> sh));
-            i0 += (uint32_t)settle() << sh;
-            nb = sh;
-            ilim = min((1u << nb) - 1u, (uint32_t)n_cand - 1u - i0);
+                if (key[e] - d0 <= lim && cand(e)) put_last(key[e], e);
+            bool more;
+            rank_last(T, more);
+            T = big - T;
         }
     }
 
-#pragma unroll
-    for (int e = 0; e < EPT; ++e)
-        if (key[e] - d0 <= lim && cand(e) && in_indices(e)) put_last(key[e], e);
-    uint32_t at;
-    int X;
-    bool more;
-    rank_last(at, X, more);
-    const uint32_t T = big - at;
-    write([&](int e) {
-        const uint32_t k = live(e) ? max(order_key(x[e]), 1u) : 0u;
-        return k > T || (k == T && tid <= X - e * NT);
-    });
+    if (divided) {                                 // (all scores are finite)
+        write_first(__float_as_uint(key_value(T)), [&](int e, uint32_t v) { return x[e] > __uint_as_float(v); },
+                    [&](int e, uint32_t v) { return x[e] == __uint_as_float(v); });
+    } else {
+        const auto order = [&](int e) { return live(e) ? max(order_key(x[e]), 1u) : 0u; };
+        write_first(T, [&](int e, uint32_t v) { return order(e) > v; }, [&](int e, uint32_t v) { return order(e) == v; });
+    }
 }
 
 // Heads longer than 32 * 1024 tokens: the keys do not fit the registers of one workgroup, so every counting pass

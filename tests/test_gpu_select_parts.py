@@ -104,3 +104,35 @@ def test_combining_chunks_stays_inside_the_head(A, lens):
     assert len(at) == 1
     gap = words[at[0] + n:(at[0] + n + 63) // 64 * 64]
     assert bool((gap == poison).all())
+
+
+def _ties(kind, rng, L):
+    if kind == "one value":   return np.full(L, -0.75)
+    if kind == "two values":  return np.where(rng.random(L) < 0.5, 1.0, 1.0 + 2.0**-23)
+    if kind == "ten values":  return np.floor(5 * rng.standard_normal(L)) / 8
+    if kind == "few above":   return np.where(np.arange(L) % 97 == 5, 3.0, np.where(np.arange(L) % 3 == 0, 1.0, -1.0))
+    if kind == "last":        return np.where(np.arange(L) < L - 70, -2.0, rng.standard_normal(L))
+    if kind == "infinite":    return np.where(rng.random(L) < 0.4, np.inf, np.where(rng.random(L) < 0.5, -np.inf, 0.5))
+    if kind == "no numbers":  return np.where(rng.random(L) < 0.4, np.nan, np.where(rng.random(L) < 0.5, -np.nan, 0.5))
+    raise ValueError(kind)
+
+
+@pytest.mark.parametrize("W", [0, 5])
+@pytest.mark.parametrize("L", [40, 64, 65, 71, 513, 2048, 4095, 8192, 8193, 16384, 16385, 24577, 32768])
+@pytest.mark.parametrize("kind", ["one value", "two values", "ten values", "few above", "last", "infinite", "no numbers"])
+def test_equal_scores_are_kept_in_index_order(A, kind, L, W):
+    """Thresholds that many tokens share, up to all of the longest head's, with none, some and all of them kept."""
+    shares = [0.0, 0.03, 0.2, 0.4, 0.5, 0.71, 0.95, 1.0]
+    rng = np.random.default_rng(L)
+    s = np.stack([_ties(kind, rng, L) for _ in shares]).astype(np.float32)
+    b = np.array([W + int(r * (L - W)) for r in shares], dtype=np.int32)
+    cu = np.concatenate([[0], np.cumsum(b)]).astype(np.int32)
+    p = A.Params(len(shares), len(shares), 64, W)
+    got = A.select(p, torch.from_numpy(s).cuda().reshape(-1), torch.from_numpy(b).cuda(), torch.from_numpy(cu).cuda(), [L], int(cu[-1]))
+    got = got.cpu().numpy()
+    key = (s + np.float32(0)).view(np.uint32).astype(np.int64)
+    key = np.where(key & 0x80000000, 0xffffffff - key, key | 0x80000000)
+    for h in range(len(shares)):
+        order = np.lexsort((np.arange(L - W), -key[h, :L - W]))
+        want = np.concatenate([np.sort(order[:b[h] - W]), np.arange(L - W, L)])
+        assert np.array_equal(got[cu[h]:cu[h + 1]], want), (kind, L, W, shares[h])
