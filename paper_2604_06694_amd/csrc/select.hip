@@ -178,8 +178,11 @@ __device__ __forceinline__ uint32_t wave_max63(uint32_t x) {
 }
 
 // Scores of tokens tid + NT e that a convolution left in chunks: token n + C t from points n of all chunks, and every thread's
-// points are those of its own tokens. They go to `smoothed` as well; from n_cand on they are zero here. In place of a launch that combined them: evict
-// on one layer of 5000 tokens 40.2 -> 38.8 us, 13577 54.9 -> 52.9, 28 layers of 13577 439 -> 433.
+// points are those of its own tokens. From n_cand on they are zero here. In place of a launch that combined them: evict on one layer
+// of 5000 tokens 40.2 -> 38.8 us, 13577 54.9 -> 52.9, 28 layers of 13577 439 -> 433.
+// They go to `smoothed` as well, for every head: nothing in evict reads them there, but what a workspace holds of a call afterwards
+// does not depend on who combined the chunks (tests compare it with smooth's result). The stores cost 0.8 us of 53 at 13577 tokens
+// and 1.2 of 137 on 40 layers of 12000.
 template <int EPT, int NT, int R>
 __device__ __forceinline__ void joined_scores(const Geom& g, const ConvJoin& j, const ConvHead& w, int head, int n_cand, float* smoothed,
                                               float (&x)[EPT]) {
@@ -257,7 +260,7 @@ __global__ __launch_bounds__(NT) void select_kernel(
     // the forced window tail: highest indices, so they close the ascending list
     for (int w = tid; w < W; w += NT)
         if (want + w < room) out[want + w] = n_cand + w;
-    if (want <= 0) return;
+    if (!JOIN && want <= 0) return;
     if (n_cand > EPT * NT) return;                   // launcher never allows this
 
     // (a buffer of the candidates' size reads as zero past its end: no clamped addresses, all loads of a thread in flight. As with
@@ -287,6 +290,7 @@ __global__ __launch_bounds__(NT) void select_kernel(
         if (R == 2) joined_scores<EPT, NT, 2>(g, chunks, w, head, n_cand, smoothed + w.off, x);
         else if (R == 4) joined_scores<EPT, NT, kMaxR>(g, chunks, w, head, n_cand, smoothed + w.off, x);
         else load();
+        if (want <= 0) return;                       // (its smoothed scores are stored all the same)
     } else {
         load();
     }

@@ -85,19 +85,23 @@ def test_selection_combines_the_chunks_of_a_convolution(A, lens, alpha, kernel, 
 
 
 @pytest.mark.parametrize("lens", [[4097], [8193], [5000, 700], [8193, 600, 4099, 1025], [12289, 4096, 333]])
-def test_combining_chunks_stays_inside_the_head(A, lens):
-    """The combined scores that evict leaves in its workspace: those of every head what smooth gives, whole batches through, and
-    the bytes between the last head's and the next region (regions start at multiples of 256 bytes) as they were."""
-    H, d, W = 1, 64, 8
+@pytest.mark.parametrize("weights", [[1.0], [0.0, 1.0], [1.0, 0.0]])
+def test_combining_chunks_stays_inside_the_head(A, lens, weights):
+    """The combined scores that evict leaves in its workspace: those of every head what smooth gives, whole batches through, also
+    of heads that keep no more than the window, and the bytes between the last head's and the next region (regions start at
+    multiples of 256 bytes) as they were."""
+    H, d, W = len(weights), 64, 8
     gen = torch.Generator(device="cuda").manual_seed(sum(lens))
     q = torch.randn(len(lens) * H * W * d, generator=gen, device="cuda").to(torch.bfloat16)
     k = torch.randn(sum(lens) * H * d, generator=gen, device="cuda").to(torch.bfloat16)
-    w = torch.rand(len(lens) * H, generator=gen, device="cuda")
-    p = A.Params(H, H, d, W)
+    w = torch.tensor(weights * len(lens), dtype=torch.float32, device="cuda")
+    p = A.Params(H, H, d, W, floor_frac=0.0)
     smoothed = A.smooth(p, A.score(p, q, k, lens), lens, 0.125, 1.0).view(torch.int32)
     n, poison = smoothed.numel(), 0x7f7f7f7f
     ws = torch.full((A.workspace_bytes(p, lens),), 0x7f, dtype=torch.uint8, device="cuda")
-    A.evict(p, q, k, k, w, lens, 0.3, 0.125, 1.0, alloc_scope=A.SCOPE_ITEM, workspace=ws)
+    out = A.evict(p, q, k, k, w, lens, 0.3, 0.125, 1.0, alloc_scope=A.SCOPE_ITEM, workspace=ws)
+    if H > 1:
+        assert (out["budgets"].view(-1, H)[:, weights.index(0.0)] == W).all()
     words = ws[:ws.numel() // 4 * 4].view(torch.int32)
     at = [64 * i for i in (words[:words.numel() - n + 1:64] == smoothed[0]).nonzero().view(-1).tolist()]
     at = [i for i in at if torch.equal(words[i:i + n], smoothed)]
