@@ -1,7 +1,5 @@
 // Host-side planning for the score kernels: which (row blocks per wave, row-splitting waves) instantiation
 // covers G*W window rows in each of the two sweeps, and into how many key ranges a head is cut.
-#include <vector>
-
 #include "score_impl.h"
 
 namespace audiokv {
@@ -55,11 +53,14 @@ int num_splits(const Plan& p, int H_kv, int n_items, const int32_t* seqlens_host
         if (seqlens_host[i] != seqlens_host[0]) uniform = false;
     }
     // (for ragged batches, in which every count is tried with every length: quotients rounded up, in float64 and off the whole
-    // numbers, so that they are exact. 48 lengths took 25 us with integer divisions.)
-    std::vector<double> tiles;
+    // numbers, so that they are exact. 48 lengths took 25 us with integer divisions. The first lengths' tiles are kept in an array
+    // of fixed size: a container could throw, and callers are C.)
+    constexpr int kKept = 256;
+    double kept[kKept];
+    const int tile_shift = __builtin_ctz((unsigned)p.tile_keys);
+    const auto tiles = [&](int i) { return (double)((seqlens_host[i] + p.tile_keys - 1) >> tile_shift); };
     if (!uniform)
-        for (int i = 0; i < n_items; ++i)
-            if (seqlens_host[i] > 0) tiles.push_back((double)((seqlens_host[i] + p.tile_keys - 1) / p.tile_keys));
+        for (int i = 0; i < n_items && i < kKept; ++i) kept[i] = tiles(i);
     int best = 1;
     long long best_cost = -1;
     const int ns_max = max_tiles < 64 ? max_tiles : 64;
@@ -78,13 +79,15 @@ int num_splits(const Plan& p, int H_kv, int n_items, const int32_t* seqlens_host
             const long long groups = (long long)n_items * H_kv * ns;   // launched, whether or not they hold tiles
             double sum = 0., most = 0.;
             const double per_range = 1. / ns;
-            for (const double t : tiles) {
+            for (int i = 0; i < n_items; ++i) {
+                const double t = i < kKept ? kept[i] : tiles(i);
+                if (!(t > 0.)) continue;
                 const double tps = (double)(int)((t + ns - 0.5) * per_range);
                 const double used = (double)(int)((t + tps - 0.5) / tps);       // ranges of this head that hold tiles
                 sum += t + used * overhead;
                 most = tps > most ? tps : most;
             }
-            const long long total = (long long)sum * H_kv, longest = tiles.empty() ? 0 : (long long)most + overhead;
+            const long long total = (long long)sum * H_kv, longest = most > 0. ? (long long)most + overhead : 0;
             cost = 2 * ((total + slots - 1) / slots) + longest;
             const long long rem = groups % slots;
             if (groups > slots && rem) cost += 2 * (total / groups) * (slots - rem) / slots;
