@@ -371,7 +371,7 @@ __global__ __launch_bounds__(64 * (WR + 1), (NB == 1 && D <= 128) ? 4 : 2) void 
                     const int r_ = it * T::RPI + lrow;
                     const int j_ = min(t_ * T::TK + r_, L - 1);
                     __builtin_amdgcn_global_load_lds(
-                        (global_void_ptr)(k + kv_row_offset(g, item, tok0, L, h, j_) + T::chunk_in_slot(pslot, r_) * 8),
+                        (global_void_ptr)(head_base + j_ * row_elems + T::chunk_in_slot(pslot, r_) * 8),
                         (lds_void_ptr)(dst + it * 1024), 16, 0, 0);
                 }
             }
