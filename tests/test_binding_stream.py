@@ -8,15 +8,16 @@ import torch
 from paper_2604_06694_amd import binding
 
 
-def test_without_the_short_way(monkeypatch):
-    monkeypatch.setattr(binding, "_raw_stream", None)
+@pytest.mark.parametrize("missing", ["_raw_stream", "_raw_device"])
+def test_without_the_short_way(monkeypatch, missing):
+    monkeypatch.setattr(binding, missing, None)
     monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=1234))
     assert binding._stream() == 1234
 
 
 def test_the_short_way_asks_for_the_current_device(monkeypatch):
     monkeypatch.setattr(binding, "_raw_stream", lambda device: 100 + device)
-    monkeypatch.setattr(torch.cuda, "current_device", lambda: 3)
+    monkeypatch.setattr(binding, "_raw_device", lambda: 3)
     assert binding._stream() == 103
 
 
