@@ -43,10 +43,10 @@ __device__ __forceinline__ int64_t kv_row_offset(const Geom& g, int item, int64_
     return base + ((int64_t)j * g.H_kv + h) * g.D;
 }
 
-// Workgroups (of at most 256 threads) for each of n parts of a launch: as many as wanted, but a launch holds fewer than 2^32
-// threads, and parts of it go along with others. The kernels that ask stride over what is left.
-inline int blocks_per_part(long long wanted, long long n) {
-    const long long most = n > 0 ? (1LL << 23) / n : wanted;
+// Workgroups of `threads` threads for each of n parts of a launch: as many as wanted, but a launch holds fewer than 2^32 threads,
+// and parts of it go along with others: half of that at most. The kernels that ask stride over what is left.
+inline int blocks_per_part(long long wanted, long long n, int threads = 256) {
+    const long long most = n > 0 ? (1LL << 31) / threads / n : wanted;
     return (int)(wanted < 1 || most < 1 ? 1 : wanted < most ? wanted : most);
 }
 

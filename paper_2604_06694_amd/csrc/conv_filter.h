@@ -16,7 +16,7 @@ struct ConvFilterJob {
     int taper_bins;
     int max_length;           // of the items that have taps
     // workgroups of `threads`, a tap and its mirror image per thread (in a call of very many items more)
-    int blocks_per_item(int threads) const { return blocks_per_part((max_length / 2 + threads) / threads, n_items); }
+    int blocks_per_item(int threads) const { return blocks_per_part((max_length / 2 + threads) / threads, n_items, threads); }
 };
 
 struct SmoothFilters {
