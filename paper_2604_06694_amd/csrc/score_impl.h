@@ -184,8 +184,10 @@ __device__ __forceinline__ void ride_along(const RideAlong& ride, int block) {
 // first keys, instead of reading constants that a launch in between prepared: that launch took 3.9 to 5.5 us, most of it spent on
 // starting and draining, and the host's share of it (2.4 us), where this adds 1.2 us to sweep 2 (four heads of 2048, 32 ranges of
 // 224 rows), 2.9 (13577, 54 ranges of 256) and, the most there is, 4 (32768, 64 ranges of 448). Whole calls on one layer of
-// 2048 30.8 -> 28.7 us, 13577 63.5 -> 61.1, 32768 the same; 28 layers of 8192 280 -> 277; with the log-sum-exp given, where two
-// launches fall away, 13577 53.3 -> 45.2. (64 ranges in flight spill registers: 32.2 us instead of 27.9 at 32768.)
+// 2048 30.8 -> 28.7 us, 13577 63.5 -> 61.1, 32768 and whole stacks the same; with the log-sum-exp given, where two launches fall
+// away, 13577 53.3 -> 45.2. (64 ranges in flight spill registers: 32.2 us instead of 27.9 at 32768.) Above 448 rows two launches
+// merge their rows one after the other, and with five to seven heads it costs more than it saves (576 rows, six heads of 16000
+// 54.6 -> 56.3 us; one launch merging for both 55.5 there, but two heads of 9000 48.6 -> 50.1).
 // HALVES: the two halves of a wave share a row (the caller's r is the same in both) and take the batches of sixteen in turn.
 template <int N, bool HALVES>
 __device__ __forceinline__ float merged_row(const float* __restrict__ stats, int nsplit, int rows_pad, int head, int r, int half) {

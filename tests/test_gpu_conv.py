@@ -126,7 +126,7 @@ def found(ws, close_to):
 @pytest.mark.parametrize("T", [0, 1, 1000])
 @pytest.mark.parametrize("lens,H_kv", [([13577], 2), ([5003] * 20, 2), ([3000, 700], 2)])
 def test_taps_are_the_same_bits_wherever_they_are_evaluated(A, T, lens, H_kv):
-    """The filter's taps are evaluated in the launch that merges the statistics, on the helper stream, or by smooth itself; evict
+    """The filter's taps are evaluated in extra workgroups of the first sweep, on the helper stream, or by smooth itself; evict
     equals the calls composed only if they are the same bits from all of them, with a taper as well."""
     rng = np.random.default_rng(T + len(lens))
     H_q, d, W, n, L, cutoff = 2 * H_kv, 64, 8, len(lens), lens[0], 0.25
