@@ -2,11 +2,7 @@
 // because the order is checked on the host as well (tests/score_ring_check.cpp).
 #pragma once
 
-#if !defined(__HIPCC__)
-#define __host__
-#define __device__
-#define __forceinline__ inline
-#endif
+#include <hip/hip_runtime.h>
 
 namespace audiokv {
 namespace score_detail {
@@ -25,15 +21,11 @@ __host__ __device__ __forceinline__ void fill_ring(int n_tiles, Issue issue, Bar
     constexpr int AHEAD = STAGES - 1;
     // At the barrier that ends tile t, tiles up to t + AHEAD are requested and t + 1 is opened.
     static_assert(AHEAD - kInFlight >= 1 + kLookAhead, "what an iteration reads has landed when it opens");
-#if defined(__clang__)
 #pragma unroll
-#endif
     for (int a = 0; a < AHEAD; ++a)
         if (a < n_tiles) issue(a);
     barrier();                                      // opens iteration 0
-#if defined(__clang__)
 #pragma unroll 1
-#endif
     for (int t = 0; t < n_tiles; ++t) {
         // its slot held tile t - 1, which every wave left at the barrier that ended it
         if (t + AHEAD < n_tiles) issue(t + AHEAD);

@@ -12,11 +12,12 @@ from test_kernel_code import assembly, code_objects, named, pytestmark as needs_
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
-@pytest.mark.skipif(shutil.which("g++") is None, reason="g++ not available")
+@pytest.mark.skipif(shutil.which("hipcc") is None, reason="hipcc not available")
 def test_tiles_have_landed_when_they_are_read(tmp_path):
     exe = str(tmp_path / "score_ring_check")
-    r = subprocess.run(["g++", "-std=c++20", "-O1", "-Wall", "-I", os.path.join(ROOT, "paper_2604_06694_amd", "csrc"),
-                        os.path.join(ROOT, "tests", "score_ring_check.cpp"), "-o", exe], capture_output=True, text=True)
+    r = subprocess.run(["hipcc", "-x", "hip", "--offload-host-only", "-std=c++20", "-O1", "-I",
+                        os.path.join(ROOT, "paper_2604_06694_amd", "csrc"), os.path.join(ROOT, "tests", "score_ring_check.cpp"),
+                        "-o", exe], capture_output=True, text=True)
     assert r.returncode == 0, r.stderr
     r = subprocess.run([exe], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0 and "the ring holds" in r.stdout, r.stdout + r.stderr
