@@ -17,9 +17,20 @@ struct Combo { int NB, WR; };
 const Combo kSweep1_128[] = {{1, 1}, {1, 2}, {1, 4}, {1, 7}, {2, 4}, {2, 7}, {3, 6}};   // d = 64, 128
 const Combo kSweep2_128[] = {{1, 1}, {1, 2}, {1, 4}, {1, 7}, {2, 4}, {2, 7}};
 const Combo kCombos256[] = {{1, 1}, {1, 2}, {1, 4}, {1, 7}, {1, 8}};                    // d = 256, both sweeps
+// 225 to 256 rows of calls that are over before the chip reaches its power limit: one row tile on each of eight waves instead of two
+// on each of four, in both sweeps. Twice the waves hide the latencies of a tile and merge the statistics; each key fragment read from
+// LDS feeds one product instead of two, which costs power. Score calls at d = 128, two tiles and one: 1 x 2048 15.7 and 14.8 us,
+// 1 x 13577 22.6 and 21.3, 2 x 16384 35.2 and 30.4, 4 x 8192 34.4 and 30.8, 8 x 8192 51.5 and 49.7; 8 x 16384 87.5 and 88.8,
+// 16 x 8192 88.0 and 90.0, 48 x 16384 521 and 554 (four KV heads each).
+constexpr long long kNarrowTileKeys = 3 << 17;     // keys of all heads: between 8 and 16 items of 8192 tokens and four heads
 
-bool make_plan(int rows, int D, int sweep, Plan* out) {
+// keys: of all heads of the call (what a row pitch is asked for without: any)
+bool make_plan(int rows, int D, int sweep, long long keys, Plan* out) {
     const Combo* cs; int n;
+    if (D <= 128 && rows > 224 && rows <= 256 && keys <= kNarrowTileKeys) {
+        *out = Plan{1, 8, 256, 32 * AUDIOKV_SCORE_KB, 1};      // nine waves of 128 registers: one workgroup per CU
+        return D == 64 || D == 128;
+    }
     if (D == 64 || D == 128) { cs = sweep == 1 ? kSweep1_128 : kSweep2_128; n = sweep == 1 ? 7 : 6; }
     else if (D == 256) { cs = kCombos256; n = 5; }
     else return false;
@@ -36,6 +47,12 @@ bool make_plan(int rows, int D, int sweep, Plan* out) {
         }
     }
     return false;
+}
+
+long long total_keys(int H_kv, int n_items, const int32_t* seqlens_host) {
+    long long keys = 0;
+    for (int i = 0; i < n_items; ++i) keys += (long long)seqlens_host[i] * H_kv;
+    return keys;
 }
 
 int num_splits(const Plan& p, int H_kv, int n_items, const int32_t* seqlens_host) {
@@ -108,13 +125,13 @@ bool sweep2_is_split(int rows, int D) { return D <= 128 && rows > kSweep2MaxRows
 
 int score_padded_rows(int rows, int D) {
     Plan p1, p2;
-    if (!make_plan(rows, D, 1, &p1)) return 0;
+    if (!make_plan(rows, D, 1, 0, &p1)) return 0;
     if (sweep2_is_split(rows, D)) {
-        if (!make_plan(rows - kSweep2MaxRows, D, 2, &p2)) return 0;
+        if (!make_plan(rows - kSweep2MaxRows, D, 2, 0, &p2)) return 0;
         const int pad2 = kSweep2MaxRows + p2.rows_pad;
         return p1.rows_pad > pad2 ? p1.rows_pad : pad2;
     }
-    if (!make_plan(rows, D, 2, &p2)) return 0;
+    if (!make_plan(rows, D, 2, 0, &p2)) return 0;
     return p1.rows_pad > p2.rows_pad ? p1.rows_pad : p2.rows_pad;
 }
 
@@ -123,7 +140,7 @@ bool score_needs_second_raw(int rows, int D) { return sweep2_is_split(rows, D); 
 // key ranges per head of sweep 1: what sizes the statistics in the workspace
 int score_num_splits(int H_kv, int n_items, const int32_t* seqlens_host, int rows, int D) {
     Plan p;
-    if (!make_plan(rows, D, 1, &p) || n_items <= 0 || H_kv <= 0) return 1;
+    if (n_items <= 0 || H_kv <= 0 || !make_plan(rows, D, 1, total_keys(H_kv, n_items, seqlens_host), &p)) return 1;
     return num_splits(p, H_kv, n_items, seqlens_host);
 }
 
@@ -134,15 +151,14 @@ hipError_t launch_score(const Geom& g, const void* q_win, const void* k, const i
 {
     Plan p1;
     const int rows = g.G * g.W;
-    if (!make_plan(rows, g.D, 1, &p1)) return hipErrorInvalidValue;
+    const long long keys = total_keys(g.H_kv, g.n_items, seqlens_host);
+    if (!make_plan(rows, g.D, 1, keys, &p1)) return hipErrorInvalidValue;
     const int rows_pad = score_padded_rows(rows, g.D);
     if (rows_pad == 0) return hipErrorInvalidValue;
     // What the memory-side cache (256 MB) holds of K after sweep 1 is its end: where K does not fit, sweep 2 begins there. Score
     // calls, forwards and backwards: 28 x 32768, 448 rows 929 and 915 us, 13 x 32768 452 and 442; 224 rows 30 x 9000 (276 MB) 169 and 165,
     // 48 x 10000 297 and 289; K that fits: 28 x 9000, 256 rows (258 MB) 352 and 356 with the eviction around it.
-    long long k_bytes = 0;
-    for (int i = 0; i < g.n_items; ++i) k_bytes += (long long)seqlens_host[i] * g.H_kv * g.D * 2;
-    const bool backwards = k_bytes > (1LL << 28);
+    const bool backwards = keys * g.D * 2 > (1LL << 28);
     score_detail::SweepArgs args{q_win, k, cu_seqlens, 0, rows_pad, 0, stats_ws, ns1, lse, raw_out, backwards, ride_along, ride_taps};
     auto sweep = [&](int which, const Plan& p, int ns, int row_base, float* raw) -> hipError_t {
         args.nsplit = ns;
@@ -166,12 +182,12 @@ hipError_t launch_score(const Geom& g, const void* q_win, const void* k, const i
     }
     Plan p2;
     if (!sweep2_is_split(rows, g.D)) {
-        if (!make_plan(rows, g.D, 2, &p2)) return hipErrorInvalidValue;
+        if (!make_plan(rows, g.D, 2, keys, &p2)) return hipErrorInvalidValue;
         return sweep(2, p2, num_splits(p2, g.H_kv, g.n_items, seqlens_host), 0, raw_out);
     }
     if (!raw_second) return hipErrorInvalidValue;
     Plan p2b;
-    if (!make_plan(kSweep2MaxRows, g.D, 2, &p2) || !make_plan(rows - kSweep2MaxRows, g.D, 2, &p2b)) return hipErrorInvalidValue;
+    if (!make_plan(kSweep2MaxRows, g.D, 2, keys, &p2) || !make_plan(rows - kSweep2MaxRows, g.D, 2, keys, &p2b)) return hipErrorInvalidValue;
     e = sweep(2, p2, num_splits(p2, g.H_kv, g.n_items, seqlens_host), 0, raw_out);
     if (e != hipSuccess) return e;
     e = sweep(2, p2b, num_splits(p2b, g.H_kv, g.n_items, seqlens_host), kSweep2MaxRows, raw_second);
