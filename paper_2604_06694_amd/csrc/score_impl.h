@@ -381,18 +381,6 @@ __global__ __launch_bounds__(64 * (WR + 1), (NB == 1 && D <= 128) ? 4 : 2) void 
         // (These are the only vector-memory operations of this wave. Ranges of one tile are common, so nothing is requested past
         // the end: with the last tile requested again instead, a score call on four heads of 1000 tokens and 448 rows took 23.4 us,
         // now 19.9.)
-#ifdef TOUCH
-        if constexpr (SWEEP2 && T::STAGES == 4) {
-            const int n_heads_ = n_wg / nsplit, rem_ = n_heads_ & 7;
-            const int per_ = head >= (n_heads_ & ~7) && (rem_ & (rem_ - 1)) == 0 && nsplit % (8 / rem_) == 0 ? 8 / rem_ : 1;
-            if (!lse) {
-                const char* st = reinterpret_cast<const char*>(stats + (size_t)head * stat_splits * rows_pad * 2);
-                const int kb_ = stat_splits * rows_pad * 8 / 1024;       // rows_pad is a multiple of 32, at least 128: whole KiB
-                for (int i = split / per_; i < kb_; i += nsplit / per_)
-                    __builtin_amdgcn_global_load_lds((global_void_ptr)(st + (size_t)i * 1024 + lane * 16), (lds_void_ptr)(lds + 3 * T::LDS_K), 16, 0, 0);
-            }
-        }
-#endif
         fill_ring<T::STAGES>(n_loc, issue_tile, [&]() {
             __builtin_amdgcn_s_waitcnt(vmcnt_only(kInFlight * T::CH));
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
