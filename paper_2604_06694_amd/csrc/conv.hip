@@ -244,7 +244,7 @@ __global__ __launch_bounds__(Cfft<LOGC>::THREADS) void conv_spectrum_kernel(Geom
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     ConvLds<LOGC>& m = *reinterpret_cast<ConvLds<LOGC>*>(smem);
     ConvHead w;
-    const int item = blockIdx.x >> log_r, r = blockIdx.x & ((1 << log_r) - 1), t = threadIdx.x;
+    const int item = blockIdx.x >> log_r, r = (blockIdx.x + item) & ((1 << log_r) - 1), t = threadIdx.x;   // (as in conv_chunk_kernel)
     if (!conv_head(g, job, item * g.H_kv, LOGC, w) || w.owner != item || r >= w.R) return;
     TapBlocks<LOGC == 13 ? 2 : 4> taps;
     constexpr bool kEarly = LOGC < 13;
@@ -275,7 +275,11 @@ __global__ __launch_bounds__(Cfft<LOGC>::THREADS) void conv_chunk_kernel(
     ConvLds<LOGC>& m = *reinterpret_cast<ConvLds<LOGC>*>(smem);
     constexpr int U = LOGC == 13 ? 2 : 4;                        // (1024 threads: 128 registers)
     ConvHead w;
-    const int head = blockIdx.x >> log_r, r = blockIdx.x & ((1 << log_r) - 1), t = threadIdx.x;
+    // Workgroup i runs on XCD i mod 8, and heads of fewer chunks than the longest need the first residues only: these go to another
+    // XCD from head to head. (All on the first ones: 24 sequences of two heads, 1500 to 30000 samples, put 48 of their 172 workgroups
+    // on the 32 CUs of XCD 0, one each, and 12 on XCD 7. Smooth calls, so and now: those 36.9 and 27.2 us, 40 of four heads of 3000 to
+    // 20000 80.0 and 64.4, 20 of 5000 to 100000 158 and 119; 6 of 40000 to 100000, which need nearly all residues, 65.8 and 67.2.)
+    const int head = blockIdx.x >> log_r, r = (blockIdx.x + head) & ((1 << log_r) - 1), t = threadIdx.x;
     if (!conv_head(g, job, head, LOGC, w) || r >= w.R) return;
     const float* src = in + w.off;
     const float* h = job.h + w.owner * job.item_stride;
