@@ -128,19 +128,18 @@ Geom make_geom(const audiokv_params* p, int n_items) {
 struct Workspace {
     size_t stats_off = 0, raw_off = 0, raw2_off = 0, smooth_off = 0, fft_off = 0, total = 0;
     bool raw2 = false;
-    int stat_splits = 1;      // key ranges per head in the row statistics
+    ScoreRanges ranges;       // of the row statistics
 };
 
 Workspace plan_workspace(const audiokv_params* p, const Batch& b, const int32_t* seqlens_host) {
     Workspace w;
-    const int n_heads = b.n_items * p->n_kv_heads;
     const int rows = (p->n_q_heads / p->n_kv_heads) * (p->window > 0 ? p->window : 1);
     const int rows_pad = score_padded_rows(rows, p->head_dim);
-    const int nsplit = w.stat_splits = score_num_splits(p->n_kv_heads, b.n_items, seqlens_host, rows, p->head_dim);
+    w.ranges = score_ranges(p->n_kv_heads, b.n_items, seqlens_host, rows, p->head_dim);
     size_t off = 0;
     w.stats_off = off;
-    // partial row statistics [head][split][rows_pad][2]
-    off += align_up((size_t)n_heads * (rows_pad > 0 ? rows_pad : 1) * 2 * (size_t)nsplit * sizeof(float), 256);
+    // partial row statistics [part][rows_pad][2]
+    off += align_up((size_t)w.ranges.parts * (rows_pad > 0 ? rows_pad : 1) * 2 * sizeof(float), 256);
     w.raw_off = off;
     off += align_up((size_t)b.total_tokens * p->n_kv_heads * sizeof(float), 256);
     w.raw2 = score_needs_second_raw(rows, p->head_dim);     // second row range of a split sweep 2
@@ -287,7 +286,7 @@ int32_t score_entry(const audiokv_params* params, const void* q_win, const void*
     char* ws = static_cast<char*>(workspace);
     float* stats = reinterpret_cast<float*>(ws + w.stats_off);
     float* raw = params->pool_kernel == 1 ? scores : reinterpret_cast<float*>(ws + w.raw_off);
-    AUDIOKV_HIP(launch_score(g, q_win, k, cu_seqlens_dev, seqlens_host, w.stat_splits, stats, raw, s, nullptr, lse_dev,
+    AUDIOKV_HIP(launch_score(g, q_win, k, cu_seqlens_dev, seqlens_host, w.ranges, stats, raw, s, nullptr, lse_dev,
                              w.raw2 ? reinterpret_cast<float*>(ws + w.raw2_off) : nullptr,
                              (size_t)b.total_tokens * params->n_kv_heads), "score kernels");
     if (params->pool_kernel != 1)
@@ -519,7 +518,7 @@ int32_t evict_entry(const audiokv_params* params, const void* q_win, const void*
         AUDIOKV_HIP(hipEventRecord(g_helper.join, g_helper.stream), "hipEventRecord");
     }
     AUDIOKV_MARK(1);
-    AUDIOKV_HIP(launch_score(g, q_win, k, cu_seqlens_dev, seqlens_host, w.stat_splits, stats, raw, s,
+    AUDIOKV_HIP(launch_score(g, q_win, k, cu_seqlens_dev, seqlens_host, w.ranges, stats, raw, s,
                              prof ? g_prof.ev[AUDIOKV_PROFILE_STAGES + 1] : nullptr, lse_dev,
                              w.raw2 ? reinterpret_cast<float*>(ws + w.raw2_off) : nullptr,
                              (size_t)b.total_tokens * params->n_kv_heads, ride ? &alloc_job : nullptr,

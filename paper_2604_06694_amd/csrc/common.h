@@ -43,6 +43,17 @@ __device__ __forceinline__ int64_t kv_row_offset(const Geom& g, int item, int64_
     return base + ((int64_t)j * g.H_kv + h) * g.D;
 }
 
+// Inclusive sum over the lanes of a full wave, in six data-parallel-primitive steps (no LDS).
+__device__ __forceinline__ int wave_incl(int x) {
+    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);   // row_shr 1, 2, 4, 8: prefixes within 16 lanes
+    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);   // row_bcast 15 into rows 1 and 3
+    x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);   // row_bcast 31 into rows 2 and 3
+    return x;
+}
+
 // Workgroups of `threads` threads for each of n parts of a launch: as many as wanted, but a launch holds fewer than 2^32 threads,
 // and parts of it go along with others: half of that at most. The kernels that ask stride over what is left.
 inline int blocks_per_part(long long wanted, long long n, int threads = 256) {
@@ -60,19 +71,32 @@ struct AllocateJob {
 };
 struct ConvFilterJob;      // taps of the smoothing's filter (conv_filter.h)
 
-// Number of key-range splits per head used by the score kernels; a pure
-// function of the batch so that the workspace query and the launch agree.
-int score_num_splits(int H_kv, int n_items, const int32_t* seqlens_host, int rows, int D);
+// How a sweep of score cuts the heads into key ranges, one workgroup each. Heads of one length: as many ranges for each. Items of
+// different lengths: ranges of as many keys each, range c of item i, head h being part (first + c) * H_kv + h. Up to 64 items,
+// first is the number of ranges of the items before; beyond, floor(tokens of the items before / keys of a range) + i, which a
+// workgroup finds by a search in cu_seqlens (the parts of different items never meet, at most one range per item stays empty).
+struct ScoreRanges {
+    int per_head = 1;        // equal lengths: ranges per head
+    int keys = 0;            // different lengths: keys per range, whole tiles (0: equal lengths)
+    double per_key = 0.;     // 1 / keys
+    long long parts = 1;     // workgroups of the sweep, and sets of row statistics of sweep 1
+    // ranges of a head: the quotient rounded up, in float64 and off the whole numbers, so that it is exact (host and device agree,
+    // and with integer divisions planning for 48 lengths took 25 us)
+    __host__ __device__ int of_length(int L) const { return (int)(((double)L + (double)keys - 0.5) * per_key); }
+};
+constexpr int kCountedItems = 64;
+// The ranges of sweep 1; a pure function of the batch so that the workspace query and the launch agree.
+ScoreRanges score_ranges(int H_kv, int n_items, const int32_t* seqlens_host, int rows, int D);
 // Padded row count (multiple of the MFMA row tiling) for G*W window rows; 0 if unsupported.
 int score_padded_rows(int rows, int D);
 
-// stat_splits: score_num_splits() of the batch.
+// ranges: score_ranges() of the batch.
 // between_sweeps: optional event recorded on `s` after the first sweep (timing aid), or nullptr.
 // lse: optional fp32 [items][H_q][W] natural-log softmax denominators of the window rows; given, sweep 1 is skipped.
 // ride_along, ride_taps: optional allocation (pools of at most kAllocateWaveHeads heads) and filter taps to run in extra
 // workgroups of the first sweep.
 hipError_t launch_score(const Geom& g, const void* q_win, const void* k, const int32_t* cu_seqlens,
-                        const int32_t* seqlens_host, int stat_splits, float* stats_ws, float* raw_out, hipStream_t s,
+                        const int32_t* seqlens_host, const ScoreRanges& ranges, float* stats_ws, float* raw_out, hipStream_t s,
                         hipEvent_t between_sweeps = nullptr, const float* lse = nullptr,
                         float* raw_second = nullptr, size_t raw_elems = 0, const AllocateJob* ride_along = nullptr,
                         const ConvFilterJob* ride_taps = nullptr);

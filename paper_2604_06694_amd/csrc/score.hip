@@ -6,7 +6,8 @@ namespace audiokv {
 
 namespace {
 
-struct Plan { int NB, WR, rows_pad, tile_keys, per_cu; };      // per_cu: resident workgroups
+// per_cu: resident workgroups that heads of one length are planned for; resident: what a CU holds
+struct Plan { int NB, WR, rows_pad, tile_keys, per_cu, resident; };
 
 // Instantiated (32-row blocks per wave, waves per workgroup) pairs in order of preference per sweep: the first
 // that holds the rows is taken (all must exist in score_d*.hip). More than 448 rows take three row tiles per wave in sweep 1;
@@ -28,7 +29,7 @@ constexpr long long kNarrowTileKeys = 3 << 17;     // keys of all heads: between
 bool make_plan(int rows, int D, int sweep, long long keys, Plan* out) {
     const Combo* cs; int n;
     if (D <= 128 && rows > 224 && rows <= 256 && keys <= kNarrowTileKeys) {
-        *out = Plan{1, 8, 256, 32 * AUDIOKV_SCORE_KB, 1};      // nine waves of 128 registers: one workgroup per CU
+        *out = Plan{1, 8, 256, 32 * AUDIOKV_SCORE_KB, 1, 1};      // nine waves of 128 registers: one workgroup per CU
         return D == 64 || D == 128;
     }
     if (D == 64 || D == 128) { cs = sweep == 1 ? kSweep1_128 : kSweep2_128; n = sweep == 1 ? 7 : 6; }
@@ -42,7 +43,9 @@ bool make_plan(int rows, int D, int sweep, long long keys, Plan* out) {
             // At d = 256, four waves and, in sweep 1, seven are resident twice but planned as if they were not: planned with two, 128
             // rows 28 x 8192 take 113.5 us instead of 125.4, but 4 x 8192 29.7 instead of 24.0 and 8 of 2048-32768 56.7 instead of 55.3.
             const bool two = (cs[i].NB == 1 && D <= 128) || cs[i].WR < 4 || (cs[i].NB == 2 && cs[i].WR == 4 && sweep == 1);
-            *out = Plan{cs[i].NB, cs[i].WR, pad, (D == 256) ? 32 : 32 * AUDIOKV_SCORE_KB, two ? 2 : 1};
+            // Items of different lengths, whose ranges are cut to one size, take what is resident (d = 256, 8 of 2048 to 32768 planned for one workgroup per CU 61 us, for two 50).
+            const bool resident = two || (D == 256 && (cs[i].WR == 4 || (cs[i].WR == 7 && sweep == 1)));
+            *out = Plan{cs[i].NB, cs[i].WR, pad, (D == 256) ? 32 : 32 * AUDIOKV_SCORE_KB, two ? 2 : 1, resident ? 2 : 1};
             return true;
         }
     }
@@ -55,61 +58,46 @@ long long total_keys(int H_kv, int n_items, const int32_t* seqlens_host) {
     return keys;
 }
 
-int num_splits(const Plan& p, int H_kv, int n_items, const int32_t* seqlens_host) {
-    // A head is cut into key ranges so that the grid fills the 256 CUs evenly: the split count minimises the time of
-    // the launch in units of one tile, with a fixed prologue cost per workgroup (in tiles).
-    const int slots = 256 * p.per_cu;
+ScoreRanges plan_ranges(const Plan& p, int H_kv, int n_items, const int32_t* seqlens_host) {
+    // The heads are cut into key ranges so that the grid fills the 256 CUs evenly: the division minimises the time of
+    // the launch in units of one tile, with a fixed prologue cost per workgroup (in tiles), in whole rounds of workgroups.
     // what a workgroup costs before its first and after its last tile (query fragments, filling the ring, the row
     // statistics or constants), in tiles: about 200 keys' worth, fitted to measured launches
     const int overhead = p.tile_keys >= 64 ? 3 : 7;
-    int max_tiles = 1;
-    bool uniform = true;
+    int longest = 1;
+    bool uniform = true;             // as many ranges for every head
+    long long tokens = 0;
     for (int i = 0; i < n_items; ++i) {
-        const int t = (seqlens_host[i] + p.tile_keys - 1) / p.tile_keys;
-        if (t > max_tiles) max_tiles = t;
+        if (seqlens_host[i] > longest) longest = seqlens_host[i];
         if (seqlens_host[i] != seqlens_host[0]) uniform = false;
+        tokens += seqlens_host[i];
     }
-    // (for ragged batches, in which every count is tried with every length: quotients rounded up, in float64 and off the whole
-    // numbers, so that they are exact. 48 lengths took 25 us with integer divisions. The first lengths' tiles are kept in an array
-    // of fixed size: a container could throw, and callers are C.)
-    constexpr int kKept = 256;
-    double kept[kKept];
-    const int tile_shift = __builtin_ctz((unsigned)p.tile_keys);
-    const auto tiles = [&](int i) { return (double)((seqlens_host[i] + p.tile_keys - 1) >> tile_shift); };
-    if (!uniform)
-        for (int i = 0; i < n_items && i < kKept; ++i) kept[i] = tiles(i);
-    int best = 1;
+    const int max_tiles = (longest + p.tile_keys - 1) / p.tile_keys;
+    // (lengths differ, but a workgroup for every tile of every head, were all as long as the longest, fits the chip at once: to find
+    // its item would cost each of them 0.2 us. The same answer for every sweep of a call, whatever its tiling.)
+    if (!uniform && max_tiles <= 64 && (long long)n_items * H_kv * max_tiles <= 256) uniform = true;
+    const int slots = 256 * (uniform ? p.per_cu : p.resident);
+    ScoreRanges best;
     long long best_cost = -1;
     const int ns_max = max_tiles < 64 ? max_tiles : 64;
-    for (int ns = 1; ns <= ns_max; ++ns) {
-        long long cost;
-        if (uniform) {
-            // equal workgroups run in whole rounds
-            const long long groups = (long long)n_items * H_kv * ns;
-            const long long rounds = (groups + slots - 1) / slots;
-            cost = rounds * ((max_tiles + ns - 1) / ns + overhead);
-        } else {
-            // Ragged lengths: a head's ranges are as long as the head is (tiles of the head / ns), and workgroups
-            // start as others end. The launch takes about the average load of a slot, plus part of the longest
-            // workgroup for the ones that start last, plus, when the last round of workgroups fills only part of the
-            // slots, that round's average workgroup for the slots left idle (all in twice the unit, to keep halves).
-            const long long groups = (long long)n_items * H_kv * ns;   // launched, whether or not they hold tiles
-            double sum = 0., most = 0.;
-            const double per_range = 1. / ns;
-            for (int i = 0; i < n_items; ++i) {
-                const double t = i < kKept ? kept[i] : tiles(i);
-                if (!(t > 0.)) continue;
-                const double tps = (double)(int)((t + ns - 0.5) * per_range);
-                const double used = (double)(int)((t + tps - 0.5) / tps);       // ranges of this head that hold tiles
-                sum += t + used * overhead;
-                most = tps > most ? tps : most;
+    for (int ns = 1; ns <= ns_max; ++ns) {                  // ranges of a head of the longest item
+        const int tiles = (max_tiles + ns - 1) / ns;
+        ScoreRanges r;
+        r.per_head = ns;
+        long long groups = (long long)n_items * ns;         // per KV head, empty ones included
+        if (!uniform) {
+            r.keys = tiles * p.tile_keys;
+            r.per_key = 1. / r.keys;
+            groups = tokens / r.keys + n_items;
+            if (n_items <= kCountedItems) {
+                groups = 0;
+                for (int i = 0; i < n_items; ++i) groups += r.of_length(seqlens_host[i]);
             }
-            const long long total = (long long)sum * H_kv, longest = most > 0. ? (long long)most + overhead : 0;
-            cost = 2 * ((total + slots - 1) / slots) + longest;
-            const long long rem = groups % slots;
-            if (groups > slots && rem) cost += 2 * (total / groups) * (slots - rem) / slots;
         }
-        if (best_cost < 0 || cost < best_cost) { best_cost = cost; best = ns; }
+        r.parts = groups * H_kv;
+        const long long rounds = (r.parts + slots - 1) / slots;
+        const long long cost = rounds * (tiles + overhead);
+        if (best_cost < 0 || cost < best_cost) { best_cost = cost; best = r; }
     }
     return best;
 }
@@ -137,15 +125,19 @@ int score_padded_rows(int rows, int D) {
 
 bool score_needs_second_raw(int rows, int D) { return sweep2_is_split(rows, D); }
 
-// key ranges per head of sweep 1: what sizes the statistics in the workspace
-int score_num_splits(int H_kv, int n_items, const int32_t* seqlens_host, int rows, int D) {
+// what sizes the statistics in the workspace
+ScoreRanges score_ranges(int H_kv, int n_items, const int32_t* seqlens_host, int rows, int D) {
     Plan p;
-    if (n_items <= 0 || H_kv <= 0 || !make_plan(rows, D, 1, total_keys(H_kv, n_items, seqlens_host), &p)) return 1;
-    return num_splits(p, H_kv, n_items, seqlens_host);
+    if (n_items <= 0 || H_kv <= 0 || !make_plan(rows, D, 1, total_keys(H_kv, n_items, seqlens_host), &p)) {
+        ScoreRanges none;
+        none.parts = (long long)n_items * H_kv;
+        return none;
+    }
+    return plan_ranges(p, H_kv, n_items, seqlens_host);
 }
 
 hipError_t launch_score(const Geom& g, const void* q_win, const void* k, const int32_t* cu_seqlens,
-                        const int32_t* seqlens_host, int ns1, float* stats_ws, float* raw_out, hipStream_t s, hipEvent_t between_sweeps,
+                        const int32_t* seqlens_host, const ScoreRanges& ranges1, float* stats_ws, float* raw_out, hipStream_t s, hipEvent_t between_sweeps,
                         const float* lse, float* raw_second, size_t raw_elems, const AllocateJob* ride_along,
                         const ConvFilterJob* ride_taps)
 {
@@ -159,9 +151,9 @@ hipError_t launch_score(const Geom& g, const void* q_win, const void* k, const i
     // calls, forwards and backwards: 28 x 32768, 448 rows 929 and 915 us, 13 x 32768 452 and 442; 224 rows 30 x 9000 (276 MB) 169 and 165,
     // 48 x 10000 297 and 289; K that fits: 28 x 9000, 256 rows (258 MB) 352 and 356 with the eviction around it.
     const bool backwards = keys * g.D * 2 > (1LL << 28);
-    score_detail::SweepArgs args{q_win, k, cu_seqlens, 0, rows_pad, 0, stats_ws, ns1, lse, raw_out, backwards, ride_along, ride_taps};
-    auto sweep = [&](int which, const Plan& p, int ns, int row_base, float* raw) -> hipError_t {
-        args.nsplit = ns;
+    score_detail::SweepArgs args{q_win, k, cu_seqlens, ranges1, rows_pad, 0, stats_ws, ranges1, lse, raw_out, backwards, ride_along, ride_taps};
+    auto sweep = [&](int which, const Plan& p, const ScoreRanges& ranges, int row_base, float* raw) -> hipError_t {
+        args.ranges = ranges;
         args.row_base = row_base;
         args.raw = raw;
         hipError_t e = hipErrorInvalidValue;
@@ -174,7 +166,7 @@ hipError_t launch_score(const Geom& g, const void* q_win, const void* k, const i
         args.taps = nullptr;
         return e;
     };
-    hipError_t e = lse ? hipSuccess : sweep(1, p1, ns1, 0, raw_out);
+    hipError_t e = lse ? hipSuccess : sweep(1, p1, ranges1, 0, raw_out);
     if (e != hipSuccess) return e;
     if (between_sweeps) {
         e = hipEventRecord(between_sweeps, s);
@@ -183,14 +175,14 @@ hipError_t launch_score(const Geom& g, const void* q_win, const void* k, const i
     Plan p2;
     if (!sweep2_is_split(rows, g.D)) {
         if (!make_plan(rows, g.D, 2, keys, &p2)) return hipErrorInvalidValue;
-        return sweep(2, p2, num_splits(p2, g.H_kv, g.n_items, seqlens_host), 0, raw_out);
+        return sweep(2, p2, plan_ranges(p2, g.H_kv, g.n_items, seqlens_host), 0, raw_out);
     }
     if (!raw_second) return hipErrorInvalidValue;
     Plan p2b;
     if (!make_plan(kSweep2MaxRows, g.D, 2, keys, &p2) || !make_plan(rows - kSweep2MaxRows, g.D, 2, keys, &p2b)) return hipErrorInvalidValue;
-    e = sweep(2, p2, num_splits(p2, g.H_kv, g.n_items, seqlens_host), 0, raw_out);
+    e = sweep(2, p2, plan_ranges(p2, g.H_kv, g.n_items, seqlens_host), 0, raw_out);
     if (e != hipSuccess) return e;
-    e = sweep(2, p2b, num_splits(p2b, g.H_kv, g.n_items, seqlens_host), kSweep2MaxRows, raw_second);
+    e = sweep(2, p2b, plan_ranges(p2b, g.H_kv, g.n_items, seqlens_host), kSweep2MaxRows, raw_second);
     if (e != hipSuccess) return e;
     const unsigned blocks = (unsigned)((raw_elems + 256 * 8 - 1) / (256 * 8));
     hipLaunchKernelGGL(score_detail::score_add_kernel, dim3(blocks > 0 ? blocks : 1), dim3(256), 0, s, raw_out,

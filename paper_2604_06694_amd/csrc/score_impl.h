@@ -178,7 +178,7 @@ __device__ __forceinline__ void ride_along(const RideAlong& ride, int block) {
                        j.budgets, j.cu_budgets);
 }
 
-// Row r of head `head`: the per-range softmax statistics (reference in base-2 units, sum of exp2) of sweep 1 merged into
+// One row of a head: the per-range softmax statistics (reference in base-2 units, sum of exp2) of sweep 1 merged into
 // max + log2(sum), one pass with a running reference and a sum rescaled when the reference rises, sixteen ranges at a time.
 // Every workgroup of sweep 2 merges the rows it needs for itself, N ranges' loads in flight beside those of its queries and
 // first keys, instead of reading constants that a launch in between prepared: that launch took 3.9 to 5.5 us, most of it spent on
@@ -189,9 +189,9 @@ __device__ __forceinline__ void ride_along(const RideAlong& ride, int block) {
 // merge their rows one after the other, and with five to seven heads it costs more than it saves (576 rows, six heads of 16000
 // 54.6 -> 56.3 us; one launch merging for both 55.5 there, but two heads of 9000 48.6 -> 50.1).
 // HALVES: the two halves of a wave share a row (the caller's r is the same in both) and take the batches of sixteen in turn.
+// stats: those of the row in the first of its nsplit ranges; pitch: from range to range.
 template <int N, bool HALVES>
-__device__ __forceinline__ float merged_row(const float* __restrict__ stats, int nsplit, int rows_pad, int head, int r, int half) {
-    const float2* hs = reinterpret_cast<const float2*>(stats) + (size_t)head * nsplit * rows_pad + r;
+__device__ __forceinline__ float merged_row(const float2* __restrict__ hs, int nsplit, int pitch, int half) {
     const int first = HALVES ? half * 16 : 0;
     constexpr int kStep = HALVES ? 2 * N : N;
     static_assert(!HALVES || N == 16, "batches in turn");
@@ -206,7 +206,7 @@ __device__ __forceinline__ float merged_row(const float* __restrict__ stats, int
     for (int s0 = 0; s0 < nsplit; s0 += kStep) {
         float2 v[N];
 #pragma unroll
-        for (int u = 0; u < N; ++u) v[u] = hs[(size_t)min(s0 + first + u, nsplit - 1) * rows_pad];
+        for (int u = 0; u < N; ++u) v[u] = hs[(size_t)min(s0 + first + u, nsplit - 1) * pitch];
 #pragma unroll
         for (int b = 0; b < N; b += 16) {
             float top = -INFINITY;
@@ -236,18 +236,48 @@ __device__ __forceinline__ float merged_row(const float* __restrict__ stats, int
     return M + __log2f(Z);
 }
 
-template <int D, int NB, int WR, bool SWEEP2>
-__global__ __launch_bounds__(64 * (WR + 1), (NB == 1 && D <= 128) ? 4 : 2) void score_kernel(
-    Geom g, const __bf16* __restrict__ q_win, const __bf16* __restrict__ k,
-    const int32_t* __restrict__ cu_seq, int n_wg, int nsplit,
-    int backwards,                    // sweep 2 begins with the heads that sweep 1 ended with
-    int rows_pad,                     // row pitch of stats (>= ROWS: the two sweeps may tile the rows differently)
-    int row_base,                     // first window row of this launch (sweep 2 may cover the rows in two launches)
-    float* __restrict__ stats,        // [head][split][rows_pad][2] = (max in base-2 units, sum of exp2): sweep 1 out, sweep 2 in
-    int stat_splits,                  // sweep 2: ranges per head in stats
-    const float* __restrict__ lse,    // sweep 2: instead of stats, [item][H_q][W] natural logs of the softmax denominators
-    float* __restrict__ raw,          // sweep 2 out, packed like scores
-    RideAlong ride)                   // in the workgroups from n_wg on
+// Items of different lengths: the item and the ranges of a workgroup. Up to 64 items, a lane has the place of one, and what a
+// workgroup needs of its own is a lane's: one load latency in all.
+struct RangePlace {
+    int at = 0, len = 0;         // this lane's item
+    __device__ __forceinline__ void load(const int32_t* __restrict__ cu_seq, int n_items) {
+        const int lane = threadIdx.x & 63, i = min(lane, n_items - 1);
+        at = cu_seq[i];
+        len = lane < n_items ? cu_seq[i + 1] - at : 0;
+    }
+    // ranges of the items up to the lane's
+    __device__ __forceinline__ int counts(const ScoreRanges& r) const { return wave_incl(len > 0 ? r.of_length(len) : 0); }
+    static __device__ __forceinline__ int before(int counts, int item) {
+        return item > 0 ? __builtin_amdgcn_readlane(counts, item > 0 ? item - 1 : 0) : 0;
+    }
+};
+// more than 64 items
+__device__ __forceinline__ int first_range(const int32_t* __restrict__ cu_seq, int i, unsigned keys) {
+    return (int)((unsigned)(cu_seq[i] - cu_seq[0]) / keys) + i;
+}
+// The last item whose first range is not past range q: every round probes 64 of them at equal distances, one per lane, one load
+// latency for up to 64, two up to 4096.
+__device__ __forceinline__ int item_of_range(const int32_t* __restrict__ cu_seq, int n_items, int q, unsigned keys) {
+    int item = 0;
+    for (int span = n_items; span > 1;) {
+        const int step = (span + 63) >> 6;
+        const int probe = item + (int)(threadIdx.x & 63) * step;
+        const bool at_or_before = probe < item + span && first_range(cu_seq, min(probe, n_items - 1), keys) <= q;
+        const int n = __builtin_popcountll(__builtin_amdgcn_ballot_w64(at_or_before));   // a prefix of the lanes
+        const int skip = n > 0 ? (n - 1) * step : 0;
+        item += skip;
+        span = min(step, span - skip);
+    }
+    return __builtin_amdgcn_readfirstlane(item);
+}
+
+// RAGGED: items of different lengths. Kernels of their own: with the search for an item beside it in one kernel, the prologue of calls
+// on one layer took longer (evict 13577 48.2 -> 49.3 us, 32768 with 448 rows 87.8 -> 89.3).
+template <int D, int NB, int WR, bool SWEEP2, bool RAGGED>
+__device__ __forceinline__ void score_sweep(
+    const Geom& g, const __bf16* __restrict__ q_win, const __bf16* __restrict__ k,
+    const int32_t* __restrict__ cu_seq, int n_wg, const ScoreRanges& ranges, int backwards, int rows_pad, int row_base,
+    float* __restrict__ stats, const ScoreRanges& stat_ranges, const float* __restrict__ lse, float* __restrict__ raw, const RideAlong& ride)
 {
     if ((int)blockIdx.x >= n_wg) {                    // uniform
         ride_along(ride, (int)blockIdx.x - n_wg);
@@ -258,11 +288,39 @@ __global__ __launch_bounds__(64 * (WR + 1), (NB == 1 && D <= 128) ? 4 : 2) void 
     float* lds_cols = reinterpret_cast<float*>(lds + T::STAGES * T::LDS_K);
     float* lds_rc = reinterpret_cast<float*>(lds + T::STAGES * T::LDS_K + 3 * T::LDS_COLS);
 
-    // Workgroups go to the 8 XCDs round-robin by index, and each XCD has its own L2. All key-range splits of a head
-    // are therefore given indices with the same residue mod 8, so that the head's window queries (and the tile
-    // shared by neighbouring splits) are fetched from HBM by one L2 only.
-    int head, split;
-    {
+    // Workgroups go to the 8 XCDs round-robin by index, and each XCD has its own L2. Of heads of one length, all key-range splits
+    // of a head are therefore given indices with the same residue mod 8, so that the head's window queries (and the tile
+    // shared by neighbouring splits) are fetched from HBM by one L2 only. With different lengths that would give the XCDs loads
+    // as different as their heads', and the launch the time of the fullest: there ranges of one size follow one another, and the
+    // heads of a range. Score calls, as many ranges for every head and ranges of one size: 224 rows 10 of 600 to 30000 tokens 69.7 and
+    // 51.5 us, 256 rows 8 of 2000 to 20000 70.0 and 51.8, 448 rows 24 of 1500 to 30000 372 and 333, 128 rows 30 of 500 to 16000 108 and
+    // 87, d = 256 8 of 2048 to 32768 56.7 and 49.7, 100 of 500 to 8000 234 and 231; short ones, for the search, 40 of 400 to 6000
+    // 21.7 and 21.9, 448 rows 6 of 500 to 2000 21.5 and 21.8.
+    const int nsplit = ranges.per_head;
+    int item, h, split, part, tok0, L;
+    int stat_first = 0;                               // items of different lengths: the item's first range in stats
+    if constexpr (RAGGED) {
+        const int q = blockIdx.x / g.H_kv;
+        h = blockIdx.x - q * g.H_kv;
+        part = blockIdx.x;
+        if (g.n_items <= kCountedItems) {
+            RangePlace place;
+            place.load(cu_seq, g.n_items);
+            const int counts = place.counts(ranges);
+            item = min(__builtin_popcountll(__builtin_amdgcn_ballot_w64(counts <= q)), g.n_items - 1);   // (a prefix of the lanes)
+            split = q - RangePlace::before(counts, item);
+            if (SWEEP2) stat_first = RangePlace::before(place.counts(stat_ranges), item);
+            tok0 = __builtin_amdgcn_readlane(place.at, item);
+            L = __builtin_amdgcn_readlane(place.len, item);
+        } else {
+            item = item_of_range(cu_seq, g.n_items, q, ranges.keys);
+            split = q - first_range(cu_seq, item, ranges.keys);
+            if (SWEEP2) stat_first = first_range(cu_seq, item, stat_ranges.keys);
+            tok0 = cu_seq[item];
+            L = cu_seq[item + 1] - tok0;
+        }
+    } else {
+        int head;
         const int n_heads = n_wg / nsplit;
         const int full = n_heads & ~7;                  // heads that fill whole groups of 8
         const int bid = blockIdx.x;
@@ -282,10 +340,12 @@ __global__ __launch_bounds__(64 * (WR + 1), (NB == 1 && D <= 128) ? 4 : 2) void 
                 split = r - (r / nsplit) * nsplit;
             }
         }
+        item = head / g.H_kv;
+        h = head - item * g.H_kv;
+        part = head * nsplit + split;
+        tok0 = cu_seq[item];
+        L = cu_seq[item + 1] - tok0;
     }
-    const int item = head / g.H_kv, h = head - item * g.H_kv;
-    const int tok0 = cu_seq[item];
-    const int L = cu_seq[item + 1] - tok0;
     const int R = g.G * g.W;                          // real window rows of this head
     const float c = g.c_log2;
 
@@ -296,14 +356,14 @@ __global__ __launch_bounds__(64 * (WR + 1), (NB == 1 && D <= 128) ? 4 : 2) void 
     const int rowg0 = row_base + row0;                // the same as a window row of the head
 
     const int n_tiles = (L + T::TK - 1) / T::TK;
-    const int tps = (n_tiles + nsplit - 1) / nsplit;
+    const int tps = RAGGED ? ranges.keys / T::TK : (n_tiles + nsplit - 1) / nsplit;
     const int t_begin = split * tps;
     const int t_end = min(n_tiles, t_begin + tps);
 
     const int n_loc = t_end - t_begin;                  // tiles of this workgroup
     if (t_begin >= t_end) {                           // uniform over the workgroup
         if (!SWEEP2) {
-            float* my_stats = stats + ((size_t)head * nsplit + split) * rows_pad * 2;
+            float* my_stats = stats + (size_t)part * rows_pad * 2;
             for (int r = tid; r < T::ROWS; r += T::THREADS) { my_stats[2 * r] = -INFINITY; my_stats[2 * r + 1] = 0.f; }
         }
         return;
@@ -392,14 +452,23 @@ __global__ __launch_bounds__(64 * (WR + 1), (NB == 1 && D <= 128) ? 4 : 2) void 
     // ================= compute waves =================
     // sweep 2, row constants: max + log2(sum); +inf for padded rows, whose exp2 then vanishes
     auto row_constants = [&]() {
+        // the statistics of the head's ranges: how many, where the first ones are, how far apart
+        int n_stat = stat_ranges.per_head, pitch = rows_pad;
+        size_t first = (size_t)(item * g.H_kv + h) * n_stat;
+        if (RAGGED) {
+            n_stat = stat_ranges.of_length(L);
+            first = (size_t)stat_first * g.H_kv + h;
+            pitch *= g.H_kv;
+        }
+        const float2* head_stats = reinterpret_cast<const float2*>(stats) + first * rows_pad;
         for (int i = NB == 1 ? l32 : lane; i < NB * 32; i += 64) {
             const int r = min(rowg0 + i, R - 1);
             float out;
             if (lse)                      // rows of a head follow one another: window row r % W of query head r / W of the group
                 out = lse[((size_t)item * g.H_q + (size_t)h * g.G) * g.W + r] * 1.44269504088896340736f;
-            else if constexpr (NB == 1) out = merged_row<16, true>(stats, stat_splits, rows_pad, head, r, g2);
-            else if (stat_splits <= 16) out = merged_row<16, false>(stats, stat_splits, rows_pad, head, r, 0);
-            else out = merged_row<32, false>(stats, stat_splits, rows_pad, head, r, 0);
+            else if constexpr (NB == 1) out = merged_row<16, true>(head_stats + r, n_stat, pitch, g2);
+            else if (n_stat <= 16) out = merged_row<16, false>(head_stats + r, n_stat, pitch, 0);
+            else out = merged_row<32, false>(head_stats + r, n_stat, pitch, 0);
             lds_rc[row0 + i] = rowg0 + i < R ? out : INFINITY;
         }
     };
@@ -730,7 +799,7 @@ __global__ __launch_bounds__(64 * (WR + 1), (NB == 1 && D <= 128) ? 4 : 2) void 
 
     if (!SWEEP2) {
         // a row's keys are spread over the two halves of the wave
-        float* my_stats = stats + ((size_t)head * nsplit + split) * rows_pad * 2;
+        float* my_stats = stats + (size_t)part * rows_pad * 2;
 #pragma unroll
         for (int rb = 0; rb < NB; ++rb) {
             const float m2 = __shfl_xor(run_m[rb], 32, 64), l2 = __shfl_xor(run_l[rb], 32, 64);
@@ -744,6 +813,39 @@ __global__ __launch_bounds__(64 * (WR + 1), (NB == 1 && D <= 128) ? 4 : 2) void 
     }
 }
 
+#define AUDIOKV_SCORE_BOUNDS __launch_bounds__(64 * (WR + 1), (NB == 1 && D <= 128) ? 4 : 2)
+
+template <int D, int NB, int WR, bool SWEEP2>
+__global__ AUDIOKV_SCORE_BOUNDS void score_kernel(
+    Geom g, const __bf16* __restrict__ q_win, const __bf16* __restrict__ k,
+    const int32_t* __restrict__ cu_seq, int n_wg, int nsplit,
+    int backwards,                    // sweep 2 begins with the heads that sweep 1 ended with
+    int rows_pad,                     // row pitch of stats (>= ROWS: the two sweeps may tile the rows differently)
+    int row_base,                     // first window row of this launch (sweep 2 may cover the rows in two launches)
+    float* __restrict__ stats,        // [head][split][rows_pad][2] = (max in base-2 units, sum of exp2): sweep 1 out, sweep 2 in
+    int stat_splits,                  // sweep 2: ranges per head in stats
+    const float* __restrict__ lse,    // sweep 2: instead of stats, [item][H_q][W] natural logs of the softmax denominators
+    float* __restrict__ raw,          // sweep 2 out, packed like scores
+    RideAlong ride)                   // in the workgroups from n_wg on
+{
+    ScoreRanges ranges, stat_ranges;
+    ranges.per_head = nsplit;
+    stat_ranges.per_head = stat_splits;
+    score_sweep<D, NB, WR, SWEEP2, false>(g, q_win, k, cu_seq, n_wg, ranges, backwards, rows_pad, row_base, stats, stat_ranges, lse, raw, ride);
+}
+
+template <int D, int NB, int WR, bool SWEEP2>
+__global__ AUDIOKV_SCORE_BOUNDS void score_ragged_kernel(
+    Geom g, const __bf16* __restrict__ q_win, const __bf16* __restrict__ k,
+    const int32_t* __restrict__ cu_seq, int n_wg, ScoreRanges ranges, int rows_pad, int row_base,
+    float* __restrict__ stats,        // [part of stat_ranges][rows_pad][2]
+    ScoreRanges stat_ranges,          // those of sweep 1
+    const float* __restrict__ lse, float* __restrict__ raw, RideAlong ride)
+{
+    score_sweep<D, NB, WR, SWEEP2, true>(g, q_win, k, cu_seq, n_wg, ranges, 0, rows_pad, row_base, stats, stat_ranges, lse, raw, ride);
+}
+#undef AUDIOKV_SCORE_BOUNDS
+
 // raw += raw_b: the column sums of the second row range of a split sweep 2 (fixed order: deterministic)
 static __global__ __launch_bounds__(256) void score_add_kernel(float* __restrict__ raw, const float* __restrict__ raw_b, size_t n)
 {
@@ -756,9 +858,10 @@ struct SweepArgs {
     const void* q_win;
     const void* k;
     const int32_t* cu_seq;
-    int nsplit, rows_pad, row_base;
+    ScoreRanges ranges;            // of the sweep
+    int rows_pad, row_base;
     float* stats;
-    int stat_splits;
+    ScoreRanges stat_ranges;       // of sweep 1
     const float* lse;
     float* raw;
     bool backwards;
@@ -766,20 +869,17 @@ struct SweepArgs {
     const ConvFilterJob* taps;
 };
 
-// which = 1: per-range row statistics into stats; which = 2: column sums from stats or lse into raw (of a tiling that is not
-// for sweep 1 only)
-template <int D, int NB, int WR, bool BOTH = true>
-hipError_t launch_sweep(int which, const Geom& g, const SweepArgs& a, hipStream_t s)
+template <int D, int NB, int WR, bool SWEEP2>
+hipError_t launch_sweep_kernels(const Geom& g, const SweepArgs& a, hipStream_t s)
 {
     using T = Tile<D, NB, WR>;
     static std::atomic<bool> attr_set{false};
     if (!attr_set && T::LDS_BYTES > 48 * 1024) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(score_kernel<D, NB, WR, false>),
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(score_kernel<D, NB, WR, SWEEP2>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, T::LDS_BYTES);
-        if constexpr (BOTH)
-            if (e == hipSuccess)
-                e = hipFuncSetAttribute(reinterpret_cast<const void*>(score_kernel<D, NB, WR, true>),
-                                        hipFuncAttributeMaxDynamicSharedMemorySize, T::LDS_BYTES);
+        if (e == hipSuccess)
+            e = hipFuncSetAttribute(reinterpret_cast<const void*>(score_ragged_kernel<D, NB, WR, SWEEP2>),
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, T::LDS_BYTES);
         if (e != hipSuccess) return e;
         attr_set = true;
     }
@@ -794,17 +894,26 @@ hipError_t launch_sweep(int which, const Geom& g, const SweepArgs& a, hipStream_
         ride.taps_per_item = ride.taps.blocks_per_item(T::THREADS);
         ride.tap_blocks = ride.taps_per_item * ride.taps.n_items;
     }
-    const int n_wg = g.n_items * g.H_kv * a.nsplit;
+    const int n_wg = (int)a.ranges.parts;
     const dim3 grid((unsigned)(n_wg + ride.alloc_blocks + ride.tap_blocks));
-    if (which == 1)
-        hipLaunchKernelGGL((score_kernel<D, NB, WR, false>), grid, dim3(T::THREADS), T::LDS_BYTES, s, g, (const __bf16*)a.q_win,
-                           (const __bf16*)a.k, a.cu_seq, n_wg, a.nsplit, 0, a.rows_pad, 0, a.stats, 0, (const float*)nullptr, a.raw, ride);
-    else if constexpr (BOTH)
-        hipLaunchKernelGGL((score_kernel<D, NB, WR, true>), grid, dim3(T::THREADS), T::LDS_BYTES, s, g, (const __bf16*)a.q_win,
-                           (const __bf16*)a.k, a.cu_seq, n_wg, a.nsplit, a.backwards ? 1 : 0, a.rows_pad, a.row_base, a.stats, a.stat_splits, a.lse, a.raw, ride);
+    if (a.ranges.keys)
+        hipLaunchKernelGGL((score_ragged_kernel<D, NB, WR, SWEEP2>), grid, dim3(T::THREADS), T::LDS_BYTES, s, g, (const __bf16*)a.q_win,
+                           (const __bf16*)a.k, a.cu_seq, n_wg, a.ranges, a.rows_pad, a.row_base, a.stats, a.stat_ranges, a.lse, a.raw, ride);
     else
-        return hipErrorInvalidValue;
+        hipLaunchKernelGGL((score_kernel<D, NB, WR, SWEEP2>), grid, dim3(T::THREADS), T::LDS_BYTES, s, g, (const __bf16*)a.q_win,
+                           (const __bf16*)a.k, a.cu_seq, n_wg, a.ranges.per_head, SWEEP2 && a.backwards ? 1 : 0, a.rows_pad, a.row_base, a.stats,
+                           a.stat_ranges.per_head, a.lse, a.raw, ride);
     return hipGetLastError();
+}
+
+// which = 1: per-range row statistics into stats; which = 2: column sums from stats or lse into raw (of a tiling that is not
+// for sweep 1 only)
+template <int D, int NB, int WR, bool BOTH = true>
+hipError_t launch_sweep(int which, const Geom& g, const SweepArgs& a, hipStream_t s)
+{
+    if (which == 1) return launch_sweep_kernels<D, NB, WR, false>(g, a, s);
+    if constexpr (BOTH) return launch_sweep_kernels<D, NB, WR, true>(g, a, s);
+    return hipErrorInvalidValue;
 }
 
 }  // namespace score_detail

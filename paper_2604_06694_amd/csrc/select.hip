@@ -143,18 +143,7 @@ constexpr int kCompact = 8;          // undecided keys per thread once the strea
 constexpr int kDigitBits = 11, kBins = 1 << kDigitBits;   // bins of one histogram round
 constexpr int kLast = 64;            // candidates that one wave ranks against each other
 
-// Inclusive sum over the lanes of a full wave, in six data-parallel-primitive steps (no LDS).
-__device__ __forceinline__ int wave_incl(int x) {
-    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);   // row_shr 1, 2, 4, 8: prefixes within 16 lanes
-    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);
-    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);
-    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);
-    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);   // row_bcast 15 into rows 1 and 3
-    x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);   // row_bcast 31 into rows 2 and 3
-    return x;
-}
-
-// the same over the first N lanes, a power of two up to 16
+// Inclusive sum over the first N lanes, a power of two up to 16
 template <int N>
 __device__ __forceinline__ int row_incl(int x) {
     x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);

@@ -1,0 +1,49 @@
+"""Scores of items of different lengths, whose key ranges are of one size: every way in which a workgroup finds its item (up to 64
+items, more, none needed), sweeps of one call that divide the heads differently, and what evict makes of them."""
+import numpy as np
+import pytest
+import torch
+
+from test_gpu_score_ranges import _inputs, _reference
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def A():
+    import paper_2604_06694_amd as A
+    return A
+
+
+def _spread(n, lo, hi):
+    return [int(lo * (hi / lo) ** ((i * 7 % n) / max(1, n - 1))) for i in range(n)]
+
+
+# query heads, KV heads, head_dim, window; the last ones cover 576 rows, in which the second launch of sweep 2 holds twice the workgroups
+@pytest.mark.parametrize("H_q,H_kv,d,W", [(28, 4, 128, 32), (8, 1, 128, 32), (14, 2, 128, 64), (8, 2, 256, 32), (8, 2, 64, 16), (9, 1, 128, 64)])
+@pytest.mark.parametrize("lens", [[100, 70], [64, 65, 63 + 64, 2048], [9000, 300], [300, 20011], [4000, 3900, 500, 2000, 4096], _spread(12, 90, 6000),
+                                  _spread(64, 64, 700), _spread(65, 64, 700), [5000] + [64] * 130],
+                         ids=lambda v: f"{len(v)}x{min(v)}-{max(v)}")
+def test_scores_of_ragged_items(A, H_q, H_kv, d, W, lens):
+    q, k = _inputs(H_q, H_kv, d, W, lens)
+    ref, lse = _reference(q, k, H_q, H_kv, d, W, lens, True)
+    p = A.Params(H_q, H_kv, d, W, pool_kernel=1)
+    # (the bound of test_scores_for_every_division_into_ranges)
+    for got in (A.score(p, q, k, lens), A.score(p, q, k, lens, lse=lse.float())):
+        assert ((got.double() - ref).abs() <= 3e-5 * ref + 1e-30).all()
+
+
+@pytest.mark.parametrize("n_items", [3, 70])
+def test_items_score_as_they_do_alone(A, n_items):
+    """The same item twice, and by itself: a range belongs to the right item and head in either order."""
+    H_q, H_kv, d, W = 8, 2, 64, 16
+    lens = _spread(n_items, 200, 9000)
+    q, k = _inputs(H_q, H_kv, d, W, lens)
+    p = A.Params(H_q, H_kv, d, W)
+    got = A.score(p, q, k, lens).cpu().numpy()
+    cu = np.concatenate([[0], np.cumsum(lens)])
+    for i in (0, n_items // 2, n_items - 1):
+        a, b = cu[i] * H_kv, cu[i + 1] * H_kv
+        alone = A.score(p, q.view(n_items, -1)[i].contiguous(), k[a * d:b * d].contiguous(), [lens[i]]).cpu().numpy()
+        # the statistics are added up over other ranges: a few roundings of sums of up to 9000 terms around 1
+        assert np.allclose(got[a:b], alone, rtol=1e-5, atol=0)
