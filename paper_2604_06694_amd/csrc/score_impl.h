@@ -350,7 +350,7 @@ __device__ __forceinline__ void score_sweep(
     const float c = g.c_log2;
 
     const int tid = threadIdx.x;
-    const int lane = tid & 63, wave = tid >> 6;
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31, g2 = lane >> 5;
     const int row0 = wave * NB * 32;                  // first row of this wave inside the launch's row range
     const int rowg0 = row_base + row0;                // the same as a window row of the head
@@ -456,7 +456,7 @@ __device__ __forceinline__ void score_sweep(
         int n_stat = stat_ranges.per_head, pitch = rows_pad;
         size_t first = (size_t)(item * g.H_kv + h) * n_stat;
         if (RAGGED) {
-            n_stat = stat_ranges.of_length(L);
+            n_stat = __builtin_amdgcn_readfirstlane(stat_ranges.of_length(L));
             first = (size_t)stat_first * g.H_kv + h;
             pitch *= g.H_kv;
         }
