@@ -91,6 +91,10 @@ struct Tile {
     // waves keep a shorter ring: there the number of resident workgroups matters more.
     static constexpr int STAGES = (WR >= 4) ? 4 : 3;
     static_assert(kInFlight * CH <= 63, "the outstanding loads must fit the vmcnt field");
+    // At d = 256 a tile is 32 keys and over before a load from HBM is: there the newest tile stays on its way across a barrier, where
+    // the ring is deep enough. Score calls, without and with: 128 rows 28 x 8192 125 and 98 us, 4 x 4000 15.7 and 15.4, 8 of 2048 to
+    // 32768 47.5 and 46.5; 224 rows 8 x 8192 41.6 and 41.9. (Nothing to two per cent either way at d <= 128.)
+    static constexpr bool AHEAD = D == 256 && STAGES == 4;
     static constexpr int LDS_K = TK * ROW_BYTES;      // one K buffer
     static constexpr int LDS_COLS = WR * TK * 4;      // one column-sum exchange buffer
     static constexpr int LDS_RC = ROWS * 4;           // sweep 2: per-row normalisation constants
@@ -441,11 +445,21 @@ __device__ __forceinline__ void score_sweep(
         // (These are the only vector-memory operations of this wave. Ranges of one tile are common, so nothing is requested past
         // the end: with the last tile requested again instead, a score call on four heads of 1000 tokens and 448 rows took 23.4 us,
         // now 19.9.)
-        fill_ring<T::STAGES>(n_loc, issue_tile, [&]() {
-            __builtin_amdgcn_s_waitcnt(vmcnt_only(kInFlight * T::CH));
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-            __builtin_amdgcn_s_barrier();
-        });
+        if constexpr (T::AHEAD)
+            // (no fence: it would wait for everything. What a barrier hands over are the tiles that have landed.)
+            fill_ring_ahead<T::STAGES>(n_loc, issue_tile, [&](bool newest_may_fly) {
+                if (newest_may_fly) __builtin_amdgcn_s_waitcnt(vmcnt_only(kLeftInFlight<T::STAGES> * T::CH));
+                else __builtin_amdgcn_s_waitcnt(vmcnt_only(0));
+#if defined(__HIP_DEVICE_COMPILE__)
+                asm volatile("s_barrier" ::: "memory");
+#endif
+            });
+        else
+            fill_ring<T::STAGES>(n_loc, issue_tile, [&]() {
+                __builtin_amdgcn_s_waitcnt(vmcnt_only(kInFlight * T::CH));
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+                __builtin_amdgcn_s_barrier();
+            });
         return;
     }
 
@@ -815,24 +829,30 @@ __device__ __forceinline__ void score_sweep(
 
 #define AUDIOKV_SCORE_BOUNDS __launch_bounds__(64 * (WR + 1), (NB == 1 && D <= 128) ? 4 : 2)
 
-template <int D, int NB, int WR, bool SWEEP2>
-__global__ AUDIOKV_SCORE_BOUNDS void score_kernel(
-    Geom g, const __bf16* __restrict__ q_win, const __bf16* __restrict__ k,
-    const int32_t* __restrict__ cu_seq, int n_wg, int nsplit,
-    int backwards,                    // sweep 2 begins with the heads that sweep 1 ended with
-    int rows_pad,                     // row pitch of stats (>= ROWS: the two sweeps may tile the rows differently)
-    int row_base,                     // first window row of this launch (sweep 2 may cover the rows in two launches)
-    float* __restrict__ stats,        // [head][split][rows_pad][2] = (max in base-2 units, sum of exp2): sweep 1 out, sweep 2 in
-    int stat_splits,                  // sweep 2: ranges per head in stats
-    const float* __restrict__ lse,    // sweep 2: instead of stats, [item][H_q][W] natural logs of the softmax denominators
-    float* __restrict__ raw,          // sweep 2 out, packed like scores
-    RideAlong ride)                   // in the workgroups from n_wg on
-{
-    ScoreRanges ranges, stat_ranges;
-    ranges.per_head = nsplit;
-    stat_ranges.per_head = stat_splits;
-    score_sweep<D, NB, WR, SWEEP2, false>(g, q_win, k, cu_seq, n_wg, ranges, backwards, rows_pad, row_base, stats, stat_ranges, lse, raw, ride);
-}
+// (score_ahead_kernel: the tilings that keep a tile on its way across barriers)
+#define AUDIOKV_SCORE_KERNEL(NAME)                                                                                                       \
+    template <int D, int NB, int WR, bool SWEEP2>                                                                                        \
+    __global__ AUDIOKV_SCORE_BOUNDS void NAME(                                                                                           \
+        Geom g, const __bf16* __restrict__ q_win, const __bf16* __restrict__ k,                                                          \
+        const int32_t* __restrict__ cu_seq, int n_wg, int nsplit,                                                                        \
+        int backwards,                    /* sweep 2 begins with the heads that sweep 1 ended with */                                    \
+        int rows_pad,                     /* row pitch of stats (>= ROWS: the two sweeps may tile the rows differently) */               \
+        int row_base,                     /* first window row of this launch (sweep 2 may cover the rows in two launches) */             \
+        float* __restrict__ stats,        /* [head][split][rows_pad][2] = (max in base-2 units, sum of exp2): sweep 1 out, sweep 2 in */ \
+        int stat_splits,                  /* sweep 2: ranges per head in stats */                                                        \
+        const float* __restrict__ lse,    /* sweep 2: instead of stats, [item][H_q][W] natural logs of the softmax denominators */       \
+        float* __restrict__ raw,          /* sweep 2 out, packed like scores */                                                          \
+        RideAlong ride)                   /* in the workgroups from n_wg on */                                                           \
+    {                                                                                                                                    \
+        ScoreRanges ranges, stat_ranges;                                                                                                 \
+        ranges.per_head = nsplit;                                                                                                        \
+        stat_ranges.per_head = stat_splits;                                                                                              \
+        score_sweep<D, NB, WR, SWEEP2, false>(g, q_win, k, cu_seq, n_wg, ranges, backwards, rows_pad, row_base, stats, stat_ranges, lse, \
+                                              raw, ride);                                                                                \
+    }
+AUDIOKV_SCORE_KERNEL(score_kernel)
+AUDIOKV_SCORE_KERNEL(score_ahead_kernel)
+#undef AUDIOKV_SCORE_KERNEL
 
 template <int D, int NB, int WR, bool SWEEP2>
 __global__ AUDIOKV_SCORE_BOUNDS void score_ragged_kernel(
@@ -874,8 +894,11 @@ hipError_t launch_sweep_kernels(const Geom& g, const SweepArgs& a, hipStream_t s
 {
     using T = Tile<D, NB, WR>;
     static std::atomic<bool> attr_set{false};
+    void (*kernel)(Geom, const __bf16*, const __bf16*, const int32_t*, int, int, int, int, int, float*, int, const float*, float*, RideAlong);
+    if constexpr (T::AHEAD) kernel = score_ahead_kernel<D, NB, WR, SWEEP2>;
+    else kernel = score_kernel<D, NB, WR, SWEEP2>;
     if (!attr_set && T::LDS_BYTES > 48 * 1024) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(score_kernel<D, NB, WR, SWEEP2>),
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, T::LDS_BYTES);
         if (e == hipSuccess)
             e = hipFuncSetAttribute(reinterpret_cast<const void*>(score_ragged_kernel<D, NB, WR, SWEEP2>),
@@ -900,7 +923,7 @@ hipError_t launch_sweep_kernels(const Geom& g, const SweepArgs& a, hipStream_t s
         hipLaunchKernelGGL((score_ragged_kernel<D, NB, WR, SWEEP2>), grid, dim3(T::THREADS), T::LDS_BYTES, s, g, (const __bf16*)a.q_win,
                            (const __bf16*)a.k, a.cu_seq, n_wg, a.ranges, a.rows_pad, a.row_base, a.stats, a.stat_ranges, a.lse, a.raw, ride);
     else
-        hipLaunchKernelGGL((score_kernel<D, NB, WR, SWEEP2>), grid, dim3(T::THREADS), T::LDS_BYTES, s, g, (const __bf16*)a.q_win,
+        hipLaunchKernelGGL(kernel, grid, dim3(T::THREADS), T::LDS_BYTES, s, g, (const __bf16*)a.q_win,
                            (const __bf16*)a.k, a.cu_seq, n_wg, a.ranges.per_head, SWEEP2 && a.backwards ? 1 : 0, a.rows_pad, a.row_base, a.stats,
                            a.stat_ranges.per_head, a.lse, a.raw, ride);
     return hipGetLastError();

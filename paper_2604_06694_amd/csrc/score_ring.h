@@ -33,5 +33,24 @@ __host__ __device__ __forceinline__ void fill_ring(int n_tiles, Issue issue, Bar
     }
 }
 
+// The same with the newest tiles on their way across a barrier: barrier(true) may leave those that the iteration it opens does not
+// read, STAGES - 2 - kLookAhead, barrier(false) none (the last tiles: what is outstanding is read next).
+template <int STAGES>
+constexpr int kLeftInFlight = STAGES - 2 - kLookAhead;
+template <int STAGES, class Issue, class Barrier>
+__host__ __device__ __forceinline__ void fill_ring_ahead(int n_tiles, Issue issue, Barrier barrier) {
+    constexpr int AHEAD = STAGES - 1;
+    static_assert(kLeftInFlight<STAGES> == 1, "a barrier that opens an iteration finds all its tiles or one more requested");
+#pragma unroll
+    for (int a = 0; a < AHEAD; ++a)
+        if (a < n_tiles) issue(a);
+    barrier(AHEAD - 1 < n_tiles);                   // opens iteration 0
+#pragma unroll 1
+    for (int t = 0; t < n_tiles; ++t) {
+        if (t + AHEAD < n_tiles) issue(t + AHEAD);
+        barrier(t + AHEAD < n_tiles);               // ends tile t
+    }
+}
+
 }  // namespace score_detail
 }  // namespace audiokv
