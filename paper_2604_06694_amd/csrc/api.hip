@@ -8,6 +8,7 @@
 
 #include "common.h"
 #include "conv.h"
+#include "select_head.h"
 
 using namespace audiokv;
 
@@ -530,15 +531,18 @@ int32_t evict_entry(const audiokv_params* params, const void* q_win, const void*
         helper_lock.unlock();
     }
     // (the selection combines smoothed scores from their chunks itself: a launch less)
+    // (and short heads are selected by the launch that smooths them, unless every stage is to be timed)
     ConvJoin join;
+    SelectJob select{budgets_dev, cu_budgets_dev, indices_dev};
     AUDIOKV_HIP(launch_smooth(g, raw, params->pool_kernel != 1, cu_seqlens_dev, seqlens_host, n_items, cutoff_frac,
                               alpha, smoothed, ws + w.fft_off, w.total - w.fft_off, nullptr, false, s, side_filters || ride_taps,
-                              select_joins(b.max_L) ? &join : nullptr),
+                              select_joins(b.max_L) ? &join : nullptr, prof ? nullptr : &select),
                 "smooth kernel");
     AUDIOKV_MARK(3);
-    AUDIOKV_HIP(launch_select(g, smoothed, budgets_dev, cu_budgets_dev, cu_seqlens_dev, b.max_L, indices_dev, s,
-                              join.part ? &join : nullptr),
-                "select kernel");
+    if (!select.done)
+        AUDIOKV_HIP(launch_select(g, smoothed, budgets_dev, cu_budgets_dev, cu_seqlens_dev, b.max_L, indices_dev, s,
+                                  join.part ? &join : nullptr),
+                    "select kernel");
     AUDIOKV_MARK(4);
     AUDIOKV_HIP(launch_compact(g, k, v, indices_dev, cu_budgets_dev, cu_seqlens_dev, b.total_tokens, total_rows, k_out, v_out, s),
                 "compact kernel");

@@ -121,11 +121,13 @@ size_t smooth_workspace_required(const int32_t* seqlens_host, int n_items, int H
 // kstar_out (may be null): the cutoff bin of every head; cutoffs_only stops after writing it. workspace_bytes: what
 // `workspace` holds (at least _required; with less than _bytes every power-of-two head runs in one workgroup).
 // join (conv.h): if given, the last step of some heads may be left to launch_select, and `out` without their result.
+// select (select_head.h): if given, the launch may select as well, and says so.
 struct ConvJoin;
+struct SelectJob;
 hipError_t launch_smooth(const Geom& g, const float* in, bool pool_on_load, const int32_t* cu_seqlens,
                          const int32_t* seqlens_host, int n_items, double cutoff_frac, double alpha,
                          float* out, void* workspace, size_t workspace_bytes, int32_t* kstar_out, bool cutoffs_only,
-                         hipStream_t s, bool filters_ready = false, ConvJoin* join = nullptr);
+                         hipStream_t s, bool filters_ready = false, ConvJoin* join = nullptr, SelectJob* select = nullptr);
 // What lengths that are not powers of two need that depends on the lengths and the cutoff only: launch_smooth_filters
 // prepares it in the workspace (launch_smooth does it itself unless told that it is ready). smooth_filters says how much
 // that is: several launches (long_work, worth a stream of its own), or the taps alone, which can ride along elsewhere,

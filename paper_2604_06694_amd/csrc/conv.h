@@ -48,4 +48,8 @@ hipError_t launch_conv_filter(const Geom& g, const ConvCall& c, hipStream_t s);
 hipError_t launch_conv(const Geom& g, const ConvCall& c, const float* in, bool pool_on_load, float alpha, float* out, hipStream_t s,
                        ConvJoin* join = nullptr);
 
+// Pooling (kernel 7), smoothing and selection of a call whose heads are all of one chunk of up to 4096 points
+struct SelectJob;
+hipError_t launch_conv_select(const Geom& g, const ConvCall& c, const float* in, float alpha, float* out, const SelectJob& sel, hipStream_t s);
+
 }  // namespace audiokv

@@ -32,6 +32,7 @@
 #include "conv.h"
 #include "conv_join.h"
 #include "fft_regs.h"
+#include "select_head.h"
 
 namespace audiokv {
 namespace {
@@ -265,22 +266,16 @@ __global__ __launch_bounds__(Cfft<LOGC>::THREADS) void conv_spectrum_kernel(Geom
 
 // SPEC: the filter's bins come from conv_spectrum_kernel; otherwise the workgroup transforms its share of the filter beside its
 // share of the samples (8192 points, whose 1024 threads have 128 registers each: before it).
-template <int LOGC, int POOL, bool SPEC>
-__global__ __launch_bounds__(Cfft<LOGC>::THREADS) void conv_chunk_kernel(
-    Geom g, const float* __restrict__ in, ConvFilterJob job, int log_r, const cf* __restrict__ spec, size_t spec_stride,
-    cf* __restrict__ part, size_t part_stride, float alpha, float* __restrict__ out)
+// KEEP: the result of a head of one chunk is left in LDS as well, from smem on, for whoever passes the next barrier.
+template <int LOGC, int POOL, bool SPEC, bool KEEP>
+__device__ __forceinline__ void conv_chunk(
+    const Geom& g, const float* __restrict__ in, const ConvFilterJob& job, const ConvHead& w, int head, int r, const cf* __restrict__ spec,
+    size_t spec_stride, cf* __restrict__ part, size_t part_stride, float alpha, float* __restrict__ out, unsigned char* smem)
 {
     constexpr int C = 1 << LOGC, T = Cfft<LOGC>::THREADS;
-    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     ConvLds<LOGC>& m = *reinterpret_cast<ConvLds<LOGC>*>(smem);
     constexpr int U = LOGC == 13 ? 2 : 4;                        // (1024 threads: 128 registers)
-    ConvHead w;
-    // Workgroup i runs on XCD i mod 8, and heads of fewer chunks than the longest need the first residues only: these go to another
-    // XCD from head to head. (All on the first ones: 24 sequences of two heads, 1500 to 30000 samples, put 48 of their 172 workgroups
-    // on the 32 CUs of XCD 0, one each, and 12 on XCD 7. Smooth calls, so and now: those 36.9 and 27.2 us, 40 of four heads of 3000 to
-    // 20000 80.0 and 64.4, 20 of 5000 to 100000 158 and 119; 6 of 40000 to 100000, which need nearly all residues, 65.8 and 67.2.)
-    const int head = blockIdx.x >> log_r, r = (blockIdx.x + head) & ((1 << log_r) - 1), t = threadIdx.x;
-    if (!conv_head(g, job, head, LOGC, w) || r >= w.R) return;
+    const int t = threadIdx.x;
     const float* src = in + w.off;
     const float* h = job.h + w.owner * job.item_stride;
     // Without spectra few heads are at work and a CU has one workgroup: the first blocks are on their way while the tables are
@@ -333,11 +328,13 @@ __global__ __launch_bounds__(Cfft<LOGC>::THREADS) void conv_chunk_kernel(
     cd back0 = cis_pi_f64(-(float)t * a / (float)(2 << w.log_n));
     back0 = {back0.re * inv_n, back0.im * inv_n};
     cf* dst = part + (size_t)head * part_stride + (size_t)r * C;
+    float* kept = reinterpret_cast<float*>(m.z);
+    if constexpr (KEEP) __syncthreads();                         // all points are read
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
         const cf u = mul(v[q], mul_rounded(back0, m.back[q]));
         const int n = t + T * q;
-        if (w.R > 1) dst[n] = u;
+        if (!KEEP && w.R > 1) dst[n] = u;
         else if (n < w.L) {                                      // a head of one workgroup is done
             float st = u.re;
             if (alpha != 1.f) {
@@ -345,8 +342,58 @@ __global__ __launch_bounds__(Cfft<LOGC>::THREADS) void conv_chunk_kernel(
                 st = mix(s0, st, alpha);
             }
             out[w.off + n] = st;
+            if constexpr (KEEP) kept[n] = st;
         }
     }
+}
+
+template <int LOGC, int POOL, bool SPEC>
+__global__ __launch_bounds__(Cfft<LOGC>::THREADS) void conv_chunk_kernel(
+    Geom g, const float* __restrict__ in, ConvFilterJob job, int log_r, const cf* __restrict__ spec, size_t spec_stride,
+    cf* __restrict__ part, size_t part_stride, float alpha, float* __restrict__ out)
+{
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    ConvHead w;
+    // Workgroup i runs on XCD i mod 8, and heads of fewer chunks than the longest need the first residues only: these go to another
+    // XCD from head to head. (All on the first ones: 24 sequences of two heads, 1500 to 30000 samples, put 48 of their 172 workgroups
+    // on the 32 CUs of XCD 0, one each, and 12 on XCD 7. Smooth calls, so and now: those 36.9 and 27.2 us, 40 of four heads of 3000 to
+    // 20000 80.0 and 64.4, 20 of 5000 to 100000 158 and 119; 6 of 40000 to 100000, which need nearly all residues, 65.8 and 67.2.)
+    const int head = blockIdx.x >> log_r, r = (blockIdx.x + head) & ((1 << log_r) - 1);
+    if (!conv_head(g, job, head, LOGC, w) || r >= w.R) return;
+    conv_chunk<LOGC, POOL, SPEC, false>(g, in, job, w, head, r, spec, spec_stride, part, part_stride, alpha, out, smem);
+}
+
+// A head of one chunk, pooled with the usual kernel, smoothed and selected in one workgroup, as in smooth_select_kernel (smooth_real.hip):
+// evict, two launches and one, four heads of 600 tokens 26.2 and 24.8 us, 1500 28.1 and 26.4, 3000 32.3 and 31.0; 112 heads of 3000 118 and
+// 115.
+// The barriers of conv_chunk: the constants, the points' exchange, the result, and those of the transforms.
+template <int LOGC> constexpr int kConvBarriers = 3 + 2 * Cfft<LOGC>::BARRIERS;
+// (512 threads: with the 128 registers that 1024 have, 4096 points spill 110; a selection of 4096 tokens on them takes 0.9 us more)
+constexpr int kConvFusedThreads = 512;
+template <int LOGC, bool SPEC>
+__global__ __launch_bounds__(kConvFusedThreads) void conv_select_kernel(
+    Geom g, const float* __restrict__ in, ConvFilterJob job, const cf* __restrict__ spec, size_t spec_stride, float alpha,
+    float* __restrict__ out, SelectJob sel)
+{
+    constexpr int NT = kConvFusedThreads, EPT = LOGC <= 11 ? 4 : 8;
+    static_assert(EPT * NT >= 1 << LOGC, "a head's tokens");
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    ConvHead w;
+    if (!conv_head(g, job, blockIdx.x, LOGC, w) || w.R != 1) return;     // (uniform; the launch has heads of one chunk only)
+    if (__builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6) < Cfft<LOGC>::THREADS / 64)
+        conv_chunk<LOGC, 7, SPEC, true>(g, in, job, w, blockIdx.x, 0, spec, spec_stride, nullptr, 0, alpha, out, smem);
+    else
+#pragma unroll 1
+        for (int i = 0; i < kConvBarriers<LOGC>; ++i) __syncthreads();
+    __syncthreads();
+    const float* kept = reinterpret_cast<const float*>(smem);
+    select_head<EPT, NT>(g, blockIdx.x, w.L, sel.budgets, sel.cu_b, sel.indices, false, [&](float (&x)[EPT], int n_cand) {
+#pragma unroll
+        for (int e = 0; e < EPT; ++e) {
+            const int n = (int)threadIdx.x + e * NT;
+            x[e] = n < n_cand ? kept[n] : 0.f;
+        }
+    });
 }
 
 constexpr int kJoinThreads = 64;
@@ -412,6 +459,26 @@ hipError_t launch_chunks(const Geom& g, const ConvCall& c, const float* in, floa
                        dim3(Cfft<LOGC>::THREADS), lds, s, g, in, c.job, log_residues(c), (const cf*)c.spec, c.points, (cf*)c.part, c.points, alpha, out);
     return hipGetLastError();
 }
+template <int LOGC, bool SPEC>
+hipError_t launch_fused(const Geom& g, const ConvCall& c, const float* in, float alpha, float* out, const SelectJob& sel, hipStream_t s) {
+    const int lds = (int)(sizeof(ConvLds<LOGC>) + (SPEC ? 0 : padded_len((size_t)1 << LOGC) * sizeof(cf)));
+    if (lds > 24 * 1024) {
+        static std::atomic<bool> attr_set{false};
+        if (!attr_set) {
+            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(conv_select_kernel<LOGC, SPEC>),
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+            if (e != hipSuccess) return e;
+            attr_set = true;
+        }
+    }
+    hipLaunchKernelGGL((conv_select_kernel<LOGC, SPEC>), dim3((unsigned)(g.n_items * g.H_kv)), dim3(kConvFusedThreads), lds, s, g, in,
+                       c.job, (const cf*)c.spec, c.points, alpha, out, sel);
+    return hipGetLastError();
+}
+template <int LOGC>
+hipError_t launch_fused(const Geom& g, const ConvCall& c, const float* in, float alpha, float* out, const SelectJob& sel, hipStream_t s) {
+    return c.spec ? launch_fused<LOGC, true>(g, c, in, alpha, out, sel, s) : launch_fused<LOGC, false>(g, c, in, alpha, out, sel, s);
+}
 template <int LOGC, int POOL>
 hipError_t launch_chunks(const Geom& g, const ConvCall& c, const float* in, float alpha, float* out, hipStream_t s) {
     return c.spec ? launch_chunks<LOGC, POOL, true>(g, c, in, alpha, out, s) : launch_chunks<LOGC, POOL, false>(g, c, in, alpha, out, s);
@@ -451,6 +518,16 @@ hipError_t launch_conv_filter(const Geom& g, const ConvCall& c, hipStream_t s) {
         case 12: return launch_spectra<12>(g, c, s);
         default: return launch_spectra<13>(g, c, s);
     }
+}
+
+hipError_t launch_conv_select(const Geom& g, const ConvCall& c, const float* in, float alpha, float* out, const SelectJob& sel, hipStream_t s) {
+    if (c.max_r != 1 || g.pool_kernel != 7) return hipErrorInvalidValue;
+    switch (c.log_c) {
+        case 10: return launch_fused<10>(g, c, in, alpha, out, sel, s);
+        case 11: return launch_fused<11>(g, c, in, alpha, out, sel, s);
+        case 12: return launch_fused<12>(g, c, in, alpha, out, sel, s);
+    }
+    return hipErrorInvalidValue;
 }
 
 hipError_t launch_conv(const Geom& g, const ConvCall& c, const float* in, bool pool_on_load, float alpha, float* out, hipStream_t s,

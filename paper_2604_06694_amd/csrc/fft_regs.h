@@ -86,6 +86,7 @@ struct Fft {
     static constexpr int P8 = LOGC / 3;                       // radix-8 passes
     static constexpr int REM = LOGC - 3 * P8;                 // bits left for a pass of radix 2 or 4 on the last layout
     static constexpr int TW = REM ? P8 : P8 - 1;              // passes with twiddles
+    static constexpr int BARRIERS = P8 - (REM ? 0 : 1);       // of forward, and of backward
     __host__ __device__ static constexpr int low_bit(int p) { return LOGC - 3 * (p + 1); }
 
     struct W3 { cf w1, w2, w4; };

@@ -24,6 +24,7 @@
 #include <algorithm>
 #include "smooth_common.h"
 #include "conv.h"
+#include "select_head.h"
 #include "smooth_real.h"
 
 namespace audiokv {
@@ -1326,10 +1327,15 @@ hipError_t launch_smooth_filters(const Geom& g, const int32_t* cu_seqlens, const
                           workspace, s);
 }
 
+// Heads up to which smoothing and selection go in one launch: one workgroup of 512 or 1024 threads per CU. Beyond one round of them two
+// launches, whose workgroups share CUs, are as good or better (evict, two launches and one: 320 heads of 2048 147 and 144 us, of 3000
+// 190 and 188, of 8192 251 and 265, 400 of 1500 169 and 174; 252 heads of 3000 202 and 199, 200 of 8192 164 and 161).
+constexpr int kFusedHeads = 256;
+
 hipError_t launch_smooth(const Geom& g, const float* in, bool pool_on_load, const int32_t* cu_seqlens,
                          const int32_t* seqlens_host, int n_items, double cutoff_frac, double alpha,
                          float* out, void* workspace, size_t workspace_bytes, int32_t* kstar_out, bool cutoffs_only,
-                         hipStream_t s, bool filters_ready, ConvJoin* join)
+                         hipStream_t s, bool filters_ready, ConvJoin* join, SelectJob* select)
 {
     if (cutoffs_only && !kstar_out) return hipErrorInvalidValue;
     // A kernel wider than the windows that the transforms load: pooled first, into the result, and smoothed in place. Tap by tap
@@ -1385,6 +1391,14 @@ hipError_t launch_smooth(const Geom& g, const float* in, bool pool_on_load, cons
                            pool_on_load ? 1 : 0, cu_seqlens, cutoff_frac, (float)alpha, out, kstar_out, cutoffs_only ? 1 : 0,
                            dec_L ? 1 : 0, real_lengths);
     }
+    // Every head in one workgroup, and no more of them than CUs: the same launch selects.
+    const bool fuse = select && pool_on_load && g.pool_kernel == 7 && g.cutoff_mode == AUDIOKV_CUTOFF_FRACTION && alpha != 0.0 &&
+                      n_heads <= kFusedHeads && max_small == 0 && !dec_L;
+    if (fuse && !pl.others && real_lengths && !(real_lengths & (real_lengths - 1)) && real_lengths <= (unsigned)kFusedMaxL) {
+        e = launch_smooth_select((int)real_lengths, g, in, cu_seqlens, cutoff_frac, (float)alpha, out, *select, s);
+        select->done = e == hipSuccess;
+        return e;
+    }
     if (real_lengths) {
         e = launch_smooth_real(real_lengths, g, in, pool_on_load, cu_seqlens, cutoff_frac, (float)alpha, out, kstar_out, cutoffs_only, s);
         if (e != hipSuccess) return e;
@@ -1415,6 +1429,13 @@ hipError_t launch_smooth(const Geom& g, const float* in, bool pool_on_load, cons
         hipLaunchKernelGGL(smooth_bluestein_kernel, dim3(n_heads), dim3(kFftThreads), smem, s, g, in,
                            pool_on_load ? 1 : 0, cu_seqlens, cutoff_frac, (float)alpha, out, bw, kstar_out,
                            cutoffs_only ? 1 : 0, pl.conv.job);
+    }
+    bool only_others = true;
+    for (int i = 0; i < n_items && fuse; ++i) only_others &= !pow2_length(seqlens_host[i]);
+    if (fuse && only_others && pl.conv.any && !pl.one_wg_other && pl.conv.max_r == 1 && pl.conv.log_c <= 12) {
+        e = launch_conv_select(g, pl.conv, in, (float)alpha, out, *select, s);
+        select->done = e == hipSuccess;
+        return e;
     }
     if (pl.conv.any) {
         e = launch_conv(g, pl.conv, in, pool_on_load, (float)alpha, out, s, join);

@@ -13,4 +13,10 @@ __host__ __device__ inline bool real_length(int L) { return L >= kRealMinL && L 
 hipError_t launch_smooth_real(unsigned lengths, const Geom& g, const float* in, bool pool_on_load, const int32_t* cu_seqlens, double cutoff_frac,
                               float alpha, float* out, int32_t* kstar_out, bool cutoffs_only, hipStream_t s);
 
+// Pooling (kernel 7), smoothing with a fixed cutoff and selection of a call whose heads all have L tokens, 1024 to 16384.
+struct SelectJob;
+constexpr int kFusedMaxL = 16384;
+hipError_t launch_smooth_select(int L, const Geom& g, const float* in, const int32_t* cu_seqlens, double cutoff_frac, float alpha, float* out,
+                                const SelectJob& job, hipStream_t s);
+
 }  // namespace audiokv

@@ -19,6 +19,7 @@
 #include <atomic>
 
 #include "fft_regs.h"
+#include "select_head.h"
 #include "smooth_real.h"
 
 namespace audiokv {
@@ -113,8 +114,9 @@ __device__ __forceinline__ float bin_weight(int k, int kstar, int T) {
     return 0.5f * (1.f + cis_pi((float)(k - kstar) / (float)(T + 1)).re);
 }
 
-// POOL: 0 none, 7 the usual size, 1 any size up to 9
-template <int LOGC, int POOL, bool ENERGY>
+// POOL: 0 none, 7 the usual size, 1 any size up to 9. KEEP: the result is left in LDS as well, from smem on, for whoever passes the
+// next barrier.
+template <int LOGC, int POOL, bool ENERGY, bool KEEP = false>
 __device__ __forceinline__ void smooth_real_head(
     const Geom& g, const float* __restrict__ src, double cutoff_frac, float alpha, float* __restrict__ dst,
     int32_t* __restrict__ kstar_out, int cutoffs_only, unsigned char* smem)
@@ -283,6 +285,8 @@ __device__ __forceinline__ void smooth_real_head(
 
         // residual mix (Eq. 20); 1/N completes the inverse transform
         const float inv = 1.0f / (float)N;
+        float* kept = reinterpret_cast<float*>(m.z);
+        if constexpr (KEEP) __syncthreads();                 // all points are read
 #pragma unroll
         for (int vt = 0; vt < VT; ++vt)
 #pragma unroll
@@ -302,6 +306,7 @@ __device__ __forceinline__ void smooth_real_head(
                 }
                 dst[2 * n] = o0;
                 dst[2 * n + 1] = o1;
+                if constexpr (KEEP) { kept[2 * n] = o0; kept[2 * n + 1] = o1; }
             }
     };
     if constexpr (RealLds<LOGC>::kTable) {
@@ -334,6 +339,42 @@ __global__ __launch_bounds__(kRealThreads<LOGC>) void smooth_real_kernel(
     size_t off;
     if (head_span(g, cu_seq, blockIdx.x, off) != 2 << LOGC) return;      // another launch's head
     smooth_real_head<LOGC, POOL, ENERGY>(g, in + off, cutoff_frac, alpha, out + off, kstar_out, cutoffs_only, smem);
+}
+
+// The barriers of smooth_real_head with a fixed cutoff, pooled on load and kept: filling, pooling, the spectrum's exchange (two) and the
+// result, and those of the transforms.
+template <int LOGC> constexpr int kRealBarriers = 5 + 2 * Fft<LOGC, kRealGroups<LOGC>>::BARRIERS;
+
+// Smoothing and selection of a head in one workgroup: the scores go from one to the other through LDS. In place of two launches, of
+// which the second waits for the first to drain, starts and reads the scores again (evict, two launches and one: four heads of 1024
+// 23.3 and 21.8 us, 2048 25.0 and 23.6, 8192 34.7 and 32.9, 16384 50.6 and 48.9; 112 heads of 2048 90.3 and 87.1, of 8192 with a decoding
+// step 280 and 276). The waves that the transform does not need pass its barriers.
+template <int LOGC> constexpr int kFusedThreads = LOGC <= 10 ? 512 : 1024;
+template <int LOGC> constexpr int kFusedTokens = LOGC <= 11 ? 4 : 1 << (LOGC - 9);      // per thread
+template <int LOGC>
+__global__ __launch_bounds__(kFusedThreads<LOGC>) void smooth_select_kernel(
+    Geom g, const float* __restrict__ in, const int32_t* __restrict__ cu_seq, double cutoff_frac, float alpha, float* __restrict__ out,
+    SelectJob job)
+{
+    constexpr int NT = kFusedThreads<LOGC>, EPT = kFusedTokens<LOGC>, L = 2 << LOGC;
+    static_assert(EPT * NT >= L, "a head's tokens");
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    size_t off;
+    if (head_span(g, cu_seq, blockIdx.x, off) != L) return;              // (uniform; the launch has heads of this length only)
+    if (__builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6) < kRealThreads<LOGC> / 64)
+        smooth_real_head<LOGC, 7, false, true>(g, in + off, cutoff_frac, alpha, out + off, nullptr, 0, smem);
+    else
+#pragma unroll 1
+        for (int i = 0; i < kRealBarriers<LOGC>; ++i) __syncthreads();
+    __syncthreads();
+    const float* kept = reinterpret_cast<const float*>(smem);
+    select_head<EPT, NT>(g, blockIdx.x, L, job.budgets, job.cu_b, job.indices, false, [&](float (&x)[EPT], int n_cand) {
+#pragma unroll
+        for (int e = 0; e < EPT; ++e) {
+            const int n = (int)threadIdx.x + e * NT;
+            x[e] = n < n_cand ? kept[n] : 0.f;
+        }
+    });
 }
 
 // A call of several lengths: all heads in one launch, as many threads as the longest takes. The waves that a shorter head does
@@ -443,7 +484,37 @@ hipError_t launch_lengths(unsigned lengths, const Geom& g, const float* in, bool
     return hipErrorInvalidValue;
 }
 
+template <int LOGC>
+hipError_t launch_fused(const Geom& g, const float* in, const int32_t* cu_seqlens, double cutoff_frac, float alpha, float* out,
+                        const SelectJob& job, hipStream_t s) {
+    const int lds = (int)sizeof(RealLds<LOGC>);
+    if (lds > 24 * 1024) {
+        static std::atomic<bool> attr_set{false};
+        if (!attr_set) {
+            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(smooth_select_kernel<LOGC>),
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+            if (e != hipSuccess) return e;
+            attr_set = true;
+        }
+    }
+    hipLaunchKernelGGL((smooth_select_kernel<LOGC>), dim3((unsigned)(g.n_items * g.H_kv)), dim3(kFusedThreads<LOGC>), lds, s, g, in,
+                       cu_seqlens, cutoff_frac, alpha, out, job);
+    return hipGetLastError();
+}
+
 }  // namespace
+
+hipError_t launch_smooth_select(int L, const Geom& g, const float* in, const int32_t* cu_seqlens, double cutoff_frac, float alpha, float* out,
+                                const SelectJob& job, hipStream_t s) {
+    switch (L) {
+        case 1024:  return launch_fused<9>(g, in, cu_seqlens, cutoff_frac, alpha, out, job, s);
+        case 2048:  return launch_fused<10>(g, in, cu_seqlens, cutoff_frac, alpha, out, job, s);
+        case 4096:  return launch_fused<11>(g, in, cu_seqlens, cutoff_frac, alpha, out, job, s);
+        case 8192:  return launch_fused<12>(g, in, cu_seqlens, cutoff_frac, alpha, out, job, s);
+        case 16384: return launch_fused<13>(g, in, cu_seqlens, cutoff_frac, alpha, out, job, s);
+    }
+    return hipErrorInvalidValue;
+}
 
 hipError_t launch_smooth_real(unsigned lengths, const Geom& g, const float* in, bool pool_on_load, const int32_t* cu_seqlens, double cutoff_frac,
                               float alpha, float* out, int32_t* kstar_out, bool cutoffs_only, hipStream_t s) {

@@ -1,0 +1,68 @@
+"""Smoothing and selection in one launch (heads of one workgroup each, no more of them than CUs, pooling kernel 7, a fixed cutoff): the
+tokens that the stages by themselves select, at the edges of every transform and of the conditions."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def A():
+    import paper_2604_06694_amd as A
+    return A
+
+
+def _check(A, lens, H_kv=2, ratio=0.4, cutoff=0.125, alpha=1.0, seed=0, **params):
+    H_q, d, W = 2 * H_kv, 64, 8
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    q = torch.randn(len(lens) * H_q * W * d, generator=gen, device="cuda").to(torch.bfloat16)
+    k = torch.randn(sum(lens) * H_kv * d, generator=gen, device="cuda").to(torch.bfloat16)
+    w = torch.rand(len(lens) * H_kv, generator=gen, device="cuda")
+    p = A.Params(H_q, H_kv, d, W, **params)
+    ws = torch.full((A.workspace_bytes(p, lens),), 0x7f, dtype=torch.uint8, device="cuda")
+    out = A.evict(p, q, k, k, w, lens, ratio, cutoff, alpha, alloc_scope=A.SCOPE_ITEM, workspace=ws)
+    smoothed = A.smooth(p, A.score(p, q, k, lens), lens, cutoff, alpha)
+    staged = A.select(p, smoothed, out["budgets"], out["cu_budgets"], lens, out["total_rows"])
+    assert torch.equal(out["indices"], staged)
+    # the smoothed scores are in the workspace, whoever selected
+    words = ws[: ws.numel() // 4 * 4].view(torch.int32)
+    want = smoothed.view(torch.int32)
+    at = [64 * int(i) for i in (words[: words.numel() - want.numel() + 1 : 64] == want[0]).nonzero().view(-1)]
+    assert any(torch.equal(words[i:i + want.numel()], want) for i in at)
+
+
+@pytest.mark.parametrize("L", [33, 500, 1023, 1024, 1025, 2047, 2048, 2049, 4095, 4096, 4097, 8192, 16384, 32768])
+@pytest.mark.parametrize("alpha,taper", [(1.0, 0), (0.5, 0), (1.0, 5)])
+def test_lengths(A, L, alpha, taper):
+    _check(A, [L], alpha=alpha, taper_bins=taper)
+
+
+@pytest.mark.parametrize("lens", [[100, 1000, 900], [1030, 2000], [4000, 100, 2500], [2048, 2048], [2048, 4096], [2048, 2000], [4000, 5000], [512, 600]])
+def test_items(A, lens):
+    _check(A, lens)
+
+
+@pytest.mark.parametrize("L", [700, 3000, 2048])
+@pytest.mark.parametrize("n_items", [5, 128, 129])           # filters of their own, shared ones; 256 heads and 258
+def test_numbers_of_heads(A, L, n_items):
+    _check(A, [L] * n_items)
+
+
+@pytest.mark.parametrize("L", [1500, 2048])
+@pytest.mark.parametrize("how", [dict(ratio=0.0055), dict(ratio=1.0), dict(cutoff=1.0), dict(cutoff=0.0), dict(pool_kernel=1), dict(pool_kernel=9),
+                                 dict(pool_mode=1), dict(cutoff_mode=2, cutoff=0.9)], ids=str)
+def test_conditions(A, L, how):
+    _check(A, [L], **how)
+
+
+def test_scores_that_are_not_finite(A):
+    """An infinite key makes the scores NaN: the launch ends, and every index is in range."""
+    H_q, H_kv, d, W, L = 4, 2, 64, 8, 2048
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    q = torch.randn(H_q * W * d, generator=gen, device="cuda").to(torch.bfloat16)
+    k = torch.randn(L * H_kv * d, generator=gen, device="cuda").to(torch.bfloat16)
+    k[5 * d:6 * d] = float("inf")
+    out = A.evict(A.Params(H_q, H_kv, d, W), q, k, k, torch.ones(H_kv, device="cuda"), [L], 0.4, 0.125, 1.0)
+    idx = out["indices"].cpu().numpy()
+    assert idx.min() >= 0 and idx.max() < L and np.isfinite(idx).all()
