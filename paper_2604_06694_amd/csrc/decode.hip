@@ -248,11 +248,12 @@ void decode_partial_kernel(
 // One workgroup per (KV head, query head of its group): combine the chunks. A chain of loads from end to end, so as
 // many as possible are in flight: the statistics one chunk per thread, then the accumulators with a thread on four
 // channels of every (256 / (D/4))-th chunk. Every sum has a fixed order.
-constexpr int kMergeThreads = 256;
+// THREADS: 1024 where heads have many chunks (launch_decode).
 constexpr int kMergeEarly = 4;            // accumulators per thread requested before the statistics are known
 constexpr int kMergeLds = 2048;           // chunks whose weights fit the LDS array (more: recomputed where used)
 
-__global__ __launch_bounds__(kMergeThreads) void decode_merge_kernel(
+template <int THREADS>
+__global__ __launch_bounds__(THREADS) void decode_merge_kernel(
     Geom g, const int32_t* __restrict__ cu_b, int total_rows, int log_r, const float* __restrict__ part,
     const float* __restrict__ stats, float* __restrict__ out)
 {
@@ -263,12 +264,12 @@ __global__ __launch_bounds__(kMergeThreads) void decode_merge_kernel(
     const int c0 = (b0 >> log_r) + head, nc = n > 0 ? (n + (1 << log_r) - 1) >> log_r : 0;
     float* o = out + ((size_t)item * g.H_q + (size_t)h * g.G + qh) * g.D;
     __shared__ float wgt[kMergeLds];
-    __shared__ float wave_m[kMergeThreads / 64], wave_l[kMergeThreads / 64];
-    __shared__ __attribute__((aligned(16))) f32x4 red[kMergeThreads];
+    __shared__ float wave_m[THREADS / 64], wave_l[THREADS / 64];
+    __shared__ __attribute__((aligned(16))) f32x4 red[THREADS];
 
     // The first accumulators are requested together with the statistics: one load latency less (112 heads of 13 chunks 6.3 ->
     // 5.7 us, 64 heads 4.6 -> 4.0).
-    const int quads = g.D >> 2, groups = kMergeThreads / quads;  // D = 64, 128, 256: 16, 8, 4 chunks at a time
+    const int quads = g.D >> 2, groups = THREADS / quads;  // D = 64, 128, 256: 16, 8, 4 chunks at a time
     const int ch4 = tid % quads, grp = tid / quads;
     const f32x4* col = reinterpret_cast<const f32x4*>(part + ((size_t)c0 * g.G + qh) * g.D) + ch4;
     const size_t stride = (size_t)g.G * quads;
@@ -280,7 +281,7 @@ __global__ __launch_bounds__(kMergeThreads) void decode_merge_kernel(
 
     const float2* st = reinterpret_cast<const float2*>(stats) + (size_t)c0 * g.G + qh;     // chunk c at st[c * G]
     float m = -INFINITY, l = 0.f;
-    for (int c = tid; c < nc; c += kMergeThreads) {
+    for (int c = tid; c < nc; c += THREADS) {
         const float2 s = st[(size_t)c * g.G];
         if (c < kMergeLds) wgt[c] = s.x;
         const float m2 = fmaxf(m, s.x);                          // a chunk holds at least one row: s.x is finite
@@ -293,16 +294,16 @@ __global__ __launch_bounds__(kMergeThreads) void decode_merge_kernel(
     if (lane == 0) wave_m[wave] = M;
     __syncthreads();
 #pragma unroll
-    for (int w = 0; w < kMergeThreads / 64; ++w) M = fmaxf(M, wave_m[w]);
+    for (int w = 0; w < THREADS / 64; ++w) M = fmaxf(M, wave_m[w]);
     l = m == -INFINITY ? 0.f : l * __builtin_amdgcn_exp2f(m - M);
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) l += __shfl_xor(l, off, 64);
     if (lane == 0) wave_l[wave] = l;
-    for (int c = tid; c < min(nc, kMergeLds); c += kMergeThreads) wgt[c] = __builtin_amdgcn_exp2f(wgt[c] - M);
+    for (int c = tid; c < min(nc, kMergeLds); c += THREADS) wgt[c] = __builtin_amdgcn_exp2f(wgt[c] - M);
     __syncthreads();
     float den = 0.f;
 #pragma unroll
-    for (int w = 0; w < kMergeThreads / 64; ++w) den += wave_l[w];
+    for (int w = 0; w < THREADS / 64; ++w) den += wave_l[w];
 
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -380,8 +381,18 @@ hipError_t launch_decode(const Geom& g, const void* q, const void* k_cache, cons
 #undef AUDIOKV_LAUNCH_DECODE
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(decode_merge_kernel, dim3((unsigned)(n_heads * g.G)), dim3(kMergeThreads), 0, s, g, cu_budgets,
-                       (int)total_rows, log_r, (const float*)part, (const float*)stats, out);
+    // 256 threads combine 1024 / D chunks of a head at a time. Where the average head has three such rounds or more, the chain of their
+    // loads is the launch: 1024 threads. Calls, d = 256 8 of 2048 to 32768 (5 rounds) 26.8 -> 24.0 us, 28 x 8192 (6) 40.7 -> 39.3; d = 128
+    // 1 x 8192 (3) 12.0 -> 11.7, 1 x 32768 (13) 17.1 -> 15.6; with fewer rounds than that 16 x 4096 (1.6) 19.5 and 20.7, 28 x 8192 (1.6)
+    // 39.4 and 43.1;
+    // d = 64, where a round is sixteen chunks, 1 x 20000 (4) 10.3 and 10.7.
+    const dim3 merge((unsigned)(n_heads * g.G));
+    if (g.D >= 128 && (total_rows >> log_r) >= 3LL * (1024 / g.D) * n_heads)
+        hipLaunchKernelGGL(decode_merge_kernel<1024>, merge, dim3(1024), 0, s, g, cu_budgets, (int)total_rows, log_r, (const float*)part,
+                           (const float*)stats, out);
+    else
+        hipLaunchKernelGGL(decode_merge_kernel<256>, merge, dim3(256), 0, s, g, cu_budgets, (int)total_rows, log_r, (const float*)part,
+                           (const float*)stats, out);
     return hipGetLastError();
 }
 
