@@ -6,8 +6,7 @@ namespace audiokv {
 
 namespace {
 
-// per_cu: resident workgroups that heads of one length are planned for; resident: what a CU holds
-struct Plan { int NB, WR, rows_pad, tile_keys, per_cu, resident; };
+struct Plan { int NB, WR, rows_pad, tile_keys, per_cu; };      // per_cu: resident workgroups
 
 // Instantiated (32-row blocks per wave, waves per workgroup) pairs in order of preference per sweep: the first
 // that holds the rows is taken (all must exist in score_d*.hip). More than 448 rows take three row tiles per wave in sweep 1;
@@ -29,7 +28,7 @@ constexpr long long kNarrowTileKeys = 3 << 17;     // keys of all heads: between
 bool make_plan(int rows, int D, int sweep, long long keys, Plan* out) {
     const Combo* cs; int n;
     if (D <= 128 && rows > 224 && rows <= 256 && keys <= kNarrowTileKeys) {
-        *out = Plan{1, 8, 256, 32 * AUDIOKV_SCORE_KB, 1, 1};      // nine waves of 128 registers: one workgroup per CU
+        *out = Plan{1, 8, 256, 32 * AUDIOKV_SCORE_KB, 1};      // nine waves of 128 registers: one workgroup per CU
         return D == 64 || D == 128;
     }
     if (D == 64 || D == 128) { cs = sweep == 1 ? kSweep1_128 : kSweep2_128; n = sweep == 1 ? 7 : 6; }
@@ -40,12 +39,11 @@ bool make_plan(int rows, int D, int sweep, long long keys, Plan* out) {
         if (pad >= rows) {
             // two when the waves are few or hold one row tile each (128 registers), or when the workgroup is four waves of two
             // row tiles without constants (168 registers: three waves per SIMD); one when eight waves take all the registers.
-            // At d = 256, four waves and, in sweep 1, seven are resident twice but planned as if they were not: planned with two, 128
-            // rows 28 x 8192 take 113.5 us instead of 125.4, but 4 x 8192 29.7 instead of 24.0 and 8 of 2048-32768 56.7 instead of 55.3.
+            // At d = 256, four waves and, in sweep 1, seven are resident twice but planned as if they were not: with a tile on its way
+            // across barriers one stream of keys per CU is faster than two (128 rows, planned for one and for two: 28 x 8192 98 and
+            // 110 us, 4 x 8192 22.2 and 28.4, 8 x 32768 105 and 128, ragged 8 of 2048-32768 41.4 and 49.0, 40 of 1000-4000 51.5 and 55.8).
             const bool two = (cs[i].NB == 1 && D <= 128) || cs[i].WR < 4 || (cs[i].NB == 2 && cs[i].WR == 4 && sweep == 1);
-            // Items of different lengths, whose ranges are cut to one size, take what is resident (d = 256, 8 of 2048 to 32768 planned for one workgroup per CU 61 us, for two 50).
-            const bool resident = two || (D == 256 && (cs[i].WR == 4 || (cs[i].WR == 7 && sweep == 1)));
-            *out = Plan{cs[i].NB, cs[i].WR, pad, (D == 256) ? 32 : 32 * AUDIOKV_SCORE_KB, two ? 2 : 1, resident ? 2 : 1};
+            *out = Plan{cs[i].NB, cs[i].WR, pad, (D == 256) ? 32 : 32 * AUDIOKV_SCORE_KB, two ? 2 : 1};
             return true;
         }
     }
@@ -76,7 +74,7 @@ ScoreRanges plan_ranges(const Plan& p, int H_kv, int n_items, const int32_t* seq
     // (lengths differ, but a workgroup for every tile of every head, were all as long as the longest, fits the chip at once: to find
     // its item would cost each of them 0.2 us. The same answer for every sweep of a call, whatever its tiling.)
     if (!uniform && max_tiles <= 64 && (long long)n_items * H_kv * max_tiles <= 256) uniform = true;
-    const int slots = 256 * (uniform ? p.per_cu : p.resident);
+    const int slots = 256 * p.per_cu;
     ScoreRanges best;
     long long best_cost = -1;
     const int ns_max = max_tiles < 64 ? max_tiles : 64;

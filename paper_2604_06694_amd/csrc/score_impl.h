@@ -92,8 +92,8 @@ struct Tile {
     static constexpr int STAGES = (WR >= 4) ? 4 : 3;
     static_assert(kInFlight * CH <= 63, "the outstanding loads must fit the vmcnt field");
     // At d = 256 a tile is 32 keys and over before a load from HBM is: there the newest tile stays on its way across a barrier, where
-    // the ring is deep enough. Score calls, without and with: 128 rows 28 x 8192 125 and 98 us, 4 x 4000 15.7 and 15.4, 8 of 2048 to
-    // 32768 47.5 and 46.5; 224 rows 8 x 8192 41.6 and 41.9. (Nothing to two per cent either way at d <= 128.)
+    // the ring is deep enough. Score calls, without and with: 128 rows 28 x 8192 125 and 98 us, 4 x 4000 15.7 and 15.4;
+    // 224 rows 8 x 8192 41.6 and 41.9. (Nothing to two per cent either way at d <= 128.)
     static constexpr bool AHEAD = D == 256 && STAGES == 4;
     static constexpr int LDS_K = TK * ROW_BYTES;      // one K buffer
     static constexpr int LDS_COLS = WR * TK * 4;      // one column-sum exchange buffer
@@ -298,7 +298,7 @@ __device__ __forceinline__ void score_sweep(
     // as different as their heads', and the launch the time of the fullest: there ranges of one size follow one another, and the
     // heads of a range. Score calls, as many ranges for every head and ranges of one size: 224 rows 10 of 600 to 30000 tokens 69.7 and
     // 51.5 us, 256 rows 8 of 2000 to 20000 70.0 and 51.8, 448 rows 24 of 1500 to 30000 372 and 333, 128 rows 30 of 500 to 16000 108 and
-    // 87, d = 256 8 of 2048 to 32768 56.7 and 49.7, 100 of 500 to 8000 234 and 231; short ones, for the search, 40 of 400 to 6000
+    // 87, d = 256 8 of 2048 to 32768 56.7 and 41.4 (with a tile on its way across barriers), 100 of 500 to 8000 234 and 231; short ones, for the search, 40 of 400 to 6000
     // 21.7 and 21.9, 448 rows 6 of 500 to 2000 21.5 and 21.8.
     const int nsplit = ranges.per_head;
     int item, h, split, part, tok0, L;
