@@ -530,6 +530,19 @@ __device__ __forceinline__ void score_sweep(
 #pragma unroll
     for (int rb = 0; rb < NB; ++rb) { run_m[rb] = -INFINITY; run_l[rb] = 0.f; }
 
+    // Where ranges have become longer (ragged items, and the row tile per wave that small calls of 225 to 256 rows take): a new
+    // reference every 256 keys, taken from the block that comes next, and what was summed so far merged into (past_m, past_l). Keys far
+    // from the reference's are less like it, and an exponent's rounding grows with its size. Scores against 64 bits, mean of eight
+    // inputs, shorter ranges before | one reference per range | this: 20 items of 4000 to 16000 tokens, 224 rows 4.6e-7 | 5.3 | 4.2,
+    // two of 16384, 256 rows 4.5 | 4.8 | 4.5, eight of 2048 to 32768 at d = 256 4.6 | 5.3 | 4.6, twelve of 500 to 16000, 128 rows
+    // 3.8 | 4.5 | 4.1. It costs 0.3 to 2.5 % of the call; every 512 keys half of that, and corrects half.
+    constexpr bool kRenew = !SWEEP2 && (RAGGED || (D <= 128 && NB == 1 && WR == 8));
+    constexpr int kRenewTiles = 256 / T::TK;
+    float past_m[NB], past_l[NB];
+    if constexpr (kRenew)
+#pragma unroll
+        for (int rb = 0; rb < NB; ++rb) { past_m[rb] = -INFINITY; past_l[rb] = 0.f; }
+
     // The unit of work is a block: this wave's NB*32 rows x 32 keys (NB MFMA result tiles, KK MFMAs each). Its
     // logits then need the sweep's vector work (fma, exp2, add per logit), which costs about as much ALU time as
     // the MFMAs cost matrix-pipe time. The two are software-pipelined inside the wave: while the MFMAs of block
@@ -573,6 +586,11 @@ __device__ __forceinline__ void score_sweep(
             run_m[rb] = mx * c;                         // c > 0: the scaled maximum is the maximum of the scaled logits
             red_c[rb] = run_m[rb];
         }
+    };
+    auto renew_reference = [&](f32x16 (&next)[NB]) {
+#pragma unroll
+        for (int rb = 0; rb < NB; ++rb) { merge_stats(past_m[rb], past_l[rb], run_m[rb], run_l[rb]); run_l[rb] = 0.f; }
+        reference_from(next);
     };
     auto reduce_begin = [&](auto masked_tag, f32x16 (&a)[NB], int j0b) {
         constexpr bool MASKED = decltype(masked_tag)::value;
@@ -765,6 +783,7 @@ __device__ __forceinline__ void score_sweep(
                         reduce_end(acc1, cbuf, kb);
                     }
                 }
+                if (kRenew && more && (t - t_begin) % kRenewTiles == kRenewTiles - 1) renew_reference(acc0);
                 wg_barrier();
                 flush_tile(t);
             }
@@ -785,6 +804,7 @@ __device__ __forceinline__ void score_sweep(
                 if (t + 1 < t_plain_end) run_block(Y{}, Y{}, N{}, acc0, slot_of(t + 1), 0, 0, 0, acc1);
                 else                     run_block(N{}, Y{}, N{}, acc0, 0, 0, 0, 0, acc1);
                 reduce_end(acc1, (t - t_begin) % 3, 0);
+                if (kRenew && t + 1 < t_plain_end && (t - t_begin) % kRenewTiles == kRenewTiles - 1) renew_reference(acc0);
                 wg_barrier();
                 flush_tile(t);
                 ++t;
@@ -816,6 +836,7 @@ __device__ __forceinline__ void score_sweep(
         float* my_stats = stats + (size_t)part * rows_pad * 2;
 #pragma unroll
         for (int rb = 0; rb < NB; ++rb) {
+            if constexpr (kRenew) merge_stats(run_m[rb], run_l[rb], past_m[rb], past_l[rb]);
             const float m2 = __shfl_xor(run_m[rb], 32, 64), l2 = __shfl_xor(run_l[rb], 32, 64);
             merge_stats(run_m[rb], run_l[rb], m2, l2);
             if (g2 == 0) {
