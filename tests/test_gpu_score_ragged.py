@@ -47,3 +47,26 @@ def test_items_score_as_they_do_alone(A, n_items):
         alone = A.score(p, q.view(n_items, -1)[i].contiguous(), k[a * d:b * d].contiguous(), [lens[i]]).cpu().numpy()
         # the statistics are added up over other ranges: a few roundings of sums of up to 9000 terms around 1
         assert np.allclose(got[a:b], alone, rtol=1e-5, atol=0)
+
+
+# ranges of some 300 to 900 keys, in which sweep 1 takes a new reference every 256: one and two row tiles per wave, every head dimension, and
+# the uniform call of 256 rows that renews it as well
+@pytest.mark.parametrize("H_q,H_kv,d,W,lens", [(14, 2, 128, 32, _spread(12, 3000, 24000)), (14, 2, 128, 64, _spread(12, 3000, 24000)),
+                                               (8, 2, 256, 32, _spread(8, 3000, 24000)), (8, 2, 64, 16, _spread(12, 3000, 24000)),
+                                               (32, 4, 128, 32, [16384, 16384])], ids=lambda v: str(v) if isinstance(v, int) else f"{len(v)}")
+@pytest.mark.parametrize("shape", ["ramp", "step", "sawtooth"])
+def test_logits_that_drift_past_each_new_reference(A, H_q, H_kv, d, W, lens, shape):
+    """Logits that climb, fall (every third query sees them the other way round) and jump by hundreds of octaves along an item."""
+    q, k = _inputs(H_q, H_kv, d, W, lens, 5)
+    q = (0.25 * q.view(-1, d).float() + 1.0)
+    q[::3] *= -1.0
+    q = q.to(torch.bfloat16).reshape(-1)
+    steps = []
+    for L in lens:
+        x = torch.linspace(-1, 1, L, device="cuda")
+        steps.append({"ramp": x, "step": torch.sign(x), "sawtooth": torch.remainder(x * 20, 2) - 1}[shape].repeat(H_kv))
+    k = (0.25 * k.view(-1, d).float() + 6.0 * torch.cat(steps)[:, None]).to(torch.bfloat16).reshape(-1)
+    ref, _ = _reference(q, k, H_q, H_kv, d, W, lens, True)
+    got = A.score(A.Params(H_q, H_kv, d, W, pool_kernel=1), q, k, lens)
+    # logits of up to 150 octaves, rounded in each of d / 16 products and sums, and the row's constant likewise: 2 * 16 * 150 * 2^-24 * ln 2
+    assert ((got.double() - ref).abs() <= 2e-4 * ref + 1e-30).all()
