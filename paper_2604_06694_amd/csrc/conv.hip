@@ -387,7 +387,7 @@ __global__ __launch_bounds__(kConvFusedThreads) void conv_select_kernel(
         for (int i = 0; i < kConvBarriers<LOGC>; ++i) __syncthreads();
     __syncthreads();
     const float* kept = reinterpret_cast<const float*>(smem);
-    select_head<EPT, NT>(g, blockIdx.x, w.L, sel.budgets, sel.cu_b, sel.indices, false, [&](float (&x)[EPT], int n_cand) {
+    select_head<EPT, NT>(g, blockIdx.x, w.L, sel.budgets, sel.cu_b, sel.indices, [&](float (&x)[EPT], int n_cand) {
 #pragma unroll
         for (int e = 0; e < EPT; ++e) {
             const int n = (int)threadIdx.x + e * NT;

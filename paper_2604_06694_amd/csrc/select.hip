@@ -135,20 +135,21 @@ __device__ __forceinline__ void joined_scores(const Geom& g, const ConvJoin& j, 
 // EPT, NT: tokens per thread, threads; the head must have at most EPT * NT candidates. JOIN: some heads' scores are left in chunks.
 template <int EPT, int NT, bool JOIN>
 __global__ __launch_bounds__(NT) void select_kernel(
-    Geom g, const float* __restrict__ scores, const int32_t* __restrict__ budgets,
+    Geom g, const float* __restrict__ all_scores, const int32_t* __restrict__ budgets,
     const int32_t* __restrict__ cu_b, const int32_t* __restrict__ cu_seq, int32_t* __restrict__ indices, ConvJoin chunks, float* smoothed)
 {
     const int head = blockIdx.x;
     const int item = head / g.H_kv, h = head - item * g.H_kv;
     const int tok0 = cu_seq[item];
     const int L = cu_seq[item + 1] - tok0;
-    const float* s = scores + (size_t)tok0 * g.H_kv + (size_t)h * L;
+    const float* head_scores = all_scores + (size_t)tok0 * g.H_kv + (size_t)h * L;
     // (a head that keeps only its window: its smoothed scores are stored all the same)
-    select_head<EPT, NT>(g, head, L, budgets, cu_b, indices, JOIN, [&](float (&x)[EPT], int n_cand) {
+    constexpr bool always = JOIN;
+    const auto scores = [&](float (&x)[EPT], int n_cand) {
         const auto load = [&]() {
             // (a buffer of the candidates' size reads as zero past its end: no clamped addresses, all loads of a thread in flight. As
             // with the stores above, the whole offset is in the operand that is checked.)
-            const auto buf = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(s), 0, n_cand * 4, 0x00027000);
+            const auto buf = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(head_scores), 0, n_cand * 4, 0x00027000);
 #pragma unroll
             for (int e = 0; e < EPT; ++e)
                 x[e] = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(buf, ((int)threadIdx.x + e * NT) * 4, 0, 0));
@@ -164,7 +165,8 @@ __global__ __launch_bounds__(NT) void select_kernel(
         } else {
             load();
         }
-    });
+    };
+#include "select_body.h"
 }
 
 // Heads longer than 32 * 1024 tokens: the keys do not fit the registers of one workgroup, so every counting pass

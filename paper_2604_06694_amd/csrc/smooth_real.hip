@@ -368,7 +368,7 @@ __global__ __launch_bounds__(kFusedThreads<LOGC>) void smooth_select_kernel(
         for (int i = 0; i < kRealBarriers<LOGC>; ++i) __syncthreads();
     __syncthreads();
     const float* kept = reinterpret_cast<const float*>(smem);
-    select_head<EPT, NT>(g, blockIdx.x, L, job.budgets, job.cu_b, job.indices, false, [&](float (&x)[EPT], int n_cand) {
+    select_head<EPT, NT>(g, blockIdx.x, L, job.budgets, job.cu_b, job.indices, [&](float (&x)[EPT], int n_cand) {
 #pragma unroll
         for (int e = 0; e < EPT; ++e) {
             const int n = (int)threadIdx.x + e * NT;
