@@ -32,9 +32,10 @@
 // requested has landed), so the HBM latency is paid
 // by a wave that has nothing else to do and no wave holds staging registers.
 // Every compute wave pulls all 32-key x 16-channel fragments of the tile.
-// Sweep 1 keeps no running maximum: its exponentials are taken against a fixed
-// reference (the maximum of the wave's first block) and only a block whose sum
-// leaves the safe range is redone against a new reference. Sweep 1 computes
+// Sweep 1 keeps no running maximum: its exponentials are taken against a
+// reference (the maximum of the wave's first block; where ranges are long, it
+// follows the sum) and only a block whose sum leaves the safe range is redone
+// against a new one. Sweep 1 computes
 // C = K Q^T (a lane owns one query row, so max/sum stay in the lane); sweep 2
 // computes C = Q K^T (a lane owns one key, so the column sum stays in the
 // lane). Both orientations use the same register fragments: only the operand
@@ -530,18 +531,15 @@ __device__ __forceinline__ void score_sweep(
 #pragma unroll
     for (int rb = 0; rb < NB; ++rb) { run_m[rb] = -INFINITY; run_l[rb] = 0.f; }
 
-    // Where ranges have become longer (ragged items, and the row tile per wave that small calls of 225 to 256 rows take): a new
-    // reference every 256 keys, taken from the block that comes next, and what was summed so far merged into (past_m, past_l). Keys far
-    // from the reference's are less like it, and an exponent's rounding grows with its size. Scores against 64 bits, mean of eight
-    // inputs, shorter ranges before | one reference per range | this: 20 items of 4000 to 16000 tokens, 224 rows 4.6e-7 | 5.3 | 4.2,
-    // two of 16384, 256 rows 4.5 | 4.8 | 4.5, eight of 2048 to 32768 at d = 256 4.6 | 5.3 | 4.6, twelve of 500 to 16000, 128 rows
-    // 3.8 | 4.5 | 4.1. It costs 0.3 to 2.5 % of the call; every 512 keys half of that, and corrects half.
-    constexpr bool kRenew = !SWEEP2 && (RAGGED || (D <= 128 && NB == 1 && WR == 8));
-    constexpr int kRenewTiles = 256 / T::TK;
-    float past_m[NB], past_l[NB];
-    if constexpr (kRenew)
-#pragma unroll
-        for (int rb = 0; rb < NB; ++rb) { past_m[rb] = -INFINITY; past_l[rb] = 0.f; }
+    // Where ranges are long (ragged items, and the row tile per wave that small calls of 225 to 256 rows take) the reference follows the
+    // sum: raise_reference, once per tile, moves the sum's binary exponent into it. An exponent's rounding grows with its size, and so
+    // the largest terms, which are what the sum consists of, are a few octaves from the reference instead of as far as the first block
+    // of a range lies below the range's peak. References are whole numbers there, so that neither raising nor merging them rounds
+    // anything, and it takes six vector instructions per tile and row tile. Scores against 64 bits, mean of eight inputs, as many ranges for
+    // every head | ranges of one size and a new reference from the next block every 256 keys | this: twelve items of 500 to 16000 tokens,
+    // 128 rows 3.5e-7 | 4.0 | 2.2, 224 rows 3.1 | 3.6 | 1.8, 224 rows at d = 256 3.0 | 3.6 | 1.9; eight of 2048 to 32768, 224 rows
+    // 4.0 | 4.1 | 2.3; four of 8192, 256 rows, d = 64 3.3 | 3.8 | 2.0. 60 ragged calls take 0.3 % less time than with new references.
+    constexpr bool kRaise = !SWEEP2 && (RAGGED || (D <= 128 && NB == 1 && WR == 8));
 
     // The unit of work is a block: this wave's NB*32 rows x 32 keys (NB MFMA result tiles, KK MFMAs each). Its
     // logits then need the sweep's vector work (fma, exp2, add per logit), which costs about as much ALU time as
@@ -576,6 +574,8 @@ __device__ __forceinline__ void score_sweep(
     // The scale is read through this copy. The empty asm statements in run_block take it as an in/out operand, which
     // ties every slice of vector work to its place between two MFMAs (see there).
     float c_pin = c;
+    // (a reference need not be a logit that was met)
+    auto whole = [&](float m) { return kRaise ? __builtin_rintf(m) : m; };
     // sweep 1, first block of a workgroup's plain tiles: take the reference from the logits themselves
     auto reference_from = [&](f32x16 (&a)[NB]) {
 #pragma unroll
@@ -583,14 +583,19 @@ __device__ __forceinline__ void score_sweep(
             float mx = a[rb][0];
 #pragma unroll
             for (int i = 1; i < 16; ++i) mx = fmaxf(mx, a[rb][i]);
-            run_m[rb] = mx * c;                         // c > 0: the scaled maximum is the maximum of the scaled logits
+            run_m[rb] = whole(mx * c);                  // c > 0: the scaled maximum is the maximum of the scaled logits
             red_c[rb] = run_m[rb];
         }
     };
-    auto renew_reference = [&](f32x16 (&next)[NB]) {
+    auto raise_reference = [&]() {
 #pragma unroll
-        for (int rb = 0; rb < NB; ++rb) { merge_stats(past_m[rb], past_l[rb], run_m[rb], run_l[rb]); run_l[rb] = 0.f; }
-        reference_from(next);
+        for (int rb = 0; rb < NB; ++rb) {
+            // (beyond 2^23 a reference cannot move by ones; of a sum that is zero or not finite the exponent is 0)
+            const int up = fabsf(run_m[rb]) < 0x1p23f ? __builtin_amdgcn_frexp_expf(run_l[rb]) : 0;
+            run_l[rb] = __builtin_ldexpf(run_l[rb], -up);
+            run_m[rb] += (float)up;
+            red_c[rb] = run_m[rb];
+        }
     };
     auto reduce_begin = [&](auto masked_tag, f32x16 (&a)[NB], int j0b) {
         constexpr bool MASKED = decltype(masked_tag)::value;
@@ -672,7 +677,7 @@ __device__ __forceinline__ void score_sweep(
                         float mx = a[rb][0];
 #pragma unroll
                         for (int i = 1; i < 16; ++i) mx = fmaxf(mx, a[rb][i]);
-                        const float m_new = fmaxf(run_m[rb], mx * c);    // finite: the row has a finite reference
+                        const float m_new = fmaxf(run_m[rb], whole(mx * c));    // finite: the row has a finite reference
                         run_l[rb] *= fast_exp2(run_m[rb] - m_new);
                         run_m[rb] = m_new;
                         red_c[rb] = m_new;
@@ -783,7 +788,7 @@ __device__ __forceinline__ void score_sweep(
                         reduce_end(acc1, cbuf, kb);
                     }
                 }
-                if (kRenew && more && (t - t_begin) % kRenewTiles == kRenewTiles - 1) renew_reference(acc0);
+                if constexpr (kRaise) raise_reference();
                 wg_barrier();
                 flush_tile(t);
             }
@@ -804,7 +809,7 @@ __device__ __forceinline__ void score_sweep(
                 if (t + 1 < t_plain_end) run_block(Y{}, Y{}, N{}, acc0, slot_of(t + 1), 0, 0, 0, acc1);
                 else                     run_block(N{}, Y{}, N{}, acc0, 0, 0, 0, 0, acc1);
                 reduce_end(acc1, (t - t_begin) % 3, 0);
-                if (kRenew && t + 1 < t_plain_end && (t - t_begin) % kRenewTiles == kRenewTiles - 1) renew_reference(acc0);
+                if constexpr (kRaise) raise_reference();
                 wg_barrier();
                 flush_tile(t);
                 ++t;
@@ -836,7 +841,6 @@ __device__ __forceinline__ void score_sweep(
         float* my_stats = stats + (size_t)part * rows_pad * 2;
 #pragma unroll
         for (int rb = 0; rb < NB; ++rb) {
-            if constexpr (kRenew) merge_stats(run_m[rb], run_l[rb], past_m[rb], past_l[rb]);
             const float m2 = __shfl_xor(run_m[rb], 32, 64), l2 = __shfl_xor(run_l[rb], 32, 64);
             merge_stats(run_m[rb], run_l[rb], m2, l2);
             if (g2 == 0) {

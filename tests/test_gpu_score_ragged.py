@@ -49,8 +49,8 @@ def test_items_score_as_they_do_alone(A, n_items):
         assert np.allclose(got[a:b], alone, rtol=1e-5, atol=0)
 
 
-# ranges of some 300 to 900 keys, in which sweep 1 takes a new reference every 256: one and two row tiles per wave, every head dimension, and
-# the uniform call of 256 rows that renews it as well
+# ranges of some 300 to 900 keys, in which sweep 1 raises its reference tile by tile: one and two row tiles per wave, every head dimension, and
+# the uniform call of 256 rows that raises it as well
 @pytest.mark.parametrize("H_q,H_kv,d,W,lens", [(14, 2, 128, 32, _spread(12, 3000, 24000)), (14, 2, 128, 64, _spread(12, 3000, 24000)),
                                                (8, 2, 256, 32, _spread(8, 3000, 24000)), (8, 2, 64, 16, _spread(12, 3000, 24000)),
                                                (32, 4, 128, 32, [16384, 16384])], ids=lambda v: str(v) if isinstance(v, int) else f"{len(v)}")
