@@ -677,13 +677,16 @@ __device__ __forceinline__ void score_sweep(
                         float mx = a[rb][0];
 #pragma unroll
                         for (int i = 1; i < 16; ++i) mx = fmaxf(mx, a[rb][i]);
-                        const float m_new = fmaxf(run_m[rb], whole(mx * c));    // finite: the row has a finite reference
-                        run_l[rb] *= fast_exp2(run_m[rb] - m_new);
+                        // (-inf: all logits so far were, as those of keys that overflow are. The sum stays 0, and a reference of -inf
+                        // brings the next block here as well.)
+                        const float m_new = fmaxf(run_m[rb], whole(mx * c));
+                        const float ms = m_new == -INFINITY ? 0.f : m_new;
+                        run_l[rb] *= fast_exp2(run_m[rb] - ms);
                         run_m[rb] = m_new;
                         red_c[rb] = m_new;
                         float sum = 0.f;
 #pragma unroll
-                        for (int i = 0; i < 16; ++i) sum += fast_exp2(fmaf(a[rb][i], c, -m_new));
+                        for (int i = 0; i < 16; ++i) sum += fast_exp2(fmaf(a[rb][i], c, -ms));
                         red_t[rb] = sum;
                     }
                 }

@@ -1,4 +1,4 @@
-"""What sweep 1 takes its exponentials against: the error of the scores where key ranges are long."""
+"""What sweep 1 takes its exponentials against: the error of the scores where key ranges are long, and keys without any weight."""
 import numpy as np
 import pytest
 import torch
@@ -45,3 +45,25 @@ def test_error_of_long_ranges(A, H_q, H_kv, d, W, lens, most):
         errors.append(float((got.double() - ref).norm() / ref.norm()))
     print(f"\nerror {np.mean(errors):.3e}")
     assert np.mean(errors) <= most
+
+
+# ragged items in ranges of one size; a call of 256 rows with one row tile per wave; two and three row tiles
+@pytest.mark.parametrize("H_q,H_kv,d,W,lens", [(14, 2, 128, 32, _spread(12, 500, 12000)), (8, 2, 256, 32, _spread(8, 500, 12000)),
+                                               (8, 2, 64, 16, _spread(70, 300, 2500)), (14, 2, 128, 64, _spread(12, 500, 12000)),
+                                               (16, 2, 128, 32, [4096] * 2), (7, 1, 128, 32, [5000]), (18, 2, 128, 64, [3000])],
+                         ids=lambda v: str(v) if isinstance(v, int) else f"{len(v)}x{max(v)}")
+@pytest.mark.parametrize("first,n", [(0, 40), (0, 300), (64, 65), (200, 400), (255, 2000)])
+def test_keys_whose_logits_are_minus_infinity(A, H_q, H_kv, d, W, lens, first, n):
+    """Whole blocks of such keys, from the first of a range or later: they have no weight, and the others' weights are as without them."""
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    q = (torch.rand(len(lens) * H_q * W * d, generator=gen, device="cuda") + 0.1).to(torch.bfloat16)
+    k = torch.randn(sum(lens) * H_kv * d, generator=gen, device="cuda").to(torch.bfloat16)
+    at = 0
+    for L in lens:
+        k[at:at + L * H_kv * d].view(H_kv, L, d)[:, first:min(first + n, L - W - 1)] = -torch.inf
+        at += L * H_kv * d
+    ref, _ = _reference(q, k, H_q, H_kv, d, W, lens, True)
+    assert bool(ref.isfinite().all()) and bool((ref == 0).any())
+    got = A.score(A.Params(H_q, H_kv, d, W, pool_kernel=1), q, k, lens)
+    # (the bound of test_scores_for_every_division_into_ranges)
+    assert ((got.double() - ref).abs() <= 3e-5 * ref + 1e-30).all()
