@@ -71,20 +71,18 @@ struct AllocateJob {
 };
 struct ConvFilterJob;      // taps of the smoothing's filter (conv_filter.h)
 
-// How a sweep of score cuts the heads into key ranges, one workgroup each. Heads of one length: as many ranges for each. Items of
-// different lengths: ranges of as many keys each, range c of item i, head h being part (first + c) * H_kv + h. Up to 64 items,
-// first is the number of ranges of the items before; beyond, floor(tokens of the items before / keys of a range) + i, which a
-// workgroup finds by a search in cu_seqlens (the parts of different items never meet, at most one range per item stays empty).
+// How a sweep of score cuts the heads into key ranges, one workgroup each: as many for every head, or, for few items of different
+// lengths, ranges of as many keys each, range c of item i, head h being part (number of ranges of the items before + c) * H_kv + h.
 struct ScoreRanges {
-    int per_head = 1;        // equal lengths: ranges per head
-    int keys = 0;            // different lengths: keys per range, whole tiles (0: equal lengths)
+    int per_head = 1;        // as many for every head: how many
+    int keys = 0;            // ranges of one size: keys of each, whole tiles (0: as many for every head)
     double per_key = 0.;     // 1 / keys
     long long parts = 1;     // workgroups of the sweep, and sets of row statistics of sweep 1
     // ranges of a head: the quotient rounded up, in float64 and off the whole numbers, so that it is exact (host and device agree,
     // and with integer divisions planning for 48 lengths took 25 us)
     __host__ __device__ int of_length(int L) const { return (int)(((double)L + (double)keys - 0.5) * per_key); }
 };
-constexpr int kCountedItems = 64;
+constexpr int kCountedItems = 64;        // items that ranges of one size can have: a lane each
 // The ranges of sweep 1; a pure function of the batch so that the workspace query and the launch agree.
 ScoreRanges score_ranges(int H_kv, int n_items, const int32_t* seqlens_host, int rows, int D);
 // Padded row count (multiple of the MFMA row tiling) for G*W window rows; 0 if unsupported.

@@ -56,25 +56,105 @@ long long total_keys(int H_kv, int n_items, const int32_t* seqlens_host) {
     return keys;
 }
 
-ScoreRanges plan_ranges(const Plan& p, int H_kv, int n_items, const int32_t* seqlens_host) {
+// What a workgroup costs before its first and after its last tile (query fragments, filling the ring, the row
+// statistics or constants), in tiles: about 200 keys' worth, fitted to measured launches.
+int overhead_tiles(const Plan& p) { return p.tile_keys >= 64 ? 3 : 7; }
+
+// Items of different lengths, as many ranges for every head, so that a head's ranges are as long as the head is (tiles of the head /
+// number) and workgroups start as others end. The launch takes about the average load of a slot, plus part of the longest
+// workgroup for the ones that start last, plus, when the last round of workgroups fills only part of the
+// slots, that round's average workgroup for the slots left idle (all in twice the unit, to keep halves).
+// cost: in quarter tiles.
+int same_number_for_every_head(const Plan& p, int H_kv, int n_items, const int32_t* seqlens_host, int max_tiles, long long* cost_out) {
+    const int slots = 256 * p.per_cu, overhead = overhead_tiles(p);
+    // (every number is tried with every length: quotients rounded up, in float64 and off the whole numbers, so that they are exact. 48
+    // lengths took 25 us with integer divisions. Items of as many tiles are counted together where there are more items than such
+    // lengths: 281 items of 8 or 9 tiles, score with the log-sum-exp 23.6 and 17.9 us, which the host decides. The arrays have a fixed size: a
+    // container could throw, and callers are C.)
+    constexpr int kKept = 256;
+    double kept[kKept], times[kKept];
+    const int tile_shift = __builtin_ctz((unsigned)p.tile_keys);
+    const auto tiles = [&](int i) { return (seqlens_host[i] + p.tile_keys - 1) >> tile_shift; };
+    const bool counted = max_tiles < kKept && max_tiles < n_items;
+    int entries = 0;
+    if (counted) {
+        int count[kKept] = {};
+        for (int i = 0; i < n_items; ++i) ++count[tiles(i)];
+        for (int t = 1; t <= max_tiles; ++t)
+            if (count[t]) { kept[entries] = t; times[entries++] = count[t]; }
+    } else {
+        for (int i = 0; i < n_items && i < kKept; ++i) { kept[i] = tiles(i); times[i] = 1.; }
+        entries = n_items;
+    }
+    int best = 1;
+    long long best_cost = -1;
+    const int ns_max = max_tiles < 64 ? max_tiles : 64;
+    for (int ns = 1; ns <= ns_max; ++ns) {
+        const long long groups = (long long)n_items * H_kv * ns;   // launched, whether or not they hold tiles
+        double sum = 0., most = 0.;
+        const double per_range = 1. / ns;
+        for (int i = 0; i < entries; ++i) {
+            const double t = i < kKept ? kept[i] : tiles(i), n = i < kKept ? times[i] : 1.;
+            const double tps = (double)(int)((t + ns - 0.5) * per_range);
+            const double used = (double)(int)((t + tps - 0.5) / tps);       // ranges of this head that hold tiles
+            sum += n * (t + used * overhead);
+            most = tps > most ? tps : most;
+        }
+        const long long total = (long long)sum * H_kv, load = 2 * ((total + slots - 1) / slots);
+        long long cost = load + (long long)most + overhead;
+        const long long rem = groups % slots;
+        if (groups > slots && rem) cost += 2 * (total / groups) * (slots - rem) / slots;
+        if (best_cost < 0 || cost < best_cost) { best_cost = cost; best = ns; }
+        // (the load never falls as the number grows)
+        else if (load + 1 + overhead >= best_cost) break;
+    }
+    *cost_out = 2 * best_cost;
+    return best;
+}
+
+// Which of the two divisions items of different lengths get. Ranges of one size need an item for each lane of a wave and a K that fits the
+// memory-side cache (a larger one is streamed faster by ranges that each stay with their head, read backwards by sweep 2). Up to
+// 128 heads they are the rule; with more, the loads of the XCDs even out by themselves, as many ranges for every head keep a head's queries in
+// one L2, and the other division has to promise a quarter less. Score calls, ranges of one size over as many for every head, geometric
+// mean and worst: of 803 calls of up to 64 heads 0.92 and 1.15, of 78 of 65 to 128 0.91 and 1.13, of 22 of more that promise it 0.90 and 1.05,
+// of 137 that do not 1.04 and 1.34; of 160 of a larger K 1.03 and 1.30. At the lines, as many for every head and ranges of one size: 246 x
+// 385-770 tokens of four heads, 256 rows 142 and 172 us, 41 x 212-3402, 128 rows 41 and 34; 32 rows 9 x 23902-24381 (213 MB) 80 and 73,
+// 14 x 21207-23328 (321 MB) 106 and 120, 64 rows of eight heads 7 x 11247-22494 (266 MB) 95 and 88, 8 x 24149-26564 (410 MB) 147 and 163.
+constexpr int kSizedHeads = 128;
+constexpr long long kCacheBytes = 1LL << 28;
+enum class Division { same_number, one_size, cheaper };
+Division division(int H_kv, int n_items, long long keys, int D) {
+    if (n_items > kCountedItems || keys * D * 2 > kCacheBytes) return Division::same_number;
+    return n_items * H_kv <= kSizedHeads ? Division::one_size : Division::cheaper;
+}
+
+ScoreRanges plan_ranges(const Plan& p, int H_kv, int n_items, const int32_t* seqlens_host, Division division) {
     // The heads are cut into key ranges so that the grid fills the 256 CUs evenly: the division minimises the time of
-    // the launch in units of one tile, with a fixed prologue cost per workgroup (in tiles), in whole rounds of workgroups.
-    // what a workgroup costs before its first and after its last tile (query fragments, filling the ring, the row
-    // statistics or constants), in tiles: about 200 keys' worth, fitted to measured launches
-    const int overhead = p.tile_keys >= 64 ? 3 : 7;
+    // the launch in units of a quarter tile, with a fixed prologue cost per workgroup, in whole rounds of workgroups.
+    const int overhead = overhead_tiles(p);
     int longest = 1;
     bool uniform = true;             // as many ranges for every head
-    long long tokens = 0;
     for (int i = 0; i < n_items; ++i) {
         if (seqlens_host[i] > longest) longest = seqlens_host[i];
         if (seqlens_host[i] != seqlens_host[0]) uniform = false;
-        tokens += seqlens_host[i];
     }
     const int max_tiles = (longest + p.tile_keys - 1) / p.tile_keys;
     // (lengths differ, but a workgroup for every tile of every head, were all as long as the longest, fits the chip at once: to find
     // its item would cost each of them 0.2 us. The same answer for every sweep of a call, whatever its tiling.)
     if (!uniform && max_tiles <= 64 && (long long)n_items * H_kv * max_tiles <= 256) uniform = true;
-    const int slots = 256 * p.per_cu;
+    ScoreRanges same;
+    long long same_cost = 0;
+    if (!uniform && division != Division::one_size) {
+        same.per_head = same_number_for_every_head(p, H_kv, n_items, seqlens_host, max_tiles, &same_cost);
+        same.parts = (long long)n_items * H_kv * same.per_head;
+        if (division == Division::same_number) return same;
+    }
+    // One and two compute waves at d <= 128: three workgroups share a CU, which ranges of one size put to use from a tile for each of two on
+    // (24 x 5929-6048 tokens, 64 rows at d = 64 with the log-sum-exp at hand 14.5 and 13.1 us, 7 x 12763-14040 of eight heads 67.8
+    // and 65.1, planned for two and for three; below that up to 3 % slower).
+    long long tokens = 0;
+    for (int i = 0; i < n_items; ++i) tokens += seqlens_host[i];
+    const int slots = 256 * (!uniform && p.WR < 4 && p.tile_keys >= 64 && tokens * H_kv >= 512LL * p.tile_keys ? 3 : p.per_cu);
     ScoreRanges best;
     long long best_cost = -1;
     const int ns_max = max_tiles < 64 ? max_tiles : 64;
@@ -86,17 +166,19 @@ ScoreRanges plan_ranges(const Plan& p, int H_kv, int n_items, const int32_t* seq
         if (!uniform) {
             r.keys = tiles * p.tile_keys;
             r.per_key = 1. / r.keys;
-            groups = tokens / r.keys + n_items;
-            if (n_items <= kCountedItems) {
-                groups = 0;
-                for (int i = 0; i < n_items; ++i) groups += r.of_length(seqlens_host[i]);
-            }
+            groups = 0;
+            for (int i = 0; i < n_items; ++i) groups += r.of_length(seqlens_host[i]);
         }
         r.parts = groups * H_kv;
         const long long rounds = (r.parts + slots - 1) / slots;
-        const long long cost = rounds * (tiles + overhead);
+        // Seven compute waves with a CU to themselves are faster than two sevens that share it (ranges of one size, 224 rows: 8 x 3607-3968
+        // tokens of one head in 473 ranges 20.0 us, as this plans them 16.4; 12 x 2351-2587 20.0 and 16.4; 6 x 7092-7802 22.8 and 18.9).
+        // Of one to four waves this is not so (32 rows 10 x 586-616 12.2 and 13.5).
+        const int quarters = !uniform && p.WR == 7 && p.per_cu == 2 && r.parts <= 256 ? 3 : 4;
+        const long long cost = quarters * rounds * (tiles + overhead);
         if (best_cost < 0 || cost < best_cost) { best_cost = cost; best = r; }
     }
+    if (!uniform && division == Division::cheaper && 4 * best_cost >= 3 * same_cost) return same;
     return best;
 }
 
@@ -131,7 +213,7 @@ ScoreRanges score_ranges(int H_kv, int n_items, const int32_t* seqlens_host, int
         none.parts = (long long)n_items * H_kv;
         return none;
     }
-    return plan_ranges(p, H_kv, n_items, seqlens_host);
+    return plan_ranges(p, H_kv, n_items, seqlens_host, division(H_kv, n_items, total_keys(H_kv, n_items, seqlens_host), D));
 }
 
 hipError_t launch_score(const Geom& g, const void* q_win, const void* k, const int32_t* cu_seqlens,
@@ -148,7 +230,8 @@ hipError_t launch_score(const Geom& g, const void* q_win, const void* k, const i
     // What the memory-side cache (256 MB) holds of K after sweep 1 is its end: where K does not fit, sweep 2 begins there. Score
     // calls, forwards and backwards: 28 x 32768, 448 rows 929 and 915 us, 13 x 32768 452 and 442; 224 rows 30 x 9000 (276 MB) 169 and 165,
     // 48 x 10000 297 and 289; K that fits: 28 x 9000, 256 rows (258 MB) 352 and 356 with the eviction around it.
-    const bool backwards = keys * g.D * 2 > (1LL << 28);
+    const bool backwards = keys * g.D * 2 > kCacheBytes;
+    const Division div = ranges1.keys ? Division::one_size : Division::same_number;    // (sweep 2 finds the statistics by that of sweep 1)
     score_detail::SweepArgs args{q_win, k, cu_seqlens, ranges1, rows_pad, 0, stats_ws, ranges1, lse, raw_out, backwards, ride_along, ride_taps};
     auto sweep = [&](int which, const Plan& p, const ScoreRanges& ranges, int row_base, float* raw) -> hipError_t {
         args.ranges = ranges;
@@ -173,14 +256,14 @@ hipError_t launch_score(const Geom& g, const void* q_win, const void* k, const i
     Plan p2;
     if (!sweep2_is_split(rows, g.D)) {
         if (!make_plan(rows, g.D, 2, keys, &p2)) return hipErrorInvalidValue;
-        return sweep(2, p2, plan_ranges(p2, g.H_kv, g.n_items, seqlens_host), 0, raw_out);
+        return sweep(2, p2, plan_ranges(p2, g.H_kv, g.n_items, seqlens_host, div), 0, raw_out);
     }
     if (!raw_second) return hipErrorInvalidValue;
     Plan p2b;
     if (!make_plan(kSweep2MaxRows, g.D, 2, keys, &p2) || !make_plan(rows - kSweep2MaxRows, g.D, 2, keys, &p2b)) return hipErrorInvalidValue;
-    e = sweep(2, p2, plan_ranges(p2, g.H_kv, g.n_items, seqlens_host), 0, raw_out);
+    e = sweep(2, p2, plan_ranges(p2, g.H_kv, g.n_items, seqlens_host, div), 0, raw_out);
     if (e != hipSuccess) return e;
-    e = sweep(2, p2b, plan_ranges(p2b, g.H_kv, g.n_items, seqlens_host), kSweep2MaxRows, raw_second);
+    e = sweep(2, p2b, plan_ranges(p2b, g.H_kv, g.n_items, seqlens_host, div), kSweep2MaxRows, raw_second);
     if (e != hipSuccess) return e;
     const unsigned blocks = (unsigned)((raw_elems + 256 * 8 - 1) / (256 * 8));
     hipLaunchKernelGGL(score_detail::score_add_kernel, dim3(blocks > 0 ? blocks : 1), dim3(256), 0, s, raw_out,

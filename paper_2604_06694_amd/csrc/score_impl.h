@@ -241,7 +241,7 @@ __device__ __forceinline__ float merged_row(const float2* __restrict__ hs, int n
     return M + __log2f(Z);
 }
 
-// Items of different lengths: the item and the ranges of a workgroup. Up to 64 items, a lane has the place of one, and what a
+// Ranges of one size: the item and the ranges of a workgroup. A lane has the place of an item (up to 64), and what a
 // workgroup needs of its own is a lane's: one load latency in all.
 struct RangePlace {
     int at = 0, len = 0;         // this lane's item
@@ -256,27 +256,7 @@ struct RangePlace {
         return item > 0 ? __builtin_amdgcn_readlane(counts, item > 0 ? item - 1 : 0) : 0;
     }
 };
-// more than 64 items
-__device__ __forceinline__ int first_range(const int32_t* __restrict__ cu_seq, int i, unsigned keys) {
-    return (int)((unsigned)(cu_seq[i] - cu_seq[0]) / keys) + i;
-}
-// The last item whose first range is not past range q: every round probes 64 of them at equal distances, one per lane, one load
-// latency for up to 64, two up to 4096.
-__device__ __forceinline__ int item_of_range(const int32_t* __restrict__ cu_seq, int n_items, int q, unsigned keys) {
-    int item = 0;
-    for (int span = n_items; span > 1;) {
-        const int step = (span + 63) >> 6;
-        const int probe = item + (int)(threadIdx.x & 63) * step;
-        const bool at_or_before = probe < item + span && first_range(cu_seq, min(probe, n_items - 1), keys) <= q;
-        const int n = __builtin_popcountll(__builtin_amdgcn_ballot_w64(at_or_before));   // a prefix of the lanes
-        const int skip = n > 0 ? (n - 1) * step : 0;
-        item += skip;
-        span = min(step, span - skip);
-    }
-    return __builtin_amdgcn_readfirstlane(item);
-}
-
-// RAGGED: items of different lengths. Kernels of their own: with the search for an item beside it in one kernel, the prologue of calls
+// RAGGED: ranges of one size. Kernels of their own: with the search for an item beside it in one kernel, the prologue of calls
 // on one layer took longer (evict 13577 48.2 -> 49.3 us, 32768 with 448 rows 87.8 -> 89.3).
 template <int D, int NB, int WR, bool SWEEP2, bool RAGGED>
 __device__ __forceinline__ void score_sweep(
@@ -293,37 +273,29 @@ __device__ __forceinline__ void score_sweep(
     float* lds_cols = reinterpret_cast<float*>(lds + T::STAGES * T::LDS_K);
     float* lds_rc = reinterpret_cast<float*>(lds + T::STAGES * T::LDS_K + 3 * T::LDS_COLS);
 
-    // Workgroups go to the 8 XCDs round-robin by index, and each XCD has its own L2. Of heads of one length, all key-range splits
+    // Workgroups go to the 8 XCDs round-robin by index, and each XCD has its own L2. With as many ranges for every head, all ranges
     // of a head are therefore given indices with the same residue mod 8, so that the head's window queries (and the tile
-    // shared by neighbouring splits) are fetched from HBM by one L2 only. With different lengths that would give the XCDs loads
-    // as different as their heads', and the launch the time of the fullest: there ranges of one size follow one another, and the
-    // heads of a range. Score calls, as many ranges for every head and ranges of one size: 224 rows 10 of 600 to 30000 tokens 69.7 and
+    // shared by neighbouring ranges) are fetched from HBM by one L2 only. Of few heads of different lengths that would give the XCDs loads
+    // as different as their heads', and the launch the time of the fullest: there (division, score.hip) ranges of one size follow one another, and
+    // the heads of a range. Score calls, as many ranges for every head and ranges of one size: 224 rows 10 of 600 to 30000 tokens 69.7 and
     // 51.5 us, 256 rows 8 of 2000 to 20000 70.0 and 51.8, 448 rows 24 of 1500 to 30000 372 and 333, 128 rows 30 of 500 to 16000 108 and
-    // 87, d = 256 8 of 2048 to 32768 56.7 and 41.4 (with a tile on its way across barriers), 100 of 500 to 8000 234 and 231; short ones, for the search, 40 of 400 to 6000
-    // 21.7 and 21.9, 448 rows 6 of 500 to 2000 21.5 and 21.8.
+    // 87, d = 256 8 of 2048 to 32768 56.7 and 41.4 (with a tile on its way across barriers); short ones, for the search, 448 rows 6 of 500
+    // to 2000 21.5 and 21.8.
     const int nsplit = ranges.per_head;
     int item, h, split, part, tok0, L;
-    int stat_first = 0;                               // items of different lengths: the item's first range in stats
+    int stat_first = 0;                               // ranges of one size: the item's first range in stats
     if constexpr (RAGGED) {
         const int q = blockIdx.x / g.H_kv;
         h = blockIdx.x - q * g.H_kv;
         part = blockIdx.x;
-        if (g.n_items <= kCountedItems) {
-            RangePlace place;
-            place.load(cu_seq, g.n_items);
-            const int counts = place.counts(ranges);
-            item = min(__builtin_popcountll(__builtin_amdgcn_ballot_w64(counts <= q)), g.n_items - 1);   // (a prefix of the lanes)
-            split = q - RangePlace::before(counts, item);
-            if (SWEEP2) stat_first = RangePlace::before(place.counts(stat_ranges), item);
-            tok0 = __builtin_amdgcn_readlane(place.at, item);
-            L = __builtin_amdgcn_readlane(place.len, item);
-        } else {
-            item = item_of_range(cu_seq, g.n_items, q, ranges.keys);
-            split = q - first_range(cu_seq, item, ranges.keys);
-            if (SWEEP2) stat_first = first_range(cu_seq, item, stat_ranges.keys);
-            tok0 = cu_seq[item];
-            L = cu_seq[item + 1] - tok0;
-        }
+        RangePlace place;
+        place.load(cu_seq, g.n_items);
+        const int counts = place.counts(ranges);
+        item = min(__builtin_popcountll(__builtin_amdgcn_ballot_w64(counts <= q)), g.n_items - 1);   // (a prefix of the lanes)
+        split = q - RangePlace::before(counts, item);
+        if (SWEEP2) stat_first = RangePlace::before(place.counts(stat_ranges), item);
+        tok0 = __builtin_amdgcn_readlane(place.at, item);
+        L = __builtin_amdgcn_readlane(place.len, item);
     } else {
         int head;
         const int n_heads = n_wg / nsplit;

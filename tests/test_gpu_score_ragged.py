@@ -70,3 +70,15 @@ def test_logits_that_drift_past_each_new_reference(A, H_q, H_kv, d, W, lens, sha
     got = A.score(A.Params(H_q, H_kv, d, W, pool_kernel=1), q, k, lens)
     # logits of up to 150 octaves, rounded in each of d / 16 products and sums, and the row's constant likewise: 2 * 16 * 150 * 2^-24 * ln 2
     assert ((got.double() - ref).abs() <= 2e-4 * ref + 1e-30).all()
+
+
+# as many ranges for every head, which sweep 2 takes from the last to the first: K of some 300 MB at d = 256, and 129 heads of short items
+@pytest.mark.parametrize("H_q,H_kv,d,W,lens", [(2, 2, 256, 16, _spread(41, 2000, 18000)), (3, 1, 128, 32, _spread(129, 64, 2500))],
+                         ids=lambda v: str(v) if isinstance(v, int) else f"{len(v)}x{max(v)}")
+def test_items_that_get_as_many_ranges_for_every_head(A, H_q, H_kv, d, W, lens):
+    q, k = _inputs(H_q, H_kv, d, W, lens)
+    ref, lse = _reference(q, k, H_q, H_kv, d, W, lens, True)
+    p = A.Params(H_q, H_kv, d, W, pool_kernel=1)
+    # (the bound of test_scores_for_every_division_into_ranges)
+    for got in (A.score(p, q, k, lens), A.score(p, q, k, lens, lse=lse.float())):
+        assert ((got.double() - ref).abs() <= 3e-5 * ref + 1e-30).all()
