@@ -137,20 +137,28 @@ Workspace plan_workspace(const audiokv_params* p, const Batch& b, const int32_t*
     const int rows = (p->n_q_heads / p->n_kv_heads) * (p->window > 0 ? p->window : 1);
     const int rows_pad = score_padded_rows(rows, p->head_dim);
     w.ranges = score_ranges(p->n_kv_heads, b.n_items, seqlens_host, rows, p->head_dim);
-    size_t off = 0;
-    w.stats_off = off;
-    // partial row statistics [part][rows_pad][2]
-    off += align_up((size_t)w.ranges.parts * (rows_pad > 0 ? rows_pad : 1) * 2 * sizeof(float), 256);
-    w.raw_off = off;
-    off += align_up((size_t)b.total_tokens * p->n_kv_heads * sizeof(float), 256);
     w.raw2 = score_needs_second_raw(rows, p->head_dim);     // second row range of a split sweep 2
-    w.raw2_off = off;
-    if (w.raw2) off += align_up((size_t)b.total_tokens * p->n_kv_heads * sizeof(float), 256);
-    w.smooth_off = off;
-    off += align_up((size_t)b.total_tokens * p->n_kv_heads * sizeof(float), 256);
-    w.fft_off = off;          // arbitrary-length spectral smoothing (empty when every length is a power of two)
-    off += align_up(smooth_workspace_bytes(seqlens_host, b.n_items, p->n_kv_heads), 256);
-    w.total = off;
+    const size_t scores = align_up((size_t)b.total_tokens * p->n_kv_heads * sizeof(float), 256);
+    // arbitrary-length spectral smoothing (empty when every length is a power of two)
+    const size_t fft = align_up(smooth_workspace_bytes(seqlens_host, b.n_items, p->n_kv_heads), 256);
+    const size_t rest = scores * (w.raw2 ? 3 : 2) + fft;
+    // partial row statistics [part][rows_pad][2]
+    const size_t part = (size_t)(rows_pad > 0 ? rows_pad : 1) * 2 * sizeof(float);
+    const auto stats = [&] { return align_up((size_t)w.ranges.parts * part, 256); };
+    // A batch that audiokv_evict_noalloc can take with fewer key ranges is not kept from it by a division that would be a little
+    // faster: ranges of one size, and ranges that are each alone on a CU, are up to three times as many as others.
+    constexpr size_t kNoalloc = AUDIOKV_NOALLOC_SCRATCH_BYTES;
+    if (rest + stats() > kNoalloc && rest < kNoalloc) {
+        const long long max_parts = (long long)((kNoalloc - rest) / part);
+        if (w.ranges.parts <= 3 * max_parts)
+            w.ranges = score_ranges(p->n_kv_heads, b.n_items, seqlens_host, rows, p->head_dim, max_parts);
+    }
+    w.stats_off = 0;
+    w.raw_off = stats();
+    w.raw2_off = w.raw_off + scores;
+    w.smooth_off = w.raw2_off + (w.raw2 ? scores : 0);
+    w.fft_off = w.smooth_off + scores;
+    w.total = w.fft_off + fft;
     return w;
 }
 

@@ -3,6 +3,7 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <limits.h>
 #include <stdint.h>
 
 #include "audiokv.h"
@@ -84,7 +85,8 @@ struct ScoreRanges {
 };
 constexpr int kCountedItems = 64;        // items that ranges of one size can have: a lane each
 // The ranges of sweep 1; a pure function of the batch so that the workspace query and the launch agree.
-ScoreRanges score_ranges(int H_kv, int n_items, const int32_t* seqlens_host, int rows, int D);
+// max_parts: not more parts than these, if one range for every head is not more already.
+ScoreRanges score_ranges(int H_kv, int n_items, const int32_t* seqlens_host, int rows, int D, long long max_parts = LLONG_MAX);
 // Padded row count (multiple of the MFMA row tiling) for G*W window rows; 0 if unsupported.
 int score_padded_rows(int rows, int D);
 

@@ -65,7 +65,7 @@ int overhead_tiles(const Plan& p) { return p.tile_keys >= 64 ? 3 : 7; }
 // workgroup for the ones that start last, plus, when the last round of workgroups fills only part of the
 // slots, that round's average workgroup for the slots left idle (all in twice the unit, to keep halves).
 // cost: in quarter tiles.
-int same_number_for_every_head(const Plan& p, int H_kv, int n_items, const int32_t* seqlens_host, int max_tiles, long long* cost_out) {
+int same_number_for_every_head(const Plan& p, int H_kv, int n_items, const int32_t* seqlens_host, int max_tiles, long long max_parts, long long* cost_out) {
     const int slots = 256 * p.per_cu, overhead = overhead_tiles(p);
     // (every number is tried with every length: quotients rounded up, in float64 and off the whole numbers, so that they are exact. 48
     // lengths took 25 us with integer divisions. Items of as many tiles are counted together where there are more items than such
@@ -91,6 +91,7 @@ int same_number_for_every_head(const Plan& p, int H_kv, int n_items, const int32
     const int ns_max = max_tiles < 64 ? max_tiles : 64;
     for (int ns = 1; ns <= ns_max; ++ns) {
         const long long groups = (long long)n_items * H_kv * ns;   // launched, whether or not they hold tiles
+        if (ns > 1 && groups > max_parts) break;
         double sum = 0., most = 0.;
         const double per_range = 1. / ns;
         for (int i = 0; i < entries; ++i) {
@@ -128,7 +129,8 @@ Division division(int H_kv, int n_items, long long keys, int D) {
     return n_items * H_kv <= kSizedHeads ? Division::one_size : Division::cheaper;
 }
 
-ScoreRanges plan_ranges(const Plan& p, int H_kv, int n_items, const int32_t* seqlens_host, Division division) {
+// max_parts: not more than these where one range for every head is not more than that already.
+ScoreRanges plan_ranges(const Plan& p, int H_kv, int n_items, const int32_t* seqlens_host, Division division, long long max_parts = LLONG_MAX) {
     // The heads are cut into key ranges so that the grid fills the 256 CUs evenly: the division minimises the time of
     // the launch in units of a quarter tile, with a fixed prologue cost per workgroup, in whole rounds of workgroups.
     const int overhead = overhead_tiles(p);
@@ -145,7 +147,7 @@ ScoreRanges plan_ranges(const Plan& p, int H_kv, int n_items, const int32_t* seq
     ScoreRanges same;
     long long same_cost = 0;
     if (!uniform && division != Division::one_size) {
-        same.per_head = same_number_for_every_head(p, H_kv, n_items, seqlens_host, max_tiles, &same_cost);
+        same.per_head = same_number_for_every_head(p, H_kv, n_items, seqlens_host, max_tiles, max_parts, &same_cost);
         same.parts = (long long)n_items * H_kv * same.per_head;
         if (division == Division::same_number) return same;
     }
@@ -170,6 +172,7 @@ ScoreRanges plan_ranges(const Plan& p, int H_kv, int n_items, const int32_t* seq
             for (int i = 0; i < n_items; ++i) groups += r.of_length(seqlens_host[i]);
         }
         r.parts = groups * H_kv;
+        if (ns > 1 && r.parts > max_parts) continue;
         const long long rounds = (r.parts + slots - 1) / slots;
         // Seven compute waves with a CU to themselves are faster than two sevens that share it (ranges of one size, 224 rows: 8 x 3607-3968
         // tokens of one head in 473 ranges 20.0 us, as this plans them 16.4; 12 x 2351-2587 20.0 and 16.4; 6 x 7092-7802 22.8 and 18.9).
@@ -206,14 +209,14 @@ int score_padded_rows(int rows, int D) {
 bool score_needs_second_raw(int rows, int D) { return sweep2_is_split(rows, D); }
 
 // what sizes the statistics in the workspace
-ScoreRanges score_ranges(int H_kv, int n_items, const int32_t* seqlens_host, int rows, int D) {
+ScoreRanges score_ranges(int H_kv, int n_items, const int32_t* seqlens_host, int rows, int D, long long max_parts) {
     Plan p;
     if (n_items <= 0 || H_kv <= 0 || !make_plan(rows, D, 1, total_keys(H_kv, n_items, seqlens_host), &p)) {
         ScoreRanges none;
         none.parts = (long long)n_items * H_kv;
         return none;
     }
-    return plan_ranges(p, H_kv, n_items, seqlens_host, division(H_kv, n_items, total_keys(H_kv, n_items, seqlens_host), D));
+    return plan_ranges(p, H_kv, n_items, seqlens_host, division(H_kv, n_items, total_keys(H_kv, n_items, seqlens_host), D), max_parts);
 }
 
 hipError_t launch_score(const Geom& g, const void* q_win, const void* k, const int32_t* cu_seqlens,
