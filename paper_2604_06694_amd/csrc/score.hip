@@ -115,7 +115,7 @@ int same_number_for_every_head(const Plan& p, int H_kv, int n_items, const int32
 
 // Which of the two divisions items of different lengths get. Ranges of one size need an item for each lane of a wave and a K that fits the
 // memory-side cache (a larger one is streamed faster by ranges that each stay with their head, read backwards by sweep 2). Up to
-// 128 heads they are the rule; with more, the loads of the XCDs even out by themselves, as many ranges for every head keep a head's queries in
+// 128 heads they are the rule (but for nearly equal lengths); with more, the loads of the XCDs even out by themselves, as many ranges for every head keep a head's queries in
 // one L2, and the other division has to promise a quarter less. Score calls, ranges of one size over as many for every head, geometric
 // mean and worst: of 803 calls of up to 64 heads 0.92 and 1.15, of 78 of 65 to 128 0.91 and 1.13, of 22 of more that promise it 0.90 and 1.05,
 // of 137 that do not 1.04 and 1.34; of 160 of a larger K 1.03 and 1.30. At the lines, as many for every head and ranges of one size: 246 x
@@ -124,8 +124,13 @@ int same_number_for_every_head(const Plan& p, int H_kv, int n_items, const int32
 constexpr int kSizedHeads = 128;
 constexpr long long kCacheBytes = 1LL << 28;
 enum class Division { same_number, one_size, cheaper };
-Division division(int H_kv, int n_items, long long keys, int D) {
-    if (n_items > kCountedItems || keys * D * 2 > kCacheBytes) return Division::same_number;
+Division division(int H_kv, int n_items, const int32_t* seqlens_host, int D) {
+    long long tokens = 0, longest = 0;
+    for (int i = 0; i < n_items; ++i) { tokens += seqlens_host[i]; longest = seqlens_host[i] > longest ? seqlens_host[i] : longest; }
+    if (n_items > kCountedItems || tokens * H_kv * D * 2 > kCacheBytes) return Division::same_number;
+    // (more than 64 heads of nearly one length leave the XCDs nothing to even out: 64 x 578-636 tokens of two heads, 128 rows 20.8 and
+    // 25.9 us, 32 x 832-874 of four 22.7 and 25.8)
+    if (n_items * H_kv > 64 && 5 * longest * n_items < 6 * tokens) return Division::same_number;
     return n_items * H_kv <= kSizedHeads ? Division::one_size : Division::cheaper;
 }
 
@@ -216,7 +221,7 @@ ScoreRanges score_ranges(int H_kv, int n_items, const int32_t* seqlens_host, int
         none.parts = (long long)n_items * H_kv;
         return none;
     }
-    return plan_ranges(p, H_kv, n_items, seqlens_host, division(H_kv, n_items, total_keys(H_kv, n_items, seqlens_host), D), max_parts);
+    return plan_ranges(p, H_kv, n_items, seqlens_host, division(H_kv, n_items, seqlens_host, D), max_parts);
 }
 
 hipError_t launch_score(const Geom& g, const void* q_win, const void* k, const int32_t* cu_seqlens,

@@ -56,7 +56,8 @@ int main() {
         bool good = true;
         long long cost = 0, parts = 0;
         const int number = number_for_every_head(t, H, lens, &cost);
-        const bool fits = n <= 64 && keys * D * 2 <= 1 << 28;
+        const bool even = n * H > 64 && 5.0 * *std::max_element(lens.begin(), lens.end()) * n * H < 6.0 * keys;
+        const bool fits = n <= 64 && keys * D * 2 <= 1 << 28 && !even;
         if (tiles <= 64 && n * H * tiles <= 256) {
             ++small;
             good = r.keys == 0 && r.parts == (long long)n * H * r.per_head;
