@@ -22,6 +22,7 @@ struct ConvCall {
     ConvFilterJob job{};
     int log_c = 0;
     int max_r = 1;            // chunks of the longest head
+    bool uneven = false;      // other heads have fewer
     size_t points = 0;        // points of the longest transform: stride of `part` (per head) and `spec` (per item)
     void* part = nullptr;     // complex results of the chunks (unused when max_r = 1)
     void* spec = nullptr;     // the filters' bins, or null: every workgroup transforms its own share of the filter

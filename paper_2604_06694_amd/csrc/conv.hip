@@ -239,13 +239,13 @@ __device__ __forceinline__ void to_bins(ConvLds<LOGC>& m, const typename Cfft<LO
 
 // the filter's bins of every distinct length, for calls in which many heads share them
 template <int LOGC>
-__global__ __launch_bounds__(Cfft<LOGC>::THREADS) void conv_spectrum_kernel(Geom g, ConvFilterJob job, int log_r,
+__global__ __launch_bounds__(Cfft<LOGC>::THREADS) void conv_spectrum_kernel(Geom g, ConvFilterJob job, int log_r, int turn,
                                                                            cf* __restrict__ spec, size_t spec_stride)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     ConvLds<LOGC>& m = *reinterpret_cast<ConvLds<LOGC>*>(smem);
     ConvHead w;
-    const int item = blockIdx.x >> log_r, r = (blockIdx.x + item) & ((1 << log_r) - 1), t = threadIdx.x;   // (as in conv_chunk_kernel)
+    const int item = blockIdx.x >> log_r, r = (blockIdx.x + item * turn) & ((1 << log_r) - 1), t = threadIdx.x;   // (as in conv_chunk_kernel)
     if (!conv_head(g, job, item * g.H_kv, LOGC, w) || w.owner != item || r >= w.R) return;
     TapBlocks<LOGC == 13 ? 2 : 4> taps;
     constexpr bool kEarly = LOGC < 13;
@@ -349,16 +349,17 @@ __device__ __forceinline__ void conv_chunk(
 
 template <int LOGC, int POOL, bool SPEC>
 __global__ __launch_bounds__(Cfft<LOGC>::THREADS) void conv_chunk_kernel(
-    Geom g, const float* __restrict__ in, ConvFilterJob job, int log_r, const cf* __restrict__ spec, size_t spec_stride,
+    Geom g, const float* __restrict__ in, ConvFilterJob job, int log_r, int turn, const cf* __restrict__ spec, size_t spec_stride,
     cf* __restrict__ part, size_t part_stride, float alpha, float* __restrict__ out)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     ConvHead w;
-    // Workgroup i runs on XCD i mod 8, and heads of fewer chunks than the longest need the first residues only: these go to another
-    // XCD from head to head. (All on the first ones: 24 sequences of two heads, 1500 to 30000 samples, put 48 of their 172 workgroups
-    // on the 32 CUs of XCD 0, one each, and 12 on XCD 7. Smooth calls, so and now: those 36.9 and 27.2 us, 40 of four heads of 3000 to
-    // 20000 80.0 and 64.4, 20 of 5000 to 100000 158 and 119; 6 of 40000 to 100000, which need nearly all residues, 65.8 and 67.2.)
-    const int head = blockIdx.x >> log_r, r = (blockIdx.x + head) & ((1 << log_r) - 1);
+    // Workgroup i runs on XCD i mod 8, and heads of fewer chunks than the longest need the first residues only: where there are such heads
+    // (turn = 1), these go to another XCD from head to head. (All on the first ones: 24 sequences of two heads, 1500 to 30000 samples, put
+    // 48 of their 172 workgroups on the 32 CUs of XCD 0, one each, and 12 on XCD 7. Smooth calls, so and now: those 36.9 and 27.2 us, 40 of
+    // four heads of 3000 to 20000 80.0 and 64.4, 20 of 5000 to 100000 158 and 119; 211 ragged calls 0.95 of the time in the geometric mean,
+    // the worst 1.02. Heads that all need every residue lose by it: 12 of 73557 with eight heads 169 and 178, 12 of 82908 with four 97.5 and 101.9.)
+    const int head = blockIdx.x >> log_r, r = (blockIdx.x + head * turn) & ((1 << log_r) - 1);
     if (!conv_head(g, job, head, LOGC, w) || r >= w.R) return;
     conv_chunk<LOGC, POOL, SPEC, false>(g, in, job, w, head, r, spec, spec_stride, part, part_stride, alpha, out, smem);
 }
@@ -456,7 +457,7 @@ hipError_t launch_chunks(const Geom& g, const ConvCall& c, const float* in, floa
         }
     }
     hipLaunchKernelGGL((conv_chunk_kernel<LOGC, POOL, SPEC>), dim3((unsigned)(g.n_items * g.H_kv) << log_residues(c)),
-                       dim3(Cfft<LOGC>::THREADS), lds, s, g, in, c.job, log_residues(c), (const cf*)c.spec, c.points, (cf*)c.part, c.points, alpha, out);
+                       dim3(Cfft<LOGC>::THREADS), lds, s, g, in, c.job, log_residues(c), c.uneven ? 1 : 0, (const cf*)c.spec, c.points, (cf*)c.part, c.points, alpha, out);
     return hipGetLastError();
 }
 template <int LOGC, bool SPEC>
@@ -502,7 +503,7 @@ hipError_t launch_spectra(const Geom& g, const ConvCall& c, hipStream_t s) {
         }
     }
     hipLaunchKernelGGL((conv_spectrum_kernel<LOGC>), dim3((unsigned)g.n_items << log_residues(c)), dim3(Cfft<LOGC>::THREADS), lds, s,
-                       g, c.job, log_residues(c), (cf*)c.spec, c.points);
+                       g, c.job, log_residues(c), c.uneven ? 1 : 0, (cf*)c.spec, c.points);
     return hipGetLastError();
 }
 

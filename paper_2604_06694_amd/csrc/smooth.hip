@@ -1232,6 +1232,7 @@ SmoothPlan plan_smooth(const Geom& g, const int32_t* cu_seqlens, const int32_t* 
     c.log_c = conv_chunk_log(longest);
     const int log_n = conv_log_points(longest, c.log_c);
     c.max_r = 1 << (log_n - c.log_c);
+    for (int i = 0; i < n_items; ++i) c.uneven |= !pow2_length(seqlens_host[i]) && conv_log_points(seqlens_host[i], c.log_c) < log_n;
     c.points = (size_t)1 << log_n;
     // per head the chunks' results, per item the filter's bins, per item the taps: M points each at most
     const size_t M = bluestein_bytes(seqlens_host, n_items, g.H_kv) / (((size_t)n_heads + 3 * (size_t)n_items) * sizeof(cf));

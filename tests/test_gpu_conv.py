@@ -178,3 +178,10 @@ def test_smooth_more_heads_than_a_grid_dimension_holds(A):
     ref = torch.fft.irfft(spectrum, n=L, dim=1)
     # fp32 transforms of 32 points and 21 taps: a few ulps of the mean-1/2 sequence
     assert (out.double() - ref).abs().max().item() < 5e-6
+
+
+@pytest.mark.parametrize("lens", [[9001] * 3, [9001, 9003, 16000], [9001, 1500, 30011], [40000, 70000], [70000, 70001], [2048, 9001, 9001]])
+@pytest.mark.parametrize("H", [2, 5])
+def test_heads_of_as_many_chunks_and_of_fewer(A, lens, H):
+    """The residues of a head in their order, and turned from head to head where some heads have fewer."""
+    check(A, np.random.default_rng(len(lens) + H), lens, H, 0.125)
