@@ -385,9 +385,11 @@ hipError_t launch_decode(const Geom& g, const void* q, const void* k_cache, cons
     // loads is the launch: 1024 threads. Calls, d = 256 8 of 2048 to 32768 (5 rounds) 26.8 -> 24.0 us, 28 x 8192 (6) 40.7 -> 39.3; d = 128
     // 1 x 8192 (3) 12.0 -> 11.7, 1 x 32768 (13) 17.1 -> 15.6; with fewer rounds than that 16 x 4096 (1.6) 19.5 and 20.7, 28 x 8192 (1.6)
     // 39.4 and 43.1;
-    // d = 64, where a round is sixteen chunks, 1 x 20000 (4) 10.3 and 10.7.
+    // d = 64, where a round is sixteen chunks, 1 x 20000 (4) 10.3 and 10.7. More workgroups than two of them per CU hide the chain for one
+    // another, and 256 threads leave room for more (49 caches of 16 query heads, 3.6 rounds, 37.9 and 40.8 us, 41 of two heads of eight,
+    // d = 256, 3.4 rounds 59.9 and 60.7; with 384 to 512 workgroups 1 % the other way).
     const dim3 merge((unsigned)(n_heads * g.G));
-    if (g.D >= 128 && (total_rows >> log_r) >= 3LL * (1024 / g.D) * n_heads)
+    if (g.D >= 128 && n_heads * g.G <= 512 && (total_rows >> log_r) >= 3LL * (1024 / g.D) * n_heads)
         hipLaunchKernelGGL(decode_merge_kernel<1024>, merge, dim3(1024), 0, s, g, cu_budgets, (int)total_rows, log_r, (const float*)part,
                            (const float*)stats, out);
     else

@@ -37,3 +37,19 @@ def test_merge_threads(A, D, H, rows):
         ref = torch.softmax(z, dim=1) @ v[at[h]:at[h + 1]].double()
         # fp32 logits of up to about 5 in size, weights and sums over up to 20000 rows in a few hundred partial sums: 1e-5 of the largest
         assert (got[h] - ref).abs().max() <= 1e-5 * ref.abs().max() + 1e-7
+
+
+@pytest.mark.parametrize("n", [32, 33])
+def test_merge_of_many_caches(A, n):
+    """512 workgroups and a few more, either side of the other line between the two."""
+    D, G, rows = 128, 16, 24 * 128 + 5
+    cu = torch.arange(n + 1, dtype=torch.int32, device="cuda") * rows
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    q = torch.randn(n, G, D, generator=gen, device="cuda").to(torch.bfloat16)
+    k = torch.randn(n, rows, D, generator=gen, device="cuda").to(torch.bfloat16)
+    v = torch.randn(n, rows, D, generator=gen, device="cuda").to(torch.bfloat16)
+    got = A.decode_attend(A.Params(G, 1, D, 1), q.reshape(-1), k.view(-1, D), v.view(-1, D), cu, n, n * rows).view(n, G, D).double()
+    z = torch.matmul(q.double(), k.double().transpose(1, 2).contiguous()) / D ** 0.5
+    ref = torch.matmul(torch.softmax(z, dim=2), v.double())
+    # (the bound of test_merge_threads)
+    assert (got - ref).abs().max() <= 1e-5 * ref.abs().max() + 1e-7
