@@ -170,6 +170,7 @@ def time_config(A, cfg, data, steps, warmup, dev):
         for n, ms in A.profile_read().items():
             acc[n] += ms
     A.profile_enable(False)
+    # (short heads are smoothed and selected by one launch: pool_smooth is its time, and select 0)
     stage_ms = {n: acc[n] / n_prof for n in acc}
 
     tokens = sum(lens)

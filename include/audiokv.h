@@ -329,8 +329,11 @@ int32_t audiokv_decode_attend(const audiokv_params* params,
  * waits for the most recent such call to finish and writes the elapsed
  * milliseconds of each interval to ms_out[AUDIOKV_PROFILE_STAGES] (host):
  * 0 allocate, 1 score sweep 1 (row statistics), 2 score sweep 2 (column sums),
- * 3 pooling + spectral smoothing, 4 select, 5 compact. Process-wide state (the
- * events are created by the first enable and kept); not thread-safe. */
+ * 3 pooling + spectral smoothing, 4 select, 5 compact. Where one launch smooths
+ * and selects (short heads), 3 is the time of both and 4 is 0. The allocation,
+ * which otherwise runs beside the sweeps, is in line.
+ * Process-wide state (the events are created by the first enable and kept); not
+ * thread-safe. */
 #define AUDIOKV_PROFILE_STAGES 6
 int32_t audiokv_profile_enable(int32_t enable);
 int32_t audiokv_profile_read(float* ms_out);

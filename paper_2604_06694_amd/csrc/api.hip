@@ -204,6 +204,7 @@ struct Profile {
     bool enabled = false;
     bool created = false;
     bool recorded = false;
+    bool selects = true;      // the recorded call selected in a launch of its own
     hipEvent_t ev[AUDIOKV_PROFILE_STAGES + 2] = {};    // last slot: between the two score sweeps
 } g_prof;
 
@@ -539,24 +540,25 @@ int32_t evict_entry(const audiokv_params* params, const void* q_win, const void*
         helper_lock.unlock();
     }
     // (the selection combines smoothed scores from their chunks itself: a launch less)
-    // (and short heads are selected by the launch that smooths them, unless every stage is to be timed)
+    // (and short heads are selected by the launch that smooths them)
     ConvJoin join;
     SelectJob select{budgets_dev, cu_budgets_dev, indices_dev};
     AUDIOKV_HIP(launch_smooth(g, raw, params->pool_kernel != 1, cu_seqlens_dev, seqlens_host, n_items, cutoff_frac,
                               alpha, smoothed, ws + w.fft_off, w.total - w.fft_off, nullptr, false, s, side_filters || ride_taps,
-                              select_joins(b.max_L) ? &join : nullptr, prof ? nullptr : &select),
+                              select_joins(b.max_L) ? &join : nullptr, &select),
                 "smooth kernel");
     AUDIOKV_MARK(3);
-    if (!select.done)
+    if (!select.done) {
         AUDIOKV_HIP(launch_select(g, smoothed, budgets_dev, cu_budgets_dev, cu_seqlens_dev, b.max_L, indices_dev, s,
                                   join.part ? &join : nullptr),
                     "select kernel");
-    AUDIOKV_MARK(4);
+        AUDIOKV_MARK(4);
+    }
     AUDIOKV_HIP(launch_compact(g, k, v, indices_dev, cu_budgets_dev, cu_seqlens_dev, b.total_tokens, total_rows, k_out, v_out, s),
                 "compact kernel");
     AUDIOKV_MARK(5);
 #undef AUDIOKV_MARK
-    if (prof) g_prof.recorded = true;
+    if (prof) { g_prof.recorded = true; g_prof.selects = !select.done; }
     return AUDIOKV_OK;
 }
 }  // namespace
@@ -685,11 +687,15 @@ int32_t audiokv_profile_read(float* ms_out)
         return fail(AUDIOKV_E_INVALID_ARG, "no profiled audiokv_evict call to read");
     AUDIOKV_HIP(hipEventSynchronize(g_prof.ev[5]), "hipEventSynchronize");
     hipEvent_t mid = g_prof.ev[AUDIOKV_PROFILE_STAGES + 1];
-    // intervals: [0,1] allocate, [1,mid] sweep 1, [mid,2] sweep 2, [2,3] smooth, [3,4] select, [4,5] compact
-    hipEvent_t a[AUDIOKV_PROFILE_STAGES] = {g_prof.ev[0], g_prof.ev[1], mid, g_prof.ev[2], g_prof.ev[3], g_prof.ev[4]};
-    hipEvent_t b[AUDIOKV_PROFILE_STAGES] = {g_prof.ev[1], mid, g_prof.ev[2], g_prof.ev[3], g_prof.ev[4], g_prof.ev[5]};
-    for (int i = 0; i < AUDIOKV_PROFILE_STAGES; ++i)
-        AUDIOKV_HIP(hipEventElapsedTime(&ms_out[i], a[i], b[i]), "hipEventElapsedTime");
+    // intervals: [0,1] allocate, [1,mid] sweep 1, [mid,2] sweep 2, [2,3] smooth, [3,4] select, [4,5] compact; without a launch that
+    // selects, event 4 is not recorded, and compact is [3,5]
+    const auto& ev = g_prof.ev;
+    const hipEvent_t a[AUDIOKV_PROFILE_STAGES] = {ev[0], ev[1], mid, ev[2], ev[3], ev[g_prof.selects ? 4 : 3]};
+    const hipEvent_t b[AUDIOKV_PROFILE_STAGES] = {ev[1], mid, ev[2], ev[3], ev[4], ev[5]};
+    for (int i = 0; i < AUDIOKV_PROFILE_STAGES; ++i) {
+        ms_out[i] = 0.f;
+        if (i != 4 || g_prof.selects) AUDIOKV_HIP(hipEventElapsedTime(&ms_out[i], a[i], b[i]), "hipEventElapsedTime");
+    }
     return AUDIOKV_OK;
 }
 

@@ -66,3 +66,22 @@ def test_scores_that_are_not_finite(A):
     out = A.evict(A.Params(H_q, H_kv, d, W), q, k, k, torch.ones(H_kv, device="cuda"), [L], 0.4, 0.125, 1.0)
     idx = out["indices"].cpu().numpy()
     assert idx.min() >= 0 and idx.max() < L and np.isfinite(idx).all()
+
+
+@pytest.mark.parametrize("lens,fused", [([2048], True), ([1500, 900], True), ([16384], True), ([20000], False), ([2048, 4096], False)])
+def test_stage_timing_times_the_launches_that_run(A, lens, fused):
+    """One launch for both stages is timed as the smoothing, and the selection reads 0: no other launches than without timing."""
+    H_q, H_kv, d, W = 4, 2, 64, 8
+    q = torch.randn(len(lens) * H_q * W * d, device="cuda").to(torch.bfloat16)
+    k = torch.randn(sum(lens) * H_kv * d, device="cuda").to(torch.bfloat16)
+    args = (A.Params(H_q, H_kv, d, W), q, k, k, torch.rand(len(lens) * H_kv, device="cuda"), lens, 0.4, 0.125, 1.0)
+    plain = A.evict(*args, alloc_scope=A.SCOPE_ITEM)
+    A.profile_enable(True)
+    try:
+        timed = A.evict(*args, alloc_scope=A.SCOPE_ITEM)
+        ms = A.profile_read()
+    finally:
+        A.profile_enable(False)
+    assert torch.equal(plain["indices"], timed["indices"])
+    assert all(ms[stage] > 0 for stage in A.PROFILE_STAGES if stage != "select")
+    assert (ms["select"] == 0) == fused
