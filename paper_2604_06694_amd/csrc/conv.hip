@@ -367,7 +367,8 @@ __global__ __launch_bounds__(Cfft<LOGC>::THREADS) void conv_chunk_kernel(
 // A head of one chunk, pooled with the usual kernel, smoothed and selected in one workgroup, as in smooth_select_kernel (smooth_real.hip):
 // evict, two launches and one, four heads of 600 tokens 26.2 and 24.8 us, 1500 28.1 and 26.4, 3000 32.3 and 31.0; 112 heads of 3000 118 and
 // 115.
-// The barriers of conv_chunk: the constants, the points' exchange, the result, and those of the transforms.
+// The barriers of conv_chunk: the constants, the points' exchange, the result, and those of the transforms (counted in the built kernels
+// as well, tests/test_fused_barriers.py).
 template <int LOGC> constexpr int kConvBarriers = 3 + 2 * Cfft<LOGC>::BARRIERS;
 // (512 threads: with the 128 registers that 1024 have, 4096 points spill 110; a selection of 4096 tokens on them takes 0.9 us more)
 constexpr int kConvFusedThreads = 512;

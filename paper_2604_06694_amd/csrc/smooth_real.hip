@@ -209,12 +209,14 @@ __device__ __forceinline__ void smooth_real_head(
             for (int e = 0; e < 8; ++e) asm volatile("" : "+v"(other[0][e].re), "+v"(other[0][e].im));
 #endif
         }
-        if (kstar_out && t == 0) kstar_out[head] = kstar;
-        if (cutoffs_only) return;
-        if (degenerate_mask(L, kstar, Tb) == 2) {
-            // every bin kept: the samples themselves (a fixed cutoff that says so never gets here)
-            for (int n = t; n < L; n += T) dst[n] = POOL ? pooled_at(src, L, n, g.pool_kernel, g.pool_mode) : src[n];
-            return;
+        if constexpr (!KEEP) {                               // (with KEEP other waves count on every barrier to the end)
+            if (kstar_out && t == 0) kstar_out[head] = kstar;
+            if (cutoffs_only) return;
+            if (degenerate_mask(L, kstar, Tb) == 2) {
+                // every bin kept: the samples themselves (a fixed cutoff that says so never gets here)
+                for (int n = t; n < L; n += T) dst[n] = POOL ? pooled_at(src, L, n, g.pool_kernel, g.pool_mode) : src[n];
+                return;
+            }
         }
         const int ktop = kstar + Tb;                         // last bin with a non-zero weight
         // bin k and its pair N - k, weighted and merged into what the backward transform takes in the slot of k
@@ -342,7 +344,7 @@ __global__ __launch_bounds__(kRealThreads<LOGC>) void smooth_real_kernel(
 }
 
 // The barriers of smooth_real_head with a fixed cutoff, pooled on load and kept: filling, pooling, the spectrum's exchange (two) and the
-// result, and those of the transforms.
+// result, and those of the transforms (tests/test_fused_barriers.py counts them in the built kernels).
 template <int LOGC> constexpr int kRealBarriers = 5 + 2 * Fft<LOGC, kRealGroups<LOGC>>::BARRIERS;
 
 // Smoothing and selection of a head in one workgroup: the scores go from one to the other through LDS. In place of two launches, of
