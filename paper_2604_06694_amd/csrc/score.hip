@@ -116,9 +116,9 @@ int same_number_for_every_head(const Plan& p, int H_kv, int n_items, const int32
 // Which of the two divisions items of different lengths get. Ranges of one size need an item for each lane of a wave and a K that fits the
 // memory-side cache (a larger one is streamed faster by ranges that each stay with their head, read backwards by sweep 2). Up to
 // 128 heads they are the rule (but for nearly equal lengths); with more, the loads of the XCDs even out by themselves, as many ranges for every head keep a head's queries in
-// one L2, and the other division has to promise a quarter less. Score calls, ranges of one size over as many for every head, geometric
-// mean and worst: of 803 calls of up to 64 heads 0.92 and 1.15, of 78 of 65 to 128 0.91 and 1.13, of 22 of more that promise it 0.90 and 1.05,
-// of 137 that do not 1.04 and 1.34; of 160 of a larger K 1.03 and 1.30. At the lines, as many for every head and ranges of one size: 246 x
+// one L2, and the other division has to promise a fifth less. Score calls, ranges of one size over as many for every head, geometric
+// mean and worst: of 803 calls of up to 64 heads 0.92 and 1.15, of 78 of 65 to 128 0.91 and 1.13, of 23 of more that promise it 0.90 and 1.08,
+// of 136 that do not 1.04 and 1.34; of 160 of a larger K 1.03 and 1.30. At the lines, as many for every head and ranges of one size: 246 x
 // 385-770 tokens of four heads, 256 rows 142 and 172 us, 41 x 212-3402, 128 rows 41 and 34; 32 rows 9 x 23902-24381 (213 MB) 80 and 73,
 // 14 x 21207-23328 (321 MB) 106 and 120, 64 rows of eight heads 7 x 11247-22494 (266 MB) 95 and 88, 8 x 24149-26564 (410 MB) 147 and 163.
 constexpr int kSizedHeads = 128;
@@ -186,7 +186,7 @@ ScoreRanges plan_ranges(const Plan& p, int H_kv, int n_items, const int32_t* seq
         const long long cost = quarters * rounds * (tiles + overhead);
         if (best_cost < 0 || cost < best_cost) { best_cost = cost; best = r; }
     }
-    if (!uniform && division == Division::cheaper && 4 * best_cost >= 3 * same_cost) return same;
+    if (!uniform && division == Division::cheaper && 5 * best_cost >= 4 * same_cost) return same;
     return best;
 }
 

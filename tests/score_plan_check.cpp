@@ -66,9 +66,9 @@ int main() {
             good = fits && r.keys % t.tile == 0;
             for (int L : lens) { parts += (long long)((L + r.keys - 1) / r.keys) * H; good &= r.of_length(L) == (L + r.keys - 1) / r.keys; }
             good &= r.parts == parts;
-            // in whole rounds at a quarter less, where the other division is to be had
+            // in whole rounds at a fifth less, where the other division is to be had
             const long long slots = 256LL * (t.rows <= 64 && D <= 128 && keys >= 512 * 64 ? 3 : t.per_cu), full = ((parts + slots - 1) / slots) * (r.keys / t.tile + (t.tile >= 64 ? 3 : 7));
-            if (n * H > 128) good &= 4 * (parts <= 256 && t.rows == 224 && D <= 128 ? 3 : 4) * full < 3 * 2 * cost;
+            if (n * H > 128) good &= 5 * (parts <= 256 && t.rows == 224 && D <= 128 ? 3 : 4) * full < 4 * 2 * cost;
         } else {
             ++same;
             good = !(fits && n * H <= 128) && r.per_head == number && r.parts == (long long)n * H * r.per_head;
@@ -77,7 +77,7 @@ int main() {
             std::printf("%d items of up to %lld tiles, %d heads, %d rows, D %d, %lld keys: %d ranges per head, %d keys each, %lld parts\n", n, tiles,
                         H, t.rows, D, keys, r.per_head, r.keys, r.parts);
     }
-    std::printf("%s: %d of one size, %d at a quarter less, %d as many for every head, %d small\n",
+    std::printf("%s: %d of one size, %d at a fifth less, %d as many for every head, %d small\n",
                 !bad && sized > 500 && both > 50 && same > 500 && small > 200 ? "the ranges are as planned" : "not as planned", sized, both, same, small);
     return bad ? 1 : 0;
 }
