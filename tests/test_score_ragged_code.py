@@ -7,7 +7,7 @@ import subprocess
 
 import pytest
 
-from test_kernel_code import assembly, code_objects, named, pytestmark as needs_library, resources  # noqa: F401
+from test_kernel_code import LLVM, assembly, code_objects, named, pytestmark as needs_library, resources  # noqa: F401
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -49,3 +49,76 @@ def test_loader_waits_for_what_is_read_next(assembly):  # noqa: F811
             # both waits, and no other one between the loader's loads
             waits = {m.group(1) for line in lines[loads[0]:barriers[-1]] for m in [re.match(r"s_waitcnt .*?vmcnt\((\d+)\)", line)] if m}
             assert waits == {"0", "16"}, (name, waits)
+
+
+def successors(i, what, target, flags):
+    """What may follow an instruction, with the truth values in scalar registers as far as they are known: (index, flags)."""
+    what = re.sub(r"\s+", " ", what)
+    known = dict(flags)
+    mask = re.match(r"s_(andn2|and)_b64 vcc, exec, (s\[\d+:\d+\])$", what)
+    value = known.get(mask.group(2)) if mask else None
+    written = re.match(r"[sv]_\S+ (?:s(\d+)\b|s\[(\d+):(\d+)\]|(vcc))", what)
+    if written:
+        lo, hi = int(written.group(1) or written.group(2) or -1), int(written.group(1) or written.group(3) or -1)
+        for reg in list(known):
+            span = re.match(r"s\[(\d+):(\d+)\]", reg)
+            if reg == written.group(4) or (span and lo >= 0 and int(span.group(1)) <= hi and lo <= int(span.group(2))):
+                del known[reg]
+    const = re.match(r"s_mov_b64 (s\[\d+:\d+\]), (0|-1)$", what)
+    if const:
+        known[const.group(1)] = const.group(2) == "-1"
+    elif value is not None:
+        known["vcc"] = value == (mask.group(1) == "and")
+    flags = tuple(sorted(known.items()))
+    if what.startswith("s_endpgm"):
+        return []
+    if target is None:
+        return [(i + 1, flags)]
+    taken = {"s_branch": True, "s_cbranch_execnz": True, "s_cbranch_execz": False}.get(what.split()[0])     # (a wave has lanes)
+    if "vcc" in known and what.startswith("s_cbranch_vcc"):
+        taken = known["vcc"] == what.startswith("s_cbranch_vccnz")
+    return [(target, flags)] * (taken is not False) + [(i + 1, flags)] * (taken is not True)
+
+
+@needs_library
+def test_no_tile_passes_a_barrier_without_a_wait(code_objects):  # noqa: F811
+    """Tiles in flight across barriers: on every path through the loader, a wait stands between the last load and the barrier after it
+    and between two barriers, and one that leaves sixteen loads on their way follows the sixteen of a newest tile."""
+    seen = 0
+    for f in code_objects:
+        text = subprocess.run([f"{LLVM}/llvm-objdump", "-d", "-C", f], check=True, capture_output=True, text=True).stdout
+        for block in re.split(r"\n\n(?=[0-9a-f]+ <)", text):
+            name = re.search(r"<(.+)>:\n", block)
+            if not name or not re.search(r"score_(ragged|ahead)_kernel<256, 1, [478], ", name.group(1)):
+                continue
+            seen += 1
+            rows = [re.match(r"\s*(\S.*?)\s*// ([0-9A-F]+):", line) for line in block.splitlines()[1:]]
+            rows = [(m.group(1), int(m.group(2), 16)) for m in rows if m]
+            index = {at: i for i, (_, at) in enumerate(rows)}
+            first = next(i for i, (what, _) in enumerate(rows) if what.startswith("global_load_lds"))
+            # (instruction; loads since the last barrier; whether they were waited for; the least that a wait for all but a tile's follows;
+            # known flags. That it is 48 before the first barrier depends on comparisons with the number of tiles, which are not followed.)
+            todo, met, passed = [(first, 0, False, 32, ())], set(), {"0": 0, "16": 0}
+            while todo:
+                state = todo.pop()
+                if state in met:
+                    continue
+                met.add(state)
+                i, loads, waited, newest, flags = state
+                what, at = rows[i]
+                wait = re.match(r"s_waitcnt .*?vmcnt\((\d+)\)", what)
+                if what.startswith("global_load_lds"):
+                    loads, waited = loads + 1, False
+                    assert loads <= 48, (name.group(1), i, loads)
+                elif wait:
+                    assert wait.group(1) == "0" or (wait.group(1) == "16" and loads >= newest), (name.group(1), i, what, loads)
+                    passed[wait.group(1)] += 1
+                    waited = True
+                elif what.startswith("s_barrier"):
+                    assert waited, (name.group(1), i, loads)
+                    loads, waited, newest = 0, False, 16
+                jump = re.match(r"s_c?branch\S* (\d+)$", re.sub(r"\s+", " ", what))
+                target = index[at + 4 + 4 * ((int(jump.group(1)) ^ 0x8000) - 0x8000)] if jump else None
+                todo += [(n, loads, waited, newest, known) for n, known in successors(i, what, target, flags)]
+            assert passed["0"] and passed["16"], (name.group(1), passed)
+    assert seen == 12, seen
