@@ -247,7 +247,7 @@ void decode_partial_kernel(
 
 // One workgroup per (KV head, query head of its group): combine the chunks. A chain of loads from end to end, so as
 // many as possible are in flight: the statistics one chunk per thread, then the accumulators with a thread on four
-// channels of every (256 / (D/4))-th chunk. Every sum has a fixed order.
+// channels of every (THREADS / (D/4))-th chunk. Every sum has a fixed order.
 // THREADS: 1024 where heads have many chunks (launch_decode).
 constexpr int kMergeEarly = 4;            // accumulators per thread requested before the statistics are known
 constexpr int kMergeLds = 2048;           // chunks whose weights fit the LDS array (more: recomputed where used)
@@ -269,7 +269,7 @@ __global__ __launch_bounds__(THREADS) void decode_merge_kernel(
 
     // The first accumulators are requested together with the statistics: one load latency less (112 heads of 13 chunks 6.3 ->
     // 5.7 us, 64 heads 4.6 -> 4.0).
-    const int quads = g.D >> 2, groups = THREADS / quads;  // D = 64, 128, 256: 16, 8, 4 chunks at a time
+    const int quads = g.D >> 2, groups = THREADS / quads;  // 256 threads, D = 64, 128, 256: 16, 8, 4 chunks at a time; 1024: 32 and 16
     const int ch4 = tid % quads, grp = tid / quads;
     const f32x4* col = reinterpret_cast<const f32x4*>(part + ((size_t)c0 * g.G + qh) * g.D) + ch4;
     const size_t stride = (size_t)g.G * quads;

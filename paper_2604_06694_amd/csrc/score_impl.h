@@ -29,8 +29,9 @@
 // per sweep by the loader wave (16-byte load-to-LDS instructions that go from
 // HBM straight into a ring of three or four LDS buffers, two or three tiles
 // ahead of the compute waves, one barrier per tile at which all that was
-// requested has landed), so the HBM latency is paid
-// by a wave that has nothing else to do and no wave holds staging registers.
+// requested has landed, or, at d = 256, all but the newest tile), so the HBM
+// latency is paid by a wave that has nothing else to do and no wave holds
+// staging registers.
 // Every compute wave pulls all 32-key x 16-channel fragments of the tile.
 // Sweep 1 keeps no running maximum: its exponentials are taken against a
 // reference (the maximum of the wave's first block; where ranges are long, it
@@ -87,9 +88,9 @@ struct Tile {
     static constexpr int CH = CHUNKS / 64;            // load instructions per tile
     static_assert(CHUNKS % 64 == 0, "a tile is a whole number of wave-wide 16-byte loads");
     // LDS ring: the loader wave requests tile t + STAGES - 1 while tile t is consumed, straight from HBM into the ring (no
-    // staging registers), and enters the barrier that ends tile t when all it has requested is there (score_ring.h): the loads
-    // of a tile overlap with the work on one tile, and none is on its way across a barrier. Workgroups of one or two compute
-    // waves keep a shorter ring: there the number of resident workgroups matters more.
+    // staging registers), and enters the barrier that ends tile t when all it has requested is there (score_ring.h; with AHEAD below,
+    // all but the newest tile): without it, the loads of a tile overlap with the work on one tile, and none is on its way across a
+    // barrier. Workgroups of one or two compute waves keep a shorter ring: there the number of resident workgroups matters more.
     static constexpr int STAGES = (WR >= 4) ? 4 : 3;
     static_assert(kInFlight * CH <= 63, "the outstanding loads must fit the vmcnt field");
     // At d = 256 a tile is 32 keys and over before a load from HBM is: there the newest tile stays on its way across a barrier, where
@@ -194,7 +195,7 @@ __device__ __forceinline__ void ride_along(const RideAlong& ride, int block) {
 // merge their rows one after the other, and with five to seven heads it costs more than it saves (576 rows, six heads of 16000
 // 54.6 -> 56.3 us; one launch merging for both 55.5 there, but two heads of 9000 48.6 -> 50.1).
 // HALVES: the two halves of a wave share a row (the caller's r is the same in both) and take the batches of sixteen in turn.
-// stats: those of the row in the first of its nsplit ranges; pitch: from range to range.
+// hs: the statistics of the row in the first of its nsplit ranges; pitch: from range to range.
 template <int N, bool HALVES>
 __device__ __forceinline__ float merged_row(const float2* __restrict__ hs, int nsplit, int pitch, int half) {
     const int first = HALVES ? half * 16 : 0;

@@ -1328,9 +1328,9 @@ hipError_t launch_smooth_filters(const Geom& g, const int32_t* cu_seqlens, const
                           workspace, s);
 }
 
-// Heads up to which smoothing and selection go in one launch: one workgroup of 512 or 1024 threads per CU. Beyond one round of them two
-// launches, whose workgroups share CUs, are as good or better (evict, two launches and one: 320 heads of 2048 147 and 144 us, of 3000
-// 190 and 188, of 8192 251 and 265, 400 of 1500 169 and 174; 252 heads of 3000 202 and 199, 200 of 8192 164 and 161).
+// Heads up to which smoothing and selection go in one launch: one workgroup per CU, a plain cut. Up to it one launch is faster (evict, two
+// launches and one: 252 heads of 3000 202 and 199 us, 200 of 8192 164 and 161); beyond it that depends on how many of the two kernels'
+// workgroups share a CU: 320 heads of 2048 147 and 144 us, of 3000 190 and 188, but of 8192 251 and 265, 400 of 1500 169 and 174.
 constexpr int kFusedHeads = 256;
 
 hipError_t launch_smooth(const Geom& g, const float* in, bool pool_on_load, const int32_t* cu_seqlens,

@@ -1,5 +1,5 @@
-"""Combining a head's chunks in a decoding step with 256 and 1024 threads: caches on either side of the line between them, every head
-dimension, heads of very different sizes, against attention in float64."""
+"""Combining a head's chunks in a decoding step with 256 and 1024 threads: caches on either side of the line between them at d = 128 and
+256 (d = 64 always takes 256), heads of very different sizes, against attention in float64."""
 import numpy as np
 import pytest
 import torch
