@@ -1,5 +1,6 @@
-"""Scores of items of different lengths, whose key ranges are of one size: every way in which a workgroup finds its item (up to 64
-items, more, none needed), sweeps of one call that divide the heads differently, and what evict makes of them."""
+"""Scores of items of different lengths: key ranges of one size, in which a workgroup finds its item among up to 64, as many ranges for
+every head (more items, many heads, a K beyond the memory-side cache, calls that fit the chip at once), sweeps of one call that divide the
+heads differently."""
 import numpy as np
 import pytest
 import torch
